@@ -484,7 +484,7 @@ int spectre_prepare(int n, int d) {
         }
     }
     hipError_t (*const loaders[])() = {load_kernels_mix_pow2, load_kernels_mix_slab, load_kernels_mix_chirp, load_kernels_gate,
-                                       load_kernels_prefix, load_kernels_project, load_kernels_wrm};
+                                       load_kernels_prefix, load_kernels_decode, load_kernels_project, load_kernels_wrm};
     for (auto load : loaders) {
         const hipError_t e = load();
         if (e != hipSuccess) return fail_hip(e, "prepare: loading kernels");
@@ -1404,11 +1404,26 @@ int spectre_prefix_step(spectre_prefix_cache *c, const void *v_t, const void *q_
     float2 *raw = reinterpret_cast<float2 *>(w);
     const int slot = M0 + (int)(c->t % W), evict = c->t >= W ? 1 : 0;
     const bool lazy = c->pending_cap > 0;
+    const GateDev gd = gate_dev(P);
+    if (decode_fused_supported(gd) && !(lazy && c->n_pending + 1 == c->pending_cap)) {   // a step that flushes: below
+        int slots[kMaxPending];
+        for (int i = 0; i < c->n_pending; ++i) slots[i] = c->pending_slot[i];
+        if (lazy) slots[c->n_pending] = slot;
+        const hipError_t ef = launch_decode((int)io, v_t, q_t, static_cast<float *>(c->v_buf), static_cast<float *>(c->q_buf),
+                                            static_cast<double *>(c->sum_q), slot, evict, static_cast<float2 *>(c->prefix_fft),
+                                            1.0 / (double)W, gd, static_cast<const float2 *>(c->twiddle), partial, kpart,
+                                            static_cast<float *>(c->pending), lazy ? c->n_pending + 1 : 0, slots, out, B, H,
+                                            N, st);
+        if (ef != hipSuccess) return fail_hip(ef, "decode step");
+        if (lazy) c->pending_slot[c->n_pending++] = slot;
+        c->t += 1;
+        return SPECTRE_OK;
+    }
     if (lazy) delta = static_cast<float *>(c->pending) + (size_t)c->n_pending * BH * d;   // this token's pending row
     hipError_t e = launch_ring_update((int)io, v_t, q_t, 1, 0, static_cast<float *>(c->v_buf), static_cast<float *>(c->q_buf),
                                       static_cast<double *>(c->sum_q), delta, B, H, d, N, slot, evict, st);
     if (e != hipSuccess) return fail_hip(e, "ring_update");
-    e = launch_gate_mlp(static_cast<const double *>(c->sum_q), 1.0 / (double)W, gate_dev(P), hid, raw, B, H, 0, g, st);
+    e = launch_gate_mlp(static_cast<const double *>(c->sum_q), 1.0 / (double)W, gd, hid, raw, B, H, 0, g, st);
     if (e != hipSuccess) return fail_hip(e, "gate_mlp");
     if (lazy) {
         // the ring buffers and sum_q are already updated; from here on the token counts as appended

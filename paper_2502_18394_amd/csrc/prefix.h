@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stddef.h>
 
+#include "gate.h"
+
 namespace spectre {
 
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t st);          // bytes % 16 == 0
@@ -36,6 +38,13 @@ hipError_t launch_readout_final_lazy(int io, const float *partial, const float *
                                      int BH, int F, int npend, hipStream_t st);
 // out [B,1,H,d] (io dtype) from the sweep's partial sums.
 hipError_t launch_readout_final(int io, const float *partial, void *out, int BH, int F, hipStream_t st);
+// One decode step in two launches (gate, pass over the half spectra, ring update); npend > 0: the cache is only read,
+// slots[0 .. npend-1] are the pending tokens' ring rows with this token last, whose Delta row goes to `pending`.
+bool decode_fused_supported(const GateDev &P);
+hipError_t launch_decode(int io, const void *v_t, const void *q_t, float *v_buf, float *q_buf, double *sum_q, int slot,
+                         int evict, float2 *X, double inv_count, const GateDev &P, const float2 *tw, float *partial,
+                         float *kpart, float *pending, int npend, const int *slots, void *out, int B, int H, int N,
+                         hipStream_t st);
 // Memory rows mem [mem_batch (1 or B), H, Nmem, 64] into rows 0..Nmem-1 of v_buf [B, H, N, 64].
 hipError_t launch_set_memory(const float *mem, int mem_batch, float *v_buf, int B, int H, int N, int Nmem,
                              hipStream_t st);

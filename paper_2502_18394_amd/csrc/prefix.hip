@@ -8,6 +8,7 @@
 
 #include "common.h"
 #include "mix_pow2.h"
+#include "prefix_dev.h"
 
 namespace spectre {
 
@@ -29,15 +30,6 @@ __global__ __launch_bounds__(256) void k_fill_twiddle(float2 *__restrict__ tw, i
 // ------------------------------------------------------------------------------------------
 // ring update for one token (Algorithm 1, DecodeStep: slot, eviction, buffers, running sum).
 // One lane per (b, h, c).  v_t, q_t are the rows [B, T, H, d] at position `ti`.
-template <typename T>
-__device__ __forceinline__ float load_scalar(const T *p, size_t i);
-template <>
-__device__ __forceinline__ float load_scalar<float>(const float *p, size_t i) { return p[i]; }
-template <>
-__device__ __forceinline__ float load_scalar<uint16_t>(const uint16_t *p, size_t i) {
-    return __uint_as_float((uint32_t)p[i] << 16);
-}
-
 template <typename T>
 __global__ __launch_bounds__(256) void k_ring_update(const T *__restrict__ v_new, const T *__restrict__ q_new,
                                                      int Tn, int ti, float *__restrict__ v_buf,
@@ -63,14 +55,6 @@ __global__ __launch_bounds__(256) void k_ring_update(const T *__restrict__ v_new
 // w_k = twiddle[(k*slot) mod N] (Eq. 5).  READ: partial[bh][chunk][c] = sum over the chunk's
 // bins of Re(r_k X[k,c]) with r_k = (c_k/N) g_k conj(w_k), c_k = 1 at DC and Nyquist, else 2
 // (the newest row of Cor. B.2's inverse; exp(+j 2 pi k slot/N) = conj(w_k)).
-constexpr int kSweepBins = 128;
-
-// (a b) mod N for a, b < N <= 2^17 without 64-bit division.
-__device__ __forceinline__ unsigned mul_mod(unsigned a, unsigned b, int N) {
-    if ((N & (N - 1)) == 0) return (a * b) & (unsigned)(N - 1);
-    return (((a * (b >> 9)) % (unsigned)N) * 512u + a * (b & 511u)) % (unsigned)N;
-}
-
 // The per-bin factors w_k and r_k of a chunk are prepared once by its first 128 lanes and kept in LDS; the rows
 // then cost one cache access each, four of them in flight per lane.
 template <bool UPDATE, bool READ>
@@ -151,21 +135,6 @@ __global__ __launch_bounds__(256) void k_sweep(float4 *__restrict__ X, const flo
 // every bin row (each of the 32 lanes of a row takes one pending token).
 // k_flush_mfma (the flush): X[k,:] += sum_i Delta_i tw[(k slot_i) mod N], stored; with READ the readout partials
 // are taken from the updated entries.
-struct PendingSlots {
-    int n;
-    int slot[kMaxPending];
-};
-
-__device__ __forceinline__ void index_walk(unsigned k_start, unsigned mult, int N, unsigned &m, unsigned &step) {
-    if ((N & (N - 1)) == 0) {
-        step = (8u * mult) & (unsigned)(N - 1);
-        m = (k_start * mult) & (unsigned)(N - 1);
-    } else {
-        step = (unsigned)((8ull * mult) % (unsigned)N);
-        m = (unsigned)(((unsigned long long)k_start * mult) % (unsigned)N);
-    }
-}
-
 __global__ __launch_bounds__(256) void k_sweep_lazy(const float4 *__restrict__ X, const float2 *__restrict__ tw,
                                                     const float2 *__restrict__ g, float *__restrict__ partial,
                                                     float *__restrict__ kpart, int F, int N, int BH, int slot_new,
