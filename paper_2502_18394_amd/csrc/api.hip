@@ -1177,7 +1177,7 @@ size_t spectre_prefix_update_workspace_bytes(const spectre_prefix_cache *c, int 
     (void)io;
     if (!c || T < 1 || c->B < 1 || c->H < 1 || c->d < 2 || c->N_max < 1 || c->N_mem < 0) return 0;
     const int BH = c->B * c->H;
-    const int rows = T < kMaxPending ? T : kMaxPending;      // delta rows of one batch of appended tokens
+    const int rows = T < kMaxBatch ? T : kMaxBatch;          // delta rows of one batch of appended tokens
     return align256((size_t)rows * BH * c->d * sizeof(float)) + align256(gate_partial_bytes(c->B, T, c->H, c->d)) +
            scratch_bytes(BH, window_len(c), c->d);
 }
@@ -1203,7 +1203,7 @@ int spectre_prefix_update(spectre_prefix_cache *c, const void *v_new, const void
     if (rc) return rc;
     char *w = static_cast<char *>(ws);
     float *delta = reinterpret_cast<float *>(w);
-    w += align256((size_t)(T < kMaxPending ? T : kMaxPending) * BH * d * sizeof(float));
+    w += align256((size_t)(T < kMaxBatch ? T : kMaxBatch) * BH * d * sizeof(float));
     double *partial = reinterpret_cast<double *>(w);
     w += align256(gate_partial_bytes(B, T, H, d));
     float2 *scr = reinterpret_cast<float2 *>(w);
@@ -1264,20 +1264,16 @@ int spectre_prefix_update(spectre_prefix_cache *c, const void *v_new, const void
         c->t += T;
         return SPECTRE_OK;
     }
-    // several tokens: Eq. 5 is a sum of rank-one terms, so up to kMaxPending of them go into the cache in ONE sweep
-    // (the ring buffers are still updated token by token, in order: a ring shorter than the batch reuses its slots)
-    for (int t0 = 0; t0 < T; t0 += kMaxPending) {
-        const int nb = (T - t0 < kMaxPending) ? T - t0 : kMaxPending;
-        int slots[kMaxPending];
-        for (int i = 0; i < nb; ++i) {
-            const long long ti = c->t + i;
-            const int slot = M0 + (int)(ti % W), evict = ti >= W ? 1 : 0;
-            slots[i] = slot;
-            e = launch_ring_update((int)io, v_new, q_new, T, t0 + i, static_cast<float *>(c->v_buf),
-                                   static_cast<float *>(c->q_buf), static_cast<double *>(c->sum_q),
-                                   delta + (size_t)i * BH * d, B, H, d, N, slot, evict, st);
-            if (e != hipSuccess) return fail_hip(e, "ring_update");
-        }
+    // several tokens: Eq. 5 is a sum of rank-one terms, so up to kMaxBatch of them go into the cache in ONE sweep (no
+    // more than the ring holds, so that a batch never meets its own tokens)
+    for (int t0 = 0, nb; t0 < T; t0 += nb) {
+        nb = T - t0 < kMaxBatch ? T - t0 : kMaxBatch;
+        if (nb > W) nb = W;
+        int slots[kMaxBatch];
+        for (int i = 0; i < nb; ++i) slots[i] = M0 + (int)((c->t + i) % W);
+        e = launch_ring_batch((int)io, v_new, q_new, T, t0, nb, static_cast<float *>(c->v_buf), static_cast<float *>(c->q_buf),
+                              static_cast<double *>(c->sum_q), delta, B, H, N, M0, W, c->t, st);
+        if (e != hipSuccess) return fail_hip(e, "ring_batch");
         e = launch_sweep_lazy(true, false, X, delta, static_cast<const float2 *>(c->twiddle), nullptr, nullptr, nullptr, BH,
                               F, N, 0, nb, slots, st);
         if (e != hipSuccess) return fail_hip(e, "sweep(batch update)");

@@ -409,7 +409,7 @@ hipError_t launch_decode(int io, const void *v_t, const void *q_t, float *v_buf,
     if (npend < 0 || npend > kMaxPending) return hipErrorInvalidValue;
     PendingSlots ps;
     ps.n = npend;
-    for (int i = 0; i < kMaxPending; ++i) ps.slot[i] = i < npend ? slots[i] : 0;
+    for (int i = 0; i < kMaxBatch; ++i) ps.slot[i] = i < npend ? slots[i] : 0;
     const DecodeRing rg = {v_t, q_t, v_buf, q_buf, sum_q, slot, evict};
     return io ? decode_t<IoBf16, uint16_t>(rg, X, inv_count, P, tw, partial, kpart, pending, out, B, H, N, ps, st)
               : decode_t<IoF32, float>(rg, X, inv_count, P, tw, partial, kpart, pending, out, B, H, N, ps, st);

@@ -26,6 +26,12 @@ hipError_t launch_sweep(bool update, bool read, float2 *X, const float *delta, c
 //   flush: apply all npend pending updates to X;  read: readout partials for the row `slot_new` with gate g;
 //   without flush the kappa partials kpart [BH][chunks][32] of the pending tokens are produced as well.
 constexpr int kMaxPending = 32;
+constexpr int kMaxBatch = 64;     // tokens of an append that one sweep takes
+// Ring-buffer bookkeeping of nb <= min(kMaxBatch, W) appended tokens, tokens i0 .. i0 + nb - 1 of v_new / q_new
+// [B, T, H, 64]: token i goes to slot M0 + (t + i) mod W, evicting what was there when t + i >= W; delta [nb][B*H][64].
+hipError_t launch_ring_batch(int io, const void *v_new, const void *q_new, int T, int i0, int nb, float *v_buf,
+                             float *q_buf, double *sum_q, float *delta, int B, int H, int N, int M0, int W, long long t,
+                             hipStream_t st);
 // Ring-buffer bookkeeping for T <= W tokens appended at once (token i -> slot (s0 + i) mod W behind M0 memory rows,
 // evicting when t0 + i >= W); partial [B][ceil(T/256)][H*64] doubles = per-chunk sums of q_new - q_evicted.
 // V == nullptr: only the query side (q_buf, partial); the value rows are then written by whoever reads V.

@@ -49,6 +49,58 @@ __global__ __launch_bounds__(256) void k_ring_update(const T *__restrict__ v_new
     q_buf[ring] = qn;
 }
 
+// The same for the tokens of one appended batch, in one launch: their slots are distinct (nb <= W).  grid B*H; 256
+// lanes = 32 channel pairs x 8 token lanes; the query sums are combined in a fixed order.
+// One launch per token cost 4 us each, 228 of the 712 us of a 57-token append with its readout at B=4 H=32 N=8192.
+template <typename IO>
+__global__ __launch_bounds__(256) void k_ring_batch(const typename IO::pair_t *__restrict__ v_new,
+                                                    const typename IO::pair_t *__restrict__ q_new, int T, int i0, int nb,
+                                                    float2 *__restrict__ v_buf, float2 *__restrict__ q_buf,
+                                                    double *__restrict__ sum_q, float2 *__restrict__ delta, int H, int N,
+                                                    int M0, int W, int s0, int evict_from, int BH) {
+    __shared__ double red[8][64];
+    constexpr int kPer = kMaxBatch / 8;
+    const int p = threadIdx.x & 31, rl = threadIdx.x >> 5, bh = blockIdx.x, h = bh % H, b = bh / H;
+    typename IO::pair_t rv[kPer], rq[kPer];
+    float2 vo[kPer], qo[kPer];
+    size_t ring[kPer];
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = min(rl + 8 * u, nb - 1);                       // clamped: neither stored nor summed past the end
+        int slot = s0 + i;
+        if (slot >= W) slot -= W;
+        ring[u] = ((size_t)bh * N + M0 + slot) * 32 + p;
+        const size_t src = (((size_t)b * T + i0 + i) * H + h) * 32 + p;
+        rv[u] = v_new[src];
+        rq[u] = q_new[src];
+        const bool ev = i >= evict_from;
+        vo[u] = ev ? v_buf[ring[u]] : make_float2(0.f, 0.f);
+        qo[u] = ev ? q_buf[ring[u]] : make_float2(0.f, 0.f);
+    }
+    double sx = 0.0, sy = 0.0;
+#pragma unroll
+    for (int u = 0; u < kPer; ++u) {
+        const int i = rl + 8 * u;
+        if (i < nb) {
+            const float2 vn = IO::unpack(rv[u]), qn = IO::unpack(rq[u]);
+            delta[((size_t)i * BH + bh) * 32 + p] = make_float2(vn.x - vo[u].x, vn.y - vo[u].y);
+            sx += (double)qn.x - (double)qo[u].x;
+            sy += (double)qn.y - (double)qo[u].y;
+            v_buf[ring[u]] = vn;
+            q_buf[ring[u]] = qn;
+        }
+    }
+    red[rl][2 * p] = sx;
+    red[rl][2 * p + 1] = sy;
+    __syncthreads();
+    if (threadIdx.x < 64) {
+        double t = red[0][threadIdx.x];
+#pragma unroll
+        for (int r = 1; r < 8; ++r) t += red[r][threadIdx.x];
+        sum_q[(size_t)bh * 64 + threadIdx.x] += t;
+    }
+}
+
 // ------------------------------------------------------------------------------------------
 // sweep over the cache.  grid (ceil(F/KCH), B*H); 256 lanes = 8 bins x 32 lanes, a lane owns
 // two adjacent channels (one 16-byte access).  UPDATE: X[k,:] += delta * w_k with
@@ -216,23 +268,27 @@ __global__ __launch_bounds__(256) void k_sweep_lazy(const float4 *__restrict__ X
 // from the cache, advanced by CAP/2 v_mfma_f32_32x32x2f32 each (two pending tokens per instruction) and
 // stored back.  Operand layout of that instruction: A[i][k] in lane 32k + i, B[k][j] in lane 32k + j,
 // D[8(v/4) + 4(lane/32) + v%4][lane%32] in register v.
-// A workgroup takes kFlushChunks chunks of kSweepBins = 4 x 32 bins, one block per wave and chunk; partial as
-// in k_sweep.
+// A workgroup takes `per_wg` <= kFlushChunks chunks of kSweepBins = 4 x 32 bins, one block per wave and chunk; partial
+// as in k_sweep.  What hides the latency of a block's loads is the other waves of the SIMD, three of them: with the next
+// block's entries prefetched into registers instead there was room for two (16 tokens and readout at B=1 H=32 N=8192:
+// 44 against 33 us), and a fourth spills (50 us).
+// Up to 64 tokens go into one sweep: B=4 H=32 N=8192 takes 105 us for 8 tokens and 151 for 64 (537 MB, and 55 us of
+// matrix instructions), against 2 x 133 us for two sweeps of 32 before.
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
-constexpr int kFlushChunks = 8;   // chunks of kSweepBins bins per workgroup
+constexpr int kFlushChunks = 8;   // chunks of kSweepBins bins per workgroup at most
 
 template <bool READ, int CAP>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k_flush_mfma(
+__global__ __launch_bounds__(256, 3) void k_flush_mfma(
     float4 *__restrict__ X, const float *__restrict__ pending, const float2 *__restrict__ tw,
     const float2 *__restrict__ g, float *__restrict__ partial, int F, int N, int BH, int slot_new, PendingSlots ps,
-    int nchunks) {
+    int nchunks, int per_wg) {
     static_assert(kSweepBins == 128, "one 32-bin block per wave and chunk");
     __shared__ float2 red[kFlushChunks][4][32];
     const int l = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int col = l & 31, half = l >> 5;
     const int bh = blockIdx.y;
-    const int chunk_end = min(nchunks, ((int)blockIdx.x + 1) * kFlushChunks);
+    const int chunk_end = min(nchunks, ((int)blockIdx.x + 1) * per_wg);
 
     // operands that do not depend on the block, kept in LDS: the delta of token i at channels 2c and 2c + 1, and
     // the factor's advance over a block's rows, tw[(c slot_i) mod N]; the block's own factor tw[(kb slot_i) mod N]
@@ -249,39 +305,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
         s_adv[i][c] = tw[mul_mod((unsigned)c, (unsigned)ps.slot[i], N)];
     }
     __syncthreads();
-    // software pipeline: the cache entries and the factors of the next block are requested before the matrix
-    // products of the current one start
     // register v of a block <-> bin row 8(v/4) + 4 half + v%4
-    float4 xs[16];
-    float2 wbl;
-    auto request = [&](int chunk) {
+    for (int chunk = blockIdx.x * per_wg; chunk < chunk_end; ++chunk) {
         const int kb = chunk * kSweepBins + 32 * wave;
         const int k1 = min(F, chunk * kSweepBins + kSweepBins);
-        const float4 *Xp = X + ((size_t)bh * F + kb) * 32 + col;
-        // lane i < CAP fetches token i's factor at the block's first bin
-        wbl = tw[mul_mod((unsigned)kb, (unsigned)s_slot[l & (CAP - 1)], N)];
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            const int r = 8 * (v / 4) + 4 * half + (v % 4);
-            xs[v] = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (kb + r < k1) xs[v] = stream_load(Xp + (size_t)r * 32);
+        if (kb >= k1) {                                              // the Nyquist bin's chunk has one block
+            if (READ && half == 0) red[chunk - blockIdx.x * per_wg][wave][col] = make_float2(0.f, 0.f);
+            continue;
         }
-    };
-    request(blockIdx.x * kFlushChunks);
-    for (int chunk = blockIdx.x * kFlushChunks; chunk < chunk_end; ++chunk) {
-        const int kb = chunk * kSweepBins + 32 * wave;
-        const int k1 = min(F, chunk * kSweepBins + kSweepBins);
         float4 *Xp = X + ((size_t)bh * F + kb) * 32 + col;
+        // lane i < CAP fetches token i's factor at the block's first bin
+        const float2 wcur = tw[mul_mod((unsigned)kb, (unsigned)s_slot[l & (CAP - 1)], N)];
         floatx16 re0, im0, re1, im1;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            re0[v] = xs[v].x;
-            im0[v] = xs[v].y;
-            re1[v] = xs[v].z;
-            im1[v] = xs[v].w;
+            const int r = 8 * (v / 4) + 4 * half + (v % 4);
+            const float4 x = stream_load(Xp + (size_t)min(r, k1 - 1 - kb) * 32);
+            re0[v] = x.x;
+            im0[v] = x.y;
+            re1[v] = x.z;
+            im1[v] = x.w;
         }
-        const float2 wcur = wbl;
-        if (chunk + 1 < chunk_end) request(chunk + 1);
+        float2 gk = make_float2(0.f, 0.f), wk = gk;                  // lane col: readout factor of bin kb + col
+        if (READ && kb + col < k1) {
+            gk = g[(size_t)bh * F + kb + col];
+            wk = tw[mul_mod((unsigned)(kb + col), (unsigned)slot_new, N)];
+        }
 #pragma unroll 2
         for (int s = 0; s < CAP / 2; ++s) {
             // token 2s + half: A = its factor at bin kb + col, B = its delta
@@ -299,16 +348,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             if (kb + r < k1) stream_store(Xp + (size_t)r * 32, make_float4(re0[v], im0[v], re1[v], im1[v]));
         }
         if (READ) {
-            // lane col prepares the readout factor of bin kb + col; the rows a lane holds fetch theirs by shuffle
+            // the rows a lane holds fetch their bin's factor by shuffle
             const int k = kb + col;
-            float rr = 0.f, ri = 0.f;
-            if (k < k1) {
-                const float invN = 1.0f / (float)N;
-                const float ck = (k == 0 || 2 * k == N) ? invN : 2.0f * invN;
-                const float2 r = cmulc(g[(size_t)bh * F + k], tw[mul_mod((unsigned)k, (unsigned)slot_new, N)]);
-                rr = r.x * ck;
-                ri = r.y * ck;
-            }
+            const float invN = 1.0f / (float)N;
+            const float ck = (k == 0 || 2 * k == N) ? invN : 2.0f * invN;
+            const float2 rk = cmulc(gk, wk);
+            const float rr = rk.x * ck, ri = rk.y * ck;
             float acc0 = 0.f, acc1 = 0.f;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
@@ -319,13 +364,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void k
             }
             acc0 += __shfl_xor(acc0, 32);
             acc1 += __shfl_xor(acc1, 32);
-            if (half == 0) red[chunk - blockIdx.x * kFlushChunks][wave][col] = make_float2(acc0, acc1);
+            if (half == 0) red[chunk - blockIdx.x * per_wg][wave][col] = make_float2(acc0, acc1);
         }
     }
     if (READ) {
         // the four waves' sums of every chunk, added in a fixed order
         __syncthreads();
-        const int c = threadIdx.x >> 5, chunk = blockIdx.x * kFlushChunks + c;
+        const int c = threadIdx.x >> 5, chunk = blockIdx.x * per_wg + c;
         static_assert(kFlushChunks == 8, "one chunk per 32 threads");
         if (chunk < chunk_end) {
             float2 t = red[c][0][col];
@@ -656,6 +701,21 @@ hipError_t launch_ring_update(int io, const void *v_new, const void *q_new, int 
     return hipGetLastError();
 }
 
+hipError_t launch_ring_batch(int io, const void *v_new, const void *q_new, int T, int i0, int nb, float *v_buf,
+                             float *q_buf, double *sum_q, float *delta, int B, int H, int N, int M0, int W, long long t,
+                             hipStream_t st) {
+    if (nb < 1 || nb > kMaxBatch || nb > W) return hipErrorInvalidValue;
+    const int s0 = (int)(t % W), evict_from = t >= W ? 0 : (int)(W - t < nb ? W - t : nb);
+#define SPECTRE_RING_BATCH(IO)                                                                                        \
+    k_ring_batch<IO><<<B * H, 256, 0, st>>>(static_cast<const IO::pair_t *>(v_new), static_cast<const IO::pair_t *>(q_new), \
+                                            T, i0, nb, reinterpret_cast<float2 *>(v_buf),                             \
+                                            reinterpret_cast<float2 *>(q_buf), sum_q, reinterpret_cast<float2 *>(delta), \
+                                            H, N, M0, W, s0, evict_from, B * H)
+    if (io) SPECTRE_RING_BATCH(IoBf16); else SPECTRE_RING_BATCH(IoF32);
+#undef SPECTRE_RING_BATCH
+    return hipGetLastError();
+}
+
 int sweep_chunks(int F) { return (F + kSweepBins - 1) / kSweepBins; }
 
 hipError_t launch_sweep(bool update, bool read, float2 *X, const float *delta, const float2 *tw, const float2 *g,
@@ -672,10 +732,10 @@ hipError_t launch_sweep(bool update, bool read, float2 *X, const float *delta, c
 hipError_t launch_sweep_lazy(bool flush, bool read, float2 *X, const float *pending, const float2 *tw, const float2 *g,
                              float *partial, float *kpart, int BH, int F, int N, int slot_new, int npend,
                              const int *slots, hipStream_t st) {
-    if (npend < 0 || npend > kMaxPending) return hipErrorInvalidValue;
+    if (npend < 0 || npend > (flush && !read ? kMaxBatch : kMaxPending)) return hipErrorInvalidValue;
     PendingSlots ps;
     ps.n = npend;
-    for (int i = 0; i < kMaxPending; ++i) ps.slot[i] = i < npend ? slots[i] : 0;
+    for (int i = 0; i < kMaxBatch; ++i) ps.slot[i] = i < npend ? slots[i] : 0;
     const int nch = sweep_chunks(F);
     dim3 grid(nch, BH);
     float4 *X4 = reinterpret_cast<float4 *>(X);
@@ -683,13 +743,18 @@ hipError_t launch_sweep_lazy(bool flush, bool read, float2 *X, const float *pend
         k_sweep_lazy<<<grid, 256, 0, st>>>(X4, tw, g, partial, kpart, F, N, BH, slot_new, ps, nch);
         return hipGetLastError();
     }
-    const dim3 fgrid((nch + kFlushChunks - 1) / kFlushChunks, BH);
+    // chunks per workgroup: all kFlushChunks share one set-up of the tokens' operands, fewer while the launch would have
+    // less than four workgroups per compute unit
+    int per_wg = kFlushChunks;
+    while (per_wg > 1 && (long long)((nch + per_wg - 1) / per_wg) * BH < 1024) per_wg /= 2;
+    const dim3 fgrid((nch + per_wg - 1) / per_wg, BH);
 #define SPECTRE_FLUSH(RD, CAPV) \
-    k_flush_mfma<RD, CAPV><<<fgrid, 256, 0, st>>>(X4, pending, tw, g, partial, F, N, BH, slot_new, ps, nch)
+    k_flush_mfma<RD, CAPV><<<fgrid, 256, 0, st>>>(X4, pending, tw, g, partial, F, N, BH, slot_new, ps, nch, per_wg)
     if (read) {
         if (npend <= 8) SPECTRE_FLUSH(true, 8); else if (npend <= 16) SPECTRE_FLUSH(true, 16); else SPECTRE_FLUSH(true, 32);
     } else {
-        if (npend <= 8) SPECTRE_FLUSH(false, 8); else if (npend <= 16) SPECTRE_FLUSH(false, 16); else SPECTRE_FLUSH(false, 32);
+        if (npend <= 8) SPECTRE_FLUSH(false, 8); else if (npend <= 16) SPECTRE_FLUSH(false, 16);
+        else if (npend <= 32) SPECTRE_FLUSH(false, 32); else SPECTRE_FLUSH(false, 64);
     }
 #undef SPECTRE_FLUSH
     return hipGetLastError();

@@ -22,10 +22,10 @@ __device__ __forceinline__ unsigned mul_mod(unsigned a, unsigned b, int N) {
     return (((a * (b >> 9)) % (unsigned)N) * 512u + a * (b & 511u)) % (unsigned)N;
 }
 
-// Ring rows of the tokens whose updates are pending, as a kernel argument.
+// Ring rows of the tokens whose updates are pending, or of the tokens of one appended batch, as a kernel argument.
 struct PendingSlots {
     int n;
-    int slot[kMaxPending];
+    int slot[kMaxBatch];
 };
 
 // table index of bin k_start for a root index `mult` per bin, and its advance over 8 bins

@@ -1,0 +1,40 @@
+"""GPU parity of appends of several tokens around the 64 that one sweep over the cache takes, and on rings shorter than
+such a batch (memory rows in front), where a batch is as long as the ring."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import rel_l2, to_device
+from paper_2502_18394_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("N_mem,N_max,T0,appends,io", [
+    (0, 256, 100, (63, 64, 65), "f32"), (0, 512, 510, (127, 128, 129), "bf16"), (0, 256, 0, (1, 2, 66), "f32"),
+    (240, 16, 10, (15, 16, 17, 40), "f32"), (193, 63, 63, (64, 130), "bf16")])
+def test_append(oracle, N_mem, N_max, T0, appends, io):
+    from paper_2502_18394_amd import binding
+    B, H, d = 2, 3, 64
+    print(f"case N_mem={N_mem} N_max={N_max} T0={T0} appends={appends} io={io}", flush=True)
+    c, oc = binding.PrefixCache(B, H, d, N_max, N_mem=N_mem), oracle.MemoryPrefixCache(B, H, d, N_mem, N_max)
+    M = np.random.default_rng(900).standard_normal((B, H, N_mem, d)).astype(np.float32)
+    if N_mem:
+        c.set_memory(torch.from_numpy(M).cuda())
+    v, vs = synth.tokens(901, (B, max(T0, 1), H, d), io)
+    q, qs = synth.tokens(902, (B, max(T0, 1), H, d), io)
+    if T0:
+        c.update(to_device(vs, io), to_device(qs, io))
+        oc.prefill(M.astype(np.float64), v.astype(np.float64), q.astype(np.float64))
+    else:
+        oc.prefill(M.astype(np.float64))
+    for j, T in enumerate(appends):
+        v, vs = synth.tokens(903 + 2 * j, (B, T, H, d), io)
+        q, qs = synth.tokens(904 + 2 * j, (B, T, H, d), io)
+        c.update(to_device(vs, io), to_device(qs, io))
+        for i in range(T):
+            oc.update(v[:, i:i + 1].astype(np.float64), q[:, i:i + 1].astype(np.float64))
+        assert c.t == oc.t
+        assert rel_l2(c.prefix_fft.cpu().numpy(), oc.spec) <= 1e-5
+        assert rel_l2(c.sum_q.cpu().numpy(), oc.sum_q) <= 1e-12
+        assert np.array_equal(c.v_buf.cpu().numpy(), oc.v_buf.astype(np.float32))
