@@ -38,17 +38,58 @@ __host__ __device__ constexpr float cos_pi16(int m) {
 }
 __host__ __device__ constexpr float sin_pi16(int m) { return cos_pi16(m - 8); }
 
-// a * exp(-/+ j 2 pi m/32), m an integer that is constant after unrolling.
+// A factor of the 32nd roots of unity split as W = scale * rotation, scale = its larger component (in magnitude) and the
+// rotation's smaller component a ratio of at most 1: rotating then costs two fused multiply-adds, and the scale is folded
+// into the butterfly that follows (x +- scale * y is one instruction per component as well), so an inner factor costs two
+// instructions instead of four.  16 points: 144 instead of 160 instructions, 32 points: 378 instead of 436.
+__host__ __device__ constexpr float root_scale(int m) {
+    const float c = cos_pi16(m), s = sin_pi16(m);
+    return (c < 0 ? -c : c) >= (s < 0 ? -s : s) ? c : s;
+}
+// a * exp(-/+ j 2 pi m/32) / root_scale(m), m an integer that is constant after unrolling.
 template <bool INV>
-__host__ __device__ __forceinline__ float2 mul_root32(float2 a, int m) {
+__host__ __device__ __forceinline__ float2 rotate_root32(float2 a, int m) {
     m &= 31;
-    if (m == 0) return a;
-    if (m == 16) return make_float2(-a.x, -a.y);
-    if (m == 8) return INV ? make_float2(-a.y, a.x) : make_float2(a.y, -a.x);
-    if (m == 24) return INV ? make_float2(a.y, -a.x) : make_float2(-a.y, a.x);
-    const float c = cos_pi16(m);
-    const float s = INV ? sin_pi16(m) : -sin_pi16(m);
-    return make_float2(a.x * c - a.y * s, a.x * s + a.y * c);
+    const float c = cos_pi16(m), s = INV ? sin_pi16(m) : -sin_pi16(m), ss = INV ? 1.0f : -1.0f;
+    if (m == 0 || m == 16) return a;                                     // scale +-1
+    if (m == 8 || m == 24) return make_float2(-ss * a.y, ss * a.x);
+    if (root_scale(m) == c) {
+        const float t = s / c;
+        return make_float2(fmaf(-t, a.y, a.x), fmaf(t, a.x, a.y));
+    }
+    const float t = c / s;                                               // W = s (t + j); root_scale carries the forward sign
+    return make_float2(ss * fmaf(t, a.x, -a.y), ss * fmaf(t, a.y, a.x));
+}
+__host__ __device__ __forceinline__ float2 fma2(float s, float2 b, float2 a) {   // a + s b
+    return make_float2(fmaf(s, b.x, a.x), fmaf(s, b.y, a.y));
+}
+
+// dft<4> of (x0, m1 x1, m2 x2, m3 x3)
+template <bool INV>
+__host__ __device__ __forceinline__ void dft4_scaled(float2 (&x)[4], float m1, float m2, float m3) {
+    const float2 t0 = fma2(m2, x[2], x[0]), t1 = fma2(-m2, x[2], x[0]);
+    const float2 t2 = fma2(m3 / m1, x[3], x[1]), t3 = fma2(-m3 / m1, x[3], x[1]);      // times m1
+    const float2 jt3 = make_float2(-t3.y, t3.x);
+    x[0] = fma2(m1, t2, t0);
+    x[2] = fma2(-m1, t2, t0);
+    x[1] = fma2(INV ? m1 : -m1, jt3, t1);
+    x[3] = fma2(INV ? -m1 : m1, jt3, t1);
+}
+
+// dft<8> of (x0, m1 x1, ..., m7 x7): two scaled dft<4>, the second with m1 left over for the last butterflies
+template <bool INV>
+__host__ __device__ __forceinline__ void dft8_scaled(float2 (&x)[8], float m1, float m2, float m3, float m4, float m5,
+                                                     float m6, float m7) {
+    float2 a[4] = {x[0], x[2], x[4], x[6]}, b[4] = {x[1], x[3], x[5], x[7]};
+    dft4_scaled<INV>(a, m2, m4, m6);
+    dft4_scaled<INV>(b, m3 / m1, m5 / m1, m7 / m1);
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const float2 r = rotate_root32<INV>(b[u], 4 * u);
+        const float s = m1 * root_scale(4 * u);
+        x[u] = fma2(s, r, a[u]);
+        x[u + 4] = fma2(-s, r, a[u]);
+    }
 }
 
 template <int R, bool INV>
@@ -68,8 +109,9 @@ __host__ __device__ __forceinline__ void dft(float2 (&x)[R]) {
         x[1] = INV ? t1 + jt3 : t1 - jt3;
         x[3] = INV ? t1 - jt3 : t1 + jt3;
     } else {
-        // Cooley-Tukey R = 4 * R2: input j = R2*j1 + j2, output u = u1 + 4*u2.
-        constexpr int R2 = R / 4;
+        // Cooley-Tukey R = 4 * R2: input j = R2*j1 + j2, output u = u1 + 4*u2; the factors W_R^(j2 u1) between the stages
+        // are rotations here and scales of the second stage's inputs.
+        constexpr int R2 = R / 4, W = 32 / R;
         float2 y[R];
 #pragma unroll
         for (int j2 = 0; j2 < R2; ++j2) {
@@ -78,14 +120,24 @@ __host__ __device__ __forceinline__ void dft(float2 (&x)[R]) {
             for (int j1 = 0; j1 < 4; ++j1) t[j1] = x[R2 * j1 + j2];
             dft<4, INV>(t);
 #pragma unroll
-            for (int u1 = 0; u1 < 4; ++u1) y[R2 * u1 + j2] = mul_root32<INV>(t[u1], j2 * u1 * (32 / R));
+            for (int u1 = 0; u1 < 4; ++u1) y[R2 * u1 + j2] = rotate_root32<INV>(t[u1], W * j2 * u1);
         }
 #pragma unroll
         for (int u1 = 0; u1 < 4; ++u1) {
             float2 t[R2];
 #pragma unroll
             for (int j2 = 0; j2 < R2; ++j2) t[j2] = y[R2 * u1 + j2];
-            dft<R2, INV>(t);
+            if constexpr (R2 == 2) {
+                const float m = root_scale(W * u1);
+                const float2 a = t[0], b = t[1];
+                t[0] = fma2(m, b, a);
+                t[1] = fma2(-m, b, a);
+            } else if constexpr (R2 == 4) {
+                dft4_scaled<INV>(t, root_scale(W * u1), root_scale(W * 2 * u1), root_scale(W * 3 * u1));
+            } else {
+                dft8_scaled<INV>(t, root_scale(W * u1), root_scale(W * 2 * u1), root_scale(W * 3 * u1), root_scale(W * 4 * u1),
+                                 root_scale(W * 5 * u1), root_scale(W * 6 * u1), root_scale(W * 7 * u1));
+            }
 #pragma unroll
             for (int u2 = 0; u2 < R2; ++u2) x[u1 + 4 * u2] = t[u2];
         }
