@@ -18,6 +18,7 @@
 #include "gate.h"
 #include "internal.h"
 #include "mix_chirp.h"
+#include "mix_line.h"
 #include "mix_slab.h"
 #include "prefix.h"
 #include "project.h"
@@ -483,7 +484,7 @@ int spectre_prepare(int n, int d) {
             if ((rc = get_slab_order(M, &o, true))) return rc;
         }
     }
-    hipError_t (*const loaders[])() = {load_kernels_mix_pow2, load_kernels_mix_slab, load_kernels_mix_chirp, load_kernels_gate,
+    hipError_t (*const loaders[])() = {load_kernels_mix_pow2, load_kernels_mix_line, load_kernels_mix_slab, load_kernels_mix_chirp, load_kernels_gate,
                                        load_kernels_prefix, load_kernels_decode, load_kernels_project, load_kernels_wrm};
     for (auto load : loaders) {
         const hipError_t e = load();
@@ -623,6 +624,17 @@ int spectre_mix_forward_ex(const void *v, const void *g, void *out, int B, int L
     if (rc) return rc;
     float2 *gp = static_cast<float2 *>(ws);
     char *scr_base = static_cast<char *>(ws) + align256((size_t)BH * L * sizeof(float2));
+    if (line_supported(L, (int)io) && !(flags & SPECTRE_MIX_BF16_SCRATCH)) {
+        // heads per group: as many as the four-step scratch of the workspace holds, 4 instead of 8 bytes per element
+        const MixGroups m = mix_groups(BH, L, d, 1);
+        int chunk = 2 * m.lanes * m.chunk < BH ? 2 * m.lanes * m.chunk : BH;
+        for (int bh0 = 0; bh0 < BH; bh0 += chunk) {
+            hipError_t e = launch_mix_line(v, static_cast<const float2 *>(g), out, gp, scr_base, pl.twL, L, H, bh0,
+                                           BH - bh0 < chunk ? BH - bh0 : chunk, st);
+            if (e != hipSuccess) return fail_hip(e, "mix_line");
+        }
+        return SPECTRE_OK;
+    }
     // on request, bf16 rows only: complex numbers cross between the three kernels as two bfloat16 instead of two
     // fp32, and twice the heads fit in a lane's scratch
     const bool scr16 = (io == SPECTRE_BF16) && (flags & SPECTRE_MIX_BF16_SCRATCH);

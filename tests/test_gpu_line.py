@@ -1,0 +1,25 @@
+"""GPU parity of the whole-column mixer (bf16 rows, L = 8192 and 16384): head counts that are and are not multiples of
+the eight XCDs, one, two and four lines per workgroup, heads taken in several groups."""
+import numpy as np
+import pytest
+import torch
+
+from gpu_util import TOL, assert_close_elementwise, from_device, rel_l2, to_device
+from paper_2502_18394_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("B,L,H,mb", [(1, 8192, 1, 0), (3, 8192, 3, 0), (1, 8192, 32, 0), (2, 8192, 9, 8),
+                                      (1, 16384, 1, 0), (2, 16384, 5, 0), (1, 16384, 16, 16)])
+def test_whole_column_mixer(oracle, options, B, L, H, mb):
+    from paper_2502_18394_amd import binding
+    print(f"case B={B} L={L} H={H} mb={mb}", flush=True)
+    if mb:
+        options(binding.OPT_SCRATCH_MB, mb)
+    v, vs = synth.tokens(1000 + L + H, (B, L, H, 64), "bf16")
+    g = synth.random_gate(1001 + H, B, H, L)
+    got = from_device(binding.mix_forward(to_device(vs, "bf16"), torch.from_numpy(g).cuda()))
+    want = oracle.mix_forward(v.astype(np.float64), g.astype(np.complex128))
+    assert rel_l2(got, want) <= TOL["bf16"]
+    assert_close_elementwise(got, want, "bf16", L)
