@@ -751,20 +751,16 @@ int spectre_gate(const void *q, int q_is_pooled, spectre_dtype q_dtype, double i
     char *w = static_cast<char *>(ws);
     double *partial = reinterpret_cast<double *>(w);
     w += align256(gate_partial_bytes(B, L, H, P->d));
-    double *sum_ws = reinterpret_cast<double *>(w);
-    w += align256((size_t)B * H * P->d * sizeof(double));
     float *hid = reinterpret_cast<float *>(w);
     w += align256((size_t)B * H * P->d_g * sizeof(float));
     float2 *raw = reinterpret_cast<float2 *>(w);
-    const double *sum_q = static_cast<const double *>(q);
-    if (!q_is_pooled) {
-        hipError_t e = launch_pool((int)q_dtype, q, partial, sum_ws, B, L, H, P->d, st);
-        if (e != hipSuccess) return fail_hip(e, "pool");
-        sum_q = sum_ws;
-    }
-    hipError_t e = launch_gate_mlp(sum_q, inv_count, gate_dev(P), hid, raw, B, H, phase_pos % P->n_fft,
-                                   static_cast<float2 *>(g_out), st);
-    if (e != hipSuccess) return fail_hip(e, "gate_mlp");
+    const long long phase = phase_pos % P->n_fft;
+    const hipError_t e =
+        q_is_pooled ? launch_gate_mlp(static_cast<const double *>(q), inv_count, gate_dev(P), hid, raw, B, H, phase,
+                                      static_cast<float2 *>(g_out), st)
+                    : launch_gate((int)q_dtype, q, partial, inv_count, gate_dev(P), hid, raw, B, L, H, phase,
+                                  static_cast<float2 *>(g_out), st);
+    if (e != hipSuccess) return fail_hip(e, "gate");
     return SPECTRE_OK;
 }
 
@@ -934,8 +930,8 @@ int spectre_wrm_apply_coeff(const void *v, const void *s, void *out, int B, int 
 struct LayerLayout {
     bool fused;                   // projection inside the row transforms (four-step route, bf16 rows)
     bool sums;                    // block sums from the inverse row transforms feed the refinement
-    size_t partial, sum_x, sum_q, hid, raw, g, wpack, mix, vbuf, s, wrm, bsum;
-    size_t total() const { return partial + sum_x + sum_q + hid + raw + g + wpack + mix + vbuf + s + wrm + bsum; }
+    size_t partial, sum_q, hid, raw, g, wpack, mix, vbuf, s, wrm, bsum;
+    size_t total() const { return partial + sum_q + hid + raw + g + wpack + mix + vbuf + s + wrm + bsum; }
 };
 static LayerLayout layer_layout(int B, int L, int H, int d, spectre_dtype io, const spectre_gate_params *P,
                                 const spectre_wrm_params *W) {
@@ -946,7 +942,7 @@ static LayerLayout layer_layout(int B, int L, int H, int d, spectre_dtype io, co
     const size_t pool = align256(gate_partial_bytes(B, L, H, d));
     const size_t proj = align256((size_t)B * project_chunks(L) * H * d * sizeof(double));
     y.partial = pool > proj ? pool : proj;
-    y.sum_x = y.sum_q = align256(BH * d * sizeof(double));
+    y.sum_q = align256(BH * d * sizeof(double));
     y.hid = align256(BH * P->d_g * sizeof(float));
     y.raw = gate_raw_bytes(B, H, P);
     y.g = align256(BH * (size_t)(L / 2 + 1) * sizeof(float2));
@@ -1010,7 +1006,6 @@ int spectre_layer_forward(const void *x, const float *Wq, const float *Wv, int H
     char *w = static_cast<char *>(ws);
     auto take = [&](size_t n) { char *p0 = w; w += n; return p0; };
     double *partial = reinterpret_cast<double *>(take(y.partial));
-    double *sum_x = reinterpret_cast<double *>(take(y.sum_x));
     double *sum_q = reinterpret_cast<double *>(take(y.sum_q));
     float *hid = reinterpret_cast<float *>(take(y.hid));
     float2 *raw = reinterpret_cast<float2 *>(take(y.raw));
@@ -1043,20 +1038,20 @@ int spectre_layer_forward(const void *x, const float *Wq, const float *Wv, int H
     if (y.fused) {
         // pooled query: sum_q = (sum_l x_l) W_q (pooling commutes with the projection); the rows of X are read once
         // more by the row transforms, V itself never exists in memory
-        e = launch_pool((int)io, x, partial, sum_x, B, L, H, d, st);
+        e = launch_pool_partial((int)io, x, partial, B, L, H, d, st);
         if (e != hipSuccess) return fail_hip(e, "pool(x)");
         e = launch_pack_w(Wv, Hw, wpack, st);
         if (e != hipSuccess) return fail_hip(e, "pack_w");
     } else {
         e = launch_project((int)io, x, Wq, Wv, Hw, vbuf, nullptr, partial, B, L, H, st);
         if (e != hipSuccess) return fail_hip(e, "project");
-        e = launch_pool_final(partial, sum_x, B, H * d, project_chunks(L), st);
-        if (e != hipSuccess) return fail_hip(e, "pool_final");
     }
-    e = launch_project_pooled(sum_x, Wq, Hw, B, H, sum_q, st);
-    if (e != hipSuccess) return fail_hip(e, "project_pooled");
-    e = launch_gate_mlp(sum_q, 1.0 / (double)L, gate_dev(P), hid, raw, B, H, 0, g, st);
-    if (e != hipSuccess) return fail_hip(e, "gate_mlp");
+    const GateDev gd = gate_dev(P);
+    e = launch_gate_prep(partial, y.fused ? pool_chunks(B, L, H, d) : project_chunks(L), Wq, Hw, W ? sum_q : nullptr,
+                         1.0 / (double)L, gd, hid, B, H, st);
+    if (e != hipSuccess) return fail_hip(e, "gate_prep");
+    e = launch_gate_out(hid, gd, raw, B, H, 0, g, st);
+    if (e != hipSuccess) return fail_hip(e, "gate_out");
     if (y.fused) {
         float2 *gp = reinterpret_cast<float2 *>(mix_ws);
         char *scr_base = mix_ws + align256((size_t)BH * L * sizeof(float2));

@@ -16,34 +16,11 @@
 #include "prefix.h"
 
 #include "common.h"
+#include "fold16.h"
 #include "gate.h"
 #include "prefix_dev.h"
 
 namespace spectre {
-
-// Sum over the 16 lanes of a DPP row of 16 values per lane: lane i of a row returns the row's total of value i.
-// Reversals of 16, 8, 4 and 2 lanes pair every lane with one that differs in the halving bit, so each step adds the
-// half a lane keeps to the half its partner gives away (15 additions instead of 64).
-template <int M>
-__device__ __forceinline__ float partner16(float v) {
-    constexpr int ctrl = (M == 8) ? 0x140 : (M == 4) ? 0x141 : (M == 2) ? 0x1B : 0xB1;   // reverse 16, 8, 4, 2 lanes
-    return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), ctrl, 0xF, 0xF, false));
-}
-template <int M>
-__device__ __forceinline__ void fold16(float (&p)[16], int i) {
-    const bool up = i & M;
-#pragma unroll
-    for (int j = 0; j < M; ++j) {
-        const float keep = up ? p[j + M] : p[j], give = up ? p[j] : p[j + M];
-        p[j] = keep + partner16<M>(give);
-    }
-}
-
-__device__ __forceinline__ double wave_sum(double x) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
-    return x;
-}
 
 struct DecodeRing {                    // the ring state as it was before this token, and the token itself
     const void *v_t, *q_t;             // [B, 1, H, 64]

@@ -28,6 +28,21 @@ hipError_t launch_pool(int io, const void *q, double *partial, double *sum_q, in
 hipError_t launch_pool_final(const double *partial, double *sum, int B, int row, int nchunks, hipStream_t st,
                              bool accumulate = false);
 
+// The two halves of launch_pool: partial [B][pool_chunks][H*d].
+int pool_chunks(int B, int L, int H, int d);
+hipError_t launch_pool_partial(int io, const void *q, double *partial, int B, int L, int H, int d, hipStream_t st);
+
+// hid [B,H,d_g] from partial sums [B][nchunks][H*d] of the query rows, or (Wq != nullptr, d = 64) of the rows X that
+// W_q [Hw,64,64] turns into queries; sum_q, if not nullptr, receives the pooled query [B,H,d].
+hipError_t launch_gate_prep(const double *partial, int nchunks, const float *Wq, int Hw, double *sum_q, double inv_count,
+                            const GateDev &P, float *hid, int B, int H, hipStream_t st);
+// g from hid: output layer, modReLU, Toeplitz update, phase.
+hipError_t launch_gate_out(const float *hid, const GateDev &P, float2 *raw, int B, int H, long long phase, float2 *g,
+                           hipStream_t st);
+// The whole gate from query rows q [B,L,H,d]; scratch partial (gate_partial_bytes), hid, raw as above.
+hipError_t launch_gate(int io, const void *q, double *partial, double inv_count, const GateDev &P, float *hid, float2 *raw,
+                       int B, int L, int H, long long phase, float2 *g, hipStream_t st);
+
 // g [B,H,F] from sum_q; hid is scratch [B,H,d_g]; raw is scratch [B,H,F] complex, only used when
 // P.toeplitz is set; phase already reduced modulo n_fft.
 hipError_t launch_gate_mlp(const double *sum_q, double inv_count, const GateDev &P, float *hid, float2 *raw,

@@ -1,14 +1,16 @@
 // Content-adaptive spectral gate (Sec. 3.2 step 3a, 3c; positional phase of Sec. 3.5;
 // Algorithm 1's decode gate) for gfx950.
 //
-//   pool    : sum of the query rows over positions, accumulated in fp64 in a fixed order
-//   hidden  : x = inv_count * sum;  qbar = LayerNorm(x);  hid = GELU(qbar W1 + b1)
+//   pool    : sum of the query rows over positions, accumulated in fp64 in a fixed order (short sequences: one kernel
+//             for everything, k_gate_small)
+//   prep    : x = inv_count * sum;  qbar = LayerNorm(x);  hid = GELU(qbar W1 + b1)
 //   out     : u = W2 hid + b2 on the matrix cores (fp32 MFMA, v_mfma_f32_4x4x1_16B_f32: 64
 //             output reals x 4 rows per instruction), with bias and modReLU in the epilogue
 //   phase   : the positional phase, a separate pass over g, only when a position is given
 #include "gate.h"
 
 #include "common.h"
+#include "fold16.h"
 
 namespace spectre {
 
@@ -123,48 +125,126 @@ __global__ __launch_bounds__(256) void k_pool_final(const double *__restrict__ p
 }
 
 // ------------------------------------------------------------------------------------------
-// hidden: one workgroup per (b, h).  LayerNorm statistics in fp64 (d <= 256 values, one per lane: two tree
-// reductions in a fixed order), then the small d x d_g product on the vector units with the d terms of an output
-// split over 256 / d_g lane groups (fixed split, partial sums added in group order).
-__device__ __forceinline__ double block_sum_256(double x, double *red, int lane, int wave) {
+// prep: one workgroup of 512 lanes per (b, h), from the pooling pass's partial sums to the hidden layer: the chunks'
+// sums (fp64, fixed order), optionally times W_q (the sums are then those of X: pooling commutes with the projection),
+// LayerNorm with fp64 statistics, and the small d x d_g product on the vector units, its d terms split over lane groups
+// (fixed split, partial sums added in group order).  sum_q != nullptr: the pooled query is also stored.
+// One dependent launch where there were two (three with W_q): 5 us each at any size.
+constexpr int kPrepLanes = 512;
+
+__device__ __forceinline__ double block_sum_512(double x, double *red, int lane, int wave) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
     if (lane == 0) red[wave] = x;
     __syncthreads();
-    return (red[0] + red[1]) + (red[2] + red[3]);
+    return ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
 }
 
-__global__ __launch_bounds__(256) void k_gate_hidden(const double *__restrict__ sum_q, double inv_count,
-                                                     const float *__restrict__ gamma,
-                                                     const float *__restrict__ beta, float eps,
-                                                     const float *__restrict__ W1,
-                                                     const float *__restrict__ b1, float *__restrict__ hid,
-                                                     int H, int Hg, int d, int dg) {
-    __shared__ float qbar[256];
-    __shared__ float part[256];
-    __shared__ double red[8];
-    const int bh = blockIdx.x, h = bh % H, hp = (Hg == 1) ? 0 : h;
+__global__ __launch_bounds__(kPrepLanes) void k_gate_prep(const double *__restrict__ partial, int nchunks,
+                                                          const float *__restrict__ Wq, int Hw,
+                                                          double *__restrict__ sum_q, double inv_count, GateDev P,
+                                                          float *__restrict__ hid, int H) {
+    __shared__ double2 acc[kPrepLanes];
+    __shared__ double xs[256], red[16];
+    __shared__ float qbar[256], part[kPrepLanes];
+    const int bh = blockIdx.x, b = bh / H, h = bh % H, hp = (P.Hg == 1) ? 0 : h, d = P.d, dg = P.d_g;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const double x = (tid < d) ? inv_count * sum_q[(size_t)bh * d + tid] : 0.0;
-    const double mean = block_sum_256(x, red, lane, wave) / d;
-    const double dev = (tid < d) ? x - mean : 0.0;
-    const double var = block_sum_256(dev * dev, red + 4, lane, wave) / d;
-    const double rstd = 1.0 / sqrt(var + (double)eps);
-    if (tid < d) qbar[tid] = (float)((double)gamma[hp * d + tid] * dev * rstd + (double)beta[hp * d + tid]);
+    // the weights' latency passes behind the sums (the usual widths only; any other is read where it is used)
+    const bool usual = d == 64 && dg == 64;
+    float w1[8], wq[8], gam = 0.f, bet = 0.f, b1 = 0.f;
+    if (usual) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) w1[i] = P.W1[(size_t)hp * 4096 + (8 * wave + i) * 64 + lane];
+        gam = P.ln_gamma[hp * 64 + lane];
+        bet = P.ln_beta[hp * 64 + lane];
+        b1 = P.b1[hp * 64 + lane];
+    }
+    if (Wq) {
+#pragma unroll
+        for (int i = 0; i < 8; ++i) wq[i] = Wq[(size_t)((Hw == 1) ? 0 : h) * 4096 + (8 * wave + i) * 64 + lane];
+    }
+    const int np = d / 2, ng = kPrepLanes / np, p = tid % np, grp = tid / np;
+    double2 s = make_double2(0.0, 0.0);
+    if (grp < ng) {
+        const size_t row = (size_t)H * np;
+        const double2 *src = reinterpret_cast<const double2 *>(partial) + (size_t)b * nchunks * row + (size_t)h * np + p;
+        int c = grp;
+        for (; c + 7 * ng < nchunks; c += 8 * ng) {      // eight loads in flight, added in chunk order
+            double2 t[8];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) t[i] = src[(size_t)(c + i * ng) * row];
+#pragma unroll
+            for (int i = 0; i < 8; ++i) { s.x += t[i].x; s.y += t[i].y; }
+        }
+        for (; c < nchunks; c += ng) {
+            const double2 t = src[(size_t)c * row];
+            s.x += t.x;
+            s.y += t.y;
+        }
+    }
+    acc[tid] = s;
     __syncthreads();
-    const int nseg = (dg <= 64) ? 4 : (dg <= 128) ? 2 : 1, cols = 256 / nseg;
+    if (tid < np) {
+        double2 t = acc[tid];
+        for (int r = 1; r < ng && r < nchunks; ++r) { t.x += acc[r * np + tid].x; t.y += acc[r * np + tid].y; }
+        xs[2 * tid] = t.x;
+        xs[2 * tid + 1] = t.y;
+    }
+    __syncthreads();
+    if (Wq) {                                            // d = 64: lane (j, seg) takes 8 of the 64 terms of output j
+        double t = 0.0;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t += xs[8 * wave + i] * (double)wq[i];
+        double *a = reinterpret_cast<double *>(acc);
+        a[tid] = t;
+        __syncthreads();
+        if (tid < 64) {
+            double q = a[tid];
+#pragma unroll
+            for (int r = 1; r < 8; ++r) q += a[64 * r + tid];
+            xs[tid] = q;
+        }
+        __syncthreads();
+    }
+    if (sum_q && tid < d) sum_q[(size_t)bh * d + tid] = xs[tid];
+    if (usual) {                                         // every wave normalises for itself (lane = channel)
+        const double x = inv_count * xs[lane];
+        const double dev = x - wave_sum(x) / 64;
+        const double rstd = 1.0 / sqrt(wave_sum(dev * dev) / 64 + (double)P.ln_eps);
+        const float qv = (float)((double)gam * dev * rstd + (double)bet);
+        float a = 0.f;
+#pragma unroll
+        for (int i = 0; i < 8; ++i) a = fmaf(__shfl(qv, 8 * wave + i), w1[i], a);
+        part[tid] = a;
+        __syncthreads();
+        if (tid < 64) {
+            float t = b1;
+#pragma unroll
+            for (int q = 0; q < 8; ++q) t += part[64 * q + tid];
+            hid[(size_t)bh * 64 + tid] = 0.5f * t * (1.0f + erff(t * 0.70710678118654752440f));
+        }
+        return;
+    }
+    const double x = (tid < d) ? inv_count * xs[tid] : 0.0;
+    const double mean = block_sum_512(x, red, lane, wave) / d;
+    const double dev = (tid < d) ? x - mean : 0.0;
+    const double var = block_sum_512(dev * dev, red + 8, lane, wave) / d;
+    const double rstd = 1.0 / sqrt(var + (double)P.ln_eps);
+    if (tid < d) qbar[tid] = (float)((double)P.ln_gamma[hp * d + tid] * dev * rstd + (double)P.ln_beta[hp * d + tid]);
+    __syncthreads();
+    const int nseg = (dg <= 64) ? 8 : (dg <= 128) ? 4 : 2, cols = kPrepLanes / nseg;
     const int jcol = tid % cols, seg = tid / cols;
     const int dseg = (d + nseg - 1) / nseg, i0 = seg * dseg, i1 = (i0 + dseg < d) ? i0 + dseg : d;
     float a = 0.f;
     if (jcol < dg) {
-        const float *w = W1 + (size_t)hp * d * dg + jcol;
+        const float *w = P.W1 + (size_t)hp * d * dg + jcol;
 #pragma unroll 8
         for (int i = i0; i < i1; ++i) a = fmaf(qbar[i], w[(size_t)i * dg], a);
     }
     part[tid] = a;
     __syncthreads();
     if (tid < dg) {
-        float t = b1[hp * dg + tid];
+        float t = P.b1[hp * dg + tid];
         for (int q = 0; q < nseg; ++q) t += part[q * cols + tid];
         hid[(size_t)bh * dg + tid] = 0.5f * t * (1.0f + erff(t * 0.70710678118654752440f));
     }
@@ -242,13 +322,22 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
                                                   const float *__restrict__ mbias, float2 *__restrict__ g,
                                                   int B, int H, int Hg, int dg, int F, int r_base0) {
     extern __shared__ float hs[];
-    const int r_base = r_base0 + 32 * (int)blockIdx.z;   // blockIdx.z: 32-row tile of the rows (sequences)                    // [4*RG][dgs] hidden rows of this pass, zero padded
+    const int r_base = r_base0 + 4 * RG * (int)blockIdx.z;   // blockIdx.z: tile of the rows (sequences)                    // [4*RG][dgs] hidden rows of this pass, zero padded
     const int dgp = (dg + 3) & ~3, dgs = dgp + 4;    // row stride padded against bank conflicts
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int twoF = 2 * F;
     const int hsel = blockIdx.y;                     // head of this block when weights are per head
     const int hp = (Hg == 1) ? 0 : hsel;
     const int M = (Hg == 1) ? B * H : B;
+    const int ntiles = (twoF + 63) / 64;
+    const float *w2h = W2 + (size_t)hp * twoF * dg;
+    // the fast path's first tile is requested before anything else (with more than two row groups the registers it would
+    // hold meanwhile cost a wave per SIMD)
+    constexpr bool kEarly = RG <= 2;
+    const int lr = lane >> 3, lc = 4 * (lane & 7), tstep = gridDim.x * 4;
+    int ftile = blockIdx.x * 4 + wave;
+    float4 a[16];
+    if (kEarly && VEC && dg == 64 && ftile < ntiles) gate_load_tile(a, w2h, ftile, lr, lc, twoF);
     for (int idx = threadIdx.x; idx < 4 * RG * dgs; idx += 256) {
         const int rr = idx / dgs, j = idx % dgs, r = r_base + rr;
         float v = 0.f;
@@ -257,20 +346,14 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
     }
     __syncthreads();
     const int jrow = lane & 3;
-    const int ntiles = (twoF + 63) / 64;
     // per-wave staging tile [64 rows][kTileStride floats]: filled with fully coalesced 16-byte
     // loads (a wave instruction covers 4 whole rows of 64 weights), read back one row per lane
     float *tile_w = hs + 4 * RG * dgs + wave * (64 * ((VEC && dg == 64) ? kHalfStride : kTileStride));
-    const float *w2h = W2 + (size_t)hp * twoF * dg;
     if (VEC && dg == 64) {
         // fast path (one 64-wide slab per tile), software pipelined: the next tile's weights and this
         // tile's bias terms are in flight while the matrix cores work on the staged tile
-        const int lr = lane >> 3, lc = 4 * (lane & 7);
-        const int tstep = gridDim.x * 4;
-        int tile = blockIdx.x * 4 + wave;
-        float4 a[16];
-        if (tile < ntiles) gate_load_tile(a, w2h, tile, lr, lc, twoF);
-        for (; tile < ntiles; tile += tstep) {
+        if (!kEarly && ftile < ntiles) gate_load_tile(a, w2h, ftile, lr, lc, twoF);
+        for (int tile = ftile; tile < ntiles; tile += tstep) {
             floatx4 acc[RG];
 #pragma unroll
             for (int q = 0; q < RG; ++q) acc[q] = floatx4{0.f, 0.f, 0.f, 0.f};
@@ -371,6 +454,128 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
     }
 }
 
+// ------------------------------------------------------------------------------------------
+// short sequences: everything in one launch.  A workgroup pools the rows of one (b, h) itself (fp64), normalises,
+// evaluates the hidden layer, and emits tiles of 64 output reals, one per wave at a time; grid (parts, B*H), the parts of
+// a head repeat the pooling from L2.
+// What bounds it is the chain of latencies (rows, first layer, output layer): the first tile's weights are requested
+// before the rows.  Against the pooling, prep and output launches: B=1 H=32 bf16 L=512 26.3 -> 20.2 us for a step of
+// gate and mixer, B=256 H=12 fp32 L=196 120 -> 105 us.
+// A lane's four weights of row 4 s + lane / 16 of a tile meet the hidden values, summed over the 16 lanes (fold16).
+template <bool BF16, int NT>
+__global__ __launch_bounds__(NT, 4) void k_gate_small(const void *__restrict__ q, double inv_count, GateDev P,
+                                                    const float *__restrict__ act_bias, float2 *__restrict__ g,
+                                                    int L, int H, int F, int ntiles) {
+    constexpr int NCH = BF16 ? 8 : 4, LPR = 64 / NCH, RPW = 64 / LPR;   // channels per lane, lanes per row, rows per wave
+    constexpr int NW = NT / 64, IPW = 64 / NW;                              // waves; first-layer inputs per wave
+    __shared__ double psum[NW][64];
+    __shared__ float qb[NW][64], part[NW][64];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int bh = blockIdx.y, b = bh / H, h = bh % H, hp = (P.Hg == 1) ? 0 : h, twoF = 2 * F;
+    // tile t = the 64 rows of W2 from tile_row(t) on: the last one is moved back to end with the matrix (2F >= 64), so that
+    // every access is in range without a test per row; its overlap is computed twice, to the same bits
+    const float4 *w2 = reinterpret_cast<const float4 *>(P.W2 + (size_t)hp * twoF * 64) + lane;
+    auto tile_row = [&](int t) { return min(64 * t, twoF - 64); };
+    int tile = __builtin_amdgcn_readfirstlane(blockIdx.x * NW + wave);
+    float4 a[16];
+    auto request = [&](int t) {
+        const float4 *src = w2 + (size_t)tile_row(t) * 16;
+#pragma unroll
+        for (int s = 0; s < 16; ++s) a[s] = src[64 * s];
+    };
+    // the small operands first, so that their latency passes behind the rows
+    const float gam = P.ln_gamma[hp * 64 + lane], bet = P.ln_beta[hp * 64 + lane], b1 = P.b1[hp * 64 + lane];
+    float w1[IPW];
+#pragma unroll
+    for (int i = 0; i < IPW; ++i) w1[i] = P.W1[(size_t)hp * 4096 + (IPW * wave + i) * 64 + lane];
+
+    const size_t rs = (size_t)H * LPR;                                  // 16-byte pieces per token row
+    const int r0 = tid / LPR;
+    // 16 bytes at any 4-byte boundary, so that the tensor's alignment does not change the order of the additions
+    typedef uint32_t u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));
+    const u32x4_a4 *src = reinterpret_cast<const u32x4_a4 *>(q) + ((size_t)b * L + r0) * rs + (size_t)h * LPR + (lane % LPR);
+    double sum[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) sum[c] = 0.0;
+    constexpr int RPS = NW * RPW, kU = 8;                                // rows per sweep, sweeps in flight
+    for (int l = r0; l < L; l += RPS * kU) {
+        u32x4_a4 w[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            w[u] = u32x4_a4{0, 0, 0, 0};
+            if (l + RPS * u < L) w[u] = src[(size_t)RPS * u * rs];
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (BF16) {
+                    const float2 v = IoBf16::unpack(w[u][i]);
+                    sum[(2 * i) % NCH] += (double)v.x;
+                    sum[(2 * i + 1) % NCH] += (double)v.y;
+                } else {
+                    sum[i] += (double)__uint_as_float(w[u][i]);
+                }
+            }
+        }
+        src += (size_t)RPS * kU * rs;
+    }
+#pragma unroll
+    for (int off = LPR; off < 64; off <<= 1) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) sum[c] += __shfl_xor(sum[c], off);
+    }
+    if (tile < ntiles) request(tile);                            // in flight during the first layer
+    if (lane < LPR) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) psum[wave][NCH * lane + c] = sum[c];
+    }
+    __syncthreads();
+    {   // every wave repeats the LayerNorm for itself (lane = channel)
+        double t = psum[0][lane];
+#pragma unroll
+        for (int r = 1; r < NW; ++r) t += psum[r][lane];
+        const double x = inv_count * t;
+        const double dev = x - wave_sum(x) / 64;
+        const double rstd = 1.0 / sqrt(wave_sum(dev * dev) / 64 + (double)P.ln_eps);
+        qb[wave][lane] = (float)((double)gam * dev * rstd + (double)bet);
+    }
+    __builtin_amdgcn_wave_barrier();
+    {   // first layer: wave w takes inputs IPW w .. IPW w + IPW - 1, lane = hidden unit
+        float t = 0.f;
+#pragma unroll
+        for (int i = 0; i < IPW; ++i) t = fmaf(qb[wave][IPW * wave + i], w1[i], t);
+        part[wave][lane] = t;
+    }
+    __syncthreads();
+    {
+        float t = b1;
+#pragma unroll
+        for (int r = 0; r < NW; ++r) t += part[r][lane];
+        qb[wave][lane] = 0.5f * t * (1.0f + erff(t * 0.70710678118654752440f));
+    }
+    __builtin_amdgcn_wave_barrier();
+    const float4 hv = *reinterpret_cast<const float4 *>(&qb[wave][4 * (lane & 15)]);
+    for (int first = tile; tile < ntiles; tile += NW * gridDim.x) {
+        if (tile != first) request(tile);
+        float p[16];
+#pragma unroll
+        for (int s = 0; s < 16; ++s) p[s] = fmaf(a[s].x, hv.x, fmaf(a[s].y, hv.y, fmaf(a[s].z, hv.z, a[s].w * hv.w)));
+        fold16<8>(p, lane);
+        fold16<4>(p, lane);
+        fold16<2>(p, lane);
+        fold16<1>(p, lane);
+        // lane holds real tile_row + 4 (lane % 16) + lane / 16: the imaginary part of an even one sits 16 lanes further
+        const float other = __shfl_xor(p[0], 16);
+        const int k = tile_row(tile) / 2 + 2 * (lane & 15) + (lane >> 5);
+        if (!(lane & 16)) {
+            const float2 bias = *reinterpret_cast<const float2 *>(P.b2 + ((size_t)hp * F + k) * 2);
+            gate_store_bin(g + (size_t)bh * F + k, p[0] + bias.x, other + bias.y, act_bias != nullptr,
+                           act_bias ? act_bias[(size_t)hp * F + k] : 0.0f);
+        }
+    }
+}
+
 // Toeplitz low-rank update (Sec. 3.2 step 3b) followed by modReLU (step 3c):
 //   g_k = act( raw_k + sum_{m=-r..r} t_m raw_{k-m} ),  raw = 0 outside 0..F-1.   One lane per bin.
 __global__ __launch_bounds__(256) void k_gate_toeplitz(const float2 *__restrict__ raw, const float2 *__restrict__ taps,
@@ -425,8 +630,12 @@ size_t gate_partial_bytes(int B, int L, int H, int d) {
     return (size_t)B * nchunks * H * d * sizeof(double);
 }
 
-hipError_t launch_pool(int io, const void *q, double *partial, double *sum_q, int B, int L, int H, int d,
-                       hipStream_t st) {
+int pool_chunks(int B, int L, int H, int d) {
+    const int rows = pool_rows(B, L, H, d);
+    return (L + rows - 1) / rows;
+}
+
+hipError_t launch_pool_partial(int io, const void *q, double *partial, int B, int L, int H, int d, hipStream_t st) {
     const int ppr = H * d / 2;
     const int rows = pool_rows(B, L, H, d);
     const int nchunks = (L + rows - 1) / rows;
@@ -444,9 +653,14 @@ hipError_t launch_pool(int io, const void *q, double *partial, double *sum_q, in
     else
         k_pool_partial<IoF32><<<grid, 256, 0, st>>>(static_cast<const float2 *>(q),
                                                     reinterpret_cast<double2 *>(partial), L, ppr, rows, nchunks);
-    hipError_t e = hipGetLastError();
+    return hipGetLastError();
+}
+
+hipError_t launch_pool(int io, const void *q, double *partial, double *sum_q, int B, int L, int H, int d,
+                       hipStream_t st) {
+    const hipError_t e = launch_pool_partial(io, q, partial, B, L, H, d, st);
     if (e != hipSuccess) return e;
-    k_pool_final<<<dim3((H * d + 31) / 32, B), 256, 0, st>>>(partial, sum_q, H * d, nchunks, 0);
+    k_pool_final<<<dim3((H * d + 31) / 32, B), 256, 0, st>>>(partial, sum_q, H * d, pool_chunks(B, L, H, d), 0);
     return hipGetLastError();
 }
 
@@ -456,12 +670,77 @@ hipError_t launch_pool_final(const double *partial, double *sum, int B, int row,
     return hipGetLastError();
 }
 
+hipError_t launch_gate_prep(const double *partial, int nchunks, const float *Wq, int Hw, double *sum_q, double inv_count,
+                            const GateDev &P, float *hid, int B, int H, hipStream_t st) {
+    if (Wq && P.d != 64) return hipErrorInvalidValue;
+    k_gate_prep<<<B * H, kPrepLanes, 0, st>>>(partial, nchunks, Wq, Hw, sum_q, inv_count, P, hid, H);
+    return hipGetLastError();
+}
+
+// Toeplitz update and positional phase, the passes over g behind the output layer.
+static hipError_t launch_gate_tail(const GateDev &P, const float2 *raw, int B, int H, long long phase, float2 *g,
+                                   hipStream_t st) {
+    const int F = P.n_fft / 2 + 1;
+    const size_t total = (size_t)B * H * F;
+    if (P.toeplitz) {
+        k_gate_toeplitz<<<(unsigned)((total + 255) / 256), 256, 0, st>>>(raw, P.toeplitz, P.modrelu_bias, g, H, P.Hg, F,
+                                                                         P.toeplitz_r, total);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    if (phase == 0) return hipSuccess;
+    k_gate_phase<<<(unsigned)((total + 255) / 256), 256, 0, st>>>(g, F, P.n_fft, phase, total);
+    return hipGetLastError();
+}
+
+// Short sequences: up to 256 KB of rows per head (B=1 H=32, step of gate and mixer: bf16 L=2048 46.0 -> 42.8 us, L=4096
+// would be 50.4 -> 53.8), unless several sequences would each read a head's output weights of more than 320 KB again
+// (B=8 H=32 L=1024, 263 KB: 82.1 -> 77.9 us; B=4 L=2048, 525 KB: 82.3 -> 88.4).
+static bool gate_small(int io, const GateDev &P, int B, int L, int H) {
+    const int F = P.n_fft / 2 + 1;
+    const size_t rows = (size_t)L * 64 * (io ? 2 : 4), w2 = (size_t)2 * F * 64 * 4;
+    if (P.d != 64 || P.d_g != 64 || F < 32 || rows > ((size_t)256 << 10)) return false;
+    if ((reinterpret_cast<uintptr_t>(P.W2) & 15) || (reinterpret_cast<uintptr_t>(P.b2) & 7)) return false;
+    return (long long)B * H <= 65535 && (B == 1 || w2 <= ((size_t)320 << 10));
+}
+
+hipError_t launch_gate(int io, const void *q, double *partial, double inv_count, const GateDev &P, float *hid, float2 *raw,
+                       int B, int L, int H, long long phase, float2 *g, hipStream_t st) {
+    if (gate_small(io, P, B, L, H)) {
+        const int F = P.n_fft / 2 + 1, ntiles = (2 * F + 63) / 64;
+        // Few heads: 16 waves each, so that a head's rows are in flight together; many: 4 waves, four workgroups on a
+        // compute unit.  Parts of a head: one wave per tile, while that leaves the pooling repeated in less than two
+        // workgroups per compute unit.
+        const bool wide = B * H < 256;
+        int parts = (ntiles + (wide ? 15 : 3)) / (wide ? 16 : 4);
+        while (parts > 1 && (long long)parts * B * H > 512) parts = (parts + 1) / 2;
+        const float *act = P.toeplitz ? nullptr : P.modrelu_bias;
+        float2 *out = P.toeplitz ? raw : g;
+        const dim3 grid(parts, B * H);
+#define SPECTRE_GATE_SMALL(BF, NT) k_gate_small<BF, NT><<<grid, NT, 0, st>>>(q, inv_count, P, act, out, L, H, F, ntiles)
+        if (io) { if (wide) SPECTRE_GATE_SMALL(true, 1024); else SPECTRE_GATE_SMALL(true, 256); }
+        else { if (wide) SPECTRE_GATE_SMALL(false, 1024); else SPECTRE_GATE_SMALL(false, 256); }
+#undef SPECTRE_GATE_SMALL
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        return launch_gate_tail(P, raw, B, H, phase, g, st);
+    }
+    hipError_t e = launch_pool_partial(io, q, partial, B, L, H, P.d, st);
+    if (e != hipSuccess) return e;
+    e = launch_gate_prep(partial, pool_chunks(B, L, H, P.d), nullptr, 1, nullptr, inv_count, P, hid, B, H, st);
+    if (e != hipSuccess) return e;
+    return launch_gate_out(hid, P, raw, B, H, phase, g, st);
+}
+
 hipError_t launch_gate_mlp(const double *sum_q, double inv_count, const GateDev &P, float *hid, float2 *raw,
                            int B, int H, long long phase, float2 *g, hipStream_t st) {
-    k_gate_hidden<<<B * H, 256, 0, st>>>(sum_q, inv_count, P.ln_gamma, P.ln_beta, P.ln_eps, P.W1, P.b1, hid, H,
-                                         P.Hg, P.d, P.d_g);
-    hipError_t e = hipGetLastError();
+    const hipError_t e = launch_gate_prep(sum_q, 1, nullptr, 1, nullptr, inv_count, P, hid, B, H, st);
     if (e != hipSuccess) return e;
+    return launch_gate_out(hid, P, raw, B, H, phase, g, st);
+}
+
+hipError_t launch_gate_out(const float *hid, const GateDev &P, float2 *raw, int B, int H, long long phase, float2 *g,
+                           hipStream_t st) {
     const int F = P.n_fft / 2 + 1;
     const int M = (P.Hg == 1) ? B * H : B;
     const int ntiles = (2 * F + 63) / 64;
@@ -479,16 +758,20 @@ hipError_t launch_gate_mlp(const double *sum_q, double inv_count, const GateDev 
     const float *out_bias = P.toeplitz ? nullptr : P.modrelu_bias;
     float2 *out_g = P.toeplitz ? raw : g;
     {
-        // every 32-row tile of the rows in one launch (grid.z); a single tile takes the narrowest kernel that fits
-        const int ntile = (M + 31) / 32;
-        const int rows = (ntile > 1) ? 32 : M;
+        // every tile of the rows in one launch (grid.z); a single tile takes the narrowest kernel that fits
+        // rows per tile: 32, fewer while the launch would have less than four workgroups per compute unit (B=256 H=12
+        // L=196, 96 workgroups of 32 rows: 15 -> 7.4 us)
+        int per = 32;
+        while (per > 4 && M > per / 2 && (long long)grid.x * grid.y * ((M + per - 1) / per) < 1024) per /= 2;
+        const int ntile = (M + per - 1) / per;
+        const int rows = (ntile > 1) ? per : M;
         const int rg = (rows + 3) / 4;            // 1..8 row groups per tile
         const size_t lds = ((size_t)4 * (rg <= 1 ? 1 : rg <= 2 ? 2 : rg <= 4 ? 4 : 8) * (dgp + 4) +
                             4 * 64 * ((vec && P.d_g == 64) ? kHalfStride : kTileStride)) * sizeof(float);
         for (int z0 = 0; z0 < ntile; z0 += 65535) {
             const int nz = (ntile - z0 < 65535) ? ntile - z0 : 65535;
             const dim3 grid3(grid.x, grid.y, nz);
-            const int r_base = 32 * z0;
+            const int r_base = per * z0;
 #define SPECTRE_GATE_OUT(V, R) k_gate_out<V, R><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F, r_base)
             if (vec) {
                 if (rg <= 1) SPECTRE_GATE_OUT(true, 1); else if (rg <= 2) SPECTRE_GATE_OUT(true, 2);
@@ -502,15 +785,7 @@ hipError_t launch_gate_mlp(const double *sum_q, double inv_count, const GateDev 
             if (e2 != hipSuccess) return e2;
         }
     }
-    const size_t total = (size_t)B * H * F;
-    if (P.toeplitz) {
-        k_gate_toeplitz<<<(unsigned)((total + 255) / 256), 256, 0, st>>>(raw, P.toeplitz, P.modrelu_bias, g, H, P.Hg, F,
-                                                                         P.toeplitz_r, total);
-    }
-    e = hipGetLastError();
-    if (e != hipSuccess || phase == 0) return e;
-    k_gate_phase<<<(unsigned)((total + 255) / 256), 256, 0, st>>>(g, F, P.n_fft, phase, total);
-    return hipGetLastError();
+    return launch_gate_tail(P, raw, B, H, phase, g, st);
 }
 
 // Loads this translation unit's code object (the runtime loads them on first use): called by spectre_prepare so

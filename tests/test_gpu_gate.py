@@ -139,3 +139,25 @@ def test_gate_seeded_shapes(oracle, B, L, H, d, dg, n, io, shared, modrelu, phas
     err = rel_l2(got, want)
     print(f"  rel_l2={err:.3e}", flush=True)
     assert err <= 1e-5
+
+
+@pytest.mark.parametrize("B,L,H,Hg,io,taps,pos", [
+    (1, 62, 1, 1, "f32", 0, 0),          # the smallest gate of the one-launch kernel: one tile that is all there is
+    (3, 63, 2, 2, "bf16", 0, 5),         # last tile moved back over the one before
+    (1, 4095, 2, 2, "bf16", 0, 0), (1, 2048, 3, 1, "bf16", 0, 0),   # the longest rows of that kernel, and past them
+    (5, 640, 60, 60, "f32", 0, 0), (4, 1024, 64, 1, "f32", 0, 0),   # many heads: the narrow workgroup
+    (2, 300, 3, 3, "f32", 2, 7),         # Toeplitz update and phase behind it
+    (256, 130, 1, 1, "f32", 0, 0), (33, 1300, 2, 2, "bf16", 0, 0)]) # tiles of fewer than 32 rows in the output layer
+def test_gate_one_launch_and_its_edges(oracle, B, L, H, Hg, io, taps, pos):
+    from paper_2502_18394_amd import binding
+    print(f"case B={B} L={L} H={H} Hg={Hg} io={io} taps={taps} pos={pos}", flush=True)
+    q, qs = synth.tokens(70 + L, (B, L, H, 64), io)
+    p = synth.gate_params(71 + L, Hg, 64, L)
+    if taps:
+        p["toeplitz"] = synth.toeplitz_taps(72, Hg, taps)
+    got = binding.gate(to_device(qs, io), binding.GateParams(p), 1.0 / L, phase_pos=pos).cpu().numpy()
+    p64 = f64(p)
+    if taps:
+        p64["toeplitz"] = p["toeplitz"].astype(np.complex128)
+    want = oracle.gate(oracle.pool_q(q.astype(np.float64)), 1.0 / L, p64, L, pos)
+    assert rel_l2(got, want) <= TOL["f32"]
