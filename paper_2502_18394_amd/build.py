@@ -13,8 +13,8 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 OBJ = os.path.join(HERE, "_build")
 LIB = os.path.join(HERE, "libspectre_hip.so")
-SOURCES = ["api.hip", "mix_pow2.hip", "mix_line.hip", "mix_slab.hip", "mix_chirp.hip", "gate.hip", "prefix.hip", "decode.hip",
-           "project.hip", "wrm.hip"]
+SOURCES = ["api.hip", "mix_pow2.hip", "mix_line.hip", "mix_slab.hip", "mix_chirp.hip", "gate.hip", "prefix.hip", "cache_cols.hip",
+           "decode.hip", "project.hip", "wrm.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fvisibility=hidden",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          "-Wall", "-Wno-unused-command-line-argument", "-Wno-unknown-warning-option"]

@@ -485,7 +485,7 @@ int spectre_prepare(int n, int d) {
         }
     }
     hipError_t (*const loaders[])() = {load_kernels_mix_pow2, load_kernels_mix_line, load_kernels_mix_slab, load_kernels_mix_chirp, load_kernels_gate,
-                                       load_kernels_prefix, load_kernels_decode, load_kernels_project, load_kernels_wrm};
+                                       load_kernels_prefix, load_kernels_cache_cols, load_kernels_decode, load_kernels_project, load_kernels_wrm};
     for (auto load : loaders) {
         const hipError_t e = load();
         if (e != hipSuccess) return fail_hip(e, "prepare: loading kernels");
@@ -1160,22 +1160,43 @@ static size_t scratch_bytes(int BH, int N, int d) {
     return align256((size_t)mix_chunk_heads(BH, N, d) * N * (d / 2) * sizeof(float2));
 }
 
+// Transform plan of a cache window: the split of cache_cols.hip (P = 0) where the length has one, else the mixer's.
+static int get_window_plan(int N, Pow2Plan *pl) {
+    const int rc = get_pow2_plan(N, pl);
+    if (rc) return rc;
+    if (cache_cols_split(N, &pl->N1, &pl->N2)) {
+        pl->P = 0;
+        pl->twN1 = nullptr;
+    }
+    return SPECTRE_OK;
+}
+
+// Row transforms in scr -> half spectra of heads bh0 .. bh0 + nbh - 1.
+static int window_columns(const Pow2Plan &pl, float2 *scr, float2 *X, int bh0, int nbh, hipStream_t st) {
+    if (pl.P == 0) {
+        const hipError_t e = launch_cache_fwd(scr, X, pl.twL, pl.N1, pl.N2, bh0, nbh, st);
+        return e == hipSuccess ? SPECTRE_OK : fail_hip(e, "cache columns (forward)");
+    }
+    hipError_t e = launch_big(pl, scr, nullptr, bh0, nbh, 1, st);
+    if (e != hipSuccess) return fail_hip(e, "big(forward)");
+    e = launch_untangle(scr, X, pl.L, pl.N1, pl.N2, pl.P, bh0, nbh, st);
+    return e == hipSuccess ? SPECTRE_OK : fail_hip(e, "untangle");
+}
+
 // prefix_fft = n-point half spectra of the rows now in v_buf ([B*H, n, d] fp32, read as B*H sequences of
 // one head each); scr holds scratch_bytes(...).
 static int transform_window(const spectre_prefix_cache *c, float2 *scr, hipStream_t st) {
     const int N = window_len(c), BH = c->B * c->H;
     Pow2Plan pl;
-    int rc = get_pow2_plan(N, &pl);
+    int rc = get_window_plan(N, &pl);
     if (rc) return rc;
     const int chunk = mix_chunk_heads(BH, N, c->d);
     for (int bh0 = 0; bh0 < BH; bh0 += chunk) {
         const int nbh = (BH - bh0 < chunk) ? BH - bh0 : chunk;
         hipError_t e = launch_small_fwd(pl, SPECTRE_F32, c->v_buf, scr, N, 1, bh0, nbh, st);
         if (e != hipSuccess) return fail_hip(e, "small_fwd(window)");
-        e = launch_big(pl, scr, nullptr, bh0, nbh, 1, st);
-        if (e != hipSuccess) return fail_hip(e, "big(forward)");
-        e = launch_untangle(scr, static_cast<float2 *>(c->prefix_fft), N, pl.N1, pl.N2, pl.P, bh0, nbh, st);
-        if (e != hipSuccess) return fail_hip(e, "untangle");
+        rc = window_columns(pl, scr, static_cast<float2 *>(c->prefix_fft), bh0, nbh, st);
+        if (rc) return rc;
     }
     return SPECTRE_OK;
 }
@@ -1203,7 +1224,7 @@ int spectre_prefix_update(spectre_prefix_cache *c, const void *v_new, const void
     const int B = c->B, H = c->H, d = c->d, N = window_len(c), W = c->N_max, M0 = c->N_mem, BH = B * H, F = N / 2 + 1;
     if (c->t == 0 && T > 1 && T > W) return fail(SPECTRE_EINVAL, "prefix_update: prompt of %d tokens exceeds N_max=%d", T, W);
     Pow2Plan pl;
-    rc = get_pow2_plan(N, &pl);                      // every route below may transform the window
+    rc = get_window_plan(N, &pl);                    // every route below may transform the window
     if (rc) return rc;
     // every host-side check has passed: from here on work is enqueued
     rc = spectre_prefix_flush(c, stream);
@@ -1239,10 +1260,8 @@ int spectre_prefix_update(spectre_prefix_cache *c, const void *v_new, const void
             e = launch_small_fwd(pl, (int)io, v_new, scr, T, H, bh0, nbh, st, false, false,
                                  static_cast<float2 *>(c->v_buf));
             if (e != hipSuccess) return fail_hip(e, "small_fwd");
-            e = launch_big(pl, scr, nullptr, bh0, nbh, 1, st);
-            if (e != hipSuccess) return fail_hip(e, "big(forward)");
-            e = launch_untangle(scr, X, N, pl.N1, pl.N2, pl.P, bh0, nbh, st);
-            if (e != hipSuccess) return fail_hip(e, "untangle");
+            rc = window_columns(pl, scr, X, bh0, nbh, st);
+            if (rc) return rc;
         }
         c->t = T;
         return SPECTRE_OK;
@@ -1307,7 +1326,7 @@ int spectre_prefix_set_memory(spectre_prefix_cache *c, const float *mem, int mem
     if (reinterpret_cast<uintptr_t>(ws) & 255) return fail(SPECTRE_EINVAL, "prefix_set_memory: ws not 256-byte aligned");
     hipStream_t st = static_cast<hipStream_t>(stream);
     Pow2Plan pl;
-    rc = get_pow2_plan(window_len(c), &pl);            // the look-up transform_window repeats: fail before any launch
+    rc = get_window_plan(window_len(c), &pl);          // the look-up transform_window repeats: fail before any launch
     if (rc) return rc;
     hipError_t e = launch_set_memory(mem, mem_batch, static_cast<float *>(c->v_buf), c->B, c->H, window_len(c), c->N_mem, st);
     if (e != hipSuccess) return fail_hip(e, "set_memory");
@@ -1351,17 +1370,22 @@ int spectre_prefix_readout(const spectre_prefix_cache *c, const void *g, int mod
         return SPECTRE_OK;
     }
     Pow2Plan pl;
-    rc = get_pow2_plan(N, &pl);
+    rc = get_window_plan(N, &pl);
     if (rc) return rc;
     float2 *scr = static_cast<float2 *>(ws);
     const int Lw = (int)(c->t < W ? c->t : W);
     const int chunk = mix_chunk_heads(BH, N, d);
     for (int bh0 = 0; bh0 < BH; bh0 += chunk) {
         const int nbh = (BH - bh0 < chunk) ? BH - bh0 : chunk;
-        e = launch_tangle(X, gg, scr, N, pl.N1, pl.N2, pl.P, bh0, nbh, st);
-        if (e != hipSuccess) return fail_hip(e, "tangle");
-        e = launch_big(pl, scr, nullptr, bh0, nbh, 2, st);
-        if (e != hipSuccess) return fail_hip(e, "big(inverse)");
+        if (pl.P == 0) {
+            e = launch_cache_inv(X, gg, scr, pl.twL, pl.N1, pl.N2, bh0, nbh, st);
+            if (e != hipSuccess) return fail_hip(e, "cache columns (inverse)");
+        } else {
+            e = launch_tangle(X, gg, scr, N, pl.N1, pl.N2, pl.P, bh0, nbh, st);
+            if (e != hipSuccess) return fail_hip(e, "tangle");
+            e = launch_big(pl, scr, nullptr, bh0, nbh, 2, st);
+            if (e != hipSuccess) return fail_hip(e, "big(inverse)");
+        }
         // with memory rows the live tokens are gathered from their ring slots, oldest first
         if (M0 > 0) e = launch_small_inv(pl, (int)io, scr, out, 0, Lw, H, bh0, nbh, st, M0, W, (int)((c->t - 1) % W));
         else e = launch_small_inv(pl, (int)io, scr, out, N - Lw, Lw, H, bh0, nbh, st);

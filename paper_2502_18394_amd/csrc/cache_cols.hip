@@ -1,0 +1,255 @@
+// Columns of the cache's window transform and full-window readout, together with the step between the pair spectrum and
+// the two channels' half spectra (N <= 32768; gfx950).
+//
+//   k_cache_fwd : scratch columns [k2][pair][t1] -> N1-point transforms -> half-spectrum rows X[k][channel]
+//   k_cache_inv : rows X, times the gate -> pair spectrum -> inverse N1-point transforms -> scratch columns
+//
+// A bin k = k2 + N2 k1 and its Hermitian partner N - k lie in the planes k2 and N2 - k2, so a workgroup that holds both
+// planes of a few channel pairs separates (or joins) the channels itself.  As kernels of their own the column transforms
+// and that step moved 16 bytes each per pair and position beside those of the row transforms; here the spectrum crosses
+// memory once less.  What bounds them is memory traffic, 16 bytes per pair and position: 25 heads of N = 32768 forward 134
+// -> 72 us (5.8 TB/s), 102 heads of N = 8192 inverse 134 -> 77 us (5.6 TB/s).  With 64-byte pieces of the rows of X and whole
+// columns in LDS the former took 105 us, with plain stores of X, which push the scratch out of the memory-side cache, 88.
+// Whole calls: prompt of 20011 tokens, B = 8 H = 32 N = 32768, 3603 -> 2956 us; 57 tokens and the window's readout, B = 4
+// H = 32 N = 8192, 427 -> 352 us.
+//
+// N1 = R * R points are two passes of R-point transforms in registers with one exchange inside R lanes of a wave.  R = 16
+// for N = 256 N2.  Above, R = 32 (N = 1024 N2) instead of the 4096-point columns of the mixer's plan: those do not fit
+// with their partners (8 pairs x 2 planes x 32 KB), and two in-register passes are shorter than three.
+#include "fft_regs.h"
+#include "internal.h"
+#include "prefix_dev.h"
+#include "scratch_elem.h"
+
+namespace spectre {
+
+// One unit of work: two planes (k2 = u and N2 - u; for u = 0 the two planes that are their own partners, 0 and, if N2 is
+// even, N2 / 2) of PW channel pairs of one head.  R adjacent lanes own a column, lane tau holds the entries k1 = tau + R v
+// in register v, and the next R lanes own the same pair in the other plane: the partner of (lane, v) is then register
+// R - 1 - v of a lane of the same 2 R, and no column has to stand in LDS as a whole.  LDS carries one component at a time
+// of the exchange, and a half of the rows at a time on their way between lanes along k1 and lines along the pairs (whole
+// 128-byte lines of X); two workgroups or more share a compute unit and fill each other's waits.
+__host__ __device__ inline int cache_plane_pairs(int N2) { return (N2 + 1) / 2; }
+
+template <int R, int PW>
+struct CacheUnit {
+    static constexpr int N1 = R * R, NT = 2 * PW * R, kRows = R * R / 2;   // kRows: rows of X in flight, of both planes
+    static constexpr int kCol = N1 + N1 / R;                         // floats: entry e at e + e / R
+    static constexpr int kRow = PW + 1;                              // float4
+    static constexpr int kStep = NT / PW, kIter = kRows / kStep;
+    static constexpr size_t kLds = 2 * PW * kCol * sizeof(float) > kRows * kRow * sizeof(float4)
+                                       ? 2 * PW * kCol * sizeof(float) : kRows * kRow * sizeof(float4);
+    static_assert(64 % (2 * R) == 0 && kRows % kStep == 0, "a wave holds whole pairs of columns");
+    int bhl, pg, u, planes, plane1;
+    // The 32 / PW units that share the rows of X get ids 8 apart, hence one XCD.
+    __device__ __forceinline__ bool init(int id, int N2, int nbh) {
+        constexpr int G = 32 / PW;
+        const int U = cache_plane_pairs(N2), xcd = id & 7, idx = id >> 3;
+        pg = idx % G;
+        const int unit = (idx / G) * 8 + xcd;
+        bhl = unit / U;
+        u = unit - bhl * U;
+        plane1 = u ? N2 - u : N2 / 2;
+        planes = (u || N2 % 2 == 0) ? 2 : 1;
+        return bhl < nbh;
+    }
+    __device__ __forceinline__ int plane(int s) const { return s ? plane1 : u; }
+    // Lane with the partners of this lane's entries, in registers R - 1 - v; for plane 0 itself that holds for tau > 0, and
+    // the partner of entry R v is entry R (R - v).
+    __device__ __forceinline__ int partner_lane(int lane) const {
+        const int tau = lane % R, s = (lane / R) & 1, base = lane & ~(2 * R - 1);
+        if (u) return base + 2 * R - 1 - (lane - base);
+        return s ? base + 2 * R - 1 - tau : base + ((R - tau) & (R - 1));
+    }
+    // entry k1 of row rr of half h
+    __device__ static __forceinline__ int row_entry(int rr, int h) { return rr % R + R * (h * (R / 4) + (rr / R) % (R / 4)); }
+    __device__ static __forceinline__ int row_plane(int rr) { return rr / (R * R / 4); }
+};
+
+// x[u] at entry u R + tau -> entry tau R + i, one component at a time; LDS operations of a wave complete in order.
+template <int R>
+__device__ __forceinline__ void cache_exchange(float2 (&x)[R], float *buf, int tau, bool forward) {
+    float *b0 = buf + tau, *b1 = buf + tau * (R + 1);
+    const int s0 = forward ? R + 1 : 1, s1 = forward ? 1 : R + 1;
+    float *w = forward ? b0 : b1, *r = forward ? b1 : b0;
+#pragma unroll
+    for (int i = 0; i < R; ++i) w[i * s0] = x[i].x;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < R; ++i) x[i].x = r[i * s1];
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < R; ++i) w[i * s0] = x[i].y;
+    __builtin_amdgcn_wave_barrier();
+#pragma unroll
+    for (int i = 0; i < R; ++i) x[i].y = r[i * s1];
+}
+
+__device__ __forceinline__ float2 shfl2(float2 v, int lane) { return make_float2(__shfl(v.x, lane), __shfl(v.y, lane)); }
+
+template <int R, int PW>
+__global__ __launch_bounds__(2 * PW * R, R == 32 ? 4 : 6) void k_cache_fwd(const float2 *__restrict__ scr,
+                                                                           float4 *__restrict__ X,
+                                                                           const float2 *__restrict__ twL, int N2, int bh0,
+                                                                           int nbh) {
+    typedef CacheUnit<R, PW> Unit;
+    constexpr int N1 = Unit::N1, V = R / 4;
+    extern __shared__ float4 lds_cc[];
+    Unit un;
+    if (!un.init(blockIdx.x, N2, nbh)) return;                       // whole workgroup: units are padded to 8
+    const int tid = threadIdx.x, lane = tid & 63, F = N1 * N2 / 2 + 1;
+    const int tau = tid % R, s = (tid / R) & 1, pw = tid / (2 * R);
+    float2 x[R];
+    const float2 *col = scr + (((size_t)un.bhl * N2 + un.plane(s)) * 32 + un.pg * PW + pw) * N1 + tau;   // in range also
+#pragma unroll                                                       // without a second plane: plane N2 / 2 twice
+    for (int j = 0; j < R; ++j) x[j] = col[R * j];
+    {
+        const SmallTwiddles<R> tw(twL, tau * N2);                    // W_N1^(tau u)
+        dft<R, false>(x);
+#pragma unroll
+        for (int u = 1; u < R; ++u) x[u] = cmul(x[u], tw(u));
+    }
+    cache_exchange<R>(x, reinterpret_cast<float *>(lds_cc) + (tid / R) * Unit::kCol, tau, true);
+    dft<R, false>(x);                                                // register v: bin k1 = tau + R v
+    const int src = un.partner_lane(lane);
+    const bool own = un.u == 0 && s == 0 && tau == 0;
+    float4 *Xh = X + (size_t)(un.bhl + bh0) * F * 32 + un.pg * PW;
+    if (own) Xh[(size_t)(F - 1) * 32 + pw] = untangle_pair(x[R / 2], x[R / 2]);   // Nyquist: its own partner
+    const int p = tid % PW, r0 = tid / PW;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        __syncthreads();                                             // the LDS of the exchange, of the half before
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            const int v = h * V + i;
+            float2 n = shfl2(x[R - 1 - v], src);
+            if (own) n = x[(R - v) % R];
+            lds_cc[((s * V + i) * R + tau) * Unit::kRow + pw] = untangle_pair(x[v], n);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < Unit::kIter; ++i) {
+            const int rr = r0 + Unit::kStep * i, sr = Unit::row_plane(rr);
+            if (sr < un.planes)
+                stream_store(Xh + (size_t)(un.plane(sr) + N2 * Unit::row_entry(rr, h)) * 32 + p, lds_cc[rr * Unit::kRow + p]);
+        }
+    }
+}
+
+template <int R, int PW>
+__global__ __launch_bounds__(2 * PW * R, R == 32 ? 4 : 6) void k_cache_inv(const float4 *__restrict__ X,
+                                                                           const float2 *__restrict__ g,
+                                                                           float2 *__restrict__ scr,
+                                                                           const float2 *__restrict__ twL, int N2, int bh0,
+                                                                           int nbh) {
+    typedef CacheUnit<R, PW> Unit;
+    constexpr int N1 = Unit::N1, V = R / 4;
+    extern __shared__ float4 lds_cc[];
+    Unit un;
+    if (!un.init(blockIdx.x, N2, nbh)) return;                       // whole workgroup: units are padded to 8
+    const int tid = threadIdx.x, lane = tid & 63, N = N1 * N2, F = N / 2 + 1;
+    const int tau = tid % R, s = (tid / R) & 1, pw = tid / (2 * R);
+    const float scale = 1.0f / (float)N;
+    const float4 *Xh = X + (size_t)(un.bhl + bh0) * F * 32 + un.pg * PW;
+    const float2 *gh = g + (size_t)(un.bhl + bh0) * F;
+    const int src = un.partner_lane(lane);
+    const bool own = un.u == 0 && s == 0 && tau == 0;
+    const int p = tid % PW, r0 = tid / PW;
+    float2 x[R];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        float4 row[Unit::kIter];
+        float2 gk[Unit::kIter];
+#pragma unroll
+        for (int i = 0; i < Unit::kIter; ++i) {
+            const int rr = r0 + Unit::kStep * i, k = un.plane(Unit::row_plane(rr)) + N2 * Unit::row_entry(rr, h);
+            row[i] = stream_load(Xh + (size_t)k * 32 + p);                        // without a second plane: plane N2 / 2, unused
+            gk[i] = gh[k];
+        }
+        if (h) __syncthreads();
+#pragma unroll
+        for (int i = 0; i < Unit::kIter; ++i) {
+            const int rr = r0 + Unit::kStep * i;
+            const bool dc = un.u == 0 && rr == 0 && h == 0;          // only the real parts count
+            const TangledPair z = tangle_pair(row[i], gk[i], dc, scale);
+            lds_cc[rr * Unit::kRow + p] = make_float4(z.k.x, z.k.y, z.n.x, z.n.y);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            const int v = h * V + i;
+            const float4 z = lds_cc[((s * V + i) * R + tau) * Unit::kRow + pw];
+            const float2 zn = make_float2(z.z, z.w);
+            x[v] = make_float2(z.x, z.y);
+            x[R - 1 - v] = shfl2(zn, src);
+            if (v > 0 && own) x[R - v] = zn;
+        }
+    }
+    if (own) x[R / 2] = tangle_pair(Xh[(size_t)(F - 1) * 32 + pw], gh[F - 1], true, scale).k;   // Nyquist
+    __syncthreads();                                                 // the rows' LDS
+    const SmallTwiddles<R> tw(twL, tau * N2);
+    dft<R, true>(x);
+    cache_exchange<R>(x, reinterpret_cast<float *>(lds_cc) + (tid / R) * Unit::kCol, tau, false);
+#pragma unroll
+    for (int u = 1; u < R; ++u) x[u] = cmulc(x[u], tw(u));
+    dft<R, true>(x);
+    if (s >= un.planes) return;
+    float2 *col = scr + (((size_t)un.bhl * N2 + un.plane(s)) * 32 + un.pg * PW + pw) * N1 + tau;
+#pragma unroll
+    for (int j = 0; j < R; ++j) col[R * j] = x[j];
+}
+
+// ------------------------------------------------------------------------------------------
+bool cache_cols_split(int N, int *N1, int *N2) {
+    for (int n1 : {256, 1024}) {
+        if (N % n1 == 0 && N / n1 <= 32 && small_dft_supported(N / n1)) {
+            *N1 = n1;
+            *N2 = N / n1;
+            return true;
+        }
+    }
+    return false;
+}
+
+template <int R, int PW>
+static hipError_t cache_cols_t(bool inverse, float2 *scr, float2 *X, const float2 *g, const float2 *twL, int N2, int bh0,
+                               int nbh, hipStream_t st) {
+    typedef CacheUnit<R, PW> Unit;
+    const size_t lds = Unit::kLds;
+    const long long units = ((long long)nbh * cache_plane_pairs(N2) + 7) / 8 * 8 * (32 / PW);
+    if (units > 0x7fffffffLL) return hipErrorInvalidValue;
+    const void *kern = inverse ? reinterpret_cast<const void *>(&k_cache_inv<R, PW>)
+                               : reinterpret_cast<const void *>(&k_cache_fwd<R, PW>);
+    const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    float4 *X4 = reinterpret_cast<float4 *>(X);
+    if (inverse) k_cache_inv<R, PW><<<(unsigned)units, Unit::NT, lds, st>>>(X4, g, scr, twL, N2, bh0, nbh);
+    else k_cache_fwd<R, PW><<<(unsigned)units, Unit::NT, lds, st>>>(scr, X4, twL, N2, bh0, nbh);
+    return hipGetLastError();
+}
+
+static hipError_t cache_cols(bool inverse, float2 *scr, float2 *X, const float2 *g, const float2 *twL, int N1, int N2,
+                             int bh0, int nbh, hipStream_t st) {
+    if (N1 == 256) return cache_cols_t<16, 16>(inverse, scr, X, g, twL, N2, bh0, nbh, st);
+    if (N1 == 1024) return cache_cols_t<32, 8>(inverse, scr, X, g, twL, N2, bh0, nbh, st);
+    return hipErrorInvalidValue;
+}
+
+hipError_t launch_cache_fwd(const float2 *scr, float2 *X, const float2 *twL, int N1, int N2, int bh0, int nbh,
+                            hipStream_t st) {
+    return cache_cols(false, const_cast<float2 *>(scr), X, nullptr, twL, N1, N2, bh0, nbh, st);
+}
+
+hipError_t launch_cache_inv(const float2 *X, const float2 *g, float2 *scr, const float2 *twL, int N1, int N2, int bh0,
+                            int nbh, hipStream_t st) {
+    return cache_cols(true, scr, const_cast<float2 *>(X), g, twL, N1, N2, bh0, nbh, st);
+}
+
+// Loads this translation unit's code object (the runtime loads them on first use): called by spectre_prepare so
+// that no compute call is the first to touch it.
+hipError_t load_kernels_cache_cols() {
+    hipFuncAttributes a;
+    return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(&k_cache_fwd<16, 16>));
+}
+
+}  // namespace spectre

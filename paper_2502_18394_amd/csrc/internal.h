@@ -25,6 +25,7 @@ hipError_t load_kernels_mix_slab();
 hipError_t load_kernels_mix_chirp();
 hipError_t load_kernels_gate();
 hipError_t load_kernels_prefix();
+hipError_t load_kernels_cache_cols();
 hipError_t load_kernels_decode();
 hipError_t load_kernels_project();
 hipError_t load_kernels_wrm();

@@ -53,7 +53,7 @@ bool pow2_split(int L, int *N1, int *N2, int *P);
 // Launchers (enqueue only).  `pairs` = d/2 must be 32.  All return hipError_t.
 //   small_fwd : rows of v (tensor [B, rows, H, d], zero beyond `rows`) -> scratch[bh_local][k2][pair][t1]
 //   big       : in-place N1-point transforms on scratch; mode 0 = forward, gate, inverse;
-//               1 = forward only; 2 = inverse only.  gp = expanded gate for mode 0, one
+//               1 = forward only; 2 = inverse only (4096-point columns).  gp = expanded gate for mode 0, one
 //               [N2][N1] block per head from head bh0 on, or (shared_gate) one block for all.
 //   small_inv : scratch -> rows [row0, row0 + out_rows) of the inverse transform into
 //               out (tensor [B, out_rows, H, d]); with ring_w > 0 instead the out_rows newest

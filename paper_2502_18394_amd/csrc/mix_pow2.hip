@@ -755,7 +755,6 @@ hipError_t launch_big(const Pow2Plan &pl, float2 *scratch, const float2 *gp, int
     if (pl.P == 2) {
         if (mode == 0) return big_t<2, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st);
         if (mode == 1) return big_t<2, 1>(pl, scratch, gp, bh0, nbh, shared_gate, st);
-        if (mode == 2) return big_t<2, 2>(pl, scratch, gp, bh0, nbh, shared_gate, st);
     } else if (pl.P == 3) {
         if (mode == 0) return big_t<3, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, 0, wide);
         if (mode == 1) return big_t<3, 1>(pl, scratch, gp, bh0, nbh, shared_gate, st);

@@ -54,6 +54,16 @@ hipError_t launch_decode(int io, const void *v_t, const void *q_t, float *v_buf,
 // Memory rows mem [mem_batch (1 or B), H, Nmem, 64] into rows 0..Nmem-1 of v_buf [B, H, N, 64].
 hipError_t launch_set_memory(const float *mem, int mem_batch, float *v_buf, int B, int H, int N, int Nmem,
                              hipStream_t st);
+// Split N = N1 N2 under which the next two take a window (N1 = 256 or 1024); false: none, use the mixer's plan with
+// launch_big and launch_untangle / launch_tangle.
+bool cache_cols_split(int N, int *N1, int *N2);
+// scratch of the row transforms (k2 planes of t1 columns) -> N1-point transforms -> cache rows, and, with the gate g,
+// the inverse; twL = roots of unity of order N.
+hipError_t launch_cache_fwd(const float2 *scr, float2 *X, const float2 *twL, int N1, int N2, int bh0, int nbh,
+                            hipStream_t st);
+hipError_t launch_cache_inv(const float2 *X, const float2 *g, float2 *scr, const float2 *twL, int N1, int N2, int bh0,
+                            int nbh, hipStream_t st);
+
 // scratch (complex transforms of channel pairs, big-kernel order) <-> cache rows.
 hipError_t launch_untangle(const float2 *scr, float2 *X, int N, int N1, int N2, int P, int bh0, int nbh,
                            hipStream_t st);

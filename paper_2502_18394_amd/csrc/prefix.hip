@@ -560,7 +560,8 @@ __global__ __launch_bounds__(256) void k_set_memory(const float *__restrict__ me
     v_buf[(bh * N + m) * d + c] = mem[(src_bh * Nmem + m) * d + c];
 }
 
-// Scratch <-> cache rows.  A scratch column (head, k2, pair) is handled in lines of 16 adjacent entries (128 bytes):
+// Scratch <-> cache rows, for windows whose columns do not fit one compute unit together with their partners (N > 32768;
+// the others: cache_cols.hip).  A scratch column (head, k2, pair) is handled in lines of 16 adjacent entries (128 bytes):
 // entry e = 16 q + c holds bin k1 = big_position(e), and the lines q < N1 / 32 are exactly the bins k = k2 + N2 k1
 // below N / 2.  The partner bin N - k lies in column (N2 - k2) mod N2 and, for k2 > 0, its 16 entries are again one
 // line (in reverse order), so a workgroup that owns one line of all 32 pairs touches whole 128-byte lines of the
@@ -570,17 +571,6 @@ constexpr int kTileStride = 33;                       // float4 entries per bin 
 
 __device__ __forceinline__ size_t column_base(int bhl, int k2, int p, int N1, int N2) {
     return (((size_t)bhl * N2 + k2) * 32 + p) * N1;
-}
-
-// untangle: the complex transform Z of z = v_even + j v_odd separates into the two real
-// channels' half spectra, X_even[k] = (Z_k + conj Z_{N-k})/2, X_odd[k] = (Z_k - conj Z_{N-k})/(2j).
-__device__ __forceinline__ float4 untangle_pair(float2 zk, float2 zn) {
-    float4 o;
-    o.x = 0.5f * (zk.x + zn.x);
-    o.y = 0.5f * (zk.y - zn.y);
-    o.z = 0.5f * (zk.y + zn.y);
-    o.w = -0.5f * (zk.x - zn.x);
-    return o;
 }
 
 __global__ __launch_bounds__(256) void k_untangle(const float2 *__restrict__ scr, float4 *__restrict__ X,
@@ -618,9 +608,8 @@ __global__ __launch_bounds__(256) void k_untangle(const float2 *__restrict__ scr
     }
 }
 
-// tangle: the inverse of untangle with the gate applied.  Y_c[k] = g_k X_c[k] for k <= N/2
-// (real parts only at DC and Nyquist), Hermitian-extended to k > N/2; Z_k = (Y_even + j Y_odd)/N
-// goes to the entry the inverse big kernel reads it from.  The lane that holds bin k < N/2 also produces bin N - k.
+// tangle: the inverse of untangle with the gate applied, each bin to the entry the inverse big kernel reads it from.  The
+// lane that holds bin k < N/2 also produces bin N - k.
 __global__ __launch_bounds__(256) void k_tangle(const float4 *__restrict__ X, const float2 *__restrict__ g,
                                                 float2 *__restrict__ scr, int N, int N1, int N2, int P, int bh0,
                                                 int nbh) {
@@ -633,10 +622,8 @@ __global__ __launch_bounds__(256) void k_tangle(const float4 *__restrict__ X, co
         if (idx >= nbh * 32) return;
         const int p = idx & 31, bhl = idx >> 5;
         const size_t bh = (size_t)(bh0 + bhl);
-        const float4 x = X[(bh * F + N / 2) * 32 + p];
-        const float2 gk = g[bh * F + N / 2];
-        const float2 ya = cmul(gk, make_float2(x.x, x.y)), yb = cmul(gk, make_float2(x.z, x.w));
-        scr[column_base(bhl, 0, p, N1, N2) + big_position(N1 / 2, P)] = make_float2(ya.x * s, yb.x * s);
+        scr[column_base(bhl, 0, p, N1, N2) + big_position(N1 / 2, P)] =
+            tangle_pair(X[(bh * F + N / 2) * 32 + p], g[bh * F + N / 2], true, s).k;
         return;
     }
     const int q = blockIdx.x % lines, k2 = (blockIdx.x / lines) % N2, bhl = blockIdx.x / (lines * N2);
@@ -647,15 +634,8 @@ __global__ __launch_bounds__(256) void k_tangle(const float4 *__restrict__ X, co
         for (int rr = 0; rr < 2; ++rr) {
             const int c = c0 + 8 * rr;
             const int k = k2 + N2 * big_position(16 * q + c, P);
-            const float4 x = X[(bh * F + k) * 32 + p];
-            const float2 gk = g[bh * F + k];
-            float2 ya = cmul(gk, make_float2(x.x, x.y)), yb = cmul(gk, make_float2(x.z, x.w));
-            if (k == 0) {
-                ya.y = 0.f;
-                yb.y = 0.f;
-            }
-            // Z_k = Y_even[k] + j Y_odd[k];  Z_{N-k} = conj(Y_even[k]) + j conj(Y_odd[k])
-            tile[c * kTileStride + p] = make_float4((ya.x - yb.y) * s, (ya.y + yb.x) * s, (ya.x + yb.y) * s, (yb.x - ya.y) * s);
+            const TangledPair z = tangle_pair(X[(bh * F + k) * 32 + p], g[bh * F + k], k == 0, s);
+            tile[c * kTileStride + p] = make_float4(z.k.x, z.k.y, z.n.x, z.n.y);
         }
     }
     __syncthreads();

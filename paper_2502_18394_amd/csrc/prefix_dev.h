@@ -39,4 +39,29 @@ __device__ __forceinline__ void index_walk(unsigned k_start, unsigned mult, int 
     }
 }
 
+// The complex transform Z of z = v_even + j v_odd separates into the two real channels' half spectra,
+// X_even[k] = (Z_k + conj Z_{N-k})/2, X_odd[k] = (Z_k - conj Z_{N-k})/(2j).
+__device__ __forceinline__ float4 untangle_pair(float2 zk, float2 zn) {
+    float4 o;
+    o.x = 0.5f * (zk.x + zn.x);
+    o.y = 0.5f * (zk.y - zn.y);
+    o.z = 0.5f * (zk.y + zn.y);
+    o.w = -0.5f * (zk.x - zn.x);
+    return o;
+}
+
+// The inverse with the gate applied: Y_c[k] = g_k X_c[k] for k <= N/2 (real parts only at DC and Nyquist: `real`),
+// Hermitian-extended, then Z_k = Y_even[k] + j Y_odd[k] and Z_{N-k} = conj(Y_even[k]) + j conj(Y_odd[k]), times s.
+struct TangledPair {
+    float2 k, n;
+};
+__device__ __forceinline__ TangledPair tangle_pair(float4 x, float2 gk, bool real, float s) {
+    float2 ya = cmul(gk, make_float2(x.x, x.y)), yb = cmul(gk, make_float2(x.z, x.w));
+    if (real) {
+        ya.y = 0.f;
+        yb.y = 0.f;
+    }
+    return {make_float2((ya.x - yb.y) * s, (ya.y + yb.x) * s), make_float2((ya.x + yb.y) * s, (yb.x - ya.y) * s)};
+}
+
 }  // namespace spectre
