@@ -332,7 +332,7 @@ static int mix_route(int BH, int L, int d) {
     return chirp_padded_length(L) ? 3 : 0;
 }
 
-// Workspace sections of the arbitrary-length route.
+// Workspace sections of the arbitrary-length route (short padded lengths use only gp, the gate of the data pass).
 struct ChirpLayout {
     int M, nph;
     size_t gp, scr, t1, t2;      // byte sizes
@@ -359,13 +359,17 @@ static int mix_chirp(const void *v, const float2 *g, void *out, int B, int L, in
     const float2 *w = nullptr, *filt = nullptr;
     rc = get_chirp(L, pl, &w, &filt);
     if (rc) return rc;
-    const float2 *slab_roots = nullptr;
-    const int *slab_order = nullptr;
-    if (slab_supported(c.M)) {                         // all table look-ups before the first launch
-        rc = get_roots(c.M, &slab_roots);
+    if (slab_supported(c.M)) {                         // short padded lengths: two launches
+        const float2 *roots = nullptr;
+        rc = get_roots(c.M, &roots);
         if (rc) return rc;
-        rc = get_slab_order(c.M, &slab_order);
+        const int *order = nullptr;
+        rc = get_slab_order(c.M, &order);
         if (rc) return rc;
+        hipError_t e = launch_chirp_lds(g, w, filt, roots, static_cast<float2 *>(ws), BH, L, c.M, st);
+        if (e != hipSuccess) return fail_hip(e, "chirp_lds");
+        e = launch_mix_slab((int)io, v, static_cast<const float2 *>(ws), out, roots, order, B, c.M, H, st, L);
+        return e == hipSuccess ? SPECTRE_OK : fail_hip(e, "mix_slab(padded)");
     }
     char *base = static_cast<char *>(ws);
     float2 *gp = reinterpret_cast<float2 *>(base);
@@ -395,15 +399,8 @@ static int mix_chirp(const void *v, const float2 *g, void *out, int B, int L, in
         if (e != hipSuccess) return fail_hip(e, "small_fwd(kernel)");
         e = launch_big(pl, scr, nullptr, 0, n, 1, st);
         if (e != hipSuccess) return fail_hip(e, "big(kernel)");
-        // short padded lengths run the data pass as one in-LDS launch, which wants the gate in plain bin order
-        e = slab_supported(c.M) ? launch_chirp_gate_plain(scr, gp, BH, c.M, pl.N1, pl.N2, pl.P, ph0, n, st)
-                                : launch_chirp_gate(scr, gp, BH, c.M, pl.N1, pl.N2, ph0, n, st);
+        e = launch_chirp_gate(scr, gp, BH, c.M, pl.N1, pl.N2, ph0, n, st);
         if (e != hipSuccess) return fail_hip(e, "chirp_gate");
-    }
-    if (slab_supported(c.M)) {
-        e = launch_mix_slab((int)io, v, gp, out, slab_roots, slab_order, B, c.M, H, st, L);
-        if (e != hipSuccess) return fail_hip(e, "mix_slab(padded)");
-        return SPECTRE_OK;
     }
     // the data: zero-padded to M, first L rows of the result kept
     const int chunk = mix_chunk_heads(BH, c.M, d);

@@ -31,10 +31,10 @@ hipError_t launch_chirp_post(const float2 *U, const float2 *w, float2 *KK, int L
 hipError_t launch_chirp_gate(const float2 *scr, float2 *gp, int BH, int M, int N1, int N2, int ph0, int nphl,
                              hipStream_t st);
 
-// The same spectra as per-head gates g [BH][M/2+1] in plain bin order, unscaled: the gate argument of the in-LDS
-// kernel when it runs the padded convolution (M <= 2048).
-hipError_t launch_chirp_gate_plain(const float2 *scr, float2 *g, int BH, int M, int N1, int N2, int P, int ph0,
-                                   int nphl, hipStream_t st);
+// All of that in one launch for M = 256 .. 2048, a multiple of 256: g [BH, L/2+1] -> gp [BH][M/2+1] in plain bin order,
+// unscaled, the gate argument of the in-LDS kernel when it runs the padded convolution.  twM [M] = exp(-j 2 pi m / M).
+hipError_t launch_chirp_lds(const float2 *g, const float2 *w, const float2 *filt, const float2 *twM, float2 *gp, int BH,
+                            int L, int M, hipStream_t st);
 
 // Host: chirp w [L] and the chirp filter's M-point spectrum in the big kernel's register order
 // ([N2][N1], scaled by 1/M), both evaluated in fp64.

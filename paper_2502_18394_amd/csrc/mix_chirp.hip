@@ -6,7 +6,7 @@
 #include <complex>
 #include <vector>
 
-#include "common.h"
+#include "fft_regs.h"
 #include "mix_pow2.h"
 
 namespace spectre {
@@ -75,28 +75,148 @@ __global__ __launch_bounds__(256) void k_chirp_gate(const float2 *__restrict__ s
     gp[(bh * N2 + k2) * N1 + r] = make_float2(z.x * scale, z.y * scale);
 }
 
-// The same spectra in plain bin order for the in-LDS kernel: g[bh][k] = spectrum bin k = k2 + N2 k1 of pseudo-head
-// column (bh / 32, bh % 32), which the forward-only big kernel left at entry big_position(k1) of column k2;
-// unscaled (that kernel divides by its length itself).
-__global__ __launch_bounds__(256) void k_chirp_gate_plain(const float2 *__restrict__ scr, float2 *__restrict__ g, int BH,
-                                                          int F, int N1, int N2, int P, int ph0, size_t total) {
-    const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
-    if (idx >= total) return;
-    const int k = (int)(idx % F);
-    const size_t lh = idx / F;                        // head index within this group of pseudo-heads
-    const int phl = (int)(lh / 32), p = (int)(lh % 32);
-    const size_t bh = (size_t)ph0 * 32 + lh;
-    if (bh >= (size_t)BH) return;
-    const int k2 = k % N2, k1 = k / N2;
-    g[bh * F + k] = scr[(((size_t)phl * N2 + k2) * 32 + p) * N1 + big_position(k1, P)];
+// Short padded lengths (M = 256 N2 <= 2048, where the data pass is one in-LDS launch): everything between the caller's
+// gate and the gate of the data pass - chirp, two transforms around the filter, periodic extension, one more transform -
+// in one launch, a head's column in LDS from start to end.  16 N2 lanes per head, 16 points per lane in every pass: the
+// N2-point transforms of the row kernels, then the two radix-16 passes of the 256-point columns (register j of lane tau
+// of column k2 holds bin k2 + N2 (16 j + tau), the order of the filter table).
+// What bounds it is the latency of this chain of passes.  As eight launches of the kernels of longer lengths, each with
+// a few microseconds of work, it took a third of the call: L = 197, 768 heads of fp32 rows, 71.4 -> 53.0 us.
+template <int N2> constexpr int kChirpHeads = N2 < 4 ? 4 : 1;        // heads per workgroup: at least a wave of lanes
+
+template <int N2>
+struct ChirpColumn {
+    static constexpr int M = 256 * N2, NL = 16 * N2, COLW = 272;     // entry e of a column at e + e / 16
+    static constexpr int kLds = N2 * COLW * 8 + M / 2 * 4;           // bytes per head: the columns, then kappa (L <= M / 2)
+    float2 *buf;
+    int t, tau;
+    float2 tw[15];                                                   // W_256^(tau u)
+    __device__ __forceinline__ float2 *own() const { return buf + (t >> 4) * COLW; }
+    template <typename F>
+    __device__ __forceinline__ void rows_fwd(const float2 *twM, F element) {
+        for (int t1 = t; t1 < 256; t1 += NL) {
+            float2 x[N2];
+#pragma unroll
+            for (int j = 0; j < N2; ++j) x[j] = element(t1 + 256 * j);
+            small_dft<N2, false>(x);
+#pragma unroll
+            for (int k2 = 0; k2 < N2; ++k2)
+                buf[k2 * COLW + t1 + (t1 >> 4)] = k2 == 0 ? x[0] : cmul(x[k2], twM[t1 * k2]);
+        }
+    }
+    __device__ __forceinline__ void cols_fwd(float2 (&y)[16]) {
+        float2 *c = own();
+#pragma unroll
+        for (int j = 0; j < 16; ++j) y[j] = c[tau + 17 * j];
+        dft<16, false>(y);
+#pragma unroll
+        for (int u = 0; u < 16; ++u) c[tau + 17 * u] = u == 0 ? y[0] : cmul(y[u], tw[u - 1]);
+        __builtin_amdgcn_wave_barrier();                             // 16 lanes of one wave; its LDS operations keep their order
+#pragma unroll
+        for (int j = 0; j < 16; ++j) y[j] = c[17 * tau + j];
+        dft<16, false>(y);
+    }
+    __device__ __forceinline__ void cols_inv(float2 (&y)[16]) {
+        float2 *c = own();
+        dft<16, true>(y);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) c[17 * tau + j] = y[j];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < 16; ++u) y[u] = u == 0 ? c[tau] : cmulc(c[tau + 17 * u], tw[u - 1]);
+        dft<16, true>(y);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) c[tau + 17 * j] = y[j];
+    }
+};
+
+// gp [BH][M / 2 + 1] = the data pass's gate in plain bin order, unscaled (the in-LDS kernel divides by its length).
+template <int N2>
+__global__ __launch_bounds__(16 * N2 * kChirpHeads<N2>) void k_chirp_lds(const float2 *__restrict__ g,
+                                                                        const float2 *__restrict__ w,
+                                                                        const float2 *__restrict__ filt,
+                                                                        const float2 *__restrict__ twM,
+                                                                        float2 *__restrict__ gp, int BH, int L) {
+    typedef ChirpColumn<N2> Col;
+    constexpr int M = Col::M, HW = kChirpHeads<N2>;
+    __shared__ __align__(16) unsigned char lds[HW * Col::kLds];
+    const int hl = threadIdx.x / Col::NL, bh = blockIdx.x * HW + hl;
+    const bool live = bh < BH;                                       // the others run along on head 0 and store nothing
+    Col col;
+    col.buf = reinterpret_cast<float2 *>(lds + hl * Col::kLds);
+    col.t = threadIdx.x % Col::NL;
+    col.tau = col.t & 15;
+    float *kap = reinterpret_cast<float *>(col.buf + N2 * Col::COLW);
+    const int t = col.t, tau = col.tau, k2 = t >> 4;
+    const float2 *gh = g + (size_t)(live ? bh : 0) * (L / 2 + 1);
+#pragma unroll
+    for (int u = 1; u < 16; ++u) col.tw[u - 1] = twM[N2 * tau * u];
+    float2 f[16], y[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) f[j] = filt[256 * k2 + 16 * j + tau];
+
+    col.rows_fwd(twM, [&](int k) {
+        if (k >= L) return make_float2(0.f, 0.f);
+        float2 ge = gh[2 * k <= L ? k : L - k];
+        if (2 * k > L) ge.y = -ge.y;
+        if (k == 0 || 2 * k == L) ge.y = 0.f;
+        return cmul(ge, w[k]);
+    });
+    __syncthreads();
+    col.cols_fwd(y);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) y[j] = cmul(y[j], f[j]);
+    col.cols_inv(y);
+    __syncthreads();
+    for (int t1 = t; t1 < 256; t1 += Col::NL) {
+        float2 x[N2];
+#pragma unroll
+        for (int q = 0; q < N2; ++q) {
+            const float2 b = col.buf[q * Col::COLW + t1 + (t1 >> 4)];
+            x[q] = q == 0 ? b : cmulc(b, twM[t1 * q]);
+        }
+        small_dft<N2, true>(x);
+#pragma unroll
+        for (int j = 0; j < N2; ++j) {
+            const int m = t1 + 256 * j;
+            if (m < L) kap[m] = (w[m].x * x[j].x - w[m].y * x[j].y) * (1.0f / (float)L);
+        }
+    }
+    __syncthreads();
+    col.rows_fwd(twM, [&](int i) {
+        return make_float2(i < L ? kap[i] : i > M - L ? kap[i - (M - L)] : 0.f, 0.f);
+    });
+    __syncthreads();
+    col.cols_fwd(y);
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const int k = k2 + N2 * (16 * j + tau);
+        if (live && 2 * k <= M) gp[(size_t)bh * (M / 2 + 1) + k] = y[j];
+    }
 }
 
-hipError_t launch_chirp_gate_plain(const float2 *scr, float2 *g, int BH, int M, int N1, int N2, int P, int ph0,
-                                   int nphl, hipStream_t st) {
-    const int F = M / 2 + 1;
-    const size_t total = (size_t)nphl * 32 * F;
-    k_chirp_gate_plain<<<(unsigned)((total + 255) / 256), 256, 0, st>>>(scr, g, BH, F, N1, N2, P, ph0, total);
+template <int N2>
+static hipError_t chirp_lds_t(const float2 *g, const float2 *w, const float2 *filt, const float2 *twM, float2 *gp, int BH,
+                              int L, hipStream_t st) {
+    constexpr int HW = kChirpHeads<N2>;
+    k_chirp_lds<N2><<<(BH + HW - 1) / HW, 16 * N2 * HW, 0, st>>>(g, w, filt, twM, gp, BH, L);
     return hipGetLastError();
+}
+
+hipError_t launch_chirp_lds(const float2 *g, const float2 *w, const float2 *filt, const float2 *twM, float2 *gp, int BH,
+                            int L, int M, hipStream_t st) {
+    if (M % 256 != 0 || 2 * L > M) return hipErrorInvalidValue;
+    switch (M / 256) {
+        case 1: return chirp_lds_t<1>(g, w, filt, twM, gp, BH, L, st);
+        case 2: return chirp_lds_t<2>(g, w, filt, twM, gp, BH, L, st);
+        case 3: return chirp_lds_t<3>(g, w, filt, twM, gp, BH, L, st);
+        case 4: return chirp_lds_t<4>(g, w, filt, twM, gp, BH, L, st);
+        case 5: return chirp_lds_t<5>(g, w, filt, twM, gp, BH, L, st);
+        case 6: return chirp_lds_t<6>(g, w, filt, twM, gp, BH, L, st);
+        case 7: return chirp_lds_t<7>(g, w, filt, twM, gp, BH, L, st);
+        case 8: return chirp_lds_t<8>(g, w, filt, twM, gp, BH, L, st);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 hipError_t launch_chirp_pre(const float2 *g, const float2 *w, float2 *A, int BH, int L, int nph, hipStream_t st) {
