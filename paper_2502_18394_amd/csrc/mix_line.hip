@@ -210,7 +210,9 @@ __global__ __launch_bounds__(16 * R1, 2) void k_line(uint32_t *__restrict__ line
 }
 
 // ------------------------------------------------------------------------------------------
-bool line_supported(int L, int io) { return io == 1 && (L == 8192 || L == 16384); }
+bool line_supported(int L, int io, const void *v, const void *out) {
+    return io == 1 && (L == 8192 || L == 16384) && ((reinterpret_cast<uintptr_t>(v) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
+}
 
 template <int R0, int R1>
 static hipError_t line_t(const uint32_t *v, const float2 *g, uint32_t *out, float2 *gp, uint32_t *lines, const float2 *twL,

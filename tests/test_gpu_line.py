@@ -23,3 +23,24 @@ def test_whole_column_mixer(oracle, options, B, L, H, mb):
     want = oracle.mix_forward(v.astype(np.float64), g.astype(np.complex128))
     assert rel_l2(got, want) <= TOL["bf16"]
     assert_close_elementwise(got, want, "bf16", L)
+
+
+@pytest.mark.parametrize("shift_in,shift_out", [(2, 0), (0, 2), (6, 2)])
+def test_tensors_off_a_16_byte_boundary_take_the_four_step_route(oracle, shift_in, shift_out):
+    """Channel pairs are 4 bytes and that is all a caller owes: same result, and not a byte outside the output."""
+    from paper_2502_18394_amd import binding
+    B, L, H = 1, 8192, 2
+    print(f"case shifts {shift_in} {shift_out} elements", flush=True)
+    v, vs = synth.tokens(77, (B, L, H, 64), "bf16")
+    g = synth.random_gate(78, B, H, L)
+    n = B * L * H * 64
+    src = torch.zeros(n + 16, dtype=torch.bfloat16, device="cuda")
+    src[shift_in:shift_in + n] = to_device(vs, "bf16").reshape(-1)
+    dst = torch.full((n + 16,), 7.0, dtype=torch.bfloat16, device="cuda")
+    got = from_device(binding.mix_forward(src[shift_in:shift_in + n].view(B, L, H, 64), torch.from_numpy(g).cuda(),
+                                          out=dst[shift_out:shift_out + n].view(B, L, H, 64)))
+    want = oracle.mix_forward(v.astype(np.float64), g.astype(np.complex128))
+    assert rel_l2(got, want) <= TOL["bf16"]
+    assert_close_elementwise(got, want, "bf16", L)
+    rest = torch.cat([dst[:shift_out], dst[shift_out + n:]]).float()
+    assert bool((rest == 7.0).all())
