@@ -461,8 +461,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
 // What bounds it is the chain of latencies (rows, first layer, output layer): the first tile's weights are requested
 // before the rows.  Against the pooling, prep and output launches: B=1 H=32 bf16 L=512 26.3 -> 20.2 us for a step of
 // gate and mixer, B=256 H=12 fp32 L=196 120 -> 105 us.
+// ONCE: one part per head, so nobody reads its rows again and they pass the caches by, which the heads' weights keep:
+// B=256 H=12 fp32 L=196 106.0 -> 100.8 us (five waves per SIMD instead of four spill: 125.7).
 // A lane's four weights of row 4 s + lane / 16 of a tile meet the hidden values, summed over the 16 lanes (fold16).
-template <bool BF16, int NT>
+template <bool BF16, int NT, bool ONCE>
 __global__ __launch_bounds__(NT, 4) void k_gate_small(const void *__restrict__ q, double inv_count, GateDev P,
                                                     const float *__restrict__ act_bias, float2 *__restrict__ g,
                                                     int L, int H, int F, int ntiles) {
@@ -503,7 +505,7 @@ __global__ __launch_bounds__(NT, 4) void k_gate_small(const void *__restrict__ q
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
             w[u] = u32x4_a4{0, 0, 0, 0};
-            if (l + RPS * u < L) w[u] = src[(size_t)RPS * u * rs];
+            if (l + RPS * u < L) w[u] = ONCE ? __builtin_nontemporal_load(src + (size_t)RPS * u * rs) : src[(size_t)RPS * u * rs];
         }
 #pragma unroll
         for (int u = 0; u < kU; ++u) {
@@ -717,9 +719,14 @@ hipError_t launch_gate(int io, const void *q, double *partial, double inv_count,
         const float *act = P.toeplitz ? nullptr : P.modrelu_bias;
         float2 *out = P.toeplitz ? raw : g;
         const dim3 grid(parts, B * H);
-#define SPECTRE_GATE_SMALL(BF, NT) k_gate_small<BF, NT><<<grid, NT, 0, st>>>(q, inv_count, P, act, out, L, H, F, ntiles)
-        if (io) { if (wide) SPECTRE_GATE_SMALL(true, 1024); else SPECTRE_GATE_SMALL(true, 256); }
-        else { if (wide) SPECTRE_GATE_SMALL(false, 1024); else SPECTRE_GATE_SMALL(false, 256); }
+#define SPECTRE_GATE_SMALL(BF, NT, ONCE) \
+    k_gate_small<BF, NT, ONCE><<<grid, NT, 0, st>>>(q, inv_count, P, act, out, L, H, F, ntiles)
+#define SPECTRE_GATE_SMALL_IO(BF)                              \
+    if (wide) SPECTRE_GATE_SMALL(BF, 1024, false);             \
+    else if (parts == 1) SPECTRE_GATE_SMALL(BF, 256, true);    \
+    else SPECTRE_GATE_SMALL(BF, 256, false)
+        if (io) { SPECTRE_GATE_SMALL_IO(true); } else { SPECTRE_GATE_SMALL_IO(false); }
+#undef SPECTRE_GATE_SMALL_IO
 #undef SPECTRE_GATE_SMALL
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;

@@ -146,6 +146,7 @@ def test_gate_seeded_shapes(oracle, B, L, H, d, dg, n, io, shared, modrelu, phas
     (3, 63, 2, 2, "bf16", 0, 5),         # last tile moved back over the one before
     (1, 4095, 2, 2, "bf16", 0, 0), (1, 2048, 3, 1, "bf16", 0, 0),   # the longest rows of that kernel, and past them
     (5, 640, 60, 60, "f32", 0, 0), (4, 1024, 64, 1, "f32", 0, 0),   # many heads: the narrow workgroup
+    (3, 201, 90, 90, "bf16", 0, 0), (4, 1024, 64, 1, "bf16", 0, 0), # the same with one part per head, and with two
     (2, 300, 3, 3, "f32", 2, 7),         # Toeplitz update and phase behind it
     (256, 130, 1, 1, "f32", 0, 0), (33, 1300, 2, 2, "bf16", 0, 0)]) # tiles of fewer than 32 rows in the output layer
 def test_gate_one_launch_and_its_edges(oracle, B, L, H, Hg, io, taps, pos):
