@@ -60,6 +60,7 @@ struct SideLane {
 
 struct DeviceTables {
     std::map<int, float2 *> roots;   // n -> device array [n] of exp(-j 2 pi m / n)
+    std::map<int, float2 *> columns; // N1 -> device array [N1]: factors of the cache's two-pass columns
     std::map<int, float2 *> chirp;   // L -> device array: chirp [L], then its filter spectrum [M]
     std::map<int, int *> slab_order; // L -> device array [L]: bin held by each position of the in-LDS transform
     std::vector<struct SideLane *> lanes;   // idle helper streams (with their fork/join events)
@@ -103,6 +104,36 @@ int get_roots(int n, const float2 **out, bool make) {
             return fail_hip(e, "hipMemcpy(roots)");
         }
         it = t.roots.emplace(n, d).first;
+    }
+    *out = it->second;
+    return SPECTRE_OK;
+}
+
+// Factors between the two passes of an N1 = R * R point column, [u][tau] = exp(-j 2 pi u tau / N1): R lanes tau read a run
+// where the plain table would give each a line of its own.
+static int get_column_factors(int N1, const float2 **out, bool make = false) {
+    int dev = 0;
+    hipError_t e = hipGetDevice(&dev);
+    if (e != hipSuccess) return fail_hip(e, "hipGetDevice");
+    std::lock_guard<std::mutex> lk(g_mu);
+    DeviceTables &t = g_tables[dev];
+    auto it = t.columns.find(N1);
+    if (it == t.columns.end()) {
+        if (!make) return not_ready("column factors", N1);
+        std::vector<float2> roots, h((size_t)N1);
+        fill_roots(roots, N1);
+        int R = 1;
+        while (R * R < N1) ++R;
+        for (int i = 0; i < N1; ++i) h[i] = roots[(i / R) * (i % R)];
+        float2 *d = nullptr;
+        e = hipMalloc(reinterpret_cast<void **>(&d), sizeof(float2) * h.size());
+        if (e != hipSuccess) return fail_hip(e, "hipMalloc(column factors)");
+        e = hipMemcpy(d, h.data(), sizeof(float2) * h.size(), hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            (void)hipFree(d);
+            return fail_hip(e, "hipMemcpy(column factors)");
+        }
+        it = t.columns.emplace(N1, d).first;
     }
     *out = it->second;
     return SPECTRE_OK;
@@ -425,6 +456,7 @@ void spectre_shutdown(void) {
     for (auto &kv : g_tables) {
         (void)hipSetDevice(kv.first);
         for (auto &r : kv.second.roots) (void)hipFree(r.second);
+        for (auto &r : kv.second.columns) (void)hipFree(r.second);
         for (auto &r : kv.second.chirp) (void)hipFree(r.second);
         for (auto &r : kv.second.slab_order) (void)hipFree(r.second);
         for (SideLane *l : kv.second.lanes) {
@@ -469,6 +501,7 @@ int spectre_prepare(int n, int d) {
         if ((rc = get_slab_order(n, &o, true))) return rc;
     }
     if (p2 && (rc = get_pow2_plan(n, &pl, true))) return rc;
+    if (p2 && cache_cols_split(n, &N1, &N2) && (rc = get_column_factors(N1, &r, true))) return rc;
     if (fused_supported(n) && (rc = get_roots(4096, &r, true))) return rc;
     if (!sl && !p2) {
         const int M = chirp_padded_length(n);
@@ -1160,18 +1193,15 @@ static size_t scratch_bytes(int BH, int N, int d) {
 // Transform plan of a cache window: the split of cache_cols.hip (P = 0) where the length has one, else the mixer's.
 static int get_window_plan(int N, Pow2Plan *pl) {
     const int rc = get_pow2_plan(N, pl);
-    if (rc) return rc;
-    if (cache_cols_split(N, &pl->N1, &pl->N2)) {
-        pl->P = 0;
-        pl->twN1 = nullptr;
-    }
-    return SPECTRE_OK;
+    if (rc || !cache_cols_split(N, &pl->N1, &pl->N2)) return rc;
+    pl->P = 0;
+    return get_column_factors(pl->N1, &pl->twN1);
 }
 
 // Row transforms in scr -> half spectra of heads bh0 .. bh0 + nbh - 1.
 static int window_columns(const Pow2Plan &pl, float2 *scr, float2 *X, int bh0, int nbh, hipStream_t st) {
     if (pl.P == 0) {
-        const hipError_t e = launch_cache_fwd(scr, X, pl.twL, pl.N1, pl.N2, bh0, nbh, st);
+        const hipError_t e = launch_cache_fwd(pl, scr, X, bh0, nbh, st);
         return e == hipSuccess ? SPECTRE_OK : fail_hip(e, "cache columns (forward)");
     }
     hipError_t e = launch_big(pl, scr, nullptr, bh0, nbh, 1, st);
@@ -1375,7 +1405,7 @@ int spectre_prefix_readout(const spectre_prefix_cache *c, const void *g, int mod
     for (int bh0 = 0; bh0 < BH; bh0 += chunk) {
         const int nbh = (BH - bh0 < chunk) ? BH - bh0 : chunk;
         if (pl.P == 0) {
-            e = launch_cache_inv(X, gg, scr, pl.twL, pl.N1, pl.N2, bh0, nbh, st);
+            e = launch_cache_inv(pl, X, gg, scr, bh0, nbh, st);
             if (e != hipSuccess) return fail_hip(e, "cache columns (inverse)");
         } else {
             e = launch_tangle(X, gg, scr, N, pl.N1, pl.N2, pl.P, bh0, nbh, st);

@@ -16,8 +16,14 @@
 // N1 = R * R points are two passes of R-point transforms in registers with one exchange inside R lanes of a wave.  R = 16
 // for N = 256 N2.  Above, R = 32 (N = 1024 N2) instead of the 4096-point columns of the mixer's plan: those do not fit
 // with their partners (8 pairs x 2 planes x 32 KB), and two in-register passes are shorter than three.
+//
+// The factors between the two passes come from a table of R x R values, copied into LDS behind the exchange buffers (2 or
+// 8 KB).  As products of two to five values of the long table, which the row kernels use to save loads, they took the
+// spectra of 16384 rows from 1.34e-7 to 1.42e-7 of 64 bits; with the table 1.33e-7, at the same speed (prompt of 20011
+// tokens as above 2951 and 2939 us; read from memory where they are used 3015 us).
 #include "fft_regs.h"
 #include "internal.h"
+#include "mix_pow2.h"
 #include "prefix_dev.h"
 #include "scratch_elem.h"
 
@@ -37,9 +43,10 @@ struct CacheUnit {
     static constexpr int kCol = N1 + N1 / R;                         // floats: entry e at e + e / R
     static constexpr int kRow = PW + 1;                              // float4
     static constexpr int kStep = NT / PW, kIter = kRows / kStep;
-    static constexpr size_t kLds = 2 * PW * kCol * sizeof(float) > kRows * kRow * sizeof(float4)
-                                       ? 2 * PW * kCol * sizeof(float) : kRows * kRow * sizeof(float4);
+    static constexpr int kWork = 2 * PW * kCol > kRows * kRow * 4 ? 2 * PW * kCol / 4 : kRows * kRow;   // float4
+    static constexpr size_t kLds = kWork * sizeof(float4) + N1 * sizeof(float2);
     static_assert(64 % (2 * R) == 0 && kRows % kStep == 0, "a wave holds whole pairs of columns");
+    static_assert(N1 / 2 <= NT && 2 * PW * kCol % 4 == 0, "one lane copies two column factors, to a 16-byte boundary");
     int bhl, pg, u, planes, plane1;
     // The 32 / PW units that share the rows of X get ids 8 apart, hence one XCD.
     __device__ __forceinline__ bool init(int id, int N2, int nbh) {
@@ -90,8 +97,8 @@ __device__ __forceinline__ float2 shfl2(float2 v, int lane) { return make_float2
 template <int R, int PW>
 __global__ __launch_bounds__(2 * PW * R, R == 32 ? 4 : 6) void k_cache_fwd(const float2 *__restrict__ scr,
                                                                            float4 *__restrict__ X,
-                                                                           const float2 *__restrict__ twL, int N2, int bh0,
-                                                                           int nbh) {
+                                                                           const float4 *__restrict__ tw, int N2,
+                                                                           int bh0, int nbh) {
     typedef CacheUnit<R, PW> Unit;
     constexpr int N1 = Unit::N1, V = R / 4;
     extern __shared__ float4 lds_cc[];
@@ -99,16 +106,18 @@ __global__ __launch_bounds__(2 * PW * R, R == 32 ? 4 : 6) void k_cache_fwd(const
     if (!un.init(blockIdx.x, N2, nbh)) return;                       // whole workgroup: units are padded to 8
     const int tid = threadIdx.x, lane = tid & 63, F = N1 * N2 / 2 + 1;
     const int tau = tid % R, s = (tid / R) & 1, pw = tid / (2 * R);
+    float4 factors = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (tid < N1 / 2) factors = tw[tid];
     float2 x[R];
     const float2 *col = scr + (((size_t)un.bhl * N2 + un.plane(s)) * 32 + un.pg * PW + pw) * N1 + tau;   // in range also
 #pragma unroll                                                       // without a second plane: plane N2 / 2 twice
     for (int j = 0; j < R; ++j) x[j] = col[R * j];
-    {
-        const SmallTwiddles<R> tw(twL, tau * N2);                    // W_N1^(tau u)
-        dft<R, false>(x);
+    if (tid < N1 / 2) lds_cc[Unit::kWork + tid] = factors;
+    dft<R, false>(x);
+    __syncthreads();
+    const float2 *w = reinterpret_cast<const float2 *>(lds_cc + Unit::kWork) + tau;
 #pragma unroll
-        for (int u = 1; u < R; ++u) x[u] = cmul(x[u], tw(u));
-    }
+    for (int u = 1; u < R; ++u) x[u] = cmul(x[u], w[u * R]);         // W_N1^(tau u)
     cache_exchange<R>(x, reinterpret_cast<float *>(lds_cc) + (tid / R) * Unit::kCol, tau, true);
     dft<R, false>(x);                                                // register v: bin k1 = tau + R v
     const int src = un.partner_lane(lane);
@@ -140,8 +149,8 @@ template <int R, int PW>
 __global__ __launch_bounds__(2 * PW * R, R == 32 ? 4 : 6) void k_cache_inv(const float4 *__restrict__ X,
                                                                            const float2 *__restrict__ g,
                                                                            float2 *__restrict__ scr,
-                                                                           const float2 *__restrict__ twL, int N2, int bh0,
-                                                                           int nbh) {
+                                                                           const float4 *__restrict__ tw, int N2,
+                                                                           int bh0, int nbh) {
     typedef CacheUnit<R, PW> Unit;
     constexpr int N1 = Unit::N1, V = R / 4;
     extern __shared__ float4 lds_cc[];
@@ -155,6 +164,7 @@ __global__ __launch_bounds__(2 * PW * R, R == 32 ? 4 : 6) void k_cache_inv(const
     const int src = un.partner_lane(lane);
     const bool own = un.u == 0 && s == 0 && tau == 0;
     const int p = tid % PW, r0 = tid / PW;
+    if (tid < N1 / 2) lds_cc[Unit::kWork + tid] = tw[tid];
     float2 x[R];
 #pragma unroll
     for (int h = 0; h < 2; ++h) {
@@ -187,11 +197,11 @@ __global__ __launch_bounds__(2 * PW * R, R == 32 ? 4 : 6) void k_cache_inv(const
     }
     if (own) x[R / 2] = tangle_pair(Xh[(size_t)(F - 1) * 32 + pw], gh[F - 1], true, scale).k;   // Nyquist
     __syncthreads();                                                 // the rows' LDS
-    const SmallTwiddles<R> tw(twL, tau * N2);
+    const float2 *w = reinterpret_cast<const float2 *>(lds_cc + Unit::kWork) + tau;
     dft<R, true>(x);
     cache_exchange<R>(x, reinterpret_cast<float *>(lds_cc) + (tid / R) * Unit::kCol, tau, false);
 #pragma unroll
-    for (int u = 1; u < R; ++u) x[u] = cmulc(x[u], tw(u));
+    for (int u = 1; u < R; ++u) x[u] = cmulc(x[u], w[u * R]);        // W_N1^(-tau u)
     dft<R, true>(x);
     if (s >= un.planes) return;
     float2 *col = scr + (((size_t)un.bhl * N2 + un.plane(s)) * 32 + un.pg * PW + pw) * N1 + tau;
@@ -212,37 +222,38 @@ bool cache_cols_split(int N, int *N1, int *N2) {
 }
 
 template <int R, int PW>
-static hipError_t cache_cols_t(bool inverse, float2 *scr, float2 *X, const float2 *g, const float2 *twL, int N2, int bh0,
-                               int nbh, hipStream_t st) {
+static hipError_t cache_cols_t(bool inverse, const Pow2Plan &pl, float2 *scr, float2 *X, const float2 *g, int bh0, int nbh,
+                               hipStream_t st) {
     typedef CacheUnit<R, PW> Unit;
     const size_t lds = Unit::kLds;
-    const long long units = ((long long)nbh * cache_plane_pairs(N2) + 7) / 8 * 8 * (32 / PW);
+    const long long units = ((long long)nbh * cache_plane_pairs(pl.N2) + 7) / 8 * 8 * (32 / PW);
     if (units > 0x7fffffffLL) return hipErrorInvalidValue;
     const void *kern = inverse ? reinterpret_cast<const void *>(&k_cache_inv<R, PW>)
                                : reinterpret_cast<const void *>(&k_cache_fwd<R, PW>);
     const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     float4 *X4 = reinterpret_cast<float4 *>(X);
-    if (inverse) k_cache_inv<R, PW><<<(unsigned)units, Unit::NT, lds, st>>>(X4, g, scr, twL, N2, bh0, nbh);
-    else k_cache_fwd<R, PW><<<(unsigned)units, Unit::NT, lds, st>>>(scr, X4, twL, N2, bh0, nbh);
+    const float4 *tw = reinterpret_cast<const float4 *>(pl.twN1);
+    const unsigned grid = (unsigned)units;
+    if (inverse) k_cache_inv<R, PW><<<grid, Unit::NT, lds, st>>>(X4, g, scr, tw, pl.N2, bh0, nbh);
+    else k_cache_fwd<R, PW><<<grid, Unit::NT, lds, st>>>(scr, X4, tw, pl.N2, bh0, nbh);
     return hipGetLastError();
 }
 
-static hipError_t cache_cols(bool inverse, float2 *scr, float2 *X, const float2 *g, const float2 *twL, int N1, int N2,
-                             int bh0, int nbh, hipStream_t st) {
-    if (N1 == 256) return cache_cols_t<16, 16>(inverse, scr, X, g, twL, N2, bh0, nbh, st);
-    if (N1 == 1024) return cache_cols_t<32, 8>(inverse, scr, X, g, twL, N2, bh0, nbh, st);
+static hipError_t cache_cols(bool inverse, const Pow2Plan &pl, float2 *scr, float2 *X, const float2 *g, int bh0, int nbh,
+                             hipStream_t st) {
+    if (pl.N1 == 256) return cache_cols_t<16, 16>(inverse, pl, scr, X, g, bh0, nbh, st);
+    if (pl.N1 == 1024) return cache_cols_t<32, 8>(inverse, pl, scr, X, g, bh0, nbh, st);
     return hipErrorInvalidValue;
 }
 
-hipError_t launch_cache_fwd(const float2 *scr, float2 *X, const float2 *twL, int N1, int N2, int bh0, int nbh,
-                            hipStream_t st) {
-    return cache_cols(false, const_cast<float2 *>(scr), X, nullptr, twL, N1, N2, bh0, nbh, st);
+hipError_t launch_cache_fwd(const Pow2Plan &pl, const float2 *scr, float2 *X, int bh0, int nbh, hipStream_t st) {
+    return cache_cols(false, pl, const_cast<float2 *>(scr), X, nullptr, bh0, nbh, st);
 }
 
-hipError_t launch_cache_inv(const float2 *X, const float2 *g, float2 *scr, const float2 *twL, int N1, int N2, int bh0,
-                            int nbh, hipStream_t st) {
-    return cache_cols(true, scr, const_cast<float2 *>(X), g, twL, N1, N2, bh0, nbh, st);
+hipError_t launch_cache_inv(const Pow2Plan &pl, const float2 *X, const float2 *g, float2 *scr, int bh0, int nbh,
+                            hipStream_t st) {
+    return cache_cols(true, pl, scr, const_cast<float2 *>(X), g, bh0, nbh, st);
 }
 
 // Loads this translation unit's code object (the runtime loads them on first use): called by spectre_prepare so

@@ -17,7 +17,7 @@ struct Pow2Plan {
     int N1 = 0, N2 = 0;   // L = N1 * N2; N1 = 16^P, N2 <= 32 of the form {1,3,5,7} * 2^a
     int P = 0;
     const float2 *twL = nullptr;   // [L]  exp(-j 2 pi m / L), device
-    const float2 *twN1 = nullptr;  // [N1] exp(-j 2 pi m / N1), device
+    const float2 *twN1 = nullptr;  // [N1] exp(-j 2 pi m / N1), device; P = 0: factors between a column's two passes
 };
 
 // Order of a scratch column of N1 = 16^P entries around the big kernel (all modes, input and output): entry

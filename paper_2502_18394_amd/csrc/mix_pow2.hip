@@ -78,7 +78,7 @@ __global__ __launch_bounds__(RowTile<IO>::kPairs * TT) void k_small_fwd(const ty
     for (int t2 = 0; t2 < N2; ++t2) x[t2] = IO::unpack(lds[(t2 * TT + tl) * S + p]);
     small_dft<N2, false>(x);
     typename SC::elem_t *dst = scr + (((size_t)bhl * N2) * 32 + p0 + p) * N1 + t1;
-    const SmallTwiddles<N2> tw(twL, t1);
+    const SmallTwiddles<N2, std::is_same<SC, ScrF32Fine>::value> tw(twL, t1);
 #pragma unroll
     for (int k2 = 0; k2 < N2; ++k2) {
         const float2 y = (k2 == 0) ? x[0] : cmul(x[k2], tw(k2));
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(RowTile<IO>::kPairs * TT) void k_small_inv(const ty
         float2 y[N2];
 #pragma unroll
         for (int k2 = 0; k2 < N2; ++k2) y[k2] = SC::get(raw[k2]);
-        const SmallTwiddles<N2> tw(twL, t1);
+        const SmallTwiddles<N2, std::is_same<SC, ScrF32Fine>::value> tw(twL, t1);
 #pragma unroll
         for (int k2 = 1; k2 < N2; ++k2) y[k2] = cmulc(y[k2], tw(k2));
         small_dft<N2, true>(y);
@@ -665,11 +665,22 @@ static hipError_t small_inv_t(const Pow2Plan &pl, const void *scr_v, void *out, 
         default: return hipErrorInvalidValue;                                \
     }
 
+// Windows with 1024-point columns (N = 12288 .. 32768).
+#define SPECTRE_FINE_CASE(FN, N, ...) \
+    case N: return io ? FN<N, 16, IoBf16, ScrF32Fine>(__VA_ARGS__) : FN<N, 16, IoF32, ScrF32Fine>(__VA_ARGS__);
+#define SPECTRE_DISPATCH_FINE(FN, ...)                                       \
+    switch (pl.N2) {                                                         \
+        SPECTRE_FINE_CASE(FN, 12, __VA_ARGS__) SPECTRE_FINE_CASE(FN, 16, __VA_ARGS__) SPECTRE_FINE_CASE(FN, 20, __VA_ARGS__) \
+        SPECTRE_FINE_CASE(FN, 24, __VA_ARGS__) SPECTRE_FINE_CASE(FN, 28, __VA_ARGS__) SPECTRE_FINE_CASE(FN, 32, __VA_ARGS__) \
+        default: return hipErrorInvalidValue;                                \
+    }
+
 hipError_t launch_small_fwd(const Pow2Plan &pl, int io, const void *v, float2 *scratch, int rows, int H,
                             int bh0, int nbh, hipStream_t st, bool scr16, bool affine, float2 *ring) {
     if (scr16 && !io) return hipErrorInvalidValue;
     if (affine && nbh % 8 != 0) return hipErrorInvalidValue;
     const int aff = affine ? nbh : 0;
+    if (pl.N1 == 1024 && !scr16) SPECTRE_DISPATCH_FINE(small_fwd_t, pl, v, scratch, rows, H, bh0, nbh, st, aff, ring)
     SPECTRE_DISPATCH_N2(small_fwd_t, pl, v, scratch, rows, H, bh0, nbh, st, aff, ring)
 }
 
@@ -705,6 +716,8 @@ hipError_t launch_small_inv(const Pow2Plan &pl, int io, const float2 *scratch, v
     if (affine && nbh % 8 != 0) return hipErrorInvalidValue;
     if (bsum && (row0 != 0 || out_rows != pl.L || ring_w > 0)) return hipErrorInvalidValue;   // whole transforms only
     const int aff = affine ? nbh : 0;
+    if (pl.N1 == 1024 && !scr16)
+        SPECTRE_DISPATCH_FINE(small_inv_t, pl, scratch, out, row0, out_rows, H, bh0, nbh, st, ring0, ring_w, newest, aff, bsum)
     SPECTRE_DISPATCH_N2(small_inv_t, pl, scratch, out, row0, out_rows, H, bh0, nbh, st, ring0, ring_w, newest, aff,
                         bsum)
 }

@@ -7,6 +7,8 @@
 
 namespace spectre {
 
+struct Pow2Plan;
+
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t st);          // bytes % 16 == 0
 hipError_t launch_fill_twiddle(float2 *tw, int N, hipStream_t st);
 
@@ -58,11 +60,10 @@ hipError_t launch_set_memory(const float *mem, int mem_batch, float *v_buf, int 
 // launch_big and launch_untangle / launch_tangle.
 bool cache_cols_split(int N, int *N1, int *N2);
 // scratch of the row transforms (k2 planes of t1 columns) -> N1-point transforms -> cache rows, and, with the gate g,
-// the inverse; twL = roots of unity of order N.
-hipError_t launch_cache_fwd(const float2 *scr, float2 *X, const float2 *twL, int N1, int N2, int bh0, int nbh,
+// the inverse, for a plan with that split.
+hipError_t launch_cache_fwd(const Pow2Plan &pl, const float2 *scr, float2 *X, int bh0, int nbh, hipStream_t st);
+hipError_t launch_cache_inv(const Pow2Plan &pl, const float2 *X, const float2 *g, float2 *scr, int bh0, int nbh,
                             hipStream_t st);
-hipError_t launch_cache_inv(const float2 *X, const float2 *g, float2 *scr, const float2 *twL, int N1, int N2, int bh0,
-                            int nbh, hipStream_t st);
 
 // scratch (complex transforms of channel pairs, big-kernel order) <-> cache rows.
 hipError_t launch_untangle(const float2 *scr, float2 *X, int N, int N1, int N2, int P, int bh0, int nbh,

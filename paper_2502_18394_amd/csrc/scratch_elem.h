@@ -11,6 +11,9 @@ struct ScrF32 {
     __device__ static __forceinline__ float2 get(elem_t e) { return e; }
     __device__ static __forceinline__ elem_t put(float2 v) { return v; }
 };
+// fp32 elements, and row factors of at most one product (SmallTwiddles): the windows with 1024-point columns, whose row
+// transforms are four times as long as beside the 4096-point columns of the mixer's plan.
+struct ScrF32Fine : ScrF32 {};
 struct ScrBf16 {
     typedef uint32_t elem_t;
     __device__ static __forceinline__ float2 get(elem_t e) { return IoBf16::unpack(e); }
@@ -34,10 +37,18 @@ __device__ __forceinline__ void head_affine(int id, int per_head, int aff, bool 
 // 31 scattered ones at N2 = 32: the gathers were most of the kernel's cache-line requests).  With k2 = 4a + b the
 // others are hi[a] * lo[b], products of at most five table values in all, i.e. within 4 rounding errors of the table
 // value; only hi and lo stay in registers, the product is formed where it is used.
-template <int N2>
+// FINE: hi and lo all come from the table (ten loads at N2 = 32), which takes the factors' error from 4.5e-8 to 3.3e-8.
+template <int N2, bool FINE = false>
 struct SmallTwiddles {
     float2 lo[4], hi[8];
     __device__ __forceinline__ SmallTwiddles(const float2 *__restrict__ twL, int t1) {
+        if (FINE) {
+#pragma unroll
+            for (int b = 0; b < 4; ++b) lo[b] = (b && b < N2) ? twL[t1 * b] : make_float2(1.f, 0.f);
+#pragma unroll
+            for (int a = 0; a < 8; ++a) hi[a] = (a && 4 * a < N2) ? twL[t1 * 4 * a] : make_float2(1.f, 0.f);
+            return;
+        }
         float2 p[5];
 #pragma unroll
         for (int e = 0; e < 5; ++e) p[e] = ((1 << e) < N2) ? twL[t1 << e] : make_float2(1.f, 0.f);
