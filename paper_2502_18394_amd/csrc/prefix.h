@@ -29,7 +29,7 @@ hipError_t launch_sweep(bool update, bool read, float2 *X, const float *delta, c
 //   without flush the kappa partials kpart [BH][chunks][32] of the pending tokens are produced as well.
 constexpr int kMaxPending = 32;
 constexpr int kMaxBatch = 64;     // tokens of an append that one sweep takes
-// Ring-buffer bookkeeping of nb <= min(kMaxBatch, W) appended tokens, tokens i0 .. i0 + nb - 1 of v_new / q_new
+// Ring-buffer bookkeeping of nb <= kMaxBatch appended tokens, tokens i0 .. i0 + nb - 1 of v_new / q_new
 // [B, T, H, 64]: token i goes to slot M0 + (t + i) mod W, evicting what was there when t + i >= W; delta [nb][B*H][64].
 hipError_t launch_ring_batch(int io, const void *v_new, const void *q_new, int T, int i0, int nb, float *v_buf,
                              float *q_buf, double *sum_q, float *delta, int B, int H, int N, int M0, int W, long long t,

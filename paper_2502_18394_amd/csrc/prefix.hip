@@ -49,8 +49,9 @@ __global__ __launch_bounds__(256) void k_ring_update(const T *__restrict__ v_new
     q_buf[ring] = qn;
 }
 
-// The same for the tokens of one appended batch, in one launch: their slots are distinct (nb <= W).  grid B*H; 256
-// lanes = 32 channel pairs x 8 token lanes; the query sums are combined in a fixed order.
+// The same for the tokens of one appended batch, in one launch.  On a ring shorter than the batch, token i evicts token
+// i - W of the batch itself, and a slot keeps the last of its tokens.  grid B*H; 256 lanes = 32 channel pairs x 8 token
+// lanes; the query sums are combined in a fixed order.
 // One launch per token cost 4 us each, 228 of the 712 us of a 57-token append with its readout at B=4 H=32 N=8192.
 template <typename IO>
 __global__ __launch_bounds__(256) void k_ring_batch(const typename IO::pair_t *__restrict__ v_new,
@@ -67,16 +68,21 @@ __global__ __launch_bounds__(256) void k_ring_batch(const typename IO::pair_t *_
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
         const int i = min(rl + 8 * u, nb - 1);                       // clamped: neither stored nor summed past the end
-        int slot = s0 + i;
-        if (slot >= W) slot -= W;
-        ring[u] = ((size_t)bh * N + M0 + slot) * 32 + p;
+        ring[u] = ((size_t)bh * N + M0 + (s0 + i) % W) * 32 + p;
         const size_t src = (((size_t)b * T + i0 + i) * H + h) * 32 + p;
         rv[u] = v_new[src];
         rq[u] = q_new[src];
-        const bool ev = i >= evict_from;
-        vo[u] = ev ? v_buf[ring[u]] : make_float2(0.f, 0.f);
-        qo[u] = ev ? q_buf[ring[u]] : make_float2(0.f, 0.f);
+        vo[u] = qo[u] = make_float2(0.f, 0.f);
+        if (i >= W) {
+            const size_t own = src - (size_t)W * H * 32;
+            vo[u] = IO::unpack(v_new[own]);
+            qo[u] = IO::unpack(q_new[own]);
+        } else if (i >= evict_from) {
+            vo[u] = v_buf[ring[u]];
+            qo[u] = q_buf[ring[u]];
+        }
     }
+    if (nb > W) __syncthreads();                                     // slots are read above and written below by different lanes
     double sx = 0.0, sy = 0.0;
 #pragma unroll
     for (int u = 0; u < kPer; ++u) {
@@ -86,8 +92,10 @@ __global__ __launch_bounds__(256) void k_ring_batch(const typename IO::pair_t *_
             delta[((size_t)i * BH + bh) * 32 + p] = make_float2(vn.x - vo[u].x, vn.y - vo[u].y);
             sx += (double)qn.x - (double)qo[u].x;
             sy += (double)qn.y - (double)qo[u].y;
-            v_buf[ring[u]] = vn;
-            q_buf[ring[u]] = qn;
+            if (i + W >= nb) {
+                v_buf[ring[u]] = vn;
+                q_buf[ring[u]] = qn;
+            }
         }
     }
     red[rl][2 * p] = sx;
@@ -684,7 +692,7 @@ hipError_t launch_ring_update(int io, const void *v_new, const void *q_new, int 
 hipError_t launch_ring_batch(int io, const void *v_new, const void *q_new, int T, int i0, int nb, float *v_buf,
                              float *q_buf, double *sum_q, float *delta, int B, int H, int N, int M0, int W, long long t,
                              hipStream_t st) {
-    if (nb < 1 || nb > kMaxBatch || nb > W) return hipErrorInvalidValue;
+    if (nb < 1 || nb > kMaxBatch) return hipErrorInvalidValue;
     const int s0 = (int)(t % W), evict_from = t >= W ? 0 : (int)(W - t < nb ? W - t : nb);
 #define SPECTRE_RING_BATCH(IO)                                                                                        \
     k_ring_batch<IO><<<B * H, 256, 0, st>>>(static_cast<const IO::pair_t *>(v_new), static_cast<const IO::pair_t *>(q_new), \

@@ -1,5 +1,7 @@
 """GPU parity of appends of several tokens around the 64 that one sweep over the cache takes, and on rings shorter than
-such a batch (memory rows in front), where a batch is as long as the ring."""
+such a batch (memory rows in front), where a batch evicts its own tokens."""
+import ctypes
+
 import numpy as np
 import pytest
 import torch
@@ -12,7 +14,8 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("N_mem,N_max,T0,appends,io", [
     (0, 256, 100, (63, 64, 65), "f32"), (0, 512, 510, (127, 128, 129), "bf16"), (0, 256, 0, (1, 2, 66), "f32"),
-    (240, 16, 10, (15, 16, 17, 40), "f32"), (193, 63, 63, (64, 130), "bf16")])
+    (240, 16, 10, (15, 16, 17, 40), "f32"), (193, 63, 63, (64, 130), "bf16"),
+    (255, 1, 1, (2, 64, 65), "f32"), (253, 3, 2, (2, 3, 4, 63), "bf16"), (504, 8, 3, (64, 100), "f32")])
 def test_append(oracle, N_mem, N_max, T0, appends, io):
     from paper_2502_18394_amd import binding
     B, H, d = 2, 3, 64
@@ -38,3 +41,24 @@ def test_append(oracle, N_mem, N_max, T0, appends, io):
         assert rel_l2(c.prefix_fft.cpu().numpy(), oc.spec) <= 1e-5
         assert rel_l2(c.sum_q.cpu().numpy(), oc.sum_q) <= 1e-12
         assert np.array_equal(c.v_buf.cpu().numpy(), oc.v_buf.astype(np.float32))
+        assert np.array_equal(c.q_buf.cpu().numpy()[:, :, N_mem:], oc.q_buf.astype(np.float32)[:, :, -N_max:])
+
+
+@pytest.mark.parametrize("N_max", [1, 8, 16, 63, 256])
+@pytest.mark.parametrize("T,batches", [(32, 1), (64, 1), (65, 2)])
+def test_append_takes_64_tokens_per_sweep_on_any_ring(N_max, T, batches):
+    """A sweep moves the whole cache, so the number of them must not grow as the ring gets shorter: an append is two
+    launches (ring buffers, sweep) per 64 tokens, counted as the nodes of a captured call."""
+    from paper_2502_18394_amd import binding
+    n = 256
+    print(f"case N_max={N_max} T={T}", flush=True)
+    c = binding.PrefixCache(1, 1, 64, N_max, N_mem=n - N_max)
+    x = torch.ones((1, T, 1, 64), device="cuda")
+    c.update(x[:, :1].contiguous(), x[:, :1].contiguous())          # set-up happens here, not under capture
+    c.update(x, x)
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        c.update(x, x)
+    nodes = ctypes.c_size_t(0)
+    assert binding.lib().hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(nodes)) == 0
+    assert nodes.value == 2 * batches
