@@ -655,9 +655,9 @@ int spectre_mix_forward_ex(const void *v, const void *g, void *out, int B, int L
     float2 *gp = static_cast<float2 *>(ws);
     char *scr_base = static_cast<char *>(ws) + align256((size_t)BH * L * sizeof(float2));
     if (line_supported(L, (int)io, v, out) && !(flags & SPECTRE_MIX_BF16_SCRATCH)) {
-        // heads per group: as many as the four-step scratch of the workspace holds, 4 instead of 8 bytes per element
+        // the four-step scratch of the workspace holds twice its heads, at 4 instead of 8 bytes per element
         const MixGroups m = mix_groups(BH, L, d, 1);
-        int chunk = 2 * m.lanes * m.chunk < BH ? 2 * m.lanes * m.chunk : BH;
+        const int chunk = line_group_heads(BH, 2 * m.lanes * m.chunk);
         for (int bh0 = 0; bh0 < BH; bh0 += chunk) {
             hipError_t e = launch_mix_line(v, static_cast<const float2 *>(g), out, gp, scr_base, pl.twL, L, H, bh0,
                                            BH - bh0 < chunk ? BH - bh0 : chunk, st);

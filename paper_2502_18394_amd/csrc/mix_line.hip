@@ -8,11 +8,10 @@
 //   k_line           : a line at a time: forward transform, gate, inverse transform, in place
 //   k_line_turn<out> : lines -> rows
 // 24 bytes per pair and position; the column kernel is bound by its vector arithmetic (about 90 instructions per point).
-// Measured: L = 8192 63 -> 54 us for 32 heads (16 + 30 + 8.5), 231 -> 185 us for 128; L = 16384 129 -> 122 us for 32
-// heads (28 + 74 + 20), 284 -> 230 us for 64.  All heads of a call go through together (groups of 32 instead of the 128
-// heads: 216 us).  Rows of fp32 would
-// move the same 48 bytes either way and are slower here (78 -> 86 us), so they stay on the four-step route, as do lengths
-// with an odd factor, whose passes would leave lanes idle.
+// Measured: L = 8192 66 -> 61 us for 32 heads, 241 -> 189 us for 128; L = 16384 132 -> 113 us for 32 heads, 253 -> 206 us
+// for 64.  As many heads go through together as the scratch holds (line_group_heads; groups of 32 for 128 heads at
+// L = 8192: 216 us).  Rows of fp32 would move the same 48 bytes either way and are slower here (78 -> 86 us), so they stay
+// on the four-step route, as do lengths with an odd factor, whose passes would leave lanes idle.
 #include "mix_line.h"
 
 #include "fft_regs.h"
@@ -106,35 +105,42 @@ __global__ __launch_bounds__(256) void k_line_turn(const uint32_t *__restrict__ 
 // R1, 16.  Pass 0: lane tau owns positions tau + NT u.  Passes 1 and 2 stay inside the blocks of NT positions that a
 // group of 16 lanes owns (blocks tau / 16 + R1 q), so only the exchange between passes 0 and 1 crosses waves.  After pass
 // 2 the 16 values of position block blk, row s of 16 are the bins blk + R0 s + R0 R1 u.
-// A workgroup takes ppw lines of one head, the next one's loads in flight during the passes.  The factors are reloaded
-// (five values per layer, from L1) where they are used: kept in registers over the loop, with the products the compiler
-// forms from them, they spilled.
+// The launch is as wide as the chip and a workgroup takes its share of the XCD's lines, the next one's loads in flight during
+// the passes.  Workgroups of one, two or four lines ended in a ragged round, and with the head and the number of lines as
+// arguments 24 registers spilled at L = 16384: 32, 40, 64, 65, 100, 128 and 256 heads took 126, 190, 233, 285, 395, 510 and
+// 947 us (the four-step route 132, 162, 253, 270, 380, 478 and 935), now 113, 137, 206, 218, 315, 408 and 794; L = 8192,
+// 32, 100, 128 and 256 heads 61, 168, 187 and 402 us (66, 175, 241 and 464), now 61, 150, 189 and 374.
+// The factors are reloaded (five values per layer, from L1) where they are used: kept in registers over the loop, with the
+// products the compiler forms from them, they spilled.
 template <int R0, int R1>
 __global__ __launch_bounds__(16 * R1, 2) void k_line(uint32_t *__restrict__ lines, const float2 *__restrict__ gp,
-                                                     const float2 *__restrict__ twL, int nbh, int ppw) {
+                                                     const float2 *__restrict__ twL, int nbh) {
     constexpr int NT = 16 * R1, L = R0 * NT, Q1 = R0 / R1, Q2 = R0 / 16, S0 = NT + NT / 16;   // LDS position p + p / 16
     extern __shared__ float2 lds_line[];
     const int tau = threadIdx.x, i = tau & 15, grp = tau >> 4;
-    int bhl, part;
-    line_unit(blockIdx.x, 32 / ppw, &bhl, &part);
-    if (bhl >= nbh) return;                                          // whole workgroup: heads are padded to 8
-    u32x4_t *col = reinterpret_cast<u32x4_t *>(lines + ((size_t)bhl * 32 + part * ppw) * L) + tau;
+    const int xcd = blockIdx.x & 7;
+    const LineShare mine = line_share(xcd, blockIdx.x >> 3, gridDim.x >> 3, nbh);
+    const int n0 = mine.first, n1 = n0 + mine.count;
+    if (n0 == n1) return;                                            // whole workgroup
+    auto line_of = [&](int n) {
+        return reinterpret_cast<u32x4_t *>(lines + ((size_t)(8 * (n >> 5) + xcd) * 32 + (n & 31)) * L) + tau;
+    };
     u32x4_t raw[R0 / kVW];
 #pragma unroll
-    for (int j = 0; j < R0 / kVW; ++j) raw[j] = col[j * NT];
-    const float2 *gsrc = gp + (size_t)bhl * L + tau;
+    for (int e = 0; e < R0 / kVW; ++e) raw[e] = line_of(n0)[e * NT];
     float2 *b0 = lds_line + tau + (tau >> 4);
     float2 *b1 = lds_line + grp * S0 + i;
 #pragma unroll 1
-    for (int c = 0; c < ppw; ++c) {
+    for (int n = n0; n < n1; ++n) {
+        const float2 *gsrc = gp + (size_t)(8 * (n >> 5) + xcd) * L + tau;
         const float2 *tl = twL;
         asm volatile("" : "+s"(tl));                                 // a new value to the compiler in every round
         float2 x[R0];
 #pragma unroll
         for (int j = 0; j < R0; ++j) x[j] = IoBf16::unpack(raw[j / kVW][j % kVW]);
-        if (c + 1 < ppw) {
+        if (n + 1 < n1) {
 #pragma unroll
-            for (int j = 0; j < R0 / kVW; ++j) raw[j] = col[L / kVW + j * NT];
+            for (int j = 0; j < R0 / kVW; ++j) raw[j] = line_of(n + 1)[j * NT];
         }
         {
             const SmallTwiddles<R0> tw(tl, tau);
@@ -202,10 +208,9 @@ __global__ __launch_bounds__(16 * R1, 2) void k_line(uint32_t *__restrict__ line
             u32x4_t o;
 #pragma unroll
             for (int e = 0; e < kVW; ++e) o[e] = IoBf16::pack(x[kVW * j + e]);
-            col[j * NT] = o;
+            line_of(n)[j * NT] = o;
         }
-        col += L / kVW;
-        if (c + 1 < ppw) __syncthreads();                            // the next line's pass 0 writes what is read above
+        if (n + 1 < n1) __syncthreads();                             // the next line's pass 0 writes what is read above
     }
 }
 
@@ -226,13 +231,7 @@ static hipError_t line_t(const uint32_t *v, const float2 *g, uint32_t *out, floa
     auto kern = k_line<R0, R1>;
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
-    // lines per workgroup: more of them overlap their loads with the passes, but not at the price of idle places (two
-    // workgroups per compute unit at 8192, one at 16384): 32 heads, 1 / 2 / 4 lines: 54.0 / 54.1 / 66.1 us at 8192,
-    // 131 / 123 / 122 us at 16384
-    constexpr int kPlaces = 256 * (L == 8192 ? 2 : 1);
-    int ppw = 4;
-    while (ppw > 1 && heads8 * (32 / ppw) < kPlaces) ppw /= 2;
-    kern<<<heads8 * (32 / ppw), NT, lds, st>>>(lines, gp, twL, nbh, ppw);
+    kern<<<8 * line_workgroups(L, nbh), NT, lds, st>>>(lines, gp, twL, nbh);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     k_line_turn<false><<<tiles, 256, 0, st>>>(nullptr, out, lines, L, NT, H, bh0, nbh, nullptr, nullptr, R0, R1, 0);

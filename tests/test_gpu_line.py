@@ -1,5 +1,5 @@
 """GPU parity of the whole-column mixer (bf16 rows, L = 8192 and 16384): head counts that are and are not multiples of
-the eight XCDs, one, two and four lines per workgroup, heads taken in several groups."""
+the eight XCDs, workgroups with no line, one, several and unequal shares of them, heads taken in several groups."""
 import numpy as np
 import pytest
 import torch
@@ -11,7 +11,9 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("B,L,H,mb", [(1, 8192, 1, 0), (3, 8192, 3, 0), (1, 8192, 32, 0), (2, 8192, 9, 8),
-                                      (1, 16384, 1, 0), (2, 16384, 5, 0), (1, 16384, 16, 16)])
+                                      (1, 16384, 1, 0), (2, 16384, 5, 0), (1, 16384, 16, 16),
+                                      (1, 8192, 20, 0), (5, 8192, 13, 0),       # shares of 1 or 2 lines, of 4 or 5
+                                      (1, 16384, 20, 0), (3, 16384, 11, 0)])    # of 2 or 3, of 4 or 5
 def test_whole_column_mixer(oracle, options, B, L, H, mb):
     from paper_2502_18394_amd import binding
     print(f"case B={B} L={L} H={H} mb={mb}", flush=True)

@@ -24,3 +24,18 @@ def test_entry_order_and_spectrum_pairing(tmp_path):
     print(run.stdout)
     assert run.returncode == 0, run.stdout
     assert " 0 failures" in run.stdout
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC) and shutil.which("hipcc") is None, reason="hipcc not found")
+def test_shares_of_the_whole_column_mixer(tmp_path):
+    """`line_group_heads` and `line_share` (csrc/mix_line.h): groups within the scratch, as few as possible; every line in one
+    workgroup, XCDs and compute units evenly loaded."""
+    exe = tmp_path / "line_groups"
+    csrc = os.path.join(ROOT, "paper_2502_18394_amd", "csrc")
+    cmd = [HIPCC if os.path.exists(HIPCC) else "hipcc", "--cuda-host-only", "-x", "hip", "-std=c++17", "-O1", "-I", csrc,
+           os.path.join(ROOT, "tests", "host", "line_groups.cpp"), "-o", str(exe)]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert res.returncode == 0, res.stdout[-3000:]
+    run = subprocess.run([str(exe)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    print(run.stdout)
+    assert run.returncode == 0 and " 0 failures" in run.stdout, run.stdout
