@@ -41,12 +41,21 @@ __device__ __forceinline__ void stream_store(float2 *p, float2 v) {
 // Two adjacent channels (2c, 2c+1) of one token row travel as one complex number
 // (even channel = real part).  Storage types: float2 for fp32 rows, one 32-bit
 // word holding two bfloat16 for bf16 rows.
+// Loads of two elements from where callers only promise the alignment of one (the instruction is the same).
+typedef float f32x2_elem_t __attribute__((ext_vector_type(2), aligned(4)));
+typedef double f64x2_elem_t __attribute__((ext_vector_type(2), aligned(8)));
+typedef uint32_t bf16x2_elem_t __attribute__((aligned(2)));
+
 struct IoF32 {
     typedef float2 pair_t;
     static constexpr int kBytes = 4;
     __device__ static __forceinline__ float2 unpack(pair_t p) { return p; }
     __device__ static __forceinline__ pair_t pack(float2 v) { return v; }
     __device__ static __forceinline__ pair_t zero() { return make_float2(0.f, 0.f); }
+    __device__ static __forceinline__ pair_t load_elements(const pair_t *p) {
+        const f32x2_elem_t v = *reinterpret_cast<const f32x2_elem_t *>(p);
+        return make_float2(v.x, v.y);
+    }
     __device__ static __forceinline__ pair_t load_stream(const pair_t *p) { return stream_load(p); }
     __device__ static __forceinline__ void store_stream(pair_t *p, pair_t v) { stream_store(p, v); }
 };
@@ -62,6 +71,7 @@ struct IoBf16 {
         return __builtin_bit_cast(uint32_t, b);
     }
     __device__ static __forceinline__ pair_t zero() { return 0u; }
+    __device__ static __forceinline__ pair_t load_elements(const pair_t *p) { return *reinterpret_cast<const bf16x2_elem_t *>(p); }
     __device__ static __forceinline__ pair_t load_stream(const pair_t *p) { return __builtin_nontemporal_load(p); }
     __device__ static __forceinline__ void store_stream(pair_t *p, pair_t v) { __builtin_nontemporal_store(v, p); }
 };

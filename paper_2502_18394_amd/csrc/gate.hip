@@ -167,17 +167,17 @@ __global__ __launch_bounds__(kPrepLanes) void k_gate_prep(const double *__restri
     double2 s = make_double2(0.0, 0.0);
     if (grp < ng) {
         const size_t row = (size_t)H * np;
-        const double2 *src = reinterpret_cast<const double2 *>(partial) + (size_t)b * nchunks * row + (size_t)h * np + p;
+        const f64x2_elem_t *src = reinterpret_cast<const f64x2_elem_t *>(partial) + (size_t)b * nchunks * row + (size_t)h * np + p;
         int c = grp;
         for (; c + 7 * ng < nchunks; c += 8 * ng) {      // eight loads in flight, added in chunk order
-            double2 t[8];
+            f64x2_elem_t t[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) t[i] = src[(size_t)(c + i * ng) * row];
 #pragma unroll
             for (int i = 0; i < 8; ++i) { s.x += t[i].x; s.y += t[i].y; }
         }
         for (; c < nchunks; c += ng) {
-            const double2 t = src[(size_t)c * row];
+            const f64x2_elem_t t = src[(size_t)c * row];
             s.x += t.x;
             s.y += t.y;
         }

@@ -70,13 +70,13 @@ __global__ __launch_bounds__(256) void k_ring_batch(const typename IO::pair_t *_
         const int i = min(rl + 8 * u, nb - 1);                       // clamped: neither stored nor summed past the end
         ring[u] = ((size_t)bh * N + M0 + (s0 + i) % W) * 32 + p;
         const size_t src = (((size_t)b * T + i0 + i) * H + h) * 32 + p;
-        rv[u] = v_new[src];
-        rq[u] = q_new[src];
+        rv[u] = IO::load_elements(v_new + src);
+        rq[u] = IO::load_elements(q_new + src);
         vo[u] = qo[u] = make_float2(0.f, 0.f);
         if (i >= W) {
             const size_t own = src - (size_t)W * H * 32;
-            vo[u] = IO::unpack(v_new[own]);
-            qo[u] = IO::unpack(q_new[own]);
+            vo[u] = IO::unpack(IO::load_elements(v_new + own));
+            qo[u] = IO::unpack(IO::load_elements(q_new + own));
         } else if (i >= evict_from) {
             vo[u] = v_buf[ring[u]];
             qo[u] = q_buf[ring[u]];

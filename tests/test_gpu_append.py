@@ -62,3 +62,36 @@ def test_append_takes_64_tokens_per_sweep_on_any_ring(N_max, T, batches):
     nodes = ctypes.c_size_t(0)
     assert binding.lib().hipGraphGetNodes(ctypes.c_void_p(graph.raw_cuda_graph()), None, ctypes.byref(nodes)) == 0
     assert nodes.value == 2 * batches
+
+
+def off_by_one(t):
+    """The same values one element further on than an allocation starts."""
+    flat = torch.empty(t.numel() + 1, dtype=t.dtype, device="cuda")
+    flat[1:] = t.reshape(-1)
+    return flat[1:].view(t.shape)
+
+
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+@pytest.mark.parametrize("T", [1, 2, 65, 159])
+def test_rows_and_sums_need_no_more_than_the_alignment_of_an_element(T, io):
+    """Appended rows are read in pairs and running sums two at a time: the state is the same, bit for bit, wherever the
+    elements lie, and so are the gate and the decode step that read those sums."""
+    from paper_2502_18394_amd import binding
+    B, H, N = 2, 3, 256
+    print(f"case T={T} io={io}", flush=True)
+    _, vs = synth.tokens(910, (B, 2 + T, H, 64), io)
+    _, qs = synth.tokens(911, (B, 2 + T, H, 64), io)
+    P = binding.GateParams(synth.gate_params(912, H, 64, N))
+    states = []
+    for place in (lambda t: t, off_by_one):
+        c = binding.PrefixCache(B, H, 64, N)
+        sums = place(c.sum_q)
+        c.c.sum_q = sums.data_ptr()
+        cut = lambda a, i, j: place(to_device(np.ascontiguousarray(a[:, i:j]), io))
+        for i, j in ((1, 2), (2, 2 + T)):                           # an empty cache would be pre-filled
+            c.update(cut(vs, i, j), cut(qs, i, j))
+        out = c.step(cut(vs, 0, 1), cut(qs, 0, 1), P)
+        g = binding.gate(sums, P, 1.0 / N, pooled=True)
+        states.append([c.prefix_fft, c.v_buf, c.q_buf, sums, out, g])
+    for a, b in zip(*states):
+        assert torch.equal(torch.view_as_real(a) if a.is_complex() else a, torch.view_as_real(b) if b.is_complex() else b)
