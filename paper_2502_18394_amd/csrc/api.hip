@@ -654,7 +654,7 @@ int spectre_mix_forward_ex(const void *v, const void *g, void *out, int B, int L
     if (rc) return rc;
     float2 *gp = static_cast<float2 *>(ws);
     char *scr_base = static_cast<char *>(ws) + align256((size_t)BH * L * sizeof(float2));
-    if (line_supported(L, (int)io, v, out) && !(flags & SPECTRE_MIX_BF16_SCRATCH)) {
+    if (line_supported(L, (int)io) && !(flags & SPECTRE_MIX_BF16_SCRATCH)) {
         // the four-step scratch of the workspace holds twice its heads, at 4 instead of 8 bytes per element
         const MixGroups m = mix_groups(BH, L, d, 1);
         const int chunk = line_group_heads(BH, 2 * m.lanes * m.chunk);

@@ -21,6 +21,9 @@
 namespace spectre {
 
 typedef unsigned int u32x4_t __attribute__((ext_vector_type(4)));
+// Rows lie on the 4-byte boundary of a channel pair and are read and written in 16-byte pieces all the same, so that a
+// head's result does not depend on where its tensor starts.
+typedef unsigned int u32x4_pair_t __attribute__((ext_vector_type(4), aligned(4)));
 
 // A line's element t = tau + NT j (NT = lanes of the column kernel) sits at (j / 4) 4 NT + 4 tau + j % 4: four
 // consecutive values of a lane's j are one 16-byte word.
@@ -35,7 +38,9 @@ __device__ __forceinline__ void line_unit(int id, int per_head, int *bhl, int *w
 
 // A workgroup turns 4 j x 32 tau rows of one head, 128 bytes each, through LDS: 512-byte runs on the side of the lines.
 // grid: nexp gate blocks (IN only), then the tiles of 8 ceil(nbh / 8) heads.
-template <bool IN>
+// ONCE: the rows pass the caches by; rows off a 16-byte boundary share lines with their neighbours and do not (L = 16384, 128
+// heads 528 instead of 600 us).
+template <bool IN, bool ONCE>
 __global__ __launch_bounds__(256) void k_line_turn(const uint32_t *__restrict__ rows_in, uint32_t *__restrict__ rows_out,
                                                    uint32_t *__restrict__ lines, int L, int NT, int H, int bh0, int nbh,
                                                    const float2 *__restrict__ g, float2 *__restrict__ gp, int R0, int R1,
@@ -69,8 +74,9 @@ __global__ __launch_bounds__(256) void k_line_turn(const uint32_t *__restrict__ 
     const size_t row0 = (((size_t)b * L + tau0 + r0 + (size_t)NT * j0) * H + h) * 32 + 4 * piece, rstep = (size_t)NT * H * 32;
     u32x4_t w[4];
     if (IN) {
+        const u32x4_pair_t *src = reinterpret_cast<const u32x4_pair_t *>(rows_in + row0);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) w[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t *>(rows_in + row0 + i * rstep));
+        for (int i = 0; i < 4; ++i) w[i] = ONCE ? __builtin_nontemporal_load(src + i * (rstep / 4)) : src[i * (rstep / 4)];
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
 #pragma unroll
@@ -96,7 +102,12 @@ __global__ __launch_bounds__(256) void k_line_turn(const uint32_t *__restrict__ 
         for (int i = 0; i < 4; ++i) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) w[i][c] = tile[(r0 + 32 * i) * S + 4 * piece + c];
-            __builtin_nontemporal_store(w[i], reinterpret_cast<u32x4_t *>(rows_out + row0 + i * rstep));
+        }
+        u32x4_pair_t *dst = reinterpret_cast<u32x4_pair_t *>(rows_out + row0);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (ONCE) __builtin_nontemporal_store(w[i], dst + i * (rstep / 4));
+            else dst[i * (rstep / 4)] = w[i];
         }
     }
 }
@@ -215,16 +226,15 @@ __global__ __launch_bounds__(16 * R1, 2) void k_line(uint32_t *__restrict__ line
 }
 
 // ------------------------------------------------------------------------------------------
-bool line_supported(int L, int io, const void *v, const void *out) {
-    return io == 1 && (L == 8192 || L == 16384) && ((reinterpret_cast<uintptr_t>(v) | reinterpret_cast<uintptr_t>(out)) & 15) == 0;
-}
+bool line_supported(int L, int io) { return io == 1 && (L == 8192 || L == 16384); }
 
 template <int R0, int R1>
 static hipError_t line_t(const uint32_t *v, const float2 *g, uint32_t *out, float2 *gp, uint32_t *lines, const float2 *twL,
                          int H, int bh0, int nbh, hipStream_t st) {
     constexpr int NT = 16 * R1, L = R0 * NT;
     const int heads8 = (nbh + 7) / 8 * 8, tiles = L / kTurnRows * heads8, nexp = nbh * (L / 256);
-    k_line_turn<true><<<nexp + tiles, 256, 0, st>>>(v, nullptr, lines, L, NT, H, bh0, nbh, g, gp, R0, R1, nexp);
+    const auto turn_in = reinterpret_cast<uintptr_t>(v) & 15 ? k_line_turn<true, false> : k_line_turn<true, true>;
+    turn_in<<<nexp + tiles, 256, 0, st>>>(v, nullptr, lines, L, NT, H, bh0, nbh, g, gp, R0, R1, nexp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t lds = (size_t)R0 * (NT + NT / 16) * sizeof(float2);
@@ -234,7 +244,8 @@ static hipError_t line_t(const uint32_t *v, const float2 *g, uint32_t *out, floa
     kern<<<8 * line_workgroups(L, nbh), NT, lds, st>>>(lines, gp, twL, nbh);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    k_line_turn<false><<<tiles, 256, 0, st>>>(nullptr, out, lines, L, NT, H, bh0, nbh, nullptr, nullptr, R0, R1, 0);
+    const auto turn_out = reinterpret_cast<uintptr_t>(out) & 15 ? k_line_turn<false, false> : k_line_turn<false, true>;
+    turn_out<<<tiles, 256, 0, st>>>(nullptr, out, lines, L, NT, H, bh0, nbh, nullptr, nullptr, R0, R1, 0);
     return hipGetLastError();
 }
 
@@ -251,7 +262,7 @@ hipError_t launch_mix_line(const void *v, const float2 *g, void *out, float2 *gp
 // that no compute call is the first to touch it.
 hipError_t load_kernels_mix_line() {
     hipFuncAttributes a;
-    return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(k_line_turn<true>));
+    return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(&k_line_turn<true, true>));
 }
 
 }  // namespace spectre

@@ -28,8 +28,8 @@ def test_whole_column_mixer(oracle, options, B, L, H, mb):
 
 
 @pytest.mark.parametrize("shift_in,shift_out", [(2, 0), (0, 2), (6, 2)])
-def test_tensors_off_a_16_byte_boundary_take_the_four_step_route(oracle, shift_in, shift_out):
-    """Channel pairs are 4 bytes and that is all a caller owes: same result, and not a byte outside the output."""
+def test_tensors_off_a_16_byte_boundary_give_the_same_rows(oracle, shift_in, shift_out):
+    """Channel pairs are 4 bytes and that is all a caller owes: same result bit for bit, and not a byte outside the output."""
     from paper_2502_18394_amd import binding
     B, L, H = 1, 8192, 2
     print(f"case shifts {shift_in} {shift_out} elements", flush=True)
@@ -44,5 +44,6 @@ def test_tensors_off_a_16_byte_boundary_take_the_four_step_route(oracle, shift_i
     want = oracle.mix_forward(v.astype(np.float64), g.astype(np.complex128))
     assert rel_l2(got, want) <= TOL["bf16"]
     assert_close_elementwise(got, want, "bf16", L)
+    assert np.array_equal(got, from_device(binding.mix_forward(to_device(vs, "bf16"), torch.from_numpy(g).cuda())))
     rest = torch.cat([dst[:shift_out], dst[shift_out + n:]]).float()
     assert bool((rest == 7.0).all())
