@@ -276,10 +276,10 @@ __global__ __launch_bounds__(256) void k_decode_final(const float *__restrict__ 
             qo = *reinterpret_cast<const float2 *>(rg.q_buf + ring);
         }
         dnew = make_float2(vn.x - vo.x, vn.y - vo.y);
-        f64x2_elem_t s = *reinterpret_cast<const f64x2_elem_t *>(rg.sum_q + i);
+        double2 s = *reinterpret_cast<const double2 *>(rg.sum_q + i);
         s.x += (double)qn.x - (double)qo.x;
         s.y += (double)qn.y - (double)qo.y;
-        *reinterpret_cast<f64x2_elem_t *>(rg.sum_q + i) = s;
+        *reinterpret_cast<double2 *>(rg.sum_q + i) = s;
         *reinterpret_cast<float2 *>(rg.v_buf + ring) = vn;
         *reinterpret_cast<float2 *>(rg.q_buf + ring) = qn;
         if (LAZY) *reinterpret_cast<float2 *>(pending + ((size_t)(npend - 1) * BH + bh) * 64 + 2 * p) = dnew;

@@ -74,8 +74,8 @@ def off_by_one(t):
 @pytest.mark.parametrize("io", ["f32", "bf16"])
 @pytest.mark.parametrize("T", [1, 2, 65, 159])
 def test_rows_and_sums_need_no_more_than_the_alignment_of_an_element(T, io):
-    """Appended rows are read in pairs and running sums two at a time: the state is the same, bit for bit, wherever the
-    elements lie, and so are the gate and the decode step that read those sums."""
+    """Appended rows are read in pairs and pooled sums two at a time: the state and the gate are the same, bit for bit,
+    wherever the elements lie (the cache's own arrays are on 16-byte boundaries)."""
     from paper_2502_18394_amd import binding
     B, H, N = 2, 3, 256
     print(f"case T={T} io={io}", flush=True)
@@ -85,13 +85,11 @@ def test_rows_and_sums_need_no_more_than_the_alignment_of_an_element(T, io):
     states = []
     for place in (lambda t: t, off_by_one):
         c = binding.PrefixCache(B, H, 64, N)
-        sums = place(c.sum_q)
-        c.c.sum_q = sums.data_ptr()
         cut = lambda a, i, j: place(to_device(np.ascontiguousarray(a[:, i:j]), io))
         for i, j in ((1, 2), (2, 2 + T)):                           # an empty cache would be pre-filled
             c.update(cut(vs, i, j), cut(qs, i, j))
         out = c.step(cut(vs, 0, 1), cut(qs, 0, 1), P)
-        g = binding.gate(sums, P, 1.0 / N, pooled=True)
-        states.append([c.prefix_fft, c.v_buf, c.q_buf, sums, out, g])
+        g = binding.gate(place(c.sum_q), P, 1.0 / N, pooled=True)
+        states.append([c.prefix_fft, c.v_buf, c.q_buf, c.sum_q, out, g])
     for a, b in zip(*states):
         assert torch.equal(torch.view_as_real(a) if a.is_complex() else a, torch.view_as_real(b) if b.is_complex() else b)
