@@ -109,7 +109,7 @@ def test_deferred_argument_checks():
                                                      (4, 32, 480, 16), (5, 0, 512, 7)])
 def test_random_sequences_of_operations_track_the_oracle(oracle, seed, N_mem, N_max, defer):
     """A seeded mix of everything the cache can be asked to do - fused steps (eager or deferred), appends of 1 to
-    N_max tokens (one sweep per token, 32 per sweep, window re-transformed), explicit flushes, both readouts - with
+    N_max tokens (one sweep per token, 64 per sweep, window re-transformed), explicit flushes, both readouts - with
     the oracle applying Eq. 5 token by token beside it; state and outputs are compared after every operation."""
     from paper_2502_18394_amd import binding
     B, H, d = 2, 2, 64

@@ -148,7 +148,8 @@ def test_gate_seeded_shapes(oracle, B, L, H, d, dg, n, io, shared, modrelu, phas
     (5, 640, 60, 60, "f32", 0, 0), (4, 1024, 64, 1, "f32", 0, 0),   # many heads: the narrow workgroup
     (3, 201, 90, 90, "bf16", 0, 0), (4, 1024, 64, 1, "bf16", 0, 0), # the same with one part per head, and with two
     (2, 300, 3, 3, "f32", 2, 7),         # Toeplitz update and phase behind it
-    (256, 130, 1, 1, "f32", 0, 0), (33, 1300, 2, 2, "bf16", 0, 0)]) # tiles of fewer than 32 rows in the output layer
+    (256, 130, 1, 1, "f32", 0, 0),       # one head of many sequences
+    (33, 1300, 2, 2, "bf16", 0, 0)])     # weights too long for that kernel: the output layer's tiles, of four rows here
 def test_gate_one_launch_and_its_edges(oracle, B, L, H, Hg, io, taps, pos):
     from paper_2502_18394_amd import binding
     print(f"case B={B} L={L} H={H} Hg={Hg} io={io} taps={taps} pos={pos}", flush=True)
@@ -162,3 +163,19 @@ def test_gate_one_launch_and_its_edges(oracle, B, L, H, Hg, io, taps, pos):
         p64["toeplitz"] = p["toeplitz"].astype(np.complex128)
     want = oracle.gate(oracle.pool_q(q.astype(np.float64)), 1.0 / L, p64, L, pos)
     assert rel_l2(got, want) <= TOL["f32"]
+
+
+@pytest.mark.parametrize("B,rows", [(455, 8), (911, 16), (1815, 32)])
+def test_gate_output_layer_tiles(oracle, B, rows):
+    """Many sequences over shared weights: tiles of 8, 16 and 32 rows, the last one ragged."""
+    from paper_2502_18394_amd import binding
+    H, n, workgroups = 3, 1300, 6                          # 21 tiles of 64 outputs, four to a workgroup
+    per = 32
+    while per > 4 and B * H > per // 2 and workgroups * -(-B * H // per) < 1024:    # the launch's rule (csrc/gate.hip)
+        per //= 2
+    assert per == rows and B * H % per
+    print(f"case B={B} rows={rows}", flush=True)
+    p = synth.gate_params(81, 1, 64, n)
+    sq = np.random.default_rng(82).standard_normal((B, H, 64)) * 40.0
+    got = binding.gate(torch.from_numpy(sq).cuda(), binding.GateParams(p), 1.0 / n, pooled=True).cpu().numpy()
+    assert rel_l2(got, oracle.gate(sq, 1.0 / n, f64(p), n, 0)) <= 1e-5
