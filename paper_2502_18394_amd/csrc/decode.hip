@@ -363,6 +363,8 @@ static hipError_t decode_t(const DecodeRing &rg, float2 *X, double inv_count, co
     int bpw = lazy ? 4 : 2;
     if (bpw > B) bpw = B;
     while (bpw > 1 && (long long)nch * H * ((B + bpw - 1) / bpw) < 1024) bpw = (bpw + 1) / 2;
+    // the same number of workgroups with even shares: five sequences as 3 + 2, not 4 + 1
+    bpw = (B + (B + bpw - 1) / bpw - 1) / ((B + bpw - 1) / bpw);
     const long long wgs = ((long long)nch * H + 7) / 8 * 8 * ((B + bpw - 1) / bpw);
     if (wgs > 0x7fffffffLL) return hipErrorInvalidValue;
     const size_t lds = kBinStride * sizeof(float2) +
