@@ -125,45 +125,46 @@ __global__ __launch_bounds__(256) void k_pool_final(const double *__restrict__ p
 }
 
 // ------------------------------------------------------------------------------------------
-// prep: one workgroup of 512 lanes per (b, h), from the pooling pass's partial sums to the hidden layer: the chunks'
+// prep: one workgroup of NT = 512 lanes, or 256 where there are many, per (b, h), from the pooling pass's partial sums to the hidden layer: the chunks'
 // sums (fp64, fixed order), optionally times W_q (the sums are then those of X: pooling commutes with the projection),
 // LayerNorm with fp64 statistics, and the small d x d_g product on the vector units, its d terms split over lane groups
 // (fixed split, partial sums added in group order).  sum_q != nullptr: the pooled query is also stored.
 // One dependent launch where there were two (three with W_q): 5 us each at any size.
-constexpr int kPrepLanes = 512;
-
-__device__ __forceinline__ double block_sum_512(double x, double *red, int lane, int wave) {
+template <int NT>
+__device__ __forceinline__ double block_sum(double x, double *red, int lane, int wave) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off);
     if (lane == 0) red[wave] = x;
     __syncthreads();
-    return ((red[0] + red[1]) + (red[2] + red[3])) + ((red[4] + red[5]) + (red[6] + red[7]));
+    const double s = (red[0] + red[1]) + (red[2] + red[3]);
+    return NT == 256 ? s : s + ((red[4] + red[5]) + (red[6] + red[7]));
 }
 
-__global__ __launch_bounds__(kPrepLanes) void k_gate_prep(const double *__restrict__ partial, int nchunks,
-                                                          const float *__restrict__ Wq, int Hw,
-                                                          double *__restrict__ sum_q, double inv_count, GateDev P,
-                                                          float *__restrict__ hid, int H) {
-    __shared__ double2 acc[kPrepLanes];
-    __shared__ double xs[256], red[16];
-    __shared__ float qbar[256], part[kPrepLanes];
+template <int NT>
+__global__ __launch_bounds__(NT) void k_gate_prep(const double *__restrict__ partial, int nchunks,
+                                                  const float *__restrict__ Wq, int Hw, double *__restrict__ sum_q,
+                                                  double inv_count, GateDev P, float *__restrict__ hid, int H) {
+    constexpr int NW = NT / 64, IPW = 64 / NW;                       // waves; inputs of a 64 x 64 product per wave
+    __shared__ double2 acc[NT];
+    __shared__ double xs[256], red[2 * NW];
+    __shared__ float qbar[256], part[NT];
     const int bh = blockIdx.x, b = bh / H, h = bh % H, hp = (P.Hg == 1) ? 0 : h, d = P.d, dg = P.d_g;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // the weights' latency passes behind the sums (the usual widths only; any other is read where it is used)
     const bool usual = d == 64 && dg == 64;
-    float w1[8], wq[8], gam = 0.f, bet = 0.f, b1 = 0.f;
+    float w1[IPW], wq[IPW], gam = 0.f, bet = 0.f, b1 = 0.f;
     if (usual) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) w1[i] = P.W1[(size_t)hp * 4096 + (8 * wave + i) * 64 + lane];
+        for (int i = 0; i < IPW; ++i) w1[i] = P.W1[(size_t)hp * 4096 + (IPW * wave + i) * 64 + lane];
         gam = P.ln_gamma[hp * 64 + lane];
         bet = P.ln_beta[hp * 64 + lane];
         b1 = P.b1[hp * 64 + lane];
     }
     if (Wq) {
 #pragma unroll
-        for (int i = 0; i < 8; ++i) wq[i] = Wq[(size_t)((Hw == 1) ? 0 : h) * 4096 + (8 * wave + i) * 64 + lane];
+        for (int i = 0; i < IPW; ++i) wq[i] = Wq[(size_t)((Hw == 1) ? 0 : h) * 4096 + (IPW * wave + i) * 64 + lane];
     }
-    const int np = d / 2, ng = kPrepLanes / np, p = tid % np, grp = tid / np;
+    const int np = d / 2, ng = NT / np, p = tid % np, grp = tid / np;
     double2 s = make_double2(0.0, 0.0);
     if (grp < ng) {
         const size_t row = (size_t)H * np;
@@ -191,17 +192,17 @@ __global__ __launch_bounds__(kPrepLanes) void k_gate_prep(const double *__restri
         xs[2 * tid + 1] = t.y;
     }
     __syncthreads();
-    if (Wq) {                                            // d = 64: lane (j, seg) takes 8 of the 64 terms of output j
+    if (Wq) {                                            // d = 64: lane (j, seg) takes IPW of the 64 terms of output j
         double t = 0.0;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) t += xs[8 * wave + i] * (double)wq[i];
+        for (int i = 0; i < IPW; ++i) t += xs[IPW * wave + i] * (double)wq[i];
         double *a = reinterpret_cast<double *>(acc);
         a[tid] = t;
         __syncthreads();
         if (tid < 64) {
             double q = a[tid];
 #pragma unroll
-            for (int r = 1; r < 8; ++r) q += a[64 * r + tid];
+            for (int r = 1; r < NW; ++r) q += a[64 * r + tid];
             xs[tid] = q;
         }
         __syncthreads();
@@ -214,25 +215,25 @@ __global__ __launch_bounds__(kPrepLanes) void k_gate_prep(const double *__restri
         const float qv = (float)((double)gam * dev * rstd + (double)bet);
         float a = 0.f;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) a = fmaf(__shfl(qv, 8 * wave + i), w1[i], a);
+        for (int i = 0; i < IPW; ++i) a = fmaf(__shfl(qv, IPW * wave + i), w1[i], a);
         part[tid] = a;
         __syncthreads();
         if (tid < 64) {
             float t = b1;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) t += part[64 * q + tid];
+            for (int q = 0; q < NW; ++q) t += part[64 * q + tid];
             hid[(size_t)bh * 64 + tid] = 0.5f * t * (1.0f + erff(t * 0.70710678118654752440f));
         }
         return;
     }
     const double x = (tid < d) ? inv_count * xs[tid] : 0.0;
-    const double mean = block_sum_512(x, red, lane, wave) / d;
+    const double mean = block_sum<NT>(x, red, lane, wave) / d;
     const double dev = (tid < d) ? x - mean : 0.0;
-    const double var = block_sum_512(dev * dev, red + 8, lane, wave) / d;
+    const double var = block_sum<NT>(dev * dev, red + NW, lane, wave) / d;
     const double rstd = 1.0 / sqrt(var + (double)P.ln_eps);
     if (tid < d) qbar[tid] = (float)((double)P.ln_gamma[hp * d + tid] * dev * rstd + (double)P.ln_beta[hp * d + tid]);
     __syncthreads();
-    const int nseg = (dg <= 64) ? 8 : (dg <= 128) ? 4 : 2, cols = kPrepLanes / nseg;
+    const int nseg = NT / (dg <= 64 ? 64 : dg <= 128 ? 128 : 256), cols = NT / nseg;
     const int jcol = tid % cols, seg = tid / cols;
     const int dseg = (d + nseg - 1) / nseg, i0 = seg * dseg, i1 = (i0 + dseg < d) ? i0 + dseg : d;
     float a = 0.f;
@@ -675,7 +676,10 @@ hipError_t launch_pool_final(const double *partial, double *sum, int B, int row,
 hipError_t launch_gate_prep(const double *partial, int nchunks, const float *Wq, int Hw, double *sum_q, double inv_count,
                             const GateDev &P, float *hid, int B, int H, hipStream_t st) {
     if (Wq && P.d != 64) return hipErrorInvalidValue;
-    k_gate_prep<<<B * H, kPrepLanes, 0, st>>>(partial, nchunks, Wq, Hw, sum_q, inv_count, P, hid, H);
+    // four workgroups of 512 lanes fit a compute unit; with more heads than twice that many the number in flight counts for
+    // more than the latency of one (from pooled sums, H=32 n=196: B=128 23 -> 18 us, B=256 38 -> 28)
+    if (B * H >= 2048) k_gate_prep<256><<<B * H, 256, 0, st>>>(partial, nchunks, Wq, Hw, sum_q, inv_count, P, hid, H);
+    else k_gate_prep<512><<<B * H, 512, 0, st>>>(partial, nchunks, Wq, Hw, sum_q, inv_count, P, hid, H);
     return hipGetLastError();
 }
 
