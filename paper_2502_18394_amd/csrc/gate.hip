@@ -701,13 +701,18 @@ static hipError_t launch_gate_tail(const GateDev &P, const float2 *raw, int B, i
 
 // Short sequences: up to 256 KB of rows per head (B=1 H=32, step of gate and mixer: bf16 L=2048 46.0 -> 42.8 us, L=4096
 // would be 50.4 -> 53.8), unless several sequences would each read a head's output weights of more than 320 KB again
-// (B=8 H=32 L=1024, 263 KB: 82.1 -> 77.9 us; B=4 L=2048, 525 KB: 82.3 -> 88.4).
+// (B=8 H=32 L=1024, 263 KB: 82.1 -> 77.9 us; B=4 L=2048, 525 KB: 82.3 -> 88.4), or all of them together would read so much
+// that way, at about 17 TB/s, that it costs more than the other route's 23 us and 3 ns a head.  Gate alone, bf16, this
+// kernel and the three launches: H=32 B=64 L=900 65 and 66 us, B=64 L=1024 73 and 66, B=128 L=1024 144 and 116, B=256
+// L=512 147 and 125, B=256 L=1240 337 and 270.
 static bool gate_small(int io, const GateDev &P, int B, int L, int H) {
     const int F = P.n_fft / 2 + 1;
     const size_t rows = (size_t)L * 64 * (io ? 2 : 4), w2 = (size_t)2 * F * 64 * 4;
+    const long long heads = (long long)B * H;
     if (P.d != 64 || P.d_g != 64 || F < 32 || rows > ((size_t)256 << 10)) return false;
     if ((reinterpret_cast<uintptr_t>(P.W2) & 15) || (reinterpret_cast<uintptr_t>(P.b2) & 7)) return false;
-    return (long long)B * H <= 65535 && (B == 1 || w2 <= ((size_t)320 << 10));
+    if (heads > 65535) return false;
+    return B == 1 || (w2 <= ((size_t)320 << 10) && heads * ((long long)w2 - 50000) <= 400000000);
 }
 
 hipError_t launch_gate(int io, const void *q, double *partial, double inv_count, const GateDev &P, float *hid, float2 *raw,
