@@ -179,3 +179,16 @@ def test_gate_output_layer_tiles(oracle, B, rows):
     sq = np.random.default_rng(82).standard_normal((B, H, 64)) * 40.0
     got = binding.gate(torch.from_numpy(sq).cuda(), binding.GateParams(p), 1.0 / n, pooled=True).cpu().numpy()
     assert rel_l2(got, oracle.gate(sq, 1.0 / n, f64(p), n, 0)) <= 1e-5
+
+
+@pytest.mark.parametrize("B,H,n,d,dg,Hg", [
+    (1024, 2, 196, 64, 64, 2), (1030, 2, 64, 256, 200, 1), (700, 3, 130, 32, 100, 3),   # 2048 heads and more: prep of 256 lanes
+    (19, 1, 20480, 64, 64, 1), (19, 2, 16384, 64, 64, 2),      # weights beyond 4 MB a set: tiles of 16 rows, a ragged one
+    (250, 1, 20480, 64, 64, 1)])                               # the same, enough workgroups with 32 rows
+def test_gate_of_many_heads_and_of_large_weights(oracle, B, H, n, d, dg, Hg):
+    from paper_2502_18394_amd import binding
+    print(f"case B={B} H={H} n={n} d={d} dg={dg} Hg={Hg}", flush=True)
+    p = synth.gate_params(83 + n, Hg, d, n, d_g=dg)
+    sq = np.random.default_rng(84).standard_normal((B, H, d)) * 40.0
+    got = binding.gate(torch.from_numpy(sq).cuda(), binding.GateParams(p), 1.0 / n, pooled=True).cpu().numpy()
+    assert rel_l2(got, oracle.gate(sq, 1.0 / n, f64(p), n, 0)) <= 1e-5

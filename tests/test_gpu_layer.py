@@ -84,6 +84,12 @@ def test_layer_on_the_other_routes_matches_oracle_chain(oracle, B, L, H, io, J):
     assert np.array_equal(got, ref)                           # the very same kernels in the same order
 
 
+def test_layer_of_many_heads(oracle):
+    """2048 heads: the gate's preparation, with the query projection in it, in workgroups of 256 lanes."""
+    got, ref, want = run_layer(oracle, 256, 60, 8, "f32", None, seed=synth.BASE_SEED + 700)
+    assert rel_l2(got, want) <= 2e-5 and rel_l2(got, ref) <= 1e-6
+
+
 def test_layer_rejects_bad_arguments():
     from paper_2502_18394_amd import binding
     d = 64
