@@ -27,8 +27,8 @@ HBM_PEAK_GBS = 8000.0            # MI355X HBM3E
 # the figures are read from the tracked summary of those passes, lines of the form `name = bytes`
 TRAFFIC_FILE = os.path.join("profiles", "traffic_llama1b_128k_and_decode_32k.txt")
 # lane-instructions per complex point (one channel pair at one position) of the three transform kernels at
-# L = 131072, counted in the ISA of the built library: 84 (column kernel) + 37 + 37 (row kernels)
-COUNTED_LANE_INSTR_PER_POINT_128K = 158
+# L = 131072, from SQ_INSTS_VALU / SQ_WAVES: 79 (column kernel) + 35 + 37 (row kernels)
+COUNTED_LANE_INSTR_PER_POINT_128K = 151
 # fp32 vector peak without packed math: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz lane-instructions/s
 VALU_PEAK_GINSTR = 256 * 4 * 16 * 2.4
 
@@ -454,7 +454,7 @@ def main():
         sweep_bytes = 2 * 8 * Bd * Hd * Fd * dd
         res["decode"] = {"workload": f"decode_32k: fused Prefix-FFT step B={Bd} H={Hd} d={dd} N_max={N}, cache full (eviction branch), fp32",
                          "tokens_per_s": Bd / (ms_dec * 1e-3), "ms_per_step": ms_dec, "steps": args.decode_steps,
-                         "roofline": {"bound": "hbm", "kernel": "k_sweep<update,read>", "achieved": sweep_bytes / (ms_dec * 1e-3) / 1e9,
+                         "roofline": {"bound": "hbm", "kernel": "k_decode<float,false>", "achieved": sweep_bytes / (ms_dec * 1e-3) / 1e9,
                                       "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": sweep_bytes / (ms_dec * 1e-3) / 1e9 / HBM_PEAK_GBS,
                                       "traffic": traffic_figures().get("decode_sweep_bytes_per_step"),
                                       "traffic_source": TRAFFIC_FILE, "algorithmic_bytes": sweep_bytes}}

@@ -256,8 +256,10 @@ int get_pow2_plan(int L, Pow2Plan *pl, bool make) {
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Appends of at least this many tokens re-transform the window instead of sweeping the cache once per 32 tokens
-// (a sweep costs about a quarter of a window transform at the decode benchmark's shape).
+// Appends of at least this many tokens re-transform the window instead of sweeping the cache once per 64 tokens.  The line
+// was drawn when a sweep took 32 tokens and a window transform one pass more; by the present kernels it could lie at 65:
+// one, two and three sweeps (64, 65 and 159 tokens) against a transform (160), B=4 H=32: N=2048 56, 87, 151 and 66 us,
+// N=8192 151, 264, 429 and 201; B=2 N=32768 276, 493, 787 and 400.
 constexpr int kAppendRetransform = 160;
 
 // Scratch columns are processed in groups of heads small enough to stay in the memory-side
@@ -363,7 +365,8 @@ static int mix_route(int BH, int L, int d) {
     return chirp_padded_length(L) ? 3 : 0;
 }
 
-// Workspace sections of the arbitrary-length route (short padded lengths use only gp, the gate of the data pass).
+// Workspace sections of the arbitrary-length route.  Short padded lengths use only BH (M / 2 + 1) complex numbers of gp, the
+// gate of the data pass; the size asked for stays what it was when they took the kernels of the longer ones.
 struct ChirpLayout {
     int M, nph;
     size_t gp, scr, t1, t2;      // byte sizes
@@ -758,6 +761,7 @@ static size_t gate_raw_bytes(int B, int H, const spectre_gate_params *P) {
 
 size_t spectre_gate_workspace_bytes(int B, int L, int H, const spectre_gate_params *P) {
     if (!P || B < 1 || L < 1 || H < 1 || P->d < 2 || P->d_g < 1) return 0;
+    // the second term, once the pooled query, is spare: the size asked for stays
     return align256(gate_partial_bytes(B, L, H, P->d)) + align256((size_t)B * H * P->d * sizeof(double)) +
            align256((size_t)B * H * P->d_g * sizeof(float)) + gate_raw_bytes(B, H, P);
 }
@@ -1303,7 +1307,7 @@ int spectre_prefix_update(spectre_prefix_cache *c, const void *v_new, const void
         c->t += 1;
         return SPECTRE_OK;
     }
-    // many tokens (T up to the ring capacity): cheaper than T / 32 sweeps is to bring the ring buffers up to date in
+    // many tokens (T up to the ring capacity): cheaper than T / 64 sweeps is to bring the ring buffers up to date in
     // one pass and transform the window afresh, as the pre-fill does (the cache IS the transform of the window)
     if (T >= kAppendRetransform && T <= W) {
         const int s0 = (int)(c->t % W);
