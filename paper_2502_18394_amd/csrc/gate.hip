@@ -777,17 +777,13 @@ hipError_t launch_gate_out(const float *hid, const GateDev &P, float2 *raw, int 
         // every tile of the rows in one launch (grid.z); a single tile takes the narrowest kernel that fits
         // rows per tile: 32, fewer while the launch would have less than four workgroups per compute unit (B=256 H=12
         // L=196, 96 workgroups of 32 rows: 15 -> 7.4 us).  Every tile reads the weights again, so where those of one set
-        // do not stay in an XCD's 4 MB of L2, 16 rows are the least, and 32 stay if they come to a round of two workgroups
-        // per compute unit and up to a third of another (from pooled sums, 32 / 16 / 8 / 4 rows: n = 20480, 24 rows over
-        // 4 sets 20 / 17 / 17 / 21 us, 96 over one 19 / 16 / 17 / 22, 256 over one (648 workgroups) 27 / 31 / 36 / 51;
-        // n = 65536, 96 over one (771) 39 / 36 / 45 / 72; n = 8192, 96 over one 18 / 13 / 12 / 12).
+        // do not stay in an XCD's 4 MB of L2, two workgroups per compute unit are enough and 16 rows the least (from pooled
+        // sums, 32 / 16 / 8 / 4 rows: n = 20480, 24 rows over 4 sets 20 / 17 / 17 / 21 us, 96 over one 19 / 16 / 17 / 22,
+        // 256 over one 27 / 31 / 36 / 51; n = 8192, 96 over one 18 / 13 / 12 / 12).
         const bool large = (size_t)twoF * P.d_g * sizeof(float) > ((size_t)4 << 20);
         int per = 32;
-        while (per > (large ? 16 : 4) && M > per / 2) {
-            const long long wgs = (long long)grid.x * grid.y * ((M + per - 1) / per);
-            if (wgs >= 1024 || (large && wgs >= 512 && wgs < 683)) break;
-            per /= 2;
-        }
+        while (per > (large ? 16 : 4) && M > per / 2 &&
+               (long long)grid.x * grid.y * ((M + per - 1) / per) < (large ? 512 : 1024)) per /= 2;
         const int ntile = (M + per - 1) / per;
         const int rows = (ntile > 1) ? per : M;
         const int rg = (rows + 3) / 4;            // 1..8 row groups per tile
