@@ -328,7 +328,7 @@ def main():
     headline = (args.workload == "llama1b_128k" and not args.L)
     traffic = traffic_figures() if headline else {}
     if headline:      # counted in the ISA; other lengths: 3.5 per point per radix-2 stage each way + 6 for the gate
-        instr_per_point, instr_src = COUNTED_LANE_INSTR_PER_POINT_128K, "counted in the ISA of the three transform kernels"
+        instr_per_point, instr_src = COUNTED_LANE_INSTR_PER_POINT_128K, "SQ_INSTS_VALU over SQ_WAVES of the three transform kernels"
     else:
         instr_per_point, instr_src = 2 * 3.5 * (L.bit_length() - 1) + 6, "model: 3.5 per point and radix-2 stage each way + 6"
     mix_flops_instr = tokens * H * (d // 2) * instr_per_point
