@@ -7,6 +7,7 @@
 #include "prefix.h"
 
 #include "common.h"
+#include "fft_regs.h"
 #include "mix_pow2.h"
 #include "prefix_dev.h"
 
@@ -280,8 +281,8 @@ __global__ __launch_bounds__(256) void k_sweep_lazy(const float4 *__restrict__ X
 // as in k_sweep.  What hides the latency of a block's loads is the other waves of the SIMD, three of them: with the next
 // block's entries prefetched into registers instead there was room for two (16 tokens and readout at B=1 H=32 N=8192:
 // 44 against 33 us), and a fourth spills (50 us).
-// Up to 64 tokens go into one sweep: B=4 H=32 N=8192 takes 105 us for 8 tokens and 151 for 64 (537 MB, and 55 us of
-// matrix instructions), against 2 x 133 us for two sweeps of 32 before.
+// It takes the tokens whose slots are not consecutive: those of a ring behind memory rows that wraps around within a batch,
+// and of one shorter than the batch; the others go to k_append_fold.
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int kFlushChunks = 8;   // chunks of kSweepBins bins per workgroup at most
@@ -389,6 +390,108 @@ __global__ __launch_bounds__(256, 3) void k_flush_mfma(
             }
             *reinterpret_cast<float2 *>(partial + ((size_t)bh * nchunks + chunk) * 64 + 2 * col) = t;
         }
+    }
+}
+
+// The same update for tokens in consecutive ring slots, as an appended batch is: X[k] += sum_i Delta_i w^(k s_i), with
+// w = exp(-j 2 pi / N), by pruned transforms on the vector units.  For bins k = kap + (N / 16) b, b = 0..15, the factor of
+// a slot s is w^(kap s) W_16^(b s): the tokens of one residue r of s mod 16 are added up with the factors w^(16 kap g)
+// of their groups of 16, turned by w^(kap s) of the first of them, and one 16-point transform over r gives all 16 bins.
+// Bins above N / 2 are the conjugates of those below, so kap = 0 .. N / 32 covers the half spectrum, with the bins of
+// kap = 0 and N / 32 counted once.  Lane = channel; a wave keeps the tokens' 16 G values of its channels in registers over
+// all its kap, whose factors are uniform: one lane each fetches them from the table.
+// What bounds it is the stream over the half spectra, and the arithmetic, 20 us of vector instructions at B=4 H=32 N=8192
+// with 57 tokens (537 MB), passes behind it: 101 us with the ring buffers' launch, 147 with k_flush_mfma, whose 55 us of
+// matrix instructions add to the stream; 8 tokens 114 -> 97; B=8 N=32768, 40 tokens 870 -> 716.  Deferred steps with their
+// flush: B=4 N=8192, 8 tokens 543 -> 523.  The spectra come out closer to 64 bits (57 tokens 2.33e-7 -> 1.37e-7).
+// READ: partial[bh][blockIdx.x] = the workgroup's share of the newest row's readout from the updated entries, as in k_sweep.
+template <int G, bool READ>
+__global__ __launch_bounds__(256, G <= 2 ? 3 : 2) void k_append_fold(float2 *__restrict__ X, const float *__restrict__ delta,
+                                                                     const float2 *__restrict__ tw, int N, int BH, int T,
+                                                                     int s0, int per_wg, const float2 *__restrict__ g,
+                                                                     float *__restrict__ partial, int slot_new) {
+    __shared__ float red[READ ? 4 : 1][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int bh = blockIdx.y, N16 = N / 16, top = N / 32, F = N / 2 + 1;
+    const int end = min(top + 1, ((int)blockIdx.x + 1) * per_wg);
+    int kap = blockIdx.x * per_wg + wave;
+    if (!READ && kap >= end) return;
+    // the slot residue r holds the tokens f + 16 g, f = (r - s0) mod 16
+    float dl[G][16];
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int f = (r - s0) & 15;
+#pragma unroll
+        for (int g = 0; g < G; ++g) {
+            const int i = f + 16 * g;
+            dl[g][r] = i < T ? delta[((size_t)i * BH + bh) * 64 + lane] : 0.0f;
+        }
+    }
+    // lanes 0..15: w^(kap (s0 + f)) of residue r = lane; lanes 16 + g: w^(16 kap g)
+    unsigned mult = lane < 16 ? (unsigned)(s0 + ((lane - s0) & 15)) : lane < 16 + G ? 16u * (lane - 16) : 0u;
+    if (mult >= (unsigned)N) mult -= (unsigned)N;
+    float2 wn = tw[mul_mod((unsigned)min(kap, top), mult, N)];
+    // READ: lane b's readout factor of bin b, (c_k / N) g_k conj(w_k)
+    const float2 *gh = READ ? g + (size_t)bh * F : nullptr;
+    auto bin = [&](int kp, int b) { return b < 8 ? kp + N16 * b : N16 * (16 - b) - kp; };
+    float2 gn = make_float2(0.f, 0.f), tn = gn;
+    const float invN = 1.0f / (float)N;
+    float acc = 0.0f;
+    if (READ) {
+        const int k = bin(min(kap, top), lane & 15);
+        gn = gh[k];
+        tn = tw[mul_mod((unsigned)k, (unsigned)slot_new, N)];
+    }
+    float2 *Xh = X + (size_t)bh * F * 64 + lane;
+    for (; kap < end; kap += 4) {
+        float2 x[16];
+#pragma unroll
+        for (int b = 0; b < 16; ++b) x[b] = stream_load(Xh + (size_t)bin(kap, b) * 64);   // in range also where a bin
+        const float2 w = wn, rd = cmulc(gn, tn);                                          // appears twice
+        const int next = min(kap + 4, top);
+        wn = tw[mul_mod((unsigned)next, mult, N)];
+        if (READ) {
+            const int k = bin(next, lane & 15);
+            gn = gh[k];
+            tn = tw[mul_mod((unsigned)k, (unsigned)slot_new, N)];
+        }
+        auto lane_value = [](float2 v, int l) {
+            return make_float2(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(v.x), l)),
+                               __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v.y), l)));
+        };
+        float2 y[16];
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+            float2 a = make_float2(dl[0][r], 0.0f);
+#pragma unroll
+            for (int g = 1; g < G; ++g) {
+                const float2 wg = lane_value(w, 16 + g);
+                a.x = fmaf(dl[g][r], wg.x, a.x);
+                a.y = g == 1 ? dl[g][r] * wg.y : fmaf(dl[g][r], wg.y, a.y);
+            }
+            const float2 wr = lane_value(w, r);
+            y[r] = G == 1 ? make_float2(a.x * wr.x, a.x * wr.y) : cmul(a, wr);
+        }
+        dft<16, false>(y);
+        const int nb = kap == 0 ? 9 : kap == top ? 8 : 16;           // uniform
+#pragma unroll
+        for (int b = 0; b < 16; ++b) {
+            if (b < 8 || b < nb) {
+                const float2 v = make_float2(x[b].x + y[b].x, b < 8 ? x[b].y + y[b].y : x[b].y - y[b].y);
+                stream_store(Xh + (size_t)bin(kap, b) * 64, v);
+                if (READ) {
+                    const float2 r = lane_value(rd, b);
+                    const float one = fmaf(r.x, v.x, -r.y * v.y);    // c_k = 2 but at DC and Nyquist
+                    acc = fmaf((b == 0 || b == 8) && kap == 0 ? invN : 2.0f * invN, one, acc);
+                }
+            }
+        }
+    }
+    if (READ) {
+        red[wave][lane] = acc;
+        __syncthreads();
+        if (wave == 0)
+            partial[((size_t)bh * gridDim.x + blockIdx.x) * 64 + lane] = (red[0][lane] + red[1][lane]) + (red[2][lane] + red[3][lane]);
     }
 }
 
@@ -729,6 +832,28 @@ hipError_t launch_sweep_lazy(bool flush, bool read, float2 *X, const float *pend
     float4 *X4 = reinterpret_cast<float4 *>(X);
     if (!flush) {
         k_sweep_lazy<<<grid, 256, 0, st>>>(X4, tw, g, partial, kpart, F, N, BH, slot_new, ps, nch);
+        return hipGetLastError();
+    }
+    bool consecutive = npend > 0;                          // as roots of order N see the slots, i.e. modulo N
+    for (int i = 1; i < npend; ++i) consecutive = consecutive && slots[i] == (slots[i - 1] + 1) % N;
+    if (consecutive) {
+        // values of kap per workgroup, two of each wave: few, so that the launch's rows lie close together (B=4 H=32 N=8192,
+        // 57 tokens, with 4, 8, 12, 16, 24 of them 114, 99, 103, 106, 110 us; B=8 N=32768, 40 tokens 812, 714, 736, 744, 801);
+        // halved while the launch would have less than four workgroups per compute unit.  With the readout as many as leave
+        // sweep_chunks(F) = N / 256 + 1 partial sums.
+        const int kaps = N / 32 + 1;
+        int per_wg = 8;
+        if (!read && (long long)((kaps + 7) / 8) * BH < 1024) per_wg = 4;
+        const dim3 fold_grid((kaps + per_wg - 1) / per_wg, BH);
+#define SPECTRE_FOLD(GV, RD) \
+    k_append_fold<GV, RD><<<fold_grid, 256, 0, st>>>(X, pending, tw, N, BH, npend, slots[0], per_wg, g, partial, slot_new)
+        if (read) {
+            if (npend <= 16) SPECTRE_FOLD(1, true); else SPECTRE_FOLD(2, true);
+        } else {
+            if (npend <= 16) SPECTRE_FOLD(1, false); else if (npend <= 32) SPECTRE_FOLD(2, false);
+            else if (npend <= 48) SPECTRE_FOLD(3, false); else SPECTRE_FOLD(4, false);
+        }
+#undef SPECTRE_FOLD
         return hipGetLastError();
     }
     // chunks per workgroup: all kFlushChunks share one set-up of the tokens' operands, fewer while the launch would have

@@ -44,6 +44,29 @@ def test_append(oracle, N_mem, N_max, T0, appends, io):
         assert np.array_equal(c.q_buf.cpu().numpy()[:, :, N_mem:], oc.q_buf.astype(np.float32)[:, :, -N_max:])
 
 
+@pytest.mark.parametrize("N_mem,N,T0", [(0, 256, 250), (0, 768, 3), (0, 1792, 1785), (16, 256, 200), (7, 256, 1)])
+def test_append_groups_of_16_tokens(oracle, N_mem, N, T0):
+    """Batches at the edges of the groups of 16 tokens that a sweep folds, in windows with and without an odd factor, around
+    the wrap of the ring; rings behind memory rows take the other sweep where a batch wraps.  1e-6: fp32 sums of at most 64
+    terms per bin and append, 1.4e-7 measured."""
+    from paper_2502_18394_amd import binding
+    B, H, d = 2, 2, 64
+    print(f"case N_mem={N_mem} N={N} T0={T0}", flush=True)
+    c, oc = binding.PrefixCache(B, H, d, N - N_mem, N_mem=N_mem), oracle.MemoryPrefixCache(B, H, d, N_mem, N - N_mem)
+    M = np.random.default_rng(950).standard_normal((B, H, N_mem, d)).astype(np.float32)
+    if N_mem:
+        c.set_memory(torch.from_numpy(M).cuda())
+    x, _ = synth.tokens(951, (B, T0, H, d))
+    c.update(to_device(x, "f32"), to_device(x, "f32"))
+    oc.prefill(M.astype(np.float64), x.astype(np.float64), x.astype(np.float64))
+    for T in (2, 15, 16, 17, 31, 32, 33, 47, 48, 49, 64):
+        x, _ = synth.tokens(952 + T, (B, T, H, d))
+        c.update(to_device(x, "f32"), to_device(x, "f32"))
+        for i in range(T):
+            oc.update(x[:, i:i + 1].astype(np.float64), x[:, i:i + 1].astype(np.float64))
+        assert rel_l2(c.prefix_fft.cpu().numpy(), oc.spec) <= 1e-6, T
+
+
 @pytest.mark.parametrize("N_max", [1, 8, 16, 63, 256])
 @pytest.mark.parametrize("T,batches", [(32, 1), (64, 1), (65, 2)])
 def test_append_takes_64_tokens_per_sweep_on_any_ring(N_max, T, batches):
