@@ -14,9 +14,11 @@
 namespace spectre {
 
 // ------------------------------------------------------------------------------------------
+// One 16-byte store per lane in workgroups as small as that: those that run together then write one narrow range (6.4 GB 946
+// us, 6.8 TB/s; 65536 workgroups that stride over the whole array 1108, four or sixteen stores per lane 1071 and 1277).
 __global__ __launch_bounds__(256) void k_fill_zero(uint4 *__restrict__ p, size_t n16) {
-    const size_t stride = (size_t)gridDim.x * 256;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n16; i += stride) p[i] = make_uint4(0, 0, 0, 0);
+    const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
+    if (i < n16) p[i] = make_uint4(0, 0, 0, 0);
 }
 
 // twiddle[m] = exp(-j 2 pi m / N), evaluated in fp64 and rounded once.
@@ -763,12 +765,15 @@ __global__ __launch_bounds__(256) void k_tangle(const float4 *__restrict__ X, co
 
 // ------------------------------------------------------------------------------------------
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t st) {
-    const size_t n16 = bytes / 16;   // callers pass multiples of 16 bytes
-    if (n16 == 0) return hipSuccess;
-    size_t blocks = (n16 + 255) / 256;
-    if (blocks > 65536) blocks = 65536;
-    k_fill_zero<<<(unsigned)blocks, 256, 0, st>>>(static_cast<uint4 *>(p), n16);
-    return hipGetLastError();
+    uint4 *q = static_cast<uint4 *>(p);
+    constexpr size_t kMost = (size_t)1 << 30;          // 16 GiB a launch
+    for (size_t n16 = bytes / 16, n; n16 > 0; n16 -= n, q += n) {    // callers pass multiples of 16 bytes
+        n = n16 < kMost ? n16 : kMost;
+        k_fill_zero<<<(unsigned)((n + 255) / 256), 256, 0, st>>>(q, n);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 hipError_t launch_fill_twiddle(float2 *tw, int N, hipStream_t st) {
