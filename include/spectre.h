@@ -382,7 +382,7 @@ int spectre_prefix_set_memory(spectre_prefix_cache *cache /*host*/, const float 
  *        sum_q += q_t - [t >= N_max] q_buf[s];  v_buf[s] = v_t;  q_buf[s] = q_t;  t += 1.
  *        The ring buffers and sum_q end as if updated token by token; the cache itself takes the
  *        rank-one terms of up to 64 tokens in one sweep (their sum, by linearity).
- *        From 160 tokens on (and T <= N_max) the ring buffers are instead brought up to date in one
+ *        From 129 tokens on (and T <= N_max) the ring buffers are instead brought up to date in one
  *        pass and the window is transformed afresh, as in the pre-fill: the same state, cheaper.
  * On success cache->t has advanced by T.
  */

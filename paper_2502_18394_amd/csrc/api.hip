@@ -256,11 +256,10 @@ int get_pow2_plan(int L, Pow2Plan *pl, bool make) {
 
 static size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
-// Appends of at least this many tokens re-transform the window instead of sweeping the cache once per 64 tokens.  The line
-// was drawn when a sweep took 32 tokens and a window transform one pass more; by the present kernels it could lie at 65:
-// one, two and three sweeps (64, 65 and 159 tokens) against a transform (160), B=4 H=32: N=2048 56, 87, 151 and 66 us,
-// N=8192 151, 264, 429 and 201; B=2 N=32768 276, 493, 787 and 400.
-constexpr int kAppendRetransform = 160;
+// Appends of at least this many tokens re-transform the window instead of sweeping the cache once per 64 tokens: three
+// sweeps cost more than the transform, two about the same (128, 129 .. 159 tokens by sweeps and 160 by the transform, H=32:
+// B=4 N=8192 198, 294 and 189 us; B=8 N=32768 1439, 2189 and 1484; B=1 N=1024 23, 32 and 21).
+constexpr int kAppendRetransform = 129;
 
 // Scratch columns are processed in groups of heads small enough to stay in the memory-side
 // cache between the three kernels of a group.
@@ -1268,6 +1267,7 @@ int spectre_prefix_update(spectre_prefix_cache *c, const void *v_new, const void
     float2 *scr = reinterpret_cast<float2 *>(w);
     float2 *X = static_cast<float2 *>(c->prefix_fft);
     hipError_t e;
+    const int ring_chunks = (T + ring_append_rows(B, T, H) - 1) / ring_append_rows(B, T, H);
     if (c->t == 0 && T > 1) {
         // the ring buffers are all zero on an empty cache (spectre_prefix_init): only the prompt's rows are written,
         // and the same pass sums the queries.  Without memory rows the value rows are read once, by the row transform,
@@ -1277,7 +1277,7 @@ int spectre_prefix_update(spectre_prefix_cache *c, const void *v_new, const void
         e = launch_ring_append((int)io, fused_ring ? nullptr : v_new, q_new, static_cast<float *>(c->v_buf),
                                static_cast<float *>(c->q_buf), partial, B, T, H, N, M0, W, 0, 0, st);
         if (e != hipSuccess) return fail_hip(e, "ring_append(prompt)");
-        e = launch_pool_final(partial, static_cast<double *>(c->sum_q), B, H * d, (T + 255) / 256, st, false);
+        e = launch_pool_final(partial, static_cast<double *>(c->sum_q), B, H * d, ring_chunks, st, false);
         if (e != hipSuccess) return fail_hip(e, "pool_final(prompt)");
         if (!fused_ring) {
             rc = transform_window(c, scr, st);
@@ -1314,7 +1314,7 @@ int spectre_prefix_update(spectre_prefix_cache *c, const void *v_new, const void
         e = launch_ring_append((int)io, v_new, q_new, static_cast<float *>(c->v_buf), static_cast<float *>(c->q_buf), partial,
                                B, T, H, N, M0, W, s0, c->t, st);
         if (e != hipSuccess) return fail_hip(e, "ring_append");
-        e = launch_pool_final(partial, static_cast<double *>(c->sum_q), B, H * d, (T + 255) / 256, st, true);
+        e = launch_pool_final(partial, static_cast<double *>(c->sum_q), B, H * d, ring_chunks, st, true);
         if (e != hipSuccess) return fail_hip(e, "pool_final(append)");
         rc = transform_window(c, scr, st);
         if (rc) return rc;

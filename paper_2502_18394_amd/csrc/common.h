@@ -45,6 +45,8 @@ __device__ __forceinline__ void stream_store(float2 *p, float2 v) {
 typedef float f32x2_elem_t __attribute__((ext_vector_type(2), aligned(4)));
 typedef double f64x2_elem_t __attribute__((ext_vector_type(2), aligned(8)));
 typedef uint32_t bf16x2_elem_t __attribute__((aligned(2)));
+typedef float f32x4_elem_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t bf16x4_elem_t __attribute__((ext_vector_type(2), aligned(2)));
 
 struct IoF32 {
     typedef float2 pair_t;
@@ -56,6 +58,9 @@ struct IoF32 {
         const f32x2_elem_t v = *reinterpret_cast<const f32x2_elem_t *>(p);
         return make_float2(v.x, v.y);
     }
+    typedef f32x4_t quad_t;                                          // two adjacent pairs
+    __device__ static __forceinline__ quad_t load_quad(const pair_t *p) { return *reinterpret_cast<const f32x4_elem_t *>(p); }
+    __device__ static __forceinline__ float4 unpack_quad(quad_t q) { return make_float4(q.x, q.y, q.z, q.w); }
     __device__ static __forceinline__ pair_t load_stream(const pair_t *p) { return stream_load(p); }
     __device__ static __forceinline__ void store_stream(pair_t *p, pair_t v) { stream_store(p, v); }
 };
@@ -72,6 +77,12 @@ struct IoBf16 {
     }
     __device__ static __forceinline__ pair_t zero() { return 0u; }
     __device__ static __forceinline__ pair_t load_elements(const pair_t *p) { return *reinterpret_cast<const bf16x2_elem_t *>(p); }
+    typedef uint32_t quad_t __attribute__((ext_vector_type(2)));
+    __device__ static __forceinline__ quad_t load_quad(const pair_t *p) { return *reinterpret_cast<const bf16x4_elem_t *>(p); }
+    __device__ static __forceinline__ float4 unpack_quad(quad_t q) {
+        const float2 a = unpack(q.x), b = unpack(q.y);
+        return make_float4(a.x, a.y, b.x, b.y);
+    }
     __device__ static __forceinline__ pair_t load_stream(const pair_t *p) { return __builtin_nontemporal_load(p); }
     __device__ static __forceinline__ void store_stream(pair_t *p, pair_t v) { __builtin_nontemporal_store(v, p); }
 };

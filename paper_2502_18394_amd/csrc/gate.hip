@@ -620,7 +620,7 @@ __global__ __launch_bounds__(256) void k_gate_phase(float2 *__restrict__ g, int 
 // ------------------------------------------------------------------------------------------
 // Rows summed by one workgroup of the pooling pass: kPoolRows, halved (down to 16) while the pass would launch
 // fewer than about two workgroups per compute unit (short sequences: 8192 rows of 32 heads are only 32 chunks of 256).
-static int pool_rows(int B, int L, int H, int d) {
+int pool_rows(int B, int L, int H, int d) {
     const long long wide = ((long long)H * d / 8 + 255) / 256;       // workgroups across a row with 16-byte lanes
     int rows = kPoolRows;
     while (rows > 16 && (long long)B * ((L + rows - 1) / rows) * wide < 512) rows /= 2;

@@ -35,8 +35,9 @@ hipError_t launch_ring_batch(int io, const void *v_new, const void *q_new, int T
                              float *q_buf, double *sum_q, float *delta, int B, int H, int N, int M0, int W, long long t,
                              hipStream_t st);
 // Ring-buffer bookkeeping for T <= W tokens appended at once (token i -> slot (s0 + i) mod W behind M0 memory rows,
-// evicting when t0 + i >= W); partial [B][ceil(T/256)][H*64] doubles = per-chunk sums of q_new - q_evicted.
+// evicting when t0 + i >= W); partial [B][ceil(T / ring_append_rows)][H*64] doubles (gate_partial_bytes) = per-chunk sums of q_new - q_evicted.
 // V == nullptr: only the query side (q_buf, partial); the value rows are then written by whoever reads V.
+int ring_append_rows(int B, int T, int H);
 hipError_t launch_ring_append(int io, const void *V, const void *Q, float *v_buf, float *q_buf, double *partial, int B,
                               int T, int H, int N, int M0, int W, int s0, long long t0, hipStream_t st);
 hipError_t launch_sweep_lazy(bool flush, bool read, float2 *X, const float *pending, const float2 *tw, const float2 *g,

@@ -8,6 +8,7 @@
 
 #include "common.h"
 #include "fft_regs.h"
+#include "gate.h"
 #include "mix_pow2.h"
 #include "prefix_dev.h"
 
@@ -611,51 +612,57 @@ __global__ __launch_bounds__(256) void k_readout_final(const float *__restrict__
 // pre-fill helpers.
 // Many tokens appended at once - the prompt on an empty cache (whose ring buffers are all zero), or a long append to
 // a cache that already holds some (T <= ring capacity W, so every slot is written at most once): token i of the call goes to ring slot (s0 + i) mod W, evicting what was there when t0 + i >= W (Eq. 5's
-// ring-buffer bookkeeping for T tokens at once).  grid (ceil(T / 256), B*H); 256 lanes = 32 channel pairs x 8 row
-// lanes; partial[b][chunk][h*64 + c] = the chunk's sum of q_new - q_evicted in fp64 (added to sum_q afterwards).
-template <typename IO>
+// ring-buffer bookkeeping for T tokens at once).  grid (B*H, nchunks of `rows` tokens); 256 lanes = 16 x four channels by
+// 16 row lanes; partial[b][chunk][h*64 + c] = the chunk's sum of q_new - q_evicted in fp64 (added to sum_q afterwards).
+// What bounds it is memory traffic, two thirds of it the fp32 rows written: workgroups that run together take adjacent heads,
+// i.e. whole token rows, and the ring's rows pass the caches by.
+template <typename IO, bool VALUES>
 __global__ __launch_bounds__(256) void k_ring_append(const typename IO::pair_t *__restrict__ V,
                                                      const typename IO::pair_t *__restrict__ Q,
-                                                     float2 *__restrict__ v_buf, float2 *__restrict__ q_buf,
+                                                     float4 *__restrict__ v_buf, float4 *__restrict__ q_buf,
                                                      double *__restrict__ partial, int T, int H, int N, int M0, int W,
-                                                     int s0, long long t0, int nchunks) {
-    __shared__ double red[8][64];
-    const int p = threadIdx.x & 31, rl = threadIdx.x >> 5;
-    const int chunk = blockIdx.x, bh = blockIdx.y, h = bh % H, b = bh / H;
-    double sx = 0.0, sy = 0.0;
-    const int i_end = min(T, chunk * 256 + 256);
-    for (int i0 = chunk * 256 + rl; i0 < i_end; i0 += 64) {          // eight rows per trip, their loads up front
-        typename IO::pair_t rv[8], rq[8];
-        float2 qo[8];
-        size_t ring[8];
+                                                     int s0, long long t0, int rows, int nchunks) {
+    __shared__ double red[16][64];
+    constexpr int kU = VALUES ? 4 : 8;                               // rows per lane and trip, their loads up front
+    const int p = threadIdx.x & 15, rl = threadIdx.x >> 4;
+    const int bh = blockIdx.x, chunk = blockIdx.y, h = bh % H, b = bh / H;
+    const int i_end = min(T, chunk * rows + rows);
+    const int evict_from = t0 >= W ? 0 : (int)(W - t0);              // tokens from this one on replace another
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    for (int i0 = chunk * rows + rl; i0 < i_end; i0 += 16 * kU) {
+        typename IO::quad_t rv[kU], rq[kU];
+        float4 qo[kU];
+        size_t ring[kU];
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            const int i = min(i0 + 8 * u, i_end - 1);               // clamped: rows past the end are not stored
-            const int slot = (int)(((long long)s0 + i) % W);
-            ring[u] = ((size_t)bh * N + M0 + slot) * 32 + p;
-            const size_t src = (((size_t)b * T + i) * H + h) * 32 + p;
-            rv[u] = V ? V[src] : IO::zero();
-            rq[u] = Q[src];
-            qo[u] = (t0 + i >= W) ? q_buf[ring[u]] : make_float2(0.f, 0.f);
+        for (int u = 0; u < kU; ++u) {
+            const int i = min(i0 + 16 * u, i_end - 1);               // clamped: rows past the end are not stored
+            const int slot = s0 + i < W ? s0 + i : s0 + i - W;
+            ring[u] = ((size_t)bh * N + M0 + slot) * 16 + p;
+            const size_t src = (((size_t)b * T + i) * H + h) * 32 + 2 * p;
+            if (VALUES) rv[u] = IO::load_quad(V + src);              // otherwise the value rows are written elsewhere
+            rq[u] = IO::load_quad(Q + src);
+            qo[u] = i >= evict_from ? q_buf[ring[u]] : make_float4(0.f, 0.f, 0.f, 0.f);
         }
 #pragma unroll
-        for (int u = 0; u < 8; ++u) {
-            if (i0 + 8 * u < i_end) {
-                const float2 vn = IO::unpack(rv[u]), qn = IO::unpack(rq[u]);
-                sx += (double)qn.x - (double)qo[u].x;
-                sy += (double)qn.y - (double)qo[u].y;
-                if (V) v_buf[ring[u]] = vn;                          // V == nullptr: the value rows are written elsewhere
-                q_buf[ring[u]] = qn;
+        for (int u = 0; u < kU; ++u) {
+            if (i0 + 16 * u < i_end) {
+                const float4 qn = IO::unpack_quad(rq[u]);
+                s[0] += (double)qn.x - (double)qo[u].x;
+                s[1] += (double)qn.y - (double)qo[u].y;
+                s[2] += (double)qn.z - (double)qo[u].z;
+                s[3] += (double)qn.w - (double)qo[u].w;
+                if (VALUES) stream_store(v_buf + ring[u], IO::unpack_quad(rv[u]));
+                stream_store(q_buf + ring[u], qn);
             }
         }
     }
-    red[rl][2 * p] = sx;
-    red[rl][2 * p + 1] = sy;
+#pragma unroll
+    for (int c = 0; c < 4; ++c) red[rl][4 * p + c] = s[c];
     __syncthreads();
     if (threadIdx.x < 64) {
         double t = red[0][threadIdx.x];
 #pragma unroll
-        for (int r = 1; r < 8; ++r) t += red[r][threadIdx.x];
+        for (int r = 1; r < 16; ++r) t += red[r][threadIdx.x];
         partial[((size_t)b * nchunks + chunk) * (H * 64) + h * 64 + threadIdx.x] = t;
     }
 }
@@ -900,18 +907,25 @@ hipError_t launch_set_memory(const float *mem, int mem_batch, float *v_buf, int 
     return hipGetLastError();
 }
 
+// Tokens per workgroup: 256, halved (down to 16, and to no more partial sums than the pooling pass of T rows has) while the
+// launch would have less than eight workgroups per compute unit.
+int ring_append_rows(int B, int T, int H) {
+    int rows = kPoolRows;
+    while (rows > pool_rows(B, T, H, 64) && (long long)B * H * ((T + rows - 1) / rows) < 2048) rows /= 2;
+    return rows;
+}
+
 hipError_t launch_ring_append(int io, const void *V, const void *Q, float *v_buf, float *q_buf, double *partial, int B,
                               int T, int H, int N, int M0, int W, int s0, long long t0, hipStream_t st) {
-    const int nchunks = (T + 255) / 256;
-    const dim3 grid(nchunks, B * H);
-    if (io)
-        k_ring_append<IoBf16><<<grid, 256, 0, st>>>(static_cast<const uint32_t *>(V), static_cast<const uint32_t *>(Q),
-                                                    reinterpret_cast<float2 *>(v_buf), reinterpret_cast<float2 *>(q_buf),
-                                                    partial, T, H, N, M0, W, s0, t0, nchunks);
-    else
-        k_ring_append<IoF32><<<grid, 256, 0, st>>>(static_cast<const float2 *>(V), static_cast<const float2 *>(Q),
-                                                   reinterpret_cast<float2 *>(v_buf), reinterpret_cast<float2 *>(q_buf),
-                                                   partial, T, H, N, M0, W, s0, t0, nchunks);
+    const int rows = ring_append_rows(B, T, H), nchunks = (T + rows - 1) / rows;
+    const dim3 grid(B * H, nchunks);
+#define SPECTRE_RING_APPEND(IO, VAL)                                                                                       \
+    k_ring_append<IO, VAL><<<grid, 256, 0, st>>>(static_cast<const IO::pair_t *>(V), static_cast<const IO::pair_t *>(Q),   \
+                                                 reinterpret_cast<float4 *>(v_buf), reinterpret_cast<float4 *>(q_buf),     \
+                                                 partial, T, H, N, M0, W, s0, t0, rows, nchunks)
+    if (io) { if (V) SPECTRE_RING_APPEND(IoBf16, true); else SPECTRE_RING_APPEND(IoBf16, false); }
+    else { if (V) SPECTRE_RING_APPEND(IoF32, true); else SPECTRE_RING_APPEND(IoF32, false); }
+#undef SPECTRE_RING_APPEND
     return hipGetLastError();
 }
 
