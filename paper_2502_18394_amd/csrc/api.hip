@@ -352,19 +352,21 @@ int spectre_version(void) { return 120; }
 
 // 0 = no kernel, 1 = whole slab in LDS, 2 = four-step power-of-two path, 3 = any other length
 // through a padded power-of-two convolution, 4 = four-step path fused into one kernel (L = 4096).
-static int mix_route(int BH, int L, int d) {
+static int mix_route(int BH, int L, int d, spectre_dtype io) {
     if (d != 64) return 0;
     int N1, N2, P;
-    const bool p2 = pow2_split(L, &N1, &N2, &P), sl = slab_supported(L);
-    // the in-LDS kernel is one launch: it wins when the length has no four-step plan, when there are many short
-    // slabs, and when the whole call is small enough to be bound by the four-step path's dependent launches
-    if (sl && (!p2 || (L <= 512 && BH >= 256) || (long long)BH * L <= 65536)) return 1;
+    const bool p2 = pow2_split(L, &N1, &N2, &P);
+    // One launch and one pass over memory beat the four-step kernels wherever the length fits (32 heads of bf16 rows 25 -> 12
+    // us at L = 1024, 1024 heads 222 -> 123; 512 heads of 2048 225 -> 206), but for bf16 rows of 1792 and 2048 that do not stay
+    // in the 256 MB memory-side cache with their results: there the in-LDS kernel takes 16 bytes of a row at a time, eight
+    // workgroups to a line (640 heads of 2048 311 instead of 275 us, of 1792 271 instead of 247; fp32 rows 300 and 328).
+    if (slab_supported(L) && !(p2 && io == SPECTRE_BF16 && L > 1536 && (long long)BH * L > (1LL << 20))) return 1;
     if (fused_supported(L) && option(SPECTRE_OPT_FUSED_4096)) return 4;
     if (p2) return 2;
     return chirp_padded_length(L) ? 3 : 0;
 }
 
-// Workspace sections of the arbitrary-length route.  Short padded lengths use only BH (M / 2 + 1) complex numbers of gp, the
+// Workspace sections of the arbitrary-length route.  Short padded lengths use only BH (D / 2 + 1) <= BH (M / 2 + 1) complex numbers of gp, the
 // gate of the data pass; the size asked for stays what it was when they took the kernels of the longer ones.
 struct ChirpLayout {
     int M, nph;
@@ -392,16 +394,16 @@ static int mix_chirp(const void *v, const float2 *g, void *out, int B, int L, in
     const float2 *w = nullptr, *filt = nullptr;
     rc = get_chirp(L, pl, &w, &filt);
     if (rc) return rc;
-    if (slab_supported(c.M)) {                         // short padded lengths: two launches
+    if (const int D = chirp_data_length(L)) {          // short padded lengths: two launches
         const float2 *roots = nullptr;
-        rc = get_roots(c.M, &roots);
+        rc = get_roots(D, &roots);
         if (rc) return rc;
         const int *order = nullptr;
-        rc = get_slab_order(c.M, &order);
+        rc = get_slab_order(D, &order);
         if (rc) return rc;
-        hipError_t e = launch_chirp_lds(g, w, filt, roots, static_cast<float2 *>(ws), BH, L, c.M, st);
+        hipError_t e = launch_chirp_lds(g, w, filt, pl.twL, roots, static_cast<float2 *>(ws), BH, L, c.M, st);
         if (e != hipSuccess) return fail_hip(e, "chirp_lds");
-        e = launch_mix_slab((int)io, v, static_cast<const float2 *>(ws), out, roots, order, B, c.M, H, st, L);
+        e = launch_mix_slab((int)io, v, static_cast<const float2 *>(ws), out, roots, order, B, D, H, st, L);
         return e == hipSuccess ? SPECTRE_OK : fail_hip(e, "mix_slab(padded)");
     }
     char *base = static_cast<char *>(ws);
@@ -449,7 +451,7 @@ static int mix_chirp(const void *v, const float2 *g, void *out, int B, int L, in
     return SPECTRE_OK;
 }
 
-int spectre_length_supported(int n, int d) { return mix_route(1, n, d) != 0; }
+int spectre_length_supported(int n, int d) { return mix_route(1, n, d, SPECTRE_F32) != 0; }
 
 void spectre_shutdown(void) {
     std::lock_guard<std::mutex> lk(g_mu);
@@ -511,9 +513,9 @@ int spectre_prepare(int n, int d) {
         if ((rc = get_pow2_plan(M, &pl, true))) return rc;
         const float2 *w = nullptr, *filt = nullptr;
         if ((rc = get_chirp(n, pl, &w, &filt, true))) return rc;
-        if (slab_supported(M)) {
-            if ((rc = get_roots(M, &r, true))) return rc;
-            if ((rc = get_slab_order(M, &o, true))) return rc;
+        if (const int D = chirp_data_length(n)) {
+            if ((rc = get_roots(D, &r, true))) return rc;
+            if ((rc = get_slab_order(D, &o, true))) return rc;
         }
     }
     hipError_t (*const loaders[])() = {load_kernels_mix_pow2, load_kernels_mix_line, load_kernels_mix_slab, load_kernels_mix_chirp, load_kernels_gate,
@@ -528,12 +530,13 @@ int spectre_prepare(int n, int d) {
 }
 
 size_t spectre_mix_workspace_bytes(int B, int L, int H, int d, spectre_dtype io) {
-    (void)io;
     if (B < 1 || L < 2 || H < 1 || d < 2) return 0;
     const int BH = B * H;
-    const int route = mix_route(BH, L, d);
+    const int route = mix_route(BH, L, d, io);
     if (route == 0) return 0;
-    if (route == 1) return 256;
+    // a length that also has a four-step plan keeps the size that asks for, except where few or short sequences never did
+    int N1, N2, P;
+    if (route == 1 && (!pow2_split(L, &N1, &N2, &P) || (L <= 512 && BH >= 256) || (long long)BH * L <= 65536)) return 256;
     if (route == 3) return chirp_layout(BH, L, d).total();
     if (route == 4) return 256;
     const MixGroups m = mix_groups(BH, L, d, 1);
@@ -616,21 +619,12 @@ static int mix_four_step(const Pow2Plan &pl, const void *v, const float2 *g, voi
     return SPECTRE_OK;
 }
 
-int spectre_mix_forward_ex(const void *v, const void *g, void *out, int B, int L, int H, int d,
-                           spectre_dtype io, unsigned flags, void *ws, size_t ws_bytes, void *stream) {
-    int rc = check_mix_args(v, g, out, B, L, H, d, io, "mix_forward");
-    if (rc) return rc;
-    if (flags & ~(unsigned)SPECTRE_MIX_BF16_SCRATCH) return fail(SPECTRE_EINVAL, "mix_forward: unknown flag bits");
-    if (!spectre_length_supported(L, d))
-        return fail(SPECTRE_EUNSUPPORTED, "mix_forward: no kernel for L=%d, d=%d", L, d);
-    const size_t need = spectre_mix_workspace_bytes(B, L, H, d, io);
-    if (!ws || ws_bytes < need)
-        return fail(SPECTRE_EWORKSPACE, "mix_forward: workspace %zu < %zu bytes", ws_bytes, need);
-    if (reinterpret_cast<uintptr_t>(ws) & 255) return fail(SPECTRE_EINVAL, "mix_forward: ws not 256-byte aligned");
-
-    hipStream_t st = static_cast<hipStream_t>(stream);
+// The mixer behind the checks of its arguments; ws holds what the route uses (at most spectre_mix_workspace_bytes).
+static int mix_forward_checked(const void *v, const void *g, void *out, int B, int L, int H, int d, spectre_dtype io,
+                               unsigned flags, void *ws, hipStream_t st) {
+    int rc;
     const int BH = B * H;
-    const int route = mix_route(BH, L, d);
+    const int route = mix_route(BH, L, d, io);
     if (route == 1) {
         const float2 *roots = nullptr;
         rc = get_roots(L, &roots);
@@ -684,6 +678,21 @@ int spectre_mix_forward_ex(const void *v, const void *g, void *out, int B, int L
                        side, st);
     if (side) release_lane(dev, side);
     return rc;
+}
+
+int spectre_mix_forward_ex(const void *v, const void *g, void *out, int B, int L, int H, int d,
+                           spectre_dtype io, unsigned flags, void *ws, size_t ws_bytes, void *stream) {
+    int rc = check_mix_args(v, g, out, B, L, H, d, io, "mix_forward");
+    if (rc) return rc;
+    if (flags & ~(unsigned)SPECTRE_MIX_BF16_SCRATCH) return fail(SPECTRE_EINVAL, "mix_forward: unknown flag bits");
+    if (!spectre_length_supported(L, d))
+        return fail(SPECTRE_EUNSUPPORTED, "mix_forward: no kernel for L=%d, d=%d", L, d);
+    const size_t need = spectre_mix_workspace_bytes(B, L, H, d, io);
+    if (!ws || ws_bytes < need)
+        return fail(SPECTRE_EWORKSPACE, "mix_forward: workspace %zu < %zu bytes", ws_bytes, need);
+    if (reinterpret_cast<uintptr_t>(ws) & 255) return fail(SPECTRE_EINVAL, "mix_forward: ws not 256-byte aligned");
+
+    return mix_forward_checked(v, g, out, B, L, H, d, io, flags, ws, static_cast<hipStream_t>(stream));
 }
 
 int spectre_mix_forward(const void *v, const void *g, void *out, int B, int L, int H, int d,
@@ -970,7 +979,7 @@ static LayerLayout layer_layout(int B, int L, int H, int d, spectre_dtype io, co
                                 const spectre_wrm_params *W) {
     LayerLayout y;
     const size_t BH = (size_t)B * H, esize = (io == SPECTRE_BF16) ? 2 : 4;
-    y.fused = (io == SPECTRE_BF16) && mix_route((int)BH, L, d) == 2;
+    y.fused = (io == SPECTRE_BF16) && mix_route((int)BH, L, d, io) == 2;
     y.sums = y.fused && W && W->levels > kWrmTileLevels;
     const size_t pool = align256(gate_partial_bytes(B, L, H, d));
     const size_t proj = align256((size_t)B * project_chunks(L) * H * d * sizeof(double));
@@ -980,7 +989,7 @@ static LayerLayout layer_layout(int B, int L, int H, int d, spectre_dtype io, co
     y.raw = gate_raw_bytes(B, H, P);
     y.g = align256(BH * (size_t)(L / 2 + 1) * sizeof(float2));
     y.wpack = y.fused ? align256((size_t)H * kProjPackBytes) : 0;
-    y.mix = align256(spectre_mix_workspace_bytes(B, L, H, d, io));
+    y.mix = mix_route((int)BH, L, d, io) == 1 ? 256 : align256(spectre_mix_workspace_bytes(B, L, H, d, io));
     y.vbuf = y.fused ? 0 : align256(BH * (size_t)L * d * esize);
     y.s = W ? align256(BH * (size_t)(W->levels + 1) * d * sizeof(float)) : 0;
     y.wrm = W ? align256(spectre_wrm_apply_workspace_bytes(B, L, H, d, W->levels)) : 0;
@@ -1061,7 +1070,7 @@ int spectre_layer_forward(const void *x, const float *Wq, const float *Wv, int H
         mg = mix_groups(BH, L, d, 1);
     } else {
         const float2 *probe = nullptr;                 // the unfused mixer call below looks its tables up itself; make
-        const int route = mix_route(BH, L, d);         // sure it cannot fail after the projection has been enqueued
+        const int route = mix_route(BH, L, d, io);     // sure it cannot fail after the projection has been enqueued
         if (route == 1 || route == 2) rc = get_roots(L, &probe);
         else if (route == 4) rc = get_roots(4096, &probe);
         else rc = get_roots(chirp_padded_length(L), &probe);
@@ -1097,7 +1106,7 @@ int spectre_layer_forward(const void *x, const float *Wq, const float *Wv, int H
         if (side) release_lane(dev, side);
         if (rc) return rc;
     } else {
-        rc = spectre_mix_forward_ex(vbuf, g, out, B, L, H, d, io, 0u, mix_ws, y.mix, stream);
+        rc = mix_forward_checked(vbuf, g, out, B, L, H, d, io, 0u, mix_ws, st);
         if (rc) return rc;
     }
     if (W) {

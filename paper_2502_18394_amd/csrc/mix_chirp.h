@@ -31,10 +31,12 @@ hipError_t launch_chirp_post(const float2 *U, const float2 *w, float2 *KK, int L
 hipError_t launch_chirp_gate(const float2 *scr, float2 *gp, int BH, int M, int N1, int N2, int ph0, int nphl,
                              hipStream_t st);
 
-// All of that in one launch for M = 256 .. 2048, a multiple of 256: g [BH, L/2+1] -> gp [BH][M/2+1] in plain bin order,
-// unscaled, the gate argument of the in-LDS kernel when it runs the padded convolution.  twM [M] = exp(-j 2 pi m / M).
-hipError_t launch_chirp_lds(const float2 *g, const float2 *w, const float2 *filt, const float2 *twM, float2 *gp, int BH,
-                            int L, int M, hipStream_t st);
+// Length D of the data pass for L <= 1024 (an in-LDS length >= 2L-1, at most the padded length); 0: none.
+int chirp_data_length(int L);
+// All of that in one launch for L <= 1024: g [BH, L/2+1] -> gp [BH][D/2+1] in plain bin order, unscaled, the gate argument
+// of the in-LDS kernel when it runs the padded convolution.  twM [M] = exp(-j 2 pi m / M), rootsD the same for D.
+hipError_t launch_chirp_lds(const float2 *g, const float2 *w, const float2 *filt, const float2 *twM, const float2 *rootsD,
+                            float2 *gp, int BH, int L, int M, hipStream_t st);
 
 // Host: chirp w [L] and the chirp filter's M-point spectrum in the big kernel's register order
 // ([N2][N1], scaled by 1/M), both evaluated in fp64.

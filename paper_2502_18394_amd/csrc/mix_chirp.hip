@@ -130,15 +130,19 @@ struct ChirpColumn {
     }
 };
 
-// gp [BH][M / 2 + 1] = the data pass's gate in plain bin order, unscaled (the in-LDS kernel divides by its length).
-template <int N2>
+// gp [BH][D / 2 + 1] = the data pass's gate in plain bin order, unscaled (the in-LDS kernel divides by its length), D
+// the length of that pass: M itself (R0 = 0) or R0 R1 < M, for which this last transform is two passes of its own with
+// rootsD [D] = exp(-j 2 pi m / D).
+template <int N2, int R0, int R1>
 __global__ __launch_bounds__(16 * N2 * kChirpHeads<N2>) void k_chirp_lds(const float2 *__restrict__ g,
                                                                         const float2 *__restrict__ w,
                                                                         const float2 *__restrict__ filt,
                                                                         const float2 *__restrict__ twM,
+                                                                        const float2 *__restrict__ rootsD,
                                                                         float2 *__restrict__ gp, int BH, int L) {
     typedef ChirpColumn<N2> Col;
-    constexpr int M = Col::M, HW = kChirpHeads<N2>;
+    constexpr int M = Col::M, HW = kChirpHeads<N2>, D = R0 ? R0 * R1 : M;
+    static_assert(R0 * (R1 + 1) <= N2 * Col::COLW, "the last transform's column fits where the others were");
     __shared__ __align__(16) unsigned char lds[HW * Col::kLds];
     const int hl = threadIdx.x / Col::NL, bh = blockIdx.x * HW + hl;
     const bool live = bh < BH;                                       // the others run along on head 0 and store nothing
@@ -183,40 +187,71 @@ __global__ __launch_bounds__(16 * N2 * kChirpHeads<N2>) void k_chirp_lds(const f
         }
     }
     __syncthreads();
-    col.rows_fwd(twM, [&](int i) {
-        return make_float2(i < L ? kap[i] : i > M - L ? kap[i - (M - L)] : 0.f, 0.f);
-    });
-    __syncthreads();
-    col.cols_fwd(y);
+    auto extended = [&](int i) {
+        return make_float2(i < L ? kap[i] : i > D - L ? kap[i - (D - L)] : 0.f, 0.f);
+    };
+    float2 *gh_out = gp + (size_t)bh * (D / 2 + 1);
+    if constexpr (R0 != 0) {
+        for (int i = t; i < R1; i += Col::NL) {                      // positions i + R1 j, padded by one per block of R1
+            float2 x[R0];
 #pragma unroll
-    for (int j = 0; j < 16; ++j) {
-        const int k = k2 + N2 * (16 * j + tau);
-        if (live && 2 * k <= M) gp[(size_t)bh * (M / 2 + 1) + k] = y[j];
+            for (int j = 0; j < R0; ++j) x[j] = extended(i + R1 * j);
+            small_dft<R0, false>(x);
+#pragma unroll
+            for (int u = 0; u < R0; ++u) col.buf[u * (R1 + 1) + i] = u == 0 ? x[0] : cmul(x[u], rootsD[i * u]);
+        }
+        __syncthreads();
+        for (int blk = t; blk < R0; blk += Col::NL) {
+            float2 x[R1];
+#pragma unroll
+            for (int j = 0; j < R1; ++j) x[j] = col.buf[blk * (R1 + 1) + j];
+            small_dft<R1, false>(x);
+#pragma unroll
+            for (int u = 0; u < R1; ++u) {
+                const int k = blk + R0 * u;
+                if (live && 2 * k <= D) gh_out[k] = x[u];
+            }
+        }
+    } else {
+        col.rows_fwd(twM, extended);
+        __syncthreads();
+        col.cols_fwd(y);
+#pragma unroll
+        for (int j = 0; j < 16; ++j) {
+            const int k = k2 + N2 * (16 * j + tau);
+            if (live && 2 * k <= D) gh_out[k] = y[j];
+        }
     }
 }
 
-template <int N2>
-static hipError_t chirp_lds_t(const float2 *g, const float2 *w, const float2 *filt, const float2 *twM, float2 *gp, int BH,
-                              int L, hipStream_t st) {
-    constexpr int HW = kChirpHeads<N2>;
-    k_chirp_lds<N2><<<(BH + HW - 1) / HW, 16 * N2 * HW, 0, st>>>(g, w, filt, twM, gp, BH, L);
-    return hipGetLastError();
+// Lengths of the data pass: the in-LDS lengths of compile-time radices, as the padded lengths of the chirp, multiples of 256,
+// are up to a third longer (B=64 H=12 fp32: L = 197 on 400 instead of 512 points 53.2 -> 41.8 us, L = 157 on 320 51 -> 32).
+static constexpr int kDataLengths[] = {256, 320, 400, 448, 512, 640, 768, 896, 1024, 1280, 1536, 1792, 2048};
+
+int chirp_data_length(int L) {
+    for (int D : kDataLengths)
+        if (D >= 2 * L - 1) return D;
+    return 0;
 }
 
-hipError_t launch_chirp_lds(const float2 *g, const float2 *w, const float2 *filt, const float2 *twM, float2 *gp, int BH,
-                            int L, int M, hipStream_t st) {
-    if (M % 256 != 0 || 2 * L > M) return hipErrorInvalidValue;
-    switch (M / 256) {
-        case 1: return chirp_lds_t<1>(g, w, filt, twM, gp, BH, L, st);
-        case 2: return chirp_lds_t<2>(g, w, filt, twM, gp, BH, L, st);
-        case 3: return chirp_lds_t<3>(g, w, filt, twM, gp, BH, L, st);
-        case 4: return chirp_lds_t<4>(g, w, filt, twM, gp, BH, L, st);
-        case 5: return chirp_lds_t<5>(g, w, filt, twM, gp, BH, L, st);
-        case 6: return chirp_lds_t<6>(g, w, filt, twM, gp, BH, L, st);
-        case 7: return chirp_lds_t<7>(g, w, filt, twM, gp, BH, L, st);
-        case 8: return chirp_lds_t<8>(g, w, filt, twM, gp, BH, L, st);
+hipError_t launch_chirp_lds(const float2 *g, const float2 *w, const float2 *filt, const float2 *twM, const float2 *rootsD,
+                            float2 *gp, int BH, int L, int M, hipStream_t st) {
+    if (M != chirp_padded_length(L)) return hipErrorInvalidValue;
+#define SPECTRE_CHIRP(D, N2, R0, R1)                                                                                       \
+    case D:                                                                                                                \
+        k_chirp_lds<N2, R0, R1><<<(BH + kChirpHeads<N2> - 1) / kChirpHeads<N2>, 16 * N2 * kChirpHeads<N2>, 0, st>>>(       \
+            g, w, filt, twM, rootsD, gp, BH, L);                                                                           \
+        break;
+    switch (chirp_data_length(L)) {
+        SPECTRE_CHIRP(256, 1, 0, 0)
+        SPECTRE_CHIRP(320, 2, 20, 16) SPECTRE_CHIRP(400, 2, 20, 20) SPECTRE_CHIRP(448, 2, 28, 16) SPECTRE_CHIRP(512, 2, 0, 0)
+        SPECTRE_CHIRP(640, 3, 20, 32) SPECTRE_CHIRP(768, 3, 0, 0)
+        SPECTRE_CHIRP(896, 4, 28, 32) SPECTRE_CHIRP(1024, 4, 0, 0)
+        SPECTRE_CHIRP(1280, 5, 0, 0) SPECTRE_CHIRP(1536, 6, 0, 0) SPECTRE_CHIRP(1792, 7, 0, 0) SPECTRE_CHIRP(2048, 8, 0, 0)
         default: return hipErrorInvalidValue;
     }
+#undef SPECTRE_CHIRP
+    return hipGetLastError();
 }
 
 hipError_t launch_chirp_pre(const float2 *g, const float2 *w, float2 *A, int BH, int L, int nph, hipStream_t st) {

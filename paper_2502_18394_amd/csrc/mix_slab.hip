@@ -1,9 +1,10 @@
 // Short-sequence path of the SPECTRE mixing layer (Sec. 3.2 steps 2-4, Eq. 3 and Eq. 4):
 // one workgroup owns the whole [L, d = 64] slab of one head of one sequence in LDS.
 //
-// Serves every L <= 512 whose prime factors are in {2, 3, 5, 7} - in particular the
-// 14 x 14 = 196 = 4 * 7 * 7 patch grid of the ViT workload and power-of-two lengths
-// below 256.  Channel pairs are transformed as complex sequences (see mix_pow2.hip).
+// Serves every L <= 2048 whose prime factors are in {2, 3, 5, 7} - in particular the
+// 14 x 14 = 196 patch grid of the ViT workload and the powers of two up to 2048.
+// Channel pairs are transformed as complex sequences (see mix_pow2.hip).
+// Lengths of compile-time radices take k_mix_ct, any other k_mix_slab.
 // The transform is an in-place mixed-radix decimation-in-frequency FFT: after the last
 // forward pass position p holds bin k = reverse(p) (mixed-radix digit reversal), the gate
 // is applied in that order from a per-workgroup table, and the inverse passes undo the
@@ -89,33 +90,18 @@ struct SlabRadices {
     int r[10];
 };
 
-// Lengths whose radix list is also known at compile time (it must equal what slab_radices() returns on the host,
-// which the launcher checks): the kernel variant for such a length has every LDS offset, stride and twiddle index
-// folded into its instructions (55-80 registers instead of 120, no address arithmetic left in the passes).
-template <int LC> struct CtRadices;
-template <> struct CtRadices<196> { static constexpr int count = 2, r0 = 14, r1 = 14, r2 = 1; };
-template <> struct CtRadices<256> { static constexpr int count = 2, r0 = 16, r1 = 16, r2 = 1; };
-template <> struct CtRadices<512> { static constexpr int count = 3, r0 = 16, r1 = 16, r2 = 2; };
-template <> struct CtRadices<1024> { static constexpr int count = 3, r0 = 16, r1 = 16, r2 = 4; };
-template <> struct CtRadices<2048> { static constexpr int count = 3, r0 = 16, r1 = 16, r2 = 8; };
-
 // grid = B*H*(32/PP) workgroups of 256 lanes, PP channel pairs each: a whole head, half a head when rows
 // are fp32 (still full 128-byte row segments, half the LDS, twice the workgroups per CU), or as little as
 // 4 pairs when there are few heads (then the call is one launch over every compute unit instead of four
 // dependent ones) or the sequence is long (the slab must fit in LDS).
 // LDS: slab [L][PP] float2, roots [L], gpos [L].
-// NT = lanes per workgroup.  LC = 0: the length and its radices are run-time arguments; LC > 0: compile-time
-// constants (CtRadices).  For LC = 196 (the 14 x 14 patch grid, radices 14, 14) with NT = 448, PP = 32 the 14 * 32
-// butterflies of a pass fill seven waves exactly (224 of 256 lanes with NT = 256, PP = 16) and a lane loads and
-// stores exactly 14 rows.
-template <typename IO, int PP, int NT = 256, int LC = 0>
+template <typename IO, int PP, int NT = 256>
 __global__ __launch_bounds__(NT) void k_mix_slab(const typename IO::pair_t *__restrict__ v,
                                                  const float2 *__restrict__ g,
                                                  typename IO::pair_t *__restrict__ out,
                                                  const float2 *__restrict__ roots_g,
-                                                 const int *__restrict__ bin_of_pos, int L_arg, int H,
+                                                 const int *__restrict__ bin_of_pos, int L, int H,
                                                  SlabRadices rad, int rows) {
-    const int L = LC ? LC : L_arg;
     extern __shared__ float2 lds_slab[];
     float2 *slab = lds_slab;
     float2 *roots = slab + (size_t)L * PP;
@@ -145,7 +131,7 @@ __global__ __launch_bounds__(NT) void k_mix_slab(const typename IO::pair_t *__re
     // the last forward pass); full-length Hermitian extension, 1/L folded in.  The two dependent loads
     // (bin, then gate) are issued for all of a lane's positions at once: L <= 2048 = 8 * 256.
     {
-        constexpr int kPos = ((LC ? LC : kSlabMaxL) + NT - 1) / NT;
+        constexpr int kPos = (kSlabMaxL + NT - 1) / NT;
         int kbin[kPos];
         float2 gv[kPos], rv[kPos];
 #pragma unroll
@@ -190,47 +176,198 @@ __global__ __launch_bounds__(NT) void k_mix_slab(const typename IO::pair_t *__re
         }
     }
     __syncthreads();
-    if constexpr (LC != 0) {
-        typedef CtRadices<LC> R;
-        constexpr int n0 = LC, n1 = n0 / R::r0, n2 = n1 / R::r1;
-        static_assert((R::count == 2 && n1 == R::r1) || (R::count == 3 && n2 == R::r2), "radices multiply to LC");
-        slab_pass<R::r0, false, false, false, PP>(slab, roots, gpos, LC, n0, tid, NT);
+    int n = L;
+    for (int q = 0; q < rad.count; ++q) {
+        if (q == rad.count - 1) slab_pass_dispatch<false, true, true, PP>(rad.r[q], slab, roots, gpos, L, n, tid, NT);
+        else slab_pass_dispatch<false, false, false, PP>(rad.r[q], slab, roots, gpos, L, n, tid, NT);
+        n /= rad.r[q];
         __syncthreads();
-        if constexpr (R::count == 3) {
-            slab_pass<R::r1, false, false, false, PP>(slab, roots, gpos, LC, n1, tid, NT);
-            __syncthreads();
-            slab_pass<R::r2, false, true, true, PP>(slab, roots, gpos, LC, n2, tid, NT);
-            __syncthreads();
-            slab_pass<R::r2, true, false, true, PP>(slab, roots, gpos, LC, n2, tid, NT);
-            __syncthreads();
-            slab_pass<R::r1, true, false, false, PP>(slab, roots, gpos, LC, n1, tid, NT);
-            __syncthreads();
-        } else {
-            slab_pass<R::r1, false, true, true, PP>(slab, roots, gpos, LC, n1, tid, NT);
-            __syncthreads();
-            slab_pass<R::r1, true, false, true, PP>(slab, roots, gpos, LC, n1, tid, NT);
-            __syncthreads();
-        }
-        slab_pass<R::r0, true, false, false, PP>(slab, roots, gpos, LC, n0, tid, NT);
+    }
+    for (int q = rad.count - 1; q >= 0; --q) {
+        n *= rad.r[q];
+        if (q == rad.count - 1) slab_pass_dispatch<true, false, true, PP>(rad.r[q], slab, roots, gpos, L, n, tid, NT);
+        else slab_pass_dispatch<true, false, false, PP>(rad.r[q], slab, roots, gpos, L, n, tid, NT);
         __syncthreads();
-    } else {
-        int n = L;
-        for (int q = 0; q < rad.count; ++q) {
-            if (q == rad.count - 1) slab_pass_dispatch<false, true, true, PP>(rad.r[q], slab, roots, gpos, L, n, tid, NT);
-            else slab_pass_dispatch<false, false, false, PP>(rad.r[q], slab, roots, gpos, L, n, tid, NT);
-            n /= rad.r[q];
-            __syncthreads();
-        }
-        for (int q = rad.count - 1; q >= 0; --q) {
-            n *= rad.r[q];
-            if (q == rad.count - 1) slab_pass_dispatch<true, false, true, PP>(rad.r[q], slab, roots, gpos, L, n, tid, NT);
-            else slab_pass_dispatch<true, false, false, PP>(rad.r[q], slab, roots, gpos, L, n, tid, NT);
-            __syncthreads();
-        }
     }
     {
         typename IO::pair_t *dst = out + (((size_t)b * rows) * H + h) * 32 + part * PP + lp_in;
         for (int l = row_in; l < rows; l += kRows) dst[(size_t)l * rs] = IO::pack(slab[l * PP + lp_in]);
+    }
+}
+
+// ------------------------------------------------------------------------------------------
+// Lengths L = R0 R1 (R2) whose radices are compile-time constants: the same transform with the row accesses inside its
+// outermost pass and the two innermost passes, forward and inverse, in one.  Rows go from memory into the registers of the
+// lane that transforms them and back, and a point crosses LDS two (three) times each way where the general kernel above
+// moves it once more on both sides of every pass.
+//   pass 0      : lane (i, pair), i < L / R0: rows i + (L / R0) j, j < R0 -> R0-point transform, times W_L^(i u)
+//   (pass 1     : the same inside every block of R1 R2 positions)
+//   inner pass  : the blocks of R = R1 (R2) positions: transform, gate, inverse transform, in registers
+//   back        : mirror images
+// Position p of the slab lies at p + p / R, so that lanes with neighbouring blocks meet different banks (not needed where a
+// row of pairs spans them all).  After the forward passes value u of block blk (blk = u0, or u0 R1 + u1) holds bin
+// u0 + R0 (u1 + R1 u).
+// What bounds it is memory at the shortest lengths and the vector units (butterflies and LDS accesses) above.  Against the
+// general structure with compile-time lengths, us: B=256 H=12 L=196 bf16 52 -> 44 (fp32, at 4.7 TB/s, 71 -> 69); 2048 heads of
+// bf16 rows at 256 47 -> 33, at 512 152 -> 92; 64 heads of fp32 at 1024 25 -> 13; 32 heads at 2048 30 -> 13; kernel alone for
+// one head of fp32 rows at 1024 10.1 -> 7.9, for 32 of bf16 at 512 9.4 -> 6.7.
+// DIRECT (few workgroups, where the chain of latencies counts and registers do not): every lane loads its factors and its
+// gate entries itself, beside its rows; otherwise both are tables in LDS, built while the rows are under way.
+template <int R0, int R1, int R2>
+struct SlabPlan {
+    static constexpr int L = R0 * R1 * R2, R = R2 > 1 ? R2 : R1, blocks = L / R;
+    static constexpr int S0 = L / R0, S1 = R2;
+    __device__ static constexpr int bin(int blk, int u) {
+        return R2 > 1 ? blk / R1 + R0 * (blk % R1 + R1 * u) : blk + R0 * u;
+    }
+    static constexpr size_t lds(int PP, bool direct) {
+        return ((size_t)(L + (PP < 16 ? blocks : 0)) * PP + (direct ? 0 : 2 * (size_t)L)) * sizeof(float2);
+    }
+};
+
+// STREAM: the rows pass the caches by.
+template <typename IO, int PP, int NT, int R0, int R1, int R2, bool DIRECT, bool STREAM>
+__global__ __launch_bounds__(NT) void k_mix_ct(const typename IO::pair_t *__restrict__ v, const float2 *__restrict__ g,
+                                               typename IO::pair_t *__restrict__ out, const float2 *__restrict__ roots_g,
+                                               int H, int BH, int rows, int affine) {
+    typedef SlabPlan<R0, R1, R2> Plan;
+    constexpr int L = Plan::L, R = Plan::R, F = L / 2 + 1, S0 = Plan::S0, PAD = PP < 16 ? 1 : 0, kParts = 32 / PP;
+    constexpr int kSlab = (L + PAD * Plan::blocks) * PP;
+    constexpr int kInner = (Plan::blocks * PP + NT - 1) / NT;        // blocks of the inner pass per lane
+    static_assert(S0 * PP <= NT && NT % 64 == 0, "one transform of the outermost pass per lane");
+    extern __shared__ float2 lds_ct[];
+    float2 *slab = lds_ct, *roots = slab + kSlab, *gpos = roots + L;
+    const int tid = threadIdx.x, col = tid % PP, i0 = tid / PP;
+    int bh = blockIdx.x / kParts, part = blockIdx.x % kParts;
+    if (affine) {                                                    // the parts of a head on one XCD: ids 8 apart
+        const int idx = blockIdx.x >> 3;
+        part = idx % kParts;
+        bh = (idx / kParts) * 8 + (blockIdx.x & 7);
+        if (bh >= BH) return;                                        // whole workgroup: heads are padded to 8
+    }
+    const int b = bh / H, h = bh % H;
+    auto at = [&](int p) { return slab + (p + PAD * (p / R)) * PP + col; };
+    const bool live = S0 * PP == NT || i0 < S0;
+    const size_t rs = (size_t)H * 32, base = ((size_t)b * rows * H + h) * 32 + part * PP + col;
+    typename IO::pair_t raw[R0];
+#pragma unroll
+    for (int j = 0; j < R0; ++j) {
+        const int l = i0 + S0 * j;
+        raw[j] = IO::zero();
+        if (live && l < rows) raw[j] = STREAM ? IO::load_stream(v + base + (size_t)l * rs) : v[base + (size_t)l * rs];
+    }
+    const float2 *gh = g + (size_t)bh * F;
+    constexpr float scale = 1.0f / (float)L;
+    auto gate_fix = [&](float2 val, int k) {                         // Hermitian extension; real at DC and Nyquist
+        const float im = (k == 0 || 2 * k == L) ? 0.0f : 2 * k > L ? -val.y : val.y;
+        return make_float2(val.x * scale, im * scale);
+    };
+    float2 tw[DIRECT ? R0 : 1], G[DIRECT ? kInner * R : 1];
+    if constexpr (DIRECT) {
+#pragma unroll
+        for (int u = 1; u < R0; ++u) tw[u] = roots_g[live ? i0 * u : 0];
+#pragma unroll
+        for (int q = 0; q < kInner; ++q) {
+            const int blk = min((tid + NT * q) / PP, Plan::blocks - 1);
+#pragma unroll
+            for (int u = 0; u < R; ++u) {
+                const int k = Plan::bin(blk, u);
+                G[q * R + u] = gh[2 * k <= L ? k : L - k];
+            }
+        }
+    } else {
+        constexpr int kPos = (L + NT - 1) / NT;
+        float2 rv[kPos], gv[kPos];
+#pragma unroll
+        for (int i = 0; i < kPos; ++i) {
+            const int p = min(tid + NT * i, L - 1), k = Plan::bin(p / R, p % R);
+            rv[i] = roots_g[p];
+            gv[i] = gh[2 * k <= L ? k : L - k];
+        }
+#pragma unroll
+        for (int i = 0; i < kPos; ++i) {
+            const int p = min(tid + NT * i, L - 1);
+            roots[p] = rv[i];
+            gpos[p] = gate_fix(gv[i], Plan::bin(p / R, p % R));
+        }
+        __syncthreads();
+    }
+    auto factor0 = [&](int u) { return DIRECT ? tw[DIRECT ? u : 0] : roots[i0 * u]; };
+    if (live) {
+        float2 x[R0];
+#pragma unroll
+        for (int j = 0; j < R0; ++j) x[j] = IO::unpack(raw[j]);
+        small_dft<R0, false>(x);
+#pragma unroll
+        for (int u = 0; u < R0; ++u) *at(i0 + S0 * u) = u == 0 ? x[0] : cmul(x[u], factor0(u));
+    }
+    __syncthreads();
+    // pass 1 of three: lane (i, pair) of block blk, i < R2
+    constexpr int kMid = R2 > 1 ? (R0 * R2 * PP + NT - 1) / NT : 0;
+    float2 tm[kMid ? R1 : 1];
+    if constexpr (R2 > 1) {
+        static_assert(NT % PP == 0 && NT / PP % R2 == 0, "a lane keeps its i over the blocks");
+        const int i1 = i0 % R2;
+#pragma unroll
+        for (int u = 1; u < R1; ++u) tm[u] = DIRECT ? roots_g[i1 * u * R0] : roots[i1 * u * R0];
+#pragma unroll
+        for (int q = 0; q < kMid; ++q) {
+            const int blk = i0 / R2 + NT / PP / R2 * q, p = blk * R1 * R2 + i1;
+            if (R0 * R2 * PP % NT != 0 && blk >= R0) break;
+            float2 x[R1];
+#pragma unroll
+            for (int j = 0; j < R1; ++j) x[j] = *at(p + R2 * j);
+            small_dft<R1, false>(x);
+#pragma unroll
+            for (int u = 0; u < R1; ++u) *at(p + R2 * u) = u == 0 ? x[0] : cmul(x[u], tm[u]);
+        }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int q = 0; q < kInner; ++q) {
+        const int blk = (tid + NT * q) / PP;
+        if (Plan::blocks * PP % NT == 0 || blk < Plan::blocks) {
+            float2 x[R];
+#pragma unroll
+            for (int j = 0; j < R; ++j) x[j] = *at(blk * R + j);
+            small_dft<R, false>(x);
+#pragma unroll
+            for (int u = 0; u < R; ++u)
+                x[u] = cmul(x[u], DIRECT ? gate_fix(G[DIRECT ? q * R + u : 0], Plan::bin(blk, u)) : gpos[blk * R + u]);
+            small_dft<R, true>(x);
+#pragma unroll
+            for (int j = 0; j < R; ++j) *at(blk * R + j) = x[j];
+        }
+    }
+    __syncthreads();
+    if constexpr (R2 > 1) {
+        const int i1 = i0 % R2;
+#pragma unroll
+        for (int q = 0; q < kMid; ++q) {
+            const int blk = i0 / R2 + NT / PP / R2 * q, p = blk * R1 * R2 + i1;
+            if (R0 * R2 * PP % NT != 0 && blk >= R0) break;
+            float2 x[R1];
+#pragma unroll
+            for (int u = 0; u < R1; ++u) x[u] = u == 0 ? *at(p) : cmulc(*at(p + R2 * u), tm[u]);
+            small_dft<R1, true>(x);
+#pragma unroll
+            for (int j = 0; j < R1; ++j) *at(p + R2 * j) = x[j];
+        }
+        __syncthreads();
+    }
+    if (live) {
+        float2 x[R0];
+#pragma unroll
+        for (int u = 0; u < R0; ++u) x[u] = u == 0 ? *at(i0) : cmulc(*at(i0 + S0 * u), factor0(u));
+        small_dft<R0, true>(x);
+#pragma unroll
+        for (int j = 0; j < R0; ++j) {
+            const int l = i0 + S0 * j;
+            if (l < rows) {
+                if (STREAM) IO::store_stream(out + base + (size_t)l * rs, IO::pack(x[j]));
+                else out[base + (size_t)l * rs] = IO::pack(x[j]);
+            }
+        }
     }
 }
 
@@ -293,26 +430,37 @@ void slab_bin_order(int L, int *bin_of_pos) {
     }
 }
 
-template <typename IO, int PP, int NT = 256, int LC = 0>
+template <typename IO, int PP>
 static hipError_t mix_slab_t(const void *v, const float2 *g, void *out, const float2 *roots, const int *bin_of_pos,
                              int B, int L, int H, int rows, hipStream_t st) {
     const size_t lds = ((size_t)L * PP + 2 * (size_t)L) * sizeof(float2);
-    const SlabRadices rad = slab_radices(L);
-    auto kern = k_mix_slab<IO, PP, NT, LC>;
-    if constexpr (LC != 0) {
-        typedef CtRadices<LC> R;
-        if (L != LC || rad.count != R::count || rad.r[0] != R::r0 || rad.r[1] != R::r1 ||
-            (R::count == 3 && rad.r[2] != R::r2))
-            return hipErrorInvalidValue;
-    }
+    auto kern = k_mix_slab<IO, PP>;
     if (lds > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    kern<<<dim3(B * H * (32 / PP)), dim3(NT), lds, st>>>(static_cast<const typename IO::pair_t *>(v), g,
-                                                         static_cast<typename IO::pair_t *>(out), roots, bin_of_pos, L, H,
-                                                         rad, rows);
+    kern<<<dim3(B * H * (32 / PP)), dim3(256), lds, st>>>(static_cast<const typename IO::pair_t *>(v), g,
+                                                          static_cast<typename IO::pair_t *>(out), roots, bin_of_pos, L, H,
+                                                          slab_radices(L), rows);
+    return hipGetLastError();
+}
+
+template <typename IO, int PP, int NT, int R0, int R1, int R2, bool DIRECT, bool STREAM = false>
+static hipError_t mix_ct_t(const void *v, const float2 *g, void *out, const float2 *roots, int B, int H, int rows,
+                           hipStream_t st) {
+    constexpr size_t lds = SlabPlan<R0, R1, R2>::lds(PP, DIRECT);
+    auto kern = k_mix_ct<IO, PP, NT, R0, R1, R2, DIRECT, STREAM>;
+    if (lds > 48 * 1024) {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    const int BH = B * H, affine = PP < 32;
+    const long long grid = (long long)(affine ? (BH + 7) / 8 * 8 : BH) * (32 / PP);
+    if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
+    kern<<<dim3((unsigned)grid), dim3(NT), lds, st>>>(static_cast<const typename IO::pair_t *>(v), g,
+                                                      static_cast<typename IO::pair_t *>(out), roots, H, BH, rows, affine);
     return hipGetLastError();
 }
 
@@ -327,41 +475,94 @@ int slab_pairs_per_workgroup(int io, int BH, int L) {
     return pp;
 }
 
+// The lengths with compile-time radices; false: not one of them.  Every length was measured with several splits: three
+// short passes on more lanes beat two passes of radix 28 and 32, which leave two waves per SIMD, and eight pairs per workgroup
+// beat four while a compute unit still holds two or more (768 heads, us: 512 as 32 x 16 / 16 x 32 / 8 x 8 x 8 on four / eight
+// pairs 54 / 54 / 45 / 43; 768 as 24 x 32 on four / eight pairs / 12 x 8 x 8 74 / 61 / 60; 896 as 28 x 32 / 14 x 8 x 8 on four /
+// eight 90 / 74 / 68; 1024 as 16 x 16 x 4 / 32 x 32 / 16 x 8 x 8 on eight / four 96 / 94 / 100 / 76; 640 as 10 x 8 x 8 / 20 x 32
+// 55 / 49; 400 as 20 x 20 on sixteen / four / eight pairs, 10 x 8 x 5 42 / 41 / 37 / 40; 384 heads of 1280 as 16 x 16 x 5 / 10 x
+// 16 x 8 / 20 x 8 x 8 108 / 95 / 75).  Few heads take four pairs and their own loads where the tables cost more than the
+// transform (kernel alone, one head: 196 6.4 -> 5.0, 256 5.9 -> 4.9, 1024 9.0 -> 7.8).
+template <typename IO>
+static bool mix_ct(int L, const void *v, const float2 *g, void *out, const float2 *roots, int B, int H, int rows,
+                   hipStream_t st, hipError_t *e) {
+    const long long pairs = (long long)B * H * 32;
+    const bool few = pairs <= 256 * 16;
+    // Rows that will not be found in the memory-side cache again pass it by, where a workgroup's piece of a row is whole
+    // 128-byte lines (fp32, L = 196, H = 12: B = 256 71 -> 68 us, 128 38 -> 36, but 64 19.6 -> 20.3; 256 at B = 256 86 -> 80,
+    // bf16 53 -> 49).
+    const bool stream = 2 * pairs * rows * (long long)sizeof(typename IO::pair_t) > 100000000 &&
+                        ((reinterpret_cast<uintptr_t>(v) | reinterpret_cast<uintptr_t>(out)) & 127) == 0;
+#define SPECTRE_CT(PP, NT, R0, R1, R2, DIRECT) \
+    { *e = mix_ct_t<IO, PP, NT, R0, R1, R2, DIRECT>(v, g, out, roots, B, H, rows, st); return true; }
+#define SPECTRE_CT_LINES(PP, NT, R0, R1, R2)                                                                            \
+    {                                                                                                                   \
+        static_assert(PP * sizeof(typename IO::pair_t) % 128 == 0, "whole lines");                                      \
+        *e = stream ? mix_ct_t<IO, PP, NT, R0, R1, R2, false, true>(v, g, out, roots, B, H, rows, st)                   \
+                    : mix_ct_t<IO, PP, NT, R0, R1, R2, false>(v, g, out, roots, B, H, rows, st);                        \
+        return true;                                                                                                    \
+    }
+    switch (L) {
+        case 196:
+            if (few) SPECTRE_CT(4, 64, 14, 14, 1, true)
+            if constexpr (IO::kBytes == 2) SPECTRE_CT_LINES(32, 448, 14, 14, 1)
+            else if (stream) SPECTRE_CT_LINES(16, 256, 14, 14, 1)
+            else SPECTRE_CT(32, 448, 14, 14, 1, false)
+        case 256:
+            if (few) SPECTRE_CT(4, 128, 8, 8, 4, true)
+            if constexpr (IO::kBytes == 2) SPECTRE_CT_LINES(32, 512, 16, 16, 1)
+            else SPECTRE_CT_LINES(16, 512, 8, 8, 4)
+        case 320: SPECTRE_CT(16, 256, 20, 16, 1, false)
+        case 400: SPECTRE_CT(8, 192, 20, 20, 1, false)
+        case 448: SPECTRE_CT(8, 512, 7, 8, 8, false)
+        case 512: SPECTRE_CT(8, 512, 8, 8, 8, false)
+        case 640: SPECTRE_CT(8, 256, 20, 32, 1, false)
+        case 768: SPECTRE_CT(8, 512, 12, 8, 8, false)
+        case 896: SPECTRE_CT(8, 512, 14, 8, 8, false)
+        case 1024:
+            if (pairs <= 256) SPECTRE_CT(2, 256, 8, 16, 8, true)
+            SPECTRE_CT(4, 256, 16, 8, 8, false)
+        case 1280: SPECTRE_CT(4, 256, 20, 8, 8, false)
+        case 1536: SPECTRE_CT(4, 256, 24, 8, 8, false)
+        case 1792: SPECTRE_CT(4, 512, 14, 16, 8, false)
+        case 2048: SPECTRE_CT(4, 512, 16, 16, 8, false)
+        default: return false;
+    }
+#undef SPECTRE_CT
+#undef SPECTRE_CT_LINES
+}
+
 hipError_t launch_mix_slab(int io, const void *v, const float2 *g, void *out, const float2 *roots,
                            const int *bin_of_pos, int B, int L, int H, hipStream_t st, int rows) {
     if (rows <= 0) rows = L;
     if (rows > L) return hipErrorInvalidValue;
     const int pp = slab_pairs_per_workgroup(io, B * H, L);
     if ((size_t)L * (pp + 2) * sizeof(float2) > (size_t)160 * 1024) return hipErrorInvalidValue;
-    if (L == 196 && pp >= 16 && (long long)B * H >= 512 && option(SPECTRE_OPT_SLAB_COMPILE_TIME) != 0)   // whole heads still fill the chip
-        return io ? mix_slab_t<IoBf16, 32, 448, 196>(v, g, out, roots, bin_of_pos, B, L, H, rows, st)
-                  : mix_slab_t<IoF32, 32, 448, 196>(v, g, out, roots, bin_of_pos, B, L, H, rows, st);
-    const bool ct = option(SPECTRE_OPT_SLAB_COMPILE_TIME) != 0;
-#define SPECTRE_SLAB_LEN(PPV, LCV)                                                                          \
-    if (ct && L == LCV)                                                                                     \
-        return io ? mix_slab_t<IoBf16, PPV, 256, LCV>(v, g, out, roots, bin_of_pos, B, L, H, rows, st)      \
-                  : mix_slab_t<IoF32, PPV, 256, LCV>(v, g, out, roots, bin_of_pos, B, L, H, rows, st);
-#define SPECTRE_SLAB_CASE(PPV, LENS)                                                                 \
-    case PPV:                                                                                       \
-        LENS                                                                                        \
-        return io ? mix_slab_t<IoBf16, PPV>(v, g, out, roots, bin_of_pos, B, L, H, rows, st)        \
+    if (option(SPECTRE_OPT_SLAB_COMPILE_TIME) != 0) {
+        hipError_t e = hipSuccess;
+        const bool done = io ? mix_ct<IoBf16>(L, v, g, out, roots, B, H, rows, st, &e)
+                             : mix_ct<IoF32>(L, v, g, out, roots, B, H, rows, st, &e);
+        if (done) return e;
+    }
+    switch (pp) {
+#define SPECTRE_SLAB_CASE(PPV)                                                                    \
+    case PPV:                                                                                    \
+        return io ? mix_slab_t<IoBf16, PPV>(v, g, out, roots, bin_of_pos, B, L, H, rows, st)     \
                   : mix_slab_t<IoF32, PPV>(v, g, out, roots, bin_of_pos, B, L, H, rows, st);
-    switch (pp) {                       // only the (pairs, length) combinations the rule above can produce
-        SPECTRE_SLAB_CASE(4, SPECTRE_SLAB_LEN(4, 256) SPECTRE_SLAB_LEN(4, 512) SPECTRE_SLAB_LEN(4, 1024) SPECTRE_SLAB_LEN(4, 2048))
-        SPECTRE_SLAB_CASE(8, SPECTRE_SLAB_LEN(8, 256) SPECTRE_SLAB_LEN(8, 512))
-        SPECTRE_SLAB_CASE(16, SPECTRE_SLAB_LEN(16, 256) SPECTRE_SLAB_LEN(16, 512))
-        SPECTRE_SLAB_CASE(32, SPECTRE_SLAB_LEN(32, 256))
+        SPECTRE_SLAB_CASE(4)
+        SPECTRE_SLAB_CASE(8)
+        SPECTRE_SLAB_CASE(16)
+        SPECTRE_SLAB_CASE(32)
+#undef SPECTRE_SLAB_CASE
         default: return hipErrorInvalidValue;
     }
-#undef SPECTRE_SLAB_LEN
-#undef SPECTRE_SLAB_CASE
 }
 
 // Loads this translation unit's code object (the runtime loads them on first use): called by spectre_prepare so
 // that no compute call is the first to touch it.
 hipError_t load_kernels_mix_slab() {
     hipFuncAttributes a;
-    return hipFuncGetAttributes(&a, reinterpret_cast<const void *>((k_mix_slab<IoF32, 4, 256, 0>)));
+    return hipFuncGetAttributes(&a, reinterpret_cast<const void *>((k_mix_slab<IoF32, 4>)));
 }
 
 }  // namespace spectre

@@ -205,6 +205,51 @@ def test_short_and_mixed_radix_lengths(oracle, B, L, H, io):
     assert_close_elementwise(got, want, io, L)
 
 
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+@pytest.mark.parametrize("B,L,H", [(1, 196, 9), (5, 196, 27), (1, 256, 3), (3, 256, 43), (1, 320, 9), (1, 400, 9), (1, 448, 3),
+                                   (1, 512, 7), (1, 640, 3), (3, 768, 3), (1, 896, 2), (1, 1024, 8), (1, 1024, 9), (1, 1280, 3),
+                                   (1, 1536, 3), (1, 1792, 9), (1, 2048, 3)])
+def test_lengths_of_compile_time_radices(oracle, options, B, L, H, io):
+    """Every split of the kernel whose radices are compile-time constants, in its forms for few and for many heads and with
+    head counts that are no multiple of 8, against the oracle and the general kernel.  Between the two: the rounding of two
+    fp32 transforms, 2.5e-7 each, or one bf16 step of a few of the rows."""
+    from paper_2502_18394_amd import binding
+    print(f"case B={B} L={L} H={H} io={io}", flush=True)
+    seed = synth.BASE_SEED + 29 * L + H
+    got, want, _ = run_case(oracle, B, L, H, 64, io, seed=seed)
+    assert rel_l2(got, want) <= (1e-6 if io == "f32" else 2e-3)
+    assert_close_elementwise(got, want, io, L)
+    options(binding.OPT_SLAB_COMPILE_TIME, 0)
+    general, _, _ = run_case(oracle, B, L, H, 64, io, seed=seed)
+    assert rel_l2(got, general) <= (1e-6 if io == "f32" else 2e-3)
+
+
+@pytest.mark.parametrize("L", [196, 256])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
+def test_streamed_rows_change_no_bit(L, dtype):
+    """Calls too large for the memory-side cache read and write their rows past the caches, from tensors on a line boundary:
+    the same bits as a part of the batch alone, and as from a tensor off that boundary."""
+    from paper_2502_18394_amd import binding
+    B, H = 256, 12
+    print(f"case L={L} {dtype}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    v = torch.randn((B, L, H, 64), generator=gen, device="cuda").to(dtype)
+    g = torch.view_as_complex(torch.randn((B, H, L // 2 + 1, 2), generator=gen, device="cuda"))
+    out = binding.mix_forward(v, g)
+    assert torch.equal(binding.mix_forward(v[64:96].contiguous(), g[64:96].contiguous()), out[64:96])
+    off = torch.empty(v.numel() + 16, dtype=dtype, device="cuda")[16:].view_as(v)
+    off.copy_(v)
+    assert off.data_ptr() % 128 != 0 and torch.equal(binding.mix_forward(off, g), out)
+
+
+@pytest.mark.parametrize("L", [127, 131, 157, 163, 199, 211, 223, 227, 251, 257, 319, 331, 383, 389, 443, 449, 509, 521])
+def test_lengths_at_the_edges_of_the_padded_ones(oracle, L):
+    """Lengths on both sides of every length that the data pass of the padded convolution has up to 1024 points."""
+    got, want, _ = run_case(oracle, 1, L, 3, 64, "f32", seed=synth.BASE_SEED + L)
+    print(f"case L={L} rel_l2={rel_l2(got, want):.3e}", flush=True)
+    assert rel_l2(got, want) <= 1e-6
+
+
 def test_vit_config_full_size(oracle):
     """Config 5 at its real size: B=256, L=196, H=12, fp32."""
     c = synth.CONFIGS["vit_196"]
