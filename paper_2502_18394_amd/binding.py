@@ -66,6 +66,24 @@ def lib():
                      "spectre_mix_static_bytes", "spectre_layer_workspace_bytes"):
             getattr(L, name).restype = ctypes.c_size_t
         L.spectre_get_option.restype = ctypes.c_long
+        # with the types declared, ctypes converts plain integers itself: a wrapper object per argument costs a few
+        # microseconds a call, as much as the kernels of the smallest ones take
+        p, i, n, f = ctypes.c_void_p, ctypes.c_int, ctypes.c_size_t, ctypes.c_double
+        for name, types in {
+                "spectre_mix_workspace_bytes": (i, i, i, i, i),
+                "spectre_mix_forward_ex": (p, p, p, i, i, i, i, i, ctypes.c_uint, p, n, p),
+                "spectre_gate_workspace_bytes": (i, i, i, p),
+                "spectre_gate": (p, i, i, f, p, i, i, i, ctypes.c_longlong, p, p, n, p),
+                "spectre_layer_workspace_bytes": (i, i, i, i, i, p, p),
+                "spectre_layer_forward": (p, p, p, i, p, p, p, i, i, i, i, i, p, n, p),
+                "spectre_prefix_init": (p, p), "spectre_prefix_flush": (p, p),
+                "spectre_prefix_update_workspace_bytes": (p, i, i),
+                "spectre_prefix_update": (p, p, p, i, i, p, n, p),
+                "spectre_prefix_readout_workspace_bytes": (p, i, i),
+                "spectre_prefix_readout": (p, p, i, p, i, p, n, p),
+                "spectre_prefix_step_workspace_bytes": (p, p),
+                "spectre_prefix_step": (p, p, p, p, p, i, p, n, p)}.items():
+            getattr(L, name).argtypes = types
         _lib = L
     return _lib
 
@@ -89,17 +107,29 @@ def _dev(t, name):
     return ctypes.c_void_p(t.data_ptr())
 
 
+def _ptr(t, name):
+    """_dev for the functions whose argument types are declared."""
+    if not (t.is_cuda and t.is_contiguous()):
+        raise ValueError(f"{name} must be a contiguous device tensor")
+    return t.data_ptr()
+
+
 def _stream(stream):
-    s = torch.cuda.current_stream() if stream is None else stream
-    return ctypes.c_void_p(s.cuda_stream)
+    """Handle of `stream`, or of the current one (without the Stream object that torch.cuda.current_stream builds)."""
+    if stream is None:
+        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
+    return ctypes.c_void_p(stream.cuda_stream)
 
 
 def _workspace(nbytes, device, ws):
     nbytes = max(int(nbytes), 256)
-    if ws is None or ws.numel() * ws.element_size() < nbytes:
-        ws = torch.empty(nbytes + 256, dtype=torch.uint8, device=device)
-    off = (-ws.data_ptr()) % 256
-    return ws, ctypes.c_void_p(ws.data_ptr() + off), ctypes.c_size_t(ws.numel() * ws.element_size() - off)
+    size = 0 if ws is None else ws.numel() * ws.element_size()
+    if size < nbytes:
+        size = nbytes + 256
+        ws = torch.empty(size, dtype=torch.uint8, device=device)
+    at = ws.data_ptr()
+    off = -at % 256
+    return ws, ctypes.c_void_p(at + off), ctypes.c_size_t(size - off)
 
 
 def version():
@@ -138,8 +168,7 @@ def get_option(which):
 
 
 def mix_workspace_bytes(B, L, H, d, io):
-    return int(lib().spectre_mix_workspace_bytes(ctypes.c_int(B), ctypes.c_int(L), ctypes.c_int(H),
-                                                 ctypes.c_int(d), ctypes.c_int(io)))
+    return lib().spectre_mix_workspace_bytes(B, L, H, d, io)
 
 
 def mix_forward(v, g, out=None, ws=None, stream=None, flags=0):
@@ -153,9 +182,8 @@ def mix_forward(v, g, out=None, ws=None, stream=None, flags=0):
     if out is None:
         out = torch.empty_like(v)
     ws, wsp, wsn = _workspace(mix_workspace_bytes(B, L, H, d, io), v.device, ws)
-    _check(lib().spectre_mix_forward_ex(_dev(v, "v"), _dev(g, "g"), _dev(out, "out"), ctypes.c_int(B), ctypes.c_int(L),
-                                        ctypes.c_int(H), ctypes.c_int(d), ctypes.c_int(io), ctypes.c_uint(flags),
-                                        wsp, wsn, _stream(stream)))
+    _check(lib().spectre_mix_forward_ex(_ptr(v, "v"), _ptr(g, "g"), _ptr(out, "out"), B, L, H, d, io, flags, wsp, wsn,
+                                        _stream(stream)))
     return out
 
 
@@ -225,7 +253,7 @@ class GateParams:
 
 
 def gate_workspace_bytes(B, L, H, P):
-    return int(lib().spectre_gate_workspace_bytes(ctypes.c_int(B), ctypes.c_int(L), ctypes.c_int(H), ctypes.byref(P.c)))
+    return lib().spectre_gate_workspace_bytes(B, L, H, ctypes.byref(P.c))
 
 
 def gate(q, P, inv_count, pooled=False, phase_pos=0, g_out=None, ws=None, stream=None):
@@ -244,10 +272,8 @@ def gate(q, P, inv_count, pooled=False, phase_pos=0, g_out=None, ws=None, stream
     if g_out is None:
         g_out = torch.empty((B, H, P.F), dtype=torch.complex64, device=q.device)
     ws, wsp, wsn = _workspace(gate_workspace_bytes(B, L, H, P), q.device, ws)
-    _check(lib().spectre_gate(_dev(q, "q"), ctypes.c_int(1 if pooled else 0), ctypes.c_int(code),
-                              ctypes.c_double(inv_count), ctypes.byref(P.c), ctypes.c_int(B), ctypes.c_int(L),
-                              ctypes.c_int(H), ctypes.c_longlong(int(phase_pos)), _dev(g_out, "g_out"),
-                              wsp, wsn, _stream(stream)))
+    _check(lib().spectre_gate(_ptr(q, "q"), 1 if pooled else 0, code, inv_count, ctypes.byref(P.c), B, L, H,
+                              int(phase_pos), _ptr(g_out, "g_out"), wsp, wsn, _stream(stream)))
     return g_out
 
 
@@ -334,14 +360,12 @@ def layer_forward(x, Wq, Wv, P, W=None, out=None, ws=None, stream=None):
     if out is None:
         out = torch.empty_like(x)
     wc = ctypes.byref(W.c) if W is not None else None
-    need = lib().spectre_layer_workspace_bytes(ctypes.c_int(B), ctypes.c_int(L), ctypes.c_int(H), ctypes.c_int(d),
-                                               ctypes.c_int(io), ctypes.byref(P.c), wc)
+    need = lib().spectre_layer_workspace_bytes(B, L, H, d, io, ctypes.byref(P.c), wc)
     if need == 0:
         raise SpectreError(EUNSUPPORTED, lib().spectre_last_error().decode())
     ws, wsp, wsn = _workspace(need, x.device, ws)
-    _check(lib().spectre_layer_forward(_dev(x, "x"), _dev(Wq, "Wq"), _dev(Wv, "Wv"), ctypes.c_int(Wq.shape[0]),
-                                       ctypes.byref(P.c), wc, _dev(out, "out"), ctypes.c_int(B), ctypes.c_int(L),
-                                       ctypes.c_int(H), ctypes.c_int(d), ctypes.c_int(io), wsp, wsn, _stream(stream)))
+    _check(lib().spectre_layer_forward(_ptr(x, "x"), _ptr(Wq, "Wq"), _ptr(Wv, "Wv"), Wq.shape[0], ctypes.byref(P.c), wc,
+                                       _ptr(out, "out"), B, L, H, d, io, wsp, wsn, _stream(stream)))
     return out
 
 
@@ -405,20 +429,20 @@ class PrefixCache:
         assert (B, H, d) == (self.B, self.H, self.d) and q_new.shape == v_new.shape and q_new.dtype == v_new.dtype
         io = _dtype_code(v_new)
         prepare(self.n, self.d)
-        need = lib().spectre_prefix_update_workspace_bytes(ctypes.byref(self.c), ctypes.c_int(T), ctypes.c_int(io))
+        need = lib().spectre_prefix_update_workspace_bytes(ctypes.byref(self.c), T, io)
         self._ws, wsp, wsn = _workspace(need, v_new.device, self._ws)
-        _check(lib().spectre_prefix_update(ctypes.byref(self.c), _dev(v_new, "v_new"), _dev(q_new, "q_new"),
-                                           ctypes.c_int(T), ctypes.c_int(io), wsp, wsn, _stream(stream)))
+        _check(lib().spectre_prefix_update(ctypes.byref(self.c), _ptr(v_new, "v_new"), _ptr(q_new, "q_new"), T, io, wsp,
+                                           wsn, _stream(stream)))
 
     def readout(self, g, mode=READ_NEWEST, dtype=torch.float32, stream=None):
         io = F32 if dtype == torch.float32 else BF16
         prepare(self.n, self.d)
         rows = 1 if mode == READ_NEWEST else min(self.t, self.N)
         out = torch.empty((self.B, rows, self.H, self.d), dtype=dtype, device=g.device)
-        need = lib().spectre_prefix_readout_workspace_bytes(ctypes.byref(self.c), ctypes.c_int(mode), ctypes.c_int(io))
+        need = lib().spectre_prefix_readout_workspace_bytes(ctypes.byref(self.c), mode, io)
         self._ws, wsp, wsn = _workspace(need, g.device, self._ws)
-        _check(lib().spectre_prefix_readout(ctypes.byref(self.c), _dev(g, "g"), ctypes.c_int(mode), _dev(out, "out"),
-                                            ctypes.c_int(io), wsp, wsn, _stream(stream)))
+        _check(lib().spectre_prefix_readout(ctypes.byref(self.c), _ptr(g, "g"), mode, _ptr(out, "out"), io, wsp, wsn,
+                                            _stream(stream)))
         return out
 
     def step(self, v_t, q_t, P, out=None, stream=None):
@@ -427,6 +451,6 @@ class PrefixCache:
             out = torch.empty((self.B, 1, self.H, self.d), dtype=v_t.dtype, device=v_t.device)
         need = lib().spectre_prefix_step_workspace_bytes(ctypes.byref(self.c), ctypes.byref(P.c))
         self._ws, wsp, wsn = _workspace(need, v_t.device, self._ws)
-        _check(lib().spectre_prefix_step(ctypes.byref(self.c), _dev(v_t, "v_t"), _dev(q_t, "q_t"), ctypes.byref(P.c),
-                                         _dev(out, "out"), ctypes.c_int(io), wsp, wsn, _stream(stream)))
+        _check(lib().spectre_prefix_step(ctypes.byref(self.c), _ptr(v_t, "v_t"), _ptr(q_t, "q_t"), ctypes.byref(P.c),
+                                         _ptr(out, "out"), io, wsp, wsn, _stream(stream)))
         return out
