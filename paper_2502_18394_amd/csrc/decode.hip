@@ -284,18 +284,32 @@ __global__ __launch_bounds__(256) void k_decode_final(const float *__restrict__ 
         *reinterpret_cast<float2 *>(rg.q_buf + ring) = qn;
         if (LAZY) *reinterpret_cast<float2 *>(pending + ((size_t)(npend - 1) * BH + bh) * 64 + 2 * p) = dnew;
     }
+    // pending tokens grp, grp + 8, ... of the earlier ones: their Delta rows are under way with the chunks' sums
+    constexpr int kPer = kMaxPending / 8;
+    float2 dlt[LAZY ? kPer : 1];
+    if (LAZY) {
+#pragma unroll
+        for (int m = 0; m < kPer; ++m) {
+            const int i = grp + 8 * m;
+            dlt[m] = i + 1 < npend ? *reinterpret_cast<const float2 *>(pending + ((size_t)i * BH + bh) * 64 + 2 * p)
+                                   : make_float2(0.f, 0.f);
+        }
+    }
     const float2 *src = reinterpret_cast<const float2 *>(partial + (size_t)bh * nchunks * 64) + p;
     const float *ksrc = LAZY ? kpart + (size_t)bh * nchunks * 32 + p : nullptr;
     float2 s = make_float2(0.f, 0.f);
     float ks = 0.f;
-    int c = grp;
-    for (; c + 56 < nchunks; c += 64) {          // eight loads of each kind in flight, added in the same order
+    for (int c = grp; c < nchunks; c += 64) {    // eight loads of each kind in flight, added in chunk order
         float2 v[8];
         float kv[8];
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
-            v[i] = src[(size_t)(c + 8 * i) * 32];
-            if (LAZY) kv[i] = ksrc[(size_t)(c + 8 * i) * 32];
+            v[i] = make_float2(0.f, 0.f);
+            kv[i] = 0.f;
+            if (c + 8 * i < nchunks) {
+                v[i] = src[(size_t)(c + 8 * i) * 32];
+                if (LAZY) kv[i] = ksrc[(size_t)(c + 8 * i) * 32];
+            }
         }
 #pragma unroll
         for (int i = 0; i < 8; ++i) {
@@ -303,43 +317,35 @@ __global__ __launch_bounds__(256) void k_decode_final(const float *__restrict__ 
             if (LAZY) ks += kv[i];
         }
     }
-    for (; c < nchunks; c += 8) {
-        s = s + src[(size_t)c * 32];
-        if (LAZY) ks += ksrc[(size_t)c * 32];
+    if (LAZY) {
+        kred[grp][p] = ks;
+        __syncthreads();
+        auto kappa = [&](int i) {
+            float k = kred[0][i];
+#pragma unroll
+            for (int r = 1; r < 8; ++r) k += kred[r][i];
+            return k;
+        };
+#pragma unroll
+        for (int m = 0; m < kPer; ++m) {
+            if (grp + 8 * m + 1 < npend) {
+                const float k = kappa(grp + 8 * m);
+                s.x = fmaf(k, dlt[m].x, s.x);
+                s.y = fmaf(k, dlt[m].y, s.y);
+            }
+        }
+        if (grp == 0) {                          // this token
+            const float k = kappa(npend - 1);
+            s.x = fmaf(k, dnew.x, s.x);
+            s.y = fmaf(k, dnew.y, s.y);
+        }
     }
     red[grp][p] = s;
-    if (LAZY) kred[grp][p] = ks;
     __syncthreads();
-    if (LAZY && grp == 0) {
-        float kap = kred[0][p];
-#pragma unroll
-        for (int r = 1; r < 8; ++r) kap += kred[r][p];
-        kred[0][p] = kap;                     // kappa of pending token p
-    }
-    if (LAZY) __syncthreads();
     if (grp == 0) {
         float2 t = red[0][p];
 #pragma unroll
         for (int r = 1; r < 8; ++r) t = t + red[r][p];
-        if (LAZY) {
-            for (int i0 = 0; i0 + 1 < npend; i0 += 8) {              // the earlier tokens, eight Delta rows in flight
-                float2 dlt[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i)
-                    dlt[i] = (i0 + i + 1 < npend)
-                                 ? *reinterpret_cast<const float2 *>(pending + ((size_t)(i0 + i) * BH + bh) * 64 + 2 * p)
-                                 : make_float2(0.f, 0.f);
-#pragma unroll
-                for (int i = 0; i < 8; ++i) {
-                    if (i0 + i + 1 < npend) {
-                        t.x = fmaf(kred[0][i0 + i], dlt[i].x, t.x);
-                        t.y = fmaf(kred[0][i0 + i], dlt[i].y, t.y);
-                    }
-                }
-            }
-            t.x = fmaf(kred[0][npend - 1], dnew.x, t.x);
-            t.y = fmaf(kred[0][npend - 1], dnew.y, t.y);
-        }
         out[(size_t)bh * 32 + p] = IO::pack(t);
     }
 }
