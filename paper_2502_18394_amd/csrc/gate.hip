@@ -6,7 +6,7 @@
 //   prep    : x = inv_count * sum;  qbar = LayerNorm(x);  hid = GELU(qbar W1 + b1)
 //   out     : u = W2 hid + b2 on the matrix cores (fp32 MFMA, v_mfma_f32_4x4x1_16B_f32: 64
 //             output reals x 4 rows per instruction), with bias and modReLU in the epilogue
-//   phase   : the positional phase, a separate pass over g, only when a position is given
+//   phase   : the positional phase, when a position is given: in the epilogue of `out`, or a separate pass over g
 #include "gate.h"
 
 #include "common.h"
@@ -305,6 +305,15 @@ __device__ __forceinline__ void gate_load_tile(float4 (&a)[16], const float *__r
     }
 }
 
+// v exp(+j 2 pi ((k p) mod n)/n), the positional phase: angle reduced in integers and evaluated in fp64
+__device__ __forceinline__ float2 gate_turn(float2 v, long long k, int n_fft, long long phase) {
+    const long long m = (k * phase) % n_fft;
+    double s, c;
+    sincospi(2.0 * (double)m / (double)n_fft, &s, &c);
+    const float cf = (float)c, sf = (float)s;
+    return make_float2(v.x * cf - v.y * sf, v.x * sf + v.y * cf);
+}
+
 // modReLU (Sec. 3.2 step 3c) of one bin and its store
 __device__ __forceinline__ void gate_store_bin(float2 *dst, float re, float im, bool act_on, float mb) {
     if (act_on) {
@@ -317,11 +326,13 @@ __device__ __forceinline__ void gate_store_bin(float2 *dst, float re, float im, 
     *dst = make_float2(re, im);
 }
 
-template <bool VEC, int RG>   // VEC: d_g % 4 == 0 and 16-byte aligned rows; RG: row groups of 4
+// TURN: the positional phase is applied as well (a pass of its own over g took 5.5 us, B=4 H=32 n=8192).
+template <bool VEC, int RG, bool TURN>   // VEC: d_g % 4 == 0 and 16-byte aligned rows; RG: row groups of 4
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4 : 2))) void k_gate_out(const float *__restrict__ hid, const float *__restrict__ W2,
                                                   const float *__restrict__ b2,
                                                   const float *__restrict__ mbias, float2 *__restrict__ g,
-                                                  int B, int H, int Hg, int dg, int F, int r_base0) {
+                                                  int B, int H, int Hg, int dg, int F, int r_base0, int n_fft,
+                                                  long long phase) {
     extern __shared__ float hs[];
     const int r_base = r_base0 + 4 * RG * (int)blockIdx.z;   // blockIdx.z: tile of the rows (sequences)                    // [4*RG][dgs] hidden rows of this pass, zero padded
     const int dgp = (dg + 3) & ~3, dgs = dgp + 4;    // row stride padded against bank conflicts
@@ -403,9 +414,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
                 const int r = r_base + 4 * q + jrow;
                 if (r >= M || !e_ok) continue;
                 const int bh = (Hg == 1) ? r : r * H + hsel;
-                gate_store_bin(g + (size_t)bh * F + (n4 >> 1), acc[q][0] + bias4.x, acc[q][1] + bias4.y, mbias != nullptr, mb2.x);
-                if (e_ok2)
-                    gate_store_bin(g + (size_t)bh * F + (n4 >> 1) + 1, acc[q][2] + bias4.z, acc[q][3] + bias4.w, mbias != nullptr, mb2.y);
+                float2 v0, v1;
+                gate_store_bin(&v0, acc[q][0] + bias4.x, acc[q][1] + bias4.y, mbias != nullptr, mb2.x);
+                gate_store_bin(&v1, acc[q][2] + bias4.z, acc[q][3] + bias4.w, mbias != nullptr, mb2.y);
+                if (TURN) {
+                    v0 = gate_turn(v0, n4 >> 1, n_fft, phase);
+                    v1 = gate_turn(v1, (n4 >> 1) + 1, n_fft, phase);
+                }
+                g[(size_t)bh * F + (n4 >> 1)] = v0;
+                if (e_ok2) g[(size_t)bh * F + (n4 >> 1) + 1] = v1;
             }
         }
         return;
@@ -447,9 +464,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
                 const int nn = n4 + 2 * half;
                 if (nn >= twoF) continue;
                 const int k = nn >> 1;
-                gate_store_bin(g + (size_t)bh * F + k, acc[q][2 * half] + b2[(size_t)hp * twoF + nn],
-                               acc[q][2 * half + 1] + b2[(size_t)hp * twoF + nn + 1], mbias != nullptr,
-                               mbias ? mbias[(size_t)hp * F + k] : 0.0f);
+                float2 v;
+                gate_store_bin(&v, acc[q][2 * half] + b2[(size_t)hp * twoF + nn], acc[q][2 * half + 1] + b2[(size_t)hp * twoF + nn + 1],
+                               mbias != nullptr, mbias ? mbias[(size_t)hp * F + k] : 0.0f);
+                g[(size_t)bh * F + k] = TURN ? gate_turn(v, k, n_fft, phase) : v;
             }
         }
     }
@@ -608,13 +626,7 @@ __global__ __launch_bounds__(256) void k_gate_phase(float2 *__restrict__ g, int 
                                                     size_t total) {
     const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= total) return;
-    const long long k = (long long)(idx % F);
-    const long long m = (k * phase) % n_fft;
-    double s, c;
-    sincospi(2.0 * (double)m / (double)n_fft, &s, &c);
-    const float cf = (float)c, sf = (float)s;
-    const float2 v = g[idx];
-    g[idx] = make_float2(v.x * cf - v.y * sf, v.x * sf + v.y * cf);
+    g[idx] = gate_turn(g[idx], (long long)(idx % F), n_fft, phase);
 }
 
 // ------------------------------------------------------------------------------------------
@@ -773,6 +785,7 @@ hipError_t launch_gate_out(const float *hid, const GateDev &P, float2 *raw, int 
     // with the Toeplitz update the MLP output goes to `raw` un-activated and a second pass finishes it
     const float *out_bias = P.toeplitz ? nullptr : P.modrelu_bias;
     float2 *out_g = P.toeplitz ? raw : g;
+    const bool turn = phase != 0 && !P.toeplitz;
     {
         // every tile of the rows in one launch (grid.z); a single tile takes the narrowest kernel that fits
         // rows per tile: 32, fewer while the launch would have less than four workgroups per compute unit (B=256 H=12
@@ -793,20 +806,24 @@ hipError_t launch_gate_out(const float *hid, const GateDev &P, float2 *raw, int 
             const int nz = (ntile - z0 < 65535) ? ntile - z0 : 65535;
             const dim3 grid3(grid.x, grid.y, nz);
             const int r_base = per * z0;
-#define SPECTRE_GATE_OUT(V, R) k_gate_out<V, R><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F, r_base)
+#define SPECTRE_GATE_OUT(V, R)                                                                                              \
+    if (turn) k_gate_out<V, R, true><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F, r_base, \
+                                                              P.n_fft, phase);                                               \
+    else k_gate_out<V, R, false><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F, r_base,     \
+                                                          P.n_fft, phase)
             if (vec) {
-                if (rg <= 1) SPECTRE_GATE_OUT(true, 1); else if (rg <= 2) SPECTRE_GATE_OUT(true, 2);
-                else if (rg <= 4) SPECTRE_GATE_OUT(true, 4); else SPECTRE_GATE_OUT(true, 8);
+                if (rg <= 1) { SPECTRE_GATE_OUT(true, 1); } else if (rg <= 2) { SPECTRE_GATE_OUT(true, 2); }
+                else if (rg <= 4) { SPECTRE_GATE_OUT(true, 4); } else { SPECTRE_GATE_OUT(true, 8); }
             } else {
-                if (rg <= 1) SPECTRE_GATE_OUT(false, 1); else if (rg <= 2) SPECTRE_GATE_OUT(false, 2);
-                else if (rg <= 4) SPECTRE_GATE_OUT(false, 4); else SPECTRE_GATE_OUT(false, 8);
+                if (rg <= 1) { SPECTRE_GATE_OUT(false, 1); } else if (rg <= 2) { SPECTRE_GATE_OUT(false, 2); }
+                else if (rg <= 4) { SPECTRE_GATE_OUT(false, 4); } else { SPECTRE_GATE_OUT(false, 8); }
             }
 #undef SPECTRE_GATE_OUT
             hipError_t e2 = hipGetLastError();
             if (e2 != hipSuccess) return e2;
         }
     }
-    return launch_gate_tail(P, raw, B, H, phase, g, st);
+    return launch_gate_tail(P, raw, B, H, turn ? 0 : phase, g, st);
 }
 
 // Loads this translation unit's code object (the runtime loads them on first use): called by spectre_prepare so
