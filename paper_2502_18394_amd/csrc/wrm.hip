@@ -3,55 +3,80 @@
 #include "wrm.h"
 
 #include "common.h"
+#include "fold16.h"
 
 namespace spectre {
 
 // ------------------------------------------------------------------------------------------
-// gates: one workgroup per (b, h).  LayerNorm statistics in fp64, both layers on the vector units
-// (d x d_w and d_w x (J+1) d are tiny).
+// gates: grid (B*H, ceil(nout / 64)); every workgroup of 256 lanes repeats the LayerNorm (statistics in fp64) and the first
+// layer and emits 64 outputs, the terms of both layers split over its four waves (sums added in wave order).
+// What bounds it is the chain of latencies: with the statistics added up by one lane and each layer's terms in one it took
+// 19 us at any size (24576 rows, 13 levels, 32 heads), now 7.
+__device__ __forceinline__ double wrm_block_sum(double x, double *red, int wave) {
+    red[wave] = wave_sum(x);                           // the same value in all lanes of the wave
+    __syncthreads();
+    return (red[0] + red[1]) + (red[2] + red[3]);
+}
+
 __global__ __launch_bounds__(256) void k_wrm_gates(const double *__restrict__ sum_q, double inv_count,
                                                    const float *__restrict__ gamma, const float *__restrict__ beta,
                                                    float eps, const float *__restrict__ W1,
                                                    const float *__restrict__ b1, const float *__restrict__ W2,
                                                    const float *__restrict__ b2, float *__restrict__ s, int H, int Hg,
                                                    int d, int dw, int nout) {
-    __shared__ double xs[256];
-    __shared__ float qbar[256];
-    __shared__ float hid[256];
-    __shared__ double stat[2];
-    // grid (B*H, ceil(nout / 256)): every workgroup repeats the tiny LayerNorm and first layer and emits 256 outputs
-    // (the output layer is a chain of d_w dependent loads per output: one workgroup per head left it latency-bound)
+    __shared__ float qbar[256], hid[256], part[256];
+    __shared__ double red[8];
     const int bh = blockIdx.x, h = bh % H, hp = (Hg == 1) ? 0 : h;
-    const int tid = threadIdx.x;
-    if (tid < d) xs[tid] = inv_count * sum_q[(size_t)bh * d + tid];
-    __syncthreads();
-    if (tid == 0) {
-        double mean = 0.0, var = 0.0;
-        for (int i = 0; i < d; ++i) mean += xs[i];
-        mean /= d;
-        for (int i = 0; i < d; ++i) var += (xs[i] - mean) * (xs[i] - mean);
-        var /= d;
-        stat[0] = mean;
-        stat[1] = 1.0 / sqrt(var + (double)eps);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int o = blockIdx.y * 64 + lane;
+    // the weights' latency passes behind the statistics (the usual widths only; any other is read where it is used)
+    const bool usual = d == 64 && dw == 64;
+    float w1[16], w2[16];
+    if (usual) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            w1[i] = W1[(size_t)hp * 4096 + (wave + 4 * i) * 64 + lane];
+            w2[i] = W2[((size_t)hp * 64 + wave + 4 * i) * nout + min(o, nout - 1)];
+        }
     }
+    const double x = tid < d ? inv_count * sum_q[(size_t)bh * d + tid] : 0.0;
+    const double gam = tid < d ? (double)gamma[hp * d + tid] : 0.0, bet = tid < d ? (double)beta[hp * d + tid] : 0.0;
+    const double mean = wrm_block_sum(x, red, wave) / d;
+    const double dev = tid < d ? x - mean : 0.0;
+    const double rstd = 1.0 / sqrt(wrm_block_sum(dev * dev, red + 4, wave) / d + (double)eps);
+    qbar[tid] = (float)(gam * dev * rstd + bet);
     __syncthreads();
-    if (tid < d)
-        qbar[tid] = (float)((double)gamma[hp * d + tid] * (xs[tid] - stat[0]) * stat[1] + (double)beta[hp * d + tid]);
-    __syncthreads();
-    if (tid < dw) {
-        float a = b1[hp * dw + tid];
-        const float *w = W1 + (size_t)hp * d * dw + tid;
-        for (int i = 0; i < d; ++i) a = fmaf(qbar[i], w[(size_t)i * dw], a);
-        hid[tid] = 0.5f * a * (1.0f + erff(a * 0.70710678118654752440f));
+    // first layer: wave w takes the inputs w, w + 4, ..., a lane every 64th hidden unit
+    for (int j0 = 0; j0 < dw; j0 += 64) {
+        const int j = j0 + lane;
+        float a = 0.f;
+        if (usual) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) a = fmaf(qbar[wave + 4 * i], w1[i], a);
+        } else if (j < dw) {
+            const float *w = W1 + (size_t)hp * d * dw + j;
+            for (int i = wave; i < d; i += 4) a = fmaf(qbar[i], w[(size_t)i * dw], a);
+        }
+        part[tid] = a;
+        __syncthreads();
+        if (wave == 0 && j < dw) {
+            const float t = b1[hp * dw + j] + ((part[lane] + part[64 + lane]) + (part[128 + lane] + part[192 + lane]));
+            hid[j] = 0.5f * t * (1.0f + erff(t * 0.70710678118654752440f));
+        }
+        __syncthreads();
     }
-    __syncthreads();
-    const int o = blockIdx.y * 256 + tid;
-    if (o < nout) {
-        float a = b2[(size_t)hp * nout + o];
+    float a = 0.f;
+    if (usual) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) a = fmaf(hid[wave + 4 * i], w2[i], a);
+    } else if (o < nout) {
         const float *w = W2 + (size_t)hp * dw * nout + o;
-        for (int j = 0; j < dw; ++j) a = fmaf(hid[j], w[(size_t)j * nout], a);
-        s[(size_t)bh * nout + o] = a;
+        for (int j = wave; j < dw; j += 4) a = fmaf(hid[j], w[(size_t)j * nout], a);
     }
+    part[tid] = a;
+    __syncthreads();
+    if (wave == 0 && o < nout)
+        s[(size_t)bh * nout + o] = b2[(size_t)hp * nout + o] + ((part[lane] + part[64 + lane]) + (part[128 + lane] + part[192 + lane]));
 }
 
 // ------------------------------------------------------------------------------------------
@@ -202,8 +227,10 @@ __global__ __launch_bounds__(256) void k_wrm_upper(const float *__restrict__ S, 
         U[((size_t)bh * ntiles + i) * 64 + c] = pyr[(off + (i >> 1)) * kUpCh + cl];
 }
 
+// What bounds it is the stream of rows in and out: L = 24576, 32 heads of bf16 rows, 201 MB, 53 -> 44 us.  16 rows per lane
+// and 512 lanes, at three or four waves per SIMD, took 59 and 57.
 template <typename IO>
-__global__ __launch_bounds__(256) void k_wrm_apply(const typename IO::pair_t *__restrict__ v,
+__global__ __launch_bounds__(256, 3) void k_wrm_apply(const typename IO::pair_t *__restrict__ v,
                                                    const float *__restrict__ s, const float2 *__restrict__ U,
                                                    typename IO::pair_t *__restrict__ out, int L, int H, int J,
                                                    int ntiles) {
@@ -211,17 +238,30 @@ __global__ __launch_bounds__(256) void k_wrm_apply(const typename IO::pair_t *__
     const int tid = threadIdx.x, p = tid & 31, r = tid >> 5;
     const int h = blockIdx.x, tile = blockIdx.y, b = blockIdx.z, bh = b * H + h;
     const int row0 = tile * kWrmTileRows + r * 32;
-    const float *sb = s + (size_t)bh * (J + 1) * 64;
     const int c0 = 2 * p;
+    // row i of the lane = uniform address of row i of the tile + the lane's own offset
+    const size_t tile_at = ((size_t)b * L + (size_t)tile * kWrmTileRows) * H * 32;
+    const unsigned lane_at = ((unsigned)r * 32 * H + h) * 32 + p;
+    // gates of bands 0 .. 9 and the upper levels' term, under way with the rows: read where they are used, a level at a
+    // time behind its test, they cost more than the arithmetic
+    f32x2_elem_t gate[kWrmTileLevels + 2];
+#pragma unroll
+    for (int l = 0; l < kWrmTileLevels + 2; ++l)
+        gate[l] = *reinterpret_cast<const f32x2_elem_t *>(s + ((size_t)bh * (J + 1) + min(l, J)) * 64 + c0);
+    float2 corr = make_float2(0.f, 0.f);
+    if (J > kWrmTileLevels) corr = U[((size_t)bh * ntiles + tile) * 32 + p];
+    auto coef = [&](int l) {                        // of the level-l block sum; levels above J carry no term
+        const f32x2_elem_t c = l < J ? gate[l + 1] - gate[l] : l == J ? gate[0] - gate[l] : f32x2_elem_t{0.f, 0.f};
+        const float sc = exp2f(-(float)l);
+        return make_float2(c.x * sc, c.y * sc);
+    };
 
     float2 x[32];
     {   // issue all loads before the first unpack (see k_wrm_tile_sums)
         typename IO::pair_t raw[32];
 #pragma unroll
-        for (int i = 0; i < 32; ++i) {
-            const int l = row0 + i;
-            raw[i] = (l < L) ? IO::load_stream(v + (((size_t)b * L + l) * H + h) * 32 + p) : IO::zero();
-        }
+        for (int i = 0; i < 32; ++i)
+            raw[i] = (row0 + i < L) ? IO::load_stream(v + tile_at + (size_t)i * H * 32 + lane_at) : IO::zero();
 #pragma unroll
         for (int i = 0; i < 32; ++i) x[i] = IO::unpack(raw[i]);
     }
@@ -239,13 +279,11 @@ __global__ __launch_bounds__(256) void k_wrm_apply(const typename IO::pair_t *__
     // levels 6..8 across the 8 row groups of the tile
     part[r][p] = s5;
     __syncthreads();
-    float2 corr = make_float2(0.f, 0.f);
-    if (J > kWrmTileLevels) corr = U[((size_t)bh * ntiles + tile) * 32 + p];
-    auto add_level = [&](int l, float2 sum) {       // corr += coef_l * (block sum / 2^l), levels above J carry no term
+    auto add_level = [&](int l, float2 sum) {       // corr += coef_l * (block sum / 2^l)
         if (l <= J) {
-            const float sc = exp2f(-(float)l);
-            corr.x = fmaf(wrm_coef(sb, l, J, c0) * sc, sum.x, corr.x);
-            corr.y = fmaf(wrm_coef(sb, l, J, c0 + 1) * sc, sum.y, corr.y);
+            const float2 c = coef(l);
+            corr.x = fmaf(c.x, sum.x, corr.x);
+            corr.y = fmaf(c.y, sum.y, corr.y);
         }
     };
     if (J >= 6) {
@@ -269,12 +307,11 @@ __global__ __launch_bounds__(256) void k_wrm_apply(const typename IO::pair_t *__
     float cf[4][2];
 #pragma unroll
     for (int l = 1; l <= 4; ++l) {
-        const float sc = exp2f(-(float)l);
-        cf[l - 1][0] = (l <= J) ? wrm_coef(sb, l, J, c0) * sc : 0.f;
-        cf[l - 1][1] = (l <= J) ? wrm_coef(sb, l, J, c0 + 1) * sc : 0.f;
+        const float2 c = coef(l);
+        cf[l - 1][0] = c.x;
+        cf[l - 1][1] = c.y;
     }
-    const int sidx = (J >= 1) ? 1 : 0;
-    const float f0x = 1.0f + sb[sidx * 64 + c0], f0y = 1.0f + sb[sidx * 64 + c0 + 1];
+    const float f0x = 1.0f + gate[1].x, f0y = 1.0f + gate[1].y;      // band min(1, J)
 #pragma unroll
     for (int i4 = 0; i4 < 2; ++i4) {
         const float2 c4 = make_float2(fmaf(cf[3][0], s4[i4].x, corr.x), fmaf(cf[3][1], s4[i4].y, corr.y));
@@ -292,10 +329,10 @@ __global__ __launch_bounds__(256) void k_wrm_apply(const typename IO::pair_t *__
                     const float2 c1 = make_float2(fmaf(cf[0][0], s1[i1].x, c2.x), fmaf(cf[0][1], s1[i1].y, c2.y));
 #pragma unroll
                     for (int j0 = 0; j0 < 2; ++j0) {
-                        const int i = 2 * i1 + j0, l = row0 + i;
-                        if (l < L) {
+                        const int i = 2 * i1 + j0;
+                        if (row0 + i < L) {
                             const float2 y = make_float2(fmaf(f0x, x[i].x, c1.x), fmaf(f0y, x[i].y, c1.y));
-                            IO::store_stream(out + (((size_t)b * L + l) * H + h) * 32 + p, IO::pack(y));
+                            IO::store_stream(out + tile_at + (size_t)i * H * 32 + lane_at, IO::pack(y));
                         }
                     }
                 }
@@ -516,7 +553,7 @@ __global__ __launch_bounds__(256) void k_wrm_upper_coeff(const float *__restrict
 hipError_t launch_wrm_gates(const double *sum_q, double inv_count, const WrmDev &P, int B, int H, float *s,
                             hipStream_t st) {
     const int nout = (P.levels + 1) * P.d;
-    k_wrm_gates<<<dim3(B * H, (nout + 255) / 256), 256, 0, st>>>(sum_q, inv_count, P.ln_gamma, P.ln_beta, P.ln_eps, P.W1,
+    k_wrm_gates<<<dim3(B * H, (nout + 63) / 64), 256, 0, st>>>(sum_q, inv_count, P.ln_gamma, P.ln_beta, P.ln_eps, P.W1,
                                                                 P.b1, P.W2, P.b2, s, H, P.Hg, P.d, P.d_w, nout);
     return hipGetLastError();
 }
