@@ -511,6 +511,7 @@ int spectre_prepare(int n, int d) {
         const int M = chirp_padded_length(n);
         if (!M) return fail(SPECTRE_EUNSUPPORTED, "prepare: no kernel for length %d", n);
         if ((rc = get_pow2_plan(M, &pl, true))) return rc;
+        if (cache_cols_split(M, &N1, &N2) && (rc = get_column_factors(N1, &r, true))) return rc;   // M itself is then ready, too
         const float2 *w = nullptr, *filt = nullptr;
         if ((rc = get_chirp(n, pl, &w, &filt, true))) return rc;
         if (const int D = chirp_data_length(n)) {
@@ -555,6 +556,21 @@ static int check_mix_args(const void *v, const void *g, const void *out, int B, 
     return SPECTRE_OK;
 }
 
+// Plan of the four-step mixer: 1024-point columns (P = 0) for L = 12288 ... 32768, else the plan of pow2_split.  Not for fp32
+// rows of 16384 and 32768, whose error against 64 bits would grow by 1.9 and 0.4 % (all others' falls by 2 to 4 %, and the
+// rounding of bf16 rows hides it) and where they gain least (32 heads, 4096- and 1024-point columns, us: bf16 12288 107 and 95,
+// 20480 164 and 147, 24576 191 and 174, 28672 231 and 217, 32768 245 and 240; fp32 12288 120 and 111, 24576 214 and 212, 16384
+// 152 and 142, 32768 289 and 293).
+static int get_mix_plan(int L, spectre_dtype io, Pow2Plan *pl) {
+    const int rc = get_pow2_plan(L, pl);
+    int N1, N2;
+    if (rc || !cache_cols_split(L, &N1, &N2) || N1 != 1024 || (io == SPECTRE_F32 && (L & (L - 1)) == 0)) return rc;
+    pl->N1 = N1;
+    pl->N2 = N2;
+    pl->P = 0;
+    return get_column_factors(N1, &pl->twN1);
+}
+
 // The four-step route: gate expansion, then per head group the row transforms, the column kernel and the inverse
 // row transforms.  gp = expanded gate [BH][L]; lane_scr[i] = transform scratch of lane i (lane_bytes each).
 // side == nullptr keeps every group on st.
@@ -589,7 +605,7 @@ static int mix_four_step(const Pow2Plan &pl, const void *v, const float2 *g, voi
         float2 *scr = reinterpret_cast<float2 *>(scr_base + (size_t)lane * lane_bytes);
         // short columns (L <= 12288): a head's scratch fits the 4 MB L2 of one XCD, see head_affine() in mix_pow2.hip;
         // measured -7 % at L = 8192, -10 % at 4096 (three kernels), nothing or a loss from 16384 on
-        const bool affine = !scr16 && nbh % 8 == 0 && (size_t)L * (d / 2) * sizeof(float2) <= ((size_t)3 << 20) &&
+        const bool affine = !scr16 && pl.P != 0 && nbh % 8 == 0 && (size_t)L * (d / 2) * sizeof(float2) <= ((size_t)3 << 20) &&
                             option(SPECTRE_OPT_HEAD_AFFINE) != 0;
         e = wpack ? launch_small_fwd_proj(pl, v, wpack, Hw, scr, L, H, bh0, nbh, ls, affine)
                   : launch_small_fwd(pl, (int)io, v, scr, L, H, bh0, nbh, ls, scr16, affine);
@@ -599,7 +615,8 @@ static int mix_four_step(const Pow2Plan &pl, const void *v, const float2 *g, voi
             if (e != hipSuccess) { what = "wait for the gate expansion"; break; }
             side_has_gate = true;
         }
-        e = launch_big(pl, scr, gp, bh0, nbh, 0, ls, false, scr16, affine, side != nullptr);
+        e = pl.P == 0 ? launch_mix_cols(pl, scr, gp, bh0, nbh, ls)
+                      : launch_big(pl, scr, gp, bh0, nbh, 0, ls, false, scr16, affine, side != nullptr);
         if (e != hipSuccess) { what = "big"; break; }
         e = launch_small_inv(pl, (int)io, scr, out, 0, L, H, bh0, nbh, ls, 0, 0, 0, scr16, affine, bsum);
         if (e != hipSuccess) { what = "small_inv"; break; }
@@ -646,7 +663,8 @@ static int mix_forward_checked(const void *v, const void *g, void *out, int B, i
         return SPECTRE_OK;
     }
     Pow2Plan pl;
-    rc = get_pow2_plan(L, &pl);
+    const bool scr16 = (io == SPECTRE_BF16) && (flags & SPECTRE_MIX_BF16_SCRATCH);
+    rc = scr16 ? get_pow2_plan(L, &pl) : get_mix_plan(L, io, &pl);
     if (rc) return rc;
     float2 *gp = static_cast<float2 *>(ws);
     char *scr_base = static_cast<char *>(ws) + align256((size_t)BH * L * sizeof(float2));
@@ -663,7 +681,6 @@ static int mix_forward_checked(const void *v, const void *g, void *out, int B, i
     }
     // on request, bf16 rows only: complex numbers cross between the three kernels as two bfloat16 instead of two
     // fp32, and twice the heads fit in a lane's scratch
-    const bool scr16 = (io == SPECTRE_BF16) && (flags & SPECTRE_MIX_BF16_SCRATCH);
     const MixGroups m1 = mix_groups(BH, L, d, 1);
     const size_t lane_bytes = align256((size_t)m1.chunk * L * (d / 2) * sizeof(float2));   // as the workspace was sized
     MixGroups mg = scr16 ? mix_groups(BH, L, d, 2) : m1;
@@ -1065,7 +1082,7 @@ int spectre_layer_forward(const void *x, const float *Wq, const float *Wv, int H
     int dev = 0;
     MixGroups mg;
     if (y.fused) {
-        rc = get_pow2_plan(L, &pl);
+        rc = get_mix_plan(L, io, &pl);
         if (rc) return rc;
         mg = mix_groups(BH, L, d, 1);
     } else {

@@ -1,8 +1,9 @@
 // Columns of the cache's window transform and full-window readout, together with the step between the pair spectrum and
-// the two channels' half spectra (N <= 32768; gfx950).
+// the two channels' half spectra (N <= 32768; gfx950), and the mixer's columns of 1024 points.
 //
 //   k_cache_fwd : scratch columns [k2][pair][t1] -> N1-point transforms -> half-spectrum rows X[k][channel]
 //   k_cache_inv : rows X, times the gate -> pair spectrum -> inverse N1-point transforms -> scratch columns
+//   k_mix_cols  : scratch columns -> transforms, gate, inverse transforms, in place
 //
 // A bin k = k2 + N2 k1 and its Hermitian partner N - k lie in the planes k2 and N2 - k2, so a workgroup that holds both
 // planes of a few channel pairs separates (or joins) the channels itself.  As kernels of their own the column transforms
@@ -209,6 +210,50 @@ __global__ __launch_bounds__(2 * PW * R, R == 32 ? 4 : 6) void k_cache_inv(const
     for (int j = 0; j < R; ++j) col[R * j] = x[j];
 }
 
+// The mixer's columns of R * R points in place: forward, times the expanded gate gp [bh][k2][k1], inverse.  R adjacent lanes
+// own a column, a workgroup PW pairs of one plane; the 32 / PW workgroups of a plane get ids 8 apart, so that its part of the
+// gate meets one L2.  grid: 8 ceil(planes / 8) * 32 / PW.
+// For L = 12288 ... 32768 instead of the 4096-point columns of k_big, whose three passes exchange twice across the waves of a
+// workgroup: here two longer passes exchange inside 32 lanes, without a barrier.  What bounds it is memory traffic, 16 bytes
+// per pair and position: 32 heads of L = 24576 94 -> 73 us (403 MB, 5.5 TB/s).
+template <int R, int PW>
+__global__ __launch_bounds__(PW * R, 3) void k_mix_cols(float2 *__restrict__ scr, const float2 *__restrict__ gp,
+                                                        const float4 *__restrict__ tw, int N2, int bh0, int planes) {
+    constexpr int N1 = R * R, NT = PW * R, kCol = N1 + N1 / R, G = 32 / PW;
+    static_assert(PW * kCol % 4 == 0 && N1 / 2 % NT == 0, "the factors on a 16-byte boundary, whole sweeps of them");
+    extern __shared__ float4 lds_cc[];
+    const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
+    const int pg = idx % G, plane = (idx / G) * 8 + xcd;
+    if (plane >= planes) return;                                     // whole workgroup: planes are padded to 8
+    const int tid = threadIdx.x, tau = tid % R, pw = tid / R;
+    float2 *col = scr + ((size_t)plane * 32 + pg * PW + pw) * N1 + tau;
+    float2 x[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) x[j] = col[R * j];
+    float4 *wl = lds_cc + PW * kCol / 4;
+#pragma unroll
+    for (int i = 0; i < N1 / 2 / NT; ++i) wl[tid + NT * i] = tw[tid + NT * i];
+    dft<R, false>(x);
+    __syncthreads();
+    const float2 *w = reinterpret_cast<const float2 *>(wl) + tau;
+    float *buf = reinterpret_cast<float *>(lds_cc) + pw * kCol;
+#pragma unroll
+    for (int u = 1; u < R; ++u) x[u] = cmul(x[u], w[u * R]);         // W_N1^(tau u)
+    cache_exchange<R>(x, buf, tau, true);
+    dft<R, false>(x);                                                // register v: bin k1 = tau + R v
+    const float2 *gsrc = gp + ((size_t)bh0 * N2 + plane) * N1 + tau;
+#pragma unroll
+    for (int v = 0; v < R; ++v) x[v] = cmul(x[v], gsrc[R * v]);
+    dft<R, true>(x);
+    __builtin_amdgcn_wave_barrier();
+    cache_exchange<R>(x, buf, tau, false);
+#pragma unroll
+    for (int u = 1; u < R; ++u) x[u] = cmulc(x[u], w[u * R]);
+    dft<R, true>(x);
+#pragma unroll
+    for (int j = 0; j < R; ++j) col[R * j] = x[j];
+}
+
 // ------------------------------------------------------------------------------------------
 bool cache_cols_split(int N, int *N1, int *N2) {
     for (int n1 : {256, 1024}) {
@@ -254,6 +299,16 @@ hipError_t launch_cache_fwd(const Pow2Plan &pl, const float2 *scr, float2 *X, in
 hipError_t launch_cache_inv(const Pow2Plan &pl, const float2 *X, const float2 *g, float2 *scr, int bh0, int nbh,
                             hipStream_t st) {
     return cache_cols(true, pl, scr, const_cast<float2 *>(X), g, bh0, nbh, st);
+}
+
+hipError_t launch_mix_cols(const Pow2Plan &pl, float2 *scr, const float2 *gp, int bh0, int nbh, hipStream_t st) {
+    constexpr int R = 32, PW = 8;
+    if (pl.N1 != R * R) return hipErrorInvalidValue;
+    const size_t lds = (size_t)PW * (pl.N1 + R) * sizeof(float) + (size_t)pl.N1 * sizeof(float2);
+    const int planes = nbh * pl.N2;
+    k_mix_cols<R, PW><<<(planes + 7) / 8 * 8 * (32 / PW), PW * R, lds, st>>>(scr, gp, reinterpret_cast<const float4 *>(pl.twN1),
+                                                                            pl.N2, bh0, planes);
+    return hipGetLastError();
 }
 
 // Loads this translation unit's code object (the runtime loads them on first use): called by spectre_prepare so

@@ -83,7 +83,10 @@ hipError_t launch_small_inv(const Pow2Plan &pl, int io, const float2 *scratch, v
 // the separate projection would have stored them, and transformed.  bf16 rows and fp32 scratch only.
 hipError_t launch_small_fwd_proj(const Pow2Plan &pl, const void *x, const void *wpack, int Hw, float2 *scratch, int rows,
                                  int H, int bh0, int nbh, hipStream_t st, bool affine = false);
-// g [BH, L/2+1] -> gp [BH][N2][N1] in the big kernel's register order, scaled by 1/L and
+// The column pass of a plan with 1024-point columns (P = 0, see cache_cols_split): forward, gate, inverse, in place, of heads
+// bh0 .. bh0 + nbh - 1; gp as launch_gate_expand lays it out for that plan.
+hipError_t launch_mix_cols(const Pow2Plan &pl, float2 *scratch, const float2 *gp, int bh0, int nbh, hipStream_t st);
+// g [BH, L/2+1] -> gp [BH][N2][N1] in the big kernel's register order (P = 0: in bin order), scaled by 1/L and
 // extended to all L bins by Hermitian symmetry (real parts only at DC and Nyquist).
 hipError_t launch_gate_expand(const Pow2Plan &pl, const float2 *g, float2 *gp, int BH, hipStream_t st);
 

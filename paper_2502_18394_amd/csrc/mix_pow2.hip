@@ -99,7 +99,7 @@ __global__ __launch_bounds__(RowTile<IO>::kPairs * TT) void k_small_fwd(const ty
 typedef float floatx16_t __attribute__((ext_vector_type(16)));
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 
-template <int N2>
+template <int N2, typename SC>
 __global__ __launch_bounds__(512) void k_small_fwd_proj(const uint32_t *__restrict__ x, const uint4 *__restrict__ wpack,
                                                         int Hw, float2 *__restrict__ scr,
                                                         const float2 *__restrict__ twL, int rows, int H, int N1,
@@ -167,7 +167,7 @@ __global__ __launch_bounds__(512) void k_small_fwd_proj(const uint32_t *__restri
     for (int t2 = 0; t2 < N2; ++t2) xv[t2] = IoBf16::unpack(lds[(t2 * TT + tl) * S + p]);
     small_dft<N2, false>(xv);
     float2 *dst = scr + (((size_t)bhl * N2) * 32 + p) * N1 + t1;
-    const SmallTwiddles<N2> tw(twL, t1);
+    const SmallTwiddles<N2, std::is_same<SC, ScrF32Fine>::value> tw(twL, t1);
 #pragma unroll
     for (int k2 = 0; k2 < N2; ++k2) {
         const float2 y = (k2 == 0) ? xv[0] : cmul(xv[k2], tw(k2));
@@ -544,12 +544,12 @@ __global__ __launch_bounds__(512) void k_fused(const typename IO::pair_t *__rest
 // passes, and ext = Hermitian extension with real DC and Nyquist bins.  Consecutive bins run over k2 first, so a
 // workgroup loads runs of N2 consecutive bins and turns them in LDS into runs of consecutive entries of each plane.
 //
-// N1 = 256, where entry r of a plane is bin k1 = r: a workgroup takes 32 consecutive k1 of one
-// head, i.e. 32 N2 consecutive bins, and writes 256-byte runs into each of the N2 planes.  Eight workgroups per head:
+// N1 = 256 and 1024, where entry r of a plane is bin k1 = r: a workgroup takes 32 consecutive k1 of one
+// head, i.e. 32 N2 consecutive bins, and writes 256-byte runs into each of the N2 planes.  N1 / 32 workgroups per head:
 // one workgroup per head kept 32 compute units busy for 8 us with a chain of dependent loads and stores (a ninth
 // of the whole call at L = 8192).
 __global__ __launch_bounds__(256) void k_gate_expand256(const float2 *__restrict__ g, float2 *__restrict__ gp, int L,
-                                                        int N2) {
+                                                        int N1, int N2) {
     __shared__ float2 tile[32 * 33];
     const int tid = threadIdx.x, bh = blockIdx.y, F = L / 2 + 1, S = N2 + 1;
     const int k1_0 = blockIdx.x * 32, k0 = k1_0 * N2;
@@ -566,7 +566,7 @@ __global__ __launch_bounds__(256) void k_gate_expand256(const float2 *__restrict
     float2 *dst = gp + (size_t)bh * L + k1_0;
     for (int i = tid; i < 32 * N2; i += 256) {
         const int q = i & 31, k2 = i >> 5;
-        dst[(size_t)k2 * 256 + q] = tile[q * S + k2];
+        dst[(size_t)k2 * N1 + q] = tile[q * S + k2];
     }
 }
 
@@ -665,7 +665,7 @@ static hipError_t small_inv_t(const Pow2Plan &pl, const void *scr_v, void *out, 
         default: return hipErrorInvalidValue;                                \
     }
 
-// Windows with 1024-point columns (N = 12288 .. 32768).
+// 1024-point columns (N = 12288 .. 32768).
 #define SPECTRE_FINE_CASE(FN, N, ...) \
     case N: return io ? FN<N, 16, IoBf16, ScrF32Fine>(__VA_ARGS__) : FN<N, 16, IoF32, ScrF32Fine>(__VA_ARGS__);
 #define SPECTRE_DISPATCH_FINE(FN, ...)                                       \
@@ -687,15 +687,17 @@ hipError_t launch_small_fwd(const Pow2Plan &pl, int io, const void *v, float2 *s
 template <int N2, int TT, typename IO, typename SC>
 static hipError_t small_fwd_proj_t(const Pow2Plan &pl, const void *x, const void *wpack, int Hw, void *scr_v, int rows,
                                    int H, int bh0, int nbh, hipStream_t st, int aff) {
-    if (!std::is_same<IO, IoBf16>::value || !std::is_same<SC, ScrF32>::value) return hipErrorInvalidValue;
+    if constexpr (!std::is_same<IO, IoBf16>::value || !std::is_base_of<ScrF32, SC>::value) return hipErrorInvalidValue;
+    else {
     const size_t lds = (size_t)N2 * 16 * TileStride<IoBf16>::value * sizeof(uint32_t);
-    auto kern = k_small_fwd_proj<N2>;
+    auto kern = k_small_fwd_proj<N2, SC>;
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
     const dim3 grid = aff ? dim3(pl.N1 / 16 * nbh) : dim3(pl.N1 / 16, nbh);
     kern<<<grid, dim3(512), lds, st>>>(static_cast<const uint32_t *>(x), static_cast<const uint4 *>(wpack), Hw,
                                        static_cast<float2 *>(scr_v), pl.twL, rows, H, pl.N1, bh0, aff);
     return hipGetLastError();
+    }
 }
 
 hipError_t launch_small_fwd_proj(const Pow2Plan &pl, const void *x, const void *wpack, int Hw, float2 *scratch, int rows,
@@ -704,6 +706,7 @@ hipError_t launch_small_fwd_proj(const Pow2Plan &pl, const void *x, const void *
     const int aff = affine ? nbh : 0;
     const int io = 1;
     const bool scr16 = false;
+    if (pl.N1 == 1024) SPECTRE_DISPATCH_FINE(small_fwd_proj_t, pl, x, wpack, Hw, scratch, rows, H, bh0, nbh, st, aff)
     SPECTRE_DISPATCH_N2(small_fwd_proj_t, pl, x, wpack, Hw, scratch, rows, H, bh0, nbh, st, aff)
 }
 
@@ -800,12 +803,13 @@ hipError_t launch_fused(int io, const void *v, const float2 *g, void *out, const
 }
 
 hipError_t launch_gate_expand(const Pow2Plan &pl, const float2 *g, float2 *gp, int BH, hipStream_t st) {
-    if (pl.P != 2 && pl.P != 3) return hipErrorInvalidValue;
+    if (pl.P != 2 && pl.P != 3 && !(pl.P == 0 && pl.N1 == 1024)) return hipErrorInvalidValue;
     for (int bh0 = 0; bh0 < BH; bh0 += 65535) {         // grid.y limit
         const int n = (BH - bh0 < 65535) ? BH - bh0 : 65535;
         const int F = pl.L / 2 + 1;
-        if (pl.P == 2)
-            k_gate_expand256<<<dim3(8, n), dim3(256), 0, st>>>(g + (size_t)bh0 * F, gp + (size_t)bh0 * pl.L, pl.L, pl.N2);
+        if (pl.P != 3)
+            k_gate_expand256<<<dim3(pl.N1 / 32, n), dim3(256), 0, st>>>(g + (size_t)bh0 * F, gp + (size_t)bh0 * pl.L, pl.L, pl.N1,
+                                                                        pl.N2);
         else
             k_gate_expand4096<<<dim3(256, n), dim3(256), 0, st>>>(g + (size_t)bh0 * F, gp + (size_t)bh0 * pl.L, pl.L, pl.N2);
         const hipError_t e = hipGetLastError();
