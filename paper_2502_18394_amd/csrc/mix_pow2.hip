@@ -435,107 +435,147 @@ __global__ __launch_bounds__(256) void k_big(typename SC::elem_t *__restrict__ s
 // ------------------------------------------------------------------------------------------
 // fused: L = 4096.  A column of this length (32 KB as complex fp32) fits in LDS, so the three kernels above and the
 // gate expansion collapse into one kernel and the tensor crosses HBM once each way.  A workgroup of 512 lanes owns
-// four adjacent channel pairs of one head (16 or 32 contiguous bytes of every row), each column with its own padded
-// exchange buffer (4 x 34 KB); its two groups of 256 lanes take two columns each, one after the other, with the big
-// kernel's lane layout and register budget.
-//   load : all lanes sweep the rows, lane pl = tid % 4 of a row reads pair pl into the buffer of column pl;
-//   core : the big kernel's passes (forward, gate, inverse) from and to the column's buffer; register j of lane
-//          tau holds bin 256 j + 16 (tau % 16) + tau / 16 after the forward passes (base-16 digit reversal), and
-//          the gate is read there directly, Hermitian extension and the 1/L of the inverse transform included;
-//   store: the mirror image of the load.
+// four adjacent channel pairs of one head (16 or 32 contiguous bytes of every row), 4 x 34 KB of LDS; calls of few heads two pairs, so that more compute units share the arithmetic.
+//   pass 0 : lane tau reads the pieces of rows tau + 512 j, j < 8, and transforms the four columns' eight values in registers;
+//   core   : 16 lanes own a block of 512 positions of one column, 32 points each: passes of radix 32 and 16, gate and
+//            inverse passes without a workgroup barrier (LDS operations of a wave complete in order); after them value u2 of
+//            row u1 of block u0 is bin u0 + 8 u1 + 256 u2, and the gate is read there directly, Hermitian extension and the
+//            1/L of the inverse transform included;
+//   pass 0 again, inverse, from LDS to the rows.
+// What bounds it is that its three phases, memory, arithmetic, memory, do not overlap in the one workgroup a compute unit
+// holds: with the rows staged in LDS on both sides of three radix-16 passes, two columns at a time, 32 heads of bf16 rows took
+// 29.5 us (38 from cold caches) and 512 heads 543, now 27 (34) and 466; fp32 rows, 128 heads 116 -> 107; one head 22 -> 16.5.
 // The eight workgroups of a head share its rows; their ids are 8 apart, so they run on the same XCD and a row is
 // fetched into one L2.  (The same construction for L = 8192, two columns per pair, leaves room for only two pairs
 // per workgroup, i.e. 8-byte pieces of every row, and measured slower than the three kernels.)
-template <typename IO>
-__global__ __launch_bounds__(512) void k_fused(const typename IO::pair_t *__restrict__ v,
-                                               const float2 *__restrict__ g,
-                                               typename IO::pair_t *__restrict__ out,
-                                               const float2 *__restrict__ twN1, int H, int BH) {
-    typedef typename IO::pair_t pair_t;
-    constexpr int P = 3, L = 4096, F = L / 2 + 1, COLW = L + L / 16, PP = 4, WPH = 32 / PP;
-    constexpr int RPS = 512 / PP, NS = L / RPS;     // rows per sweep of the workgroup, sweeps
-    constexpr int kBatch = 16;                      // sweeps whose loads are in flight together
+// CL adjacent pairs of a row at the alignment of an element, 16 bytes at most.
+template <typename IO, int CL>
+struct FusedPiece {
+    typedef uint32_t vec_t __attribute__((ext_vector_type(CL * IO::kBytes / 2), aligned(4)));
+    vec_t w;
+    __device__ __forceinline__ float2 get(int c) const {
+        if constexpr (IO::kBytes == 2) return IoBf16::unpack(w[c]);
+        else return make_float2(__uint_as_float(w[2 * c]), __uint_as_float(w[2 * c + 1]));
+    }
+    __device__ __forceinline__ void set(int c, float2 v) {
+        if constexpr (IO::kBytes == 2) {
+            w[c] = IoBf16::pack(v);
+        } else {
+            w[2 * c] = __float_as_uint(v.x);
+            w[2 * c + 1] = __float_as_uint(v.y);
+        }
+    }
+};
+
+// PP pairs per workgroup of 128 PP lanes; a lane owns CL of them, of 4 / CL taus (a lane of its own for the 32 bytes of four
+// pairs of fp32 rows asks for twice the lines: 32 heads 31 -> 35 us).
+template <typename IO, int PP, int CL>
+__global__ __launch_bounds__(128 * PP, 2) void k_fused(const typename IO::pair_t *__restrict__ v,
+                                                       const float2 *__restrict__ g,
+                                                       typename IO::pair_t *__restrict__ out,
+                                                       const float2 *__restrict__ twL, int H, int BH) {
+    typedef FusedPiece<IO, CL> piece_t;
+    constexpr int L = 4096, F = L / 2 + 1, COLW = L + L / 16, BLKW = 512 + 512 / 16, WPH = 32 / PP;
+    constexpr int NS = PP / CL, NA = 4 / CL, TS = 128 * CL;          // lanes of a row, taus of a lane and their distance
     extern __shared__ float2 lds_fused[];
-    const int tid = threadIdx.x, tau = tid & 255, grp = tid >> 8;
+    const int tid = threadIdx.x;
     const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
     const int bh = (idx / WPH) * 8 + xcd, part = idx % WPH;
     if (bh >= BH) return;                           // whole workgroup: the grid is padded to 8 heads
     const int b = bh / H, h = bh % H;
-    const int pl = tid % PP, r0 = tid / PP;
-    const size_t rs = (size_t)H * 32;
-    const size_t off = (((size_t)b * L) * H + h) * 32 + part * PP + pl;
-
-    for (int s0 = 0; s0 < NS; s0 += kBatch) {
-        pair_t raw[kBatch];
+    const int t0 = tid / NS, c0 = tid % NS * CL;
+    const size_t rs = (size_t)H * 32, off = (((size_t)b * L + t0) * H + h) * 32 + part * PP + c0;
+    piece_t row[8 * NA];                             // row t0 + TS m: value j = m / NA of tau = t0 + TS (m % NA)
 #pragma unroll
-        for (int s = 0; s < kBatch; ++s) raw[s] = v[off + (size_t)(r0 + RPS * (s0 + s)) * rs];
+    for (int m = 0; m < 8 * NA; ++m) row[m].w = *reinterpret_cast<const typename piece_t::vec_t *>(v + off + (size_t)(TS * m) * rs);
+    const int i = tid & 15, c = (tid >> 4) % PP, u0 = (tid >> 4) / PP;   // core: lane of the block u0 of column c
+    float2 tw0[NA][8], tw1[32];
 #pragma unroll
-        for (int s = 0; s < kBatch; ++s) {
-            const int r = r0 + RPS * (s0 + s);
-            lds_fused[pl * COLW + r + (r >> 4)] = IO::unpack(raw[s]);
-        }
+    for (int a = 0; a < NA; ++a) {
+#pragma unroll
+        for (int u = 1; u < 8; ++u) tw0[a][u] = twL[(t0 + TS * a) * u];   // W_4096^(tau u)
     }
-    __syncthreads();
-
-    float2 tw[P - 1][15];
 #pragma unroll
-    for (int u = 1; u < 16; ++u) {
-        tw[0][u - 1] = twN1[tau * u];
-        tw[1][u - 1] = twN1[(tau & 15) * 16 * u];
+    for (int u = 1; u < 32; ++u) tw1[u] = twL[8 * i * u];            // W_512^(i u)
+    float2 *own = lds_fused + c0 * COLW + t0 + (t0 >> 4);            // position p of a column at p + p / 16
+#pragma unroll
+    for (int a = 0; a < NA; ++a) {
+#pragma unroll
+        for (int cc = 0; cc < CL; ++cc) {
+            float2 x[8], *w = own + cc * COLW + a * (TS + TS / 16);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j] = row[NA * j + a].get(cc);
+            dft<8, false>(x);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) w[u * BLKW] = u == 0 ? x[0] : cmul(x[u], tw0[a][u]);
+        }
     }
     const float2 *gh = g + (size_t)bh * F;
-    const int kbase = 16 * (tau & 15) + (tau >> 4);
     const float scale = 1.0f / (float)L;
-#pragma unroll 1
-    for (int c = grp; c < PP; c += 2) {
-        float2 *buf = lds_fused + c * COLW;
-        float2 *own = buf + pad_base<P, 0>(tau);     // the lane's pass-0 positions: rows tau + 256 j
-        float2 x[16], G[16];
+    float2 G[16];
+    auto load_gate = [&](int u1) {
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int k = 256 * j + kbase;
-            G[j] = gh[2 * k <= L ? k : L - k];
+        for (int u2 = 0; u2 < 16; ++u2) {
+            const int k = u0 + 8 * u1 + 256 * u2;
+            G[u2] = gh[2 * k <= L ? k : L - k];
         }
+    };
+    load_gate(i);
+    __syncthreads();
+    float2 *blk = lds_fused + c * COLW + u0 * BLKW;
+    {
+        float2 x[32];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) x[j] = own[j * pad_stride<P, 0>()];
-        dft<16, false>(x);
+        for (int j = 0; j < 32; ++j) x[j] = blk[i + 17 * j];
+        dft<32, false>(x);
 #pragma unroll
-        for (int u = 1; u < 16; ++u) x[u] = cmul(x[u], tw[0][u - 1]);
-        exchange<P, 0, 1, true>(x, buf, tau);
-        dft<16, false>(x);
+        for (int u = 0; u < 32; ++u) blk[i + 17 * u] = u == 0 ? x[0] : cmul(x[u], tw1[u]);
+    }
+    __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int u = 1; u < 16; ++u) x[u] = cmul(x[u], tw[1][u - 1]);
-        exchange<P, 1, 2, false>(x, buf, tau);
-        dft<16, false>(x);
+    for (int q = 0; q < 2; ++q) {
+        const int u1 = i + 16 * q;
+        float2 *w = blk + 17 * u1, y[16];
 #pragma unroll
-        for (int j = 0; j < 16; ++j) {
-            const int k = 256 * j + kbase;
-            float2 gv = make_float2(G[j].x * scale, G[j].y * scale);
+        for (int j = 0; j < 16; ++j) y[j] = w[j];
+        dft<16, false>(y);
+#pragma unroll
+        for (int u2 = 0; u2 < 16; ++u2) {
+            const int k = u0 + 8 * u1 + 256 * u2;
+            float2 gv = make_float2(G[u2].x * scale, G[u2].y * scale);
             if (2 * k > L) gv.y = -gv.y;
             if (k == 0 || 2 * k == L) gv.y = 0.0f;
-            x[j] = cmul(x[j], gv);
+            y[u2] = cmul(y[u2], gv);
         }
-        dft<16, true>(x);
-        exchange<P, 2, 1, false>(x, buf, tau);
+        if (q == 0) load_gate(i + 16);
+        dft<16, true>(y);
 #pragma unroll
-        for (int u = 1; u < 16; ++u) x[u] = cmulc(x[u], tw[1][u - 1]);
-        dft<16, true>(x);
-        exchange<P, 1, 0, true>(x, buf, tau);
+        for (int j = 0; j < 16; ++j) w[j] = y[j];
+    }
+    __builtin_amdgcn_wave_barrier();
+    {
+        float2 x[32];
 #pragma unroll
-        for (int u = 1; u < 16; ++u) x[u] = cmulc(x[u], tw[0][u - 1]);
-        dft<16, true>(x);
+        for (int u = 0; u < 32; ++u) x[u] = u == 0 ? blk[i] : cmulc(blk[i + 17 * u], tw1[u]);
+        dft<32, true>(x);
 #pragma unroll
-        for (int j = 0; j < 16; ++j) own[j * pad_stride<P, 0>()] = x[j];   // nobody else touches these positions
+        for (int j = 0; j < 32; ++j) blk[i + 17 * j] = x[j];
     }
     __syncthreads();
-
-    for (int s0 = 0; s0 < NS; s0 += kBatch) {
 #pragma unroll
-        for (int s = 0; s < kBatch; ++s) {
-            const int r = r0 + RPS * (s0 + s);
-            out[off + (size_t)r * rs] = IO::pack(lds_fused[pl * COLW + r + (r >> 4)]);
+    for (int a = 0; a < NA; ++a) {
+#pragma unroll
+        for (int cc = 0; cc < CL; ++cc) {
+            float2 x[8], *w = own + cc * COLW + a * (TS + TS / 16);
+#pragma unroll
+            for (int u = 0; u < 8; ++u) x[u] = u == 0 ? w[0] : cmulc(w[u * BLKW], tw0[a][u]);
+            dft<8, true>(x);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) row[NA * j + a].set(cc, x[j]);
         }
     }
+#pragma unroll
+    for (int m = 0; m < 8 * NA; ++m) *reinterpret_cast<typename piece_t::vec_t *>(out + off + (size_t)(TS * m) * rs) = row[m].w;
 }
 
 // ------------------------------------------------------------------------------------------
@@ -781,25 +821,30 @@ hipError_t launch_big(const Pow2Plan &pl, float2 *scratch, const float2 *gp, int
 
 bool fused_supported(int L) { return L == 4096; }
 
-template <typename IO>
-static hipError_t fused_t(const void *v, const float2 *g, void *out, const float2 *twN1, int H, int BH,
-                          hipStream_t st) {
+template <typename IO, int PP, int CL>
+static hipError_t fused_t(const void *v, const float2 *g, void *out, const float2 *twL, int H, int BH, hipStream_t st) {
     constexpr int COLW = 4096 + 4096 / 16;
-    const size_t lds = (size_t)4 * COLW * sizeof(float2);
-    auto kern = k_fused<IO>;
+    const size_t lds = (size_t)PP * COLW * sizeof(float2);
+    auto kern = k_fused<IO, PP, CL>;
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
-    const long long grid = (long long)((BH + 7) / 8) * 8 * 8;   // heads padded to 8, 8 workgroups per head
+    const long long grid = (long long)((BH + 7) / 8) * 8 * (32 / PP);   // heads padded to 8
     if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-    kern<<<dim3((unsigned)grid), dim3(512), lds, st>>>(static_cast<const typename IO::pair_t *>(v), g,
-                                                       static_cast<typename IO::pair_t *>(out), twN1, H, BH);
+    kern<<<dim3((unsigned)grid), dim3(128 * PP), lds, st>>>(static_cast<const typename IO::pair_t *>(v), g,
+                                                            static_cast<typename IO::pair_t *>(out), twL, H, BH);
     return hipGetLastError();
 }
 
 hipError_t launch_fused(int io, const void *v, const float2 *g, void *out, const float2 *tw4096, int L, int H, int BH,
                         hipStream_t st) {
     if (!fused_supported(L)) return hipErrorInvalidValue;
-    return io ? fused_t<IoBf16>(v, g, out, tw4096, H, BH, st) : fused_t<IoF32>(v, g, out, tw4096, H, BH, st);
+    // Two pairs per workgroup while four would leave half the compute units without one (bf16, 1, 8, 16, 20 heads with four /
+    // two / one pairs 19.5 / 16.5 / 17.5, 20.6 / 17.3 / 18.1, 22.5 / 20.5 / 28.1, 24.2 / 29.3 / 38.5 us).
+#define SPECTRE_FUSED(IO, PP, CL) return fused_t<IO, PP, CL>(v, g, out, tw4096, H, BH, st)
+    if (BH <= 16) { if (io) SPECTRE_FUSED(IoBf16, 2, 2); SPECTRE_FUSED(IoF32, 2, 2); }
+    if (io) SPECTRE_FUSED(IoBf16, 4, 4);
+    SPECTRE_FUSED(IoF32, 4, 2);
+#undef SPECTRE_FUSED
 }
 
 hipError_t launch_gate_expand(const Pow2Plan &pl, const float2 *g, float2 *gp, int BH, hipStream_t st) {

@@ -235,6 +235,29 @@ def test_columns_of_1024_points(oracle, B, L, H, io):
     assert_close_elementwise(got, want, io, L)
 
 
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+@pytest.mark.parametrize("B,H", [(1, 1), (2, 8), (1, 17), (3, 11)])
+def test_4096_points_with_few_and_many_heads(oracle, options, B, H, io):
+    """Two and four pairs per workgroup (up to 16 heads and above), from tensors off a 16-byte boundary as well, against the
+    oracle and the three kernels of the four-step route."""
+    from paper_2502_18394_amd import binding
+    L = 4096
+    print(f"case B={B} H={H} io={io}", flush=True)
+    seed = synth.BASE_SEED + 37 * H + B
+    got, want, _ = run_case(oracle, B, L, H, 64, io, seed=seed)
+    assert rel_l2(got, want) <= (1e-6 if io == "f32" else 2e-3)
+    assert_close_elementwise(got, want, io, L)
+    vals, store = synth.tokens(seed, (B, L, H, 64), io)
+    v = to_device(vals, store, io)
+    g = torch.from_numpy(synth.random_gate(seed + 1, B, H, L)).cuda()
+    off = torch.empty(v.numel() + 2, dtype=v.dtype, device="cuda")[2:].view_as(v)
+    off.copy_(v)
+    assert off.data_ptr() % 16 != 0 and np.array_equal(from_device(binding.mix_forward(off, g)), got)
+    options(binding.OPT_FUSED_4096, 0)
+    three, _, _ = run_case(oracle, B, L, H, 64, io, seed=seed)
+    assert rel_l2(got, three) <= (1e-6 if io == "f32" else 2e-3)
+
+
 @pytest.mark.parametrize("L", [196, 256])
 @pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16])
 def test_streamed_rows_change_no_bit(L, dtype):
