@@ -449,8 +449,8 @@ __global__ __launch_bounds__(256, G <= 2 ? 3 : 2) void k_append_fold(float2 *__r
     for (; kap < end; kap += 4) {
         float2 x[16];
 #pragma unroll
-        for (int b = 0; b < 16; ++b) x[b] = stream_load(Xh + (size_t)bin(kap, b) * 64);   // in range also where a bin
-        const float2 w = wn, rd = cmulc(gn, tn);                                          // appears twice
+        for (int b = 0; b < 16; ++b) x[b] = stream_load(Xh + (size_t)bin(kap, b) * 64);   // kap = 0, N / 32: some bins twice
+        const float2 w = wn, rd = cmulc(gn, tn);
         const int next = min(kap + 4, top);
         wn = tw[mul_mod((unsigned)next, mult, N)];
         if (READ) {
