@@ -511,7 +511,9 @@ int spectre_prepare(int n, int d) {
         const int M = chirp_padded_length(n);
         if (!M) return fail(SPECTRE_EUNSUPPORTED, "prepare: no kernel for length %d", n);
         if ((rc = get_pow2_plan(M, &pl, true))) return rc;
-        if (cache_cols_split(M, &N1, &N2) && (rc = get_column_factors(N1, &r, true))) return rc;   // M itself is then ready, too
+        // with these two the padded length itself is ready, too
+        if (cache_cols_split(M, &N1, &N2) && (rc = get_column_factors(N1, &r, true))) return rc;
+        if (slab_supported(M) && (rc = get_slab_order(M, &o, true))) return rc;
         const float2 *w = nullptr, *filt = nullptr;
         if ((rc = get_chirp(n, pl, &w, &filt, true))) return rc;
         if (const int D = chirp_data_length(n)) {

@@ -72,6 +72,33 @@ def test_shutdown_frees_tables_and_library_recovers(oracle):
     assert torch.equal(a, b)
 
 
+def _raw_mix(L, v, g, out, B, n, H):
+    """spectre_mix_forward without the binding's own spectre_prepare."""
+    ws = torch.empty(L.spectre_mix_workspace_bytes(B, n, H, 64, 0) + 256, dtype=torch.uint8, device="cuda")
+    at = ws.data_ptr() + (-ws.data_ptr()) % 256
+    rc = L.spectre_mix_forward(ctypes.c_void_p(v.data_ptr()), ctypes.c_void_p(g.data_ptr()), ctypes.c_void_p(out.data_ptr()),
+                               B, n, H, 64, 0, ctypes.c_void_p(at), ctypes.c_size_t(ws.numel() - 256), None)
+    torch.cuda.synchronize()
+    return rc
+
+
+@pytest.mark.parametrize("n,padded", [(197, 512), (211, 512), (419, 1024), (509, 1024)])
+def test_a_padded_length_is_ready_with_the_one_it_serves(oracle, n, padded):
+    """spectre_prepare of a length without a plan also makes the tables of its padded length, whichever length the data pass
+    has: a mixer call of that length needs no spectre_prepare of its own."""
+    from paper_2502_18394_amd import binding
+    print(f"case n={n} padded={padded}", flush=True)
+    vals, store = synth.tokens(100, (1, padded, 2, 64), "f32")
+    g = synth.random_gate(101, 1, 2, padded)
+    v, gd = to_device(store, "f32"), torch.from_numpy(g).cuda()
+    out = torch.empty_like(v)
+    torch.cuda.synchronize()
+    binding.shutdown()
+    binding.prepare(n, 64)
+    assert _raw_mix(binding.lib(), v, gd, out, 1, padded, 2) == binding.OK
+    assert rel_l2(out.cpu().numpy(), oracle.mix_forward(vals.astype(np.float64), g.astype(np.complex128))) <= 1e-6
+
+
 def test_error_paths_launch_nothing():
     from paper_2502_18394_amd import binding
     v = torch.zeros((1, 8192, 1, 64), device="cuda")
