@@ -573,6 +573,24 @@ static int get_mix_plan(int L, spectre_dtype io, Pow2Plan *pl) {
     return get_column_factors(N1, &pl->twN1);
 }
 
+// Looks up the tables that mix_forward_checked looks up on `route`: for callers that enqueue work ahead of it.
+static int mix_ready(int route, int L, spectre_dtype io) {
+    const float2 *table = nullptr, *filt = nullptr;
+    const int *order = nullptr;
+    Pow2Plan pl;
+    int rc;
+    if (route == 2) return get_mix_plan(L, io, &pl);
+    if (route == 4) return get_roots(4096, &table);
+    int in_lds = L;                                    // the length the in-LDS kernel runs at, if it does
+    if (route == 3) {
+        if ((rc = get_pow2_plan(chirp_padded_length(L), &pl)) || (rc = get_chirp(L, pl, &table, &filt))) return rc;
+        in_lds = chirp_data_length(L);
+        if (!in_lds) return SPECTRE_OK;
+    }
+    rc = get_roots(in_lds, &table);
+    return rc ? rc : get_slab_order(in_lds, &order);
+}
+
 // The four-step route: gate expansion, then per head group the row transforms, the column kernel and the inverse
 // row transforms.  gp = expanded gate [BH][L]; lane_scr[i] = transform scratch of lane i (lane_bytes each).
 // side == nullptr keeps every group on st.
@@ -1088,11 +1106,7 @@ int spectre_layer_forward(const void *x, const float *Wq, const float *Wv, int H
         if (rc) return rc;
         mg = mix_groups(BH, L, d, 1);
     } else {
-        const float2 *probe = nullptr;                 // the unfused mixer call below looks its tables up itself; make
-        const int route = mix_route(BH, L, d, io);     // sure it cannot fail after the projection has been enqueued
-        if (route == 1 || route == 2) rc = get_roots(L, &probe);
-        else if (route == 4) rc = get_roots(4096, &probe);
-        else rc = get_roots(chirp_padded_length(L), &probe);
+        rc = mix_ready(mix_route(BH, L, d, io), L, io);   // the mixer behind the projection cannot fail for want of a table
         if (rc) return rc;
     }
     hipError_t e;

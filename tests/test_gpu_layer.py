@@ -90,6 +90,31 @@ def test_layer_of_many_heads(oracle):
     assert rel_l2(got, want) <= 2e-5 and rel_l2(got, ref) <= 1e-6
 
 
+@pytest.mark.parametrize("L", [256, 197])
+def test_layer_of_a_length_that_is_not_ready_enqueues_nothing(L):
+    """With only 512 points prepared the roots of unity of 256 points exist (as those of its columns), and those of the padded
+    length of 197, but not the other tables of either length: the layer has to say so before its projection runs."""
+    import ctypes
+    from paper_2502_18394_amd import binding
+    H, d = 2, 64
+    print(f"case L={L}", flush=True)
+    P = binding.GateParams(synth.gate_params(720, H, d, L))
+    x, Wm = torch.ones((1, L, H, d), device="cuda"), torch.ones((H, d, d), device="cuda")
+    out = torch.full_like(x, 7.0)
+    torch.cuda.synchronize()
+    binding.shutdown()
+    binding.prepare(512, d)
+    lib = binding.lib()
+    ws = torch.full((lib.spectre_layer_workspace_bytes(1, L, H, d, binding.F32, ctypes.byref(P.c), None) + 256,), 7,
+                    dtype=torch.uint8, device="cuda")
+    at = ws.data_ptr() + (-ws.data_ptr()) % 256
+    rc = lib.spectre_layer_forward(x.data_ptr(), Wm.data_ptr(), Wm.data_ptr(), H, ctypes.byref(P.c), None, out.data_ptr(), 1, L, H,
+                                   d, binding.F32, at, ws.numel() - 256, None)
+    torch.cuda.synchronize()
+    assert rc == binding.ENOTREADY and b"spectre_prepare" in lib.spectre_last_error()
+    assert bool((ws == 7).all()) and bool((out == 7.0).all())
+
+
 def test_layer_rejects_bad_arguments():
     from paper_2502_18394_amd import binding
     d = 64
