@@ -12,6 +12,12 @@ bool slab_supported(int L);
 // Host: bin_of_pos[p] = the bin held by position p after the forward passes (mixed-radix digit reversal).
 void slab_bin_order(int L, int *bin_of_pos);
 
+// Heads per launch, a multiple of 8, of a kernel with `parts` workgroups of `lanes` lanes to a head: the runtime takes fewer
+// than 2^32 lanes a launch (2^21 heads of 448 or 512 points, 230 to 275 GB of bf16 rows in and out, reach that).
+inline int slab_launch_heads(int parts, int lanes) {
+    return (int)(0xffffffffLL / ((long long)parts * lanes) / 8 * 8);
+}
+
 // out = irfft_L(g * rfft_L(v)) for d = 64; roots = device table [L] of exp(-j 2 pi m / L), bin_of_pos = device
 // copy of slab_bin_order(L).  With 0 < rows < L the tensors hold `rows` rows per sequence: v is taken as followed
 // by L - rows zero rows and only the first `rows` rows of the result are written.

@@ -229,7 +229,7 @@ struct SlabPlan {
 template <typename IO, int PP, int NT, int R0, int R1, int R2, bool DIRECT, bool STREAM>
 __global__ __launch_bounds__(NT) void k_mix_ct(const typename IO::pair_t *__restrict__ v, const float2 *__restrict__ g,
                                                typename IO::pair_t *__restrict__ out, const float2 *__restrict__ roots_g,
-                                               int H, int BH, int rows, int affine) {
+                                               int H, int bh0, int BH, int rows, int affine) {
     typedef SlabPlan<R0, R1, R2> Plan;
     constexpr int L = Plan::L, R = Plan::R, F = L / 2 + 1, S0 = Plan::S0, PAD = PP < 16 ? 1 : 0, kParts = 32 / PP;
     constexpr int kSlab = (L + PAD * Plan::blocks) * PP;
@@ -238,11 +238,11 @@ __global__ __launch_bounds__(NT) void k_mix_ct(const typename IO::pair_t *__rest
     extern __shared__ float2 lds_ct[];
     float2 *slab = lds_ct, *roots = slab + kSlab, *gpos = roots + L;
     const int tid = threadIdx.x, col = tid % PP, i0 = tid / PP;
-    int bh = blockIdx.x / kParts, part = blockIdx.x % kParts;
+    int bh = bh0 + blockIdx.x / kParts, part = blockIdx.x % kParts;
     if (affine) {                                                    // the parts of a head on one XCD: ids 8 apart
         const int idx = blockIdx.x >> 3;
         part = idx % kParts;
-        bh = (idx / kParts) * 8 + (blockIdx.x & 7);
+        bh = bh0 + (idx / kParts) * 8 + (blockIdx.x & 7);
         if (bh >= BH) return;                                        // whole workgroup: heads are padded to 8
     }
     const int b = bh / H, h = bh % H;
@@ -456,12 +456,16 @@ static hipError_t mix_ct_t(const void *v, const float2 *g, void *out, const floa
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
     }
-    const int BH = B * H, affine = PP < 32;
-    const long long grid = (long long)(affine ? (BH + 7) / 8 * 8 : BH) * (32 / PP);
-    if (grid > 0x7fffffffLL) return hipErrorInvalidValue;
-    kern<<<dim3((unsigned)grid), dim3(NT), lds, st>>>(static_cast<const typename IO::pair_t *>(v), g,
-                                                      static_cast<typename IO::pair_t *>(out), roots, H, BH, rows, affine);
-    return hipGetLastError();
+    const int BH = B * H, affine = PP < 32, most = slab_launch_heads(32 / PP, NT);
+    for (int bh0 = 0, n; bh0 < BH; bh0 += n) {
+        n = BH - bh0 < most ? BH - bh0 : most;
+        const int grid = (affine ? (n + 7) / 8 * 8 : n) * (32 / PP);
+        kern<<<dim3(grid), dim3(NT), lds, st>>>(static_cast<const typename IO::pair_t *>(v), g,
+                                                static_cast<typename IO::pair_t *>(out), roots, H, bh0, BH, rows, affine);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
 }
 
 // Pairs per workgroup: as many as leave room for three workgroups per compute unit (slab L*PP + two tables of L
