@@ -479,60 +479,86 @@ int slab_pairs_per_workgroup(int io, int BH, int L) {
     return pp;
 }
 
-// The lengths with compile-time radices; false: not one of them.  Every length was measured with several splits: three
-// short passes on more lanes beat two passes of radix 28 and 32, which leave two waves per SIMD, and eight pairs per workgroup
-// beat four while a compute unit still holds two or more (768 heads, us: 512 as 32 x 16 / 16 x 32 / 8 x 8 x 8 on four / eight
-// pairs 54 / 54 / 45 / 43; 768 as 24 x 32 on four / eight pairs / 12 x 8 x 8 74 / 61 / 60; 896 as 28 x 32 / 14 x 8 x 8 on four /
-// eight 90 / 74 / 68; 1024 as 16 x 16 x 4 / 32 x 32 / 16 x 8 x 8 on eight / four 96 / 94 / 100 / 76; 640 as 10 x 8 x 8 / 20 x 32
-// 55 / 49; 400 as 20 x 20 on sixteen / four / eight pairs, 10 x 8 x 5 42 / 41 / 37 / 40; 384 heads of 1280 as 16 x 16 x 5 / 10 x
-// 16 x 8 / 20 x 8 x 8 108 / 95 / 75).  Few heads take four pairs and their own loads where the tables cost more than the
-// transform (kernel alone, one head: 196 6.4 -> 5.0, 256 5.9 -> 4.9, 1024 9.0 -> 7.8).
+// The lengths with compile-time radices, false for any other: the patch grids n x n with n = 12, 14, 16, 20, 24, 28 and 32, and
+// the lengths of up to 2048 points that have a four-step plan or serve as data length of the padded convolution (mix_chirp.hip).
+// Most have two forms.
+//   few heads : four pairs per workgroup (1024, 1536 and 1792: two), every lane with its own loads of factors and gate, while the
+//               launch has at most a wave per SIMD: until then a call costs what one workgroup does, and above it the
+//               narrow pieces of rows and the repeated loads do.
+//   otherwise : the tables in LDS, at the pairs per workgroup that are fastest for many heads.
+// Kernel alone, bf16 rows, us, few form / other form:
+//   heads       1             8            32           128           768       few up to
+//    196    5.4 /  6.1    5.5 /  6.2    5.6 /  6.3    6.6 /  6.7    19.0 / 14.4    128
+//    256    5.1 /  6.2    5.2 /  6.4    5.4 /  6.5    7.3 /  6.9    24.4 / 16.4     64
+//    448    5.0 /  5.4    5.1 /  5.5    5.5 /  5.8    9.8 /  9.1    41.6 / 32.5     32
+//    896    7.4 /  8.6    7.5 /  8.7    8.7 /  9.3   18.6 / 15.5    83.7 / 70.0     32
+//   1024    7.5 /  7.9    7.7 /  8.1   10.5 /  9.5   29.1 / 21.3     161 / 87.8     16
+//   1280    9.5 / 10.1    9.7 / 10.4   11.5 / 12.1   26.8 / 27.5     140 /  132     32
+//   1536    8.9 / 10.6    9.1 / 10.7   13.4 / 12.8   47.5 / 31.8     437 /  221     16
+// None for few: 512 (5.3 / 5.4, 5.4 / 5.5, 6.1 / 5.8), 2048 (two pairs 11.1 / 10.6 at one head), and the two passes of radix 16
+// to 32 of 320, 400 and 640 (four pairs at one head 7.0 / 7.5, 7.1 / 7.9 and 7.5 / 8.1, but 9.7 / 8.5 at 48 of 400; three shorter
+// passes would take 5.8 at 320 and 400, with 3 and 5 % more error).
+// Splits of the other form: three short passes on more lanes beat two passes of radix 28 and 32, which leave two waves per SIMD
+// (24 x 24 excepted: 768 heads of 576 42 us, 12 x 6 x 8 48), and eight pairs per workgroup beat four while a compute unit
+// still holds two or more (768 heads: 512 as 32 x 16 / 16 x 32 / 8 x 8 x 8 on four / eight pairs 54 / 54 / 45 / 43; 768 as 24 x 32 on
+// four / eight pairs / 12 x 8 x 8 74 / 61 / 60; 896 as 28 x 32 / 14 x 8 x 8 on four / eight 90 / 74 / 68; 1024 as 16 x 16 x 4 / 32
+// x 32 / 16 x 8 x 8 on eight / four 96 / 94 / 100 / 76; 640 as 10 x 8 x 8 / 20 x 32 55 / 49; 400 as 20 x 20 on sixteen / four /
+// eight pairs, 10 x 8 x 5 42 / 41 / 37 / 40; 384 heads of 1280 as 16 x 16 x 5 / 10 x 16 x 8 / 20 x 8 x 8 108 / 95 / 75).
 template <typename IO>
 static bool mix_ct(int L, const void *v, const float2 *g, void *out, const float2 *roots, int B, int H, int rows,
                    hipStream_t st, hipError_t *e) {
-    const long long pairs = (long long)B * H * 32;
-    const bool few = pairs <= 256 * 16;
+    constexpr bool bf = IO::kBytes == 2;
+    constexpr int kSimds = 1024;
+    const long long heads = (long long)B * H;
     // Rows that will not be found in the memory-side cache again pass it by, where a workgroup's piece of a row is whole
     // 128-byte lines (fp32, L = 196, H = 12: B = 256 71 -> 68 us, 128 38 -> 36, but 64 19.6 -> 20.3; 256 at B = 256 86 -> 80,
     // bf16 53 -> 49).
-    const bool stream = 2 * pairs * rows * (long long)sizeof(typename IO::pair_t) > 100000000 &&
+    const bool stream = 64 * heads * rows * (long long)sizeof(typename IO::pair_t) > 100000000 &&
                         ((reinterpret_cast<uintptr_t>(v) | reinterpret_cast<uintptr_t>(out)) & 127) == 0;
-#define SPECTRE_CT(PP, NT, R0, R1, R2, DIRECT) \
-    { *e = mix_ct_t<IO, PP, NT, R0, R1, R2, DIRECT>(v, g, out, roots, B, H, rows, st); return true; }
+#define SPECTRE_CT(PP, NT, R0, R1, R2, ...)                                                                             \
+    {                                                                                                                   \
+        *e = mix_ct_t<IO, PP, NT, R0, R1, R2, __VA_ARGS__>(v, g, out, roots, B, H, rows, st);                           \
+        return true;                                                                                                    \
+    }
+#define SPECTRE_CT_FEW(PP, NT, R0, R1, R2) \
+    if (heads * (32 / PP) * (NT / 64) <= kSimds) SPECTRE_CT(PP, NT, R0, R1, R2, true)
 #define SPECTRE_CT_LINES(PP, NT, R0, R1, R2)                                                                            \
     {                                                                                                                   \
         static_assert(PP * sizeof(typename IO::pair_t) % 128 == 0, "whole lines");                                      \
-        *e = stream ? mix_ct_t<IO, PP, NT, R0, R1, R2, false, true>(v, g, out, roots, B, H, rows, st)                   \
-                    : mix_ct_t<IO, PP, NT, R0, R1, R2, false>(v, g, out, roots, B, H, rows, st);                        \
-        return true;                                                                                                    \
+        if (stream) SPECTRE_CT(PP, NT, R0, R1, R2, false, true)                                                         \
+        SPECTRE_CT(PP, NT, R0, R1, R2, false)                                                                           \
     }
     switch (L) {
+        case 144:
+            SPECTRE_CT_FEW(4, 64, 12, 12, 1)
+            if constexpr (bf) SPECTRE_CT_LINES(32, 384, 12, 12, 1)
+            else SPECTRE_CT_LINES(16, 192, 12, 12, 1)
         case 196:
-            if (few) SPECTRE_CT(4, 64, 14, 14, 1, true)
-            if constexpr (IO::kBytes == 2) SPECTRE_CT_LINES(32, 448, 14, 14, 1)
-            else if (stream) SPECTRE_CT_LINES(16, 256, 14, 14, 1)
-            else SPECTRE_CT(32, 448, 14, 14, 1, false)
+            SPECTRE_CT_FEW(4, 64, 14, 14, 1)
+            if constexpr (bf) SPECTRE_CT_LINES(32, 448, 14, 14, 1)
+            else SPECTRE_CT_LINES(16, 256, 14, 14, 1)
         case 256:
-            if (few) SPECTRE_CT(4, 128, 8, 8, 4, true)
-            if constexpr (IO::kBytes == 2) SPECTRE_CT_LINES(32, 512, 16, 16, 1)
+            SPECTRE_CT_FEW(4, 128, 8, 8, 4)
+            if constexpr (bf) SPECTRE_CT_LINES(32, 512, 16, 16, 1)
             else SPECTRE_CT_LINES(16, 512, 8, 8, 4)
         case 320: SPECTRE_CT(16, 256, 20, 16, 1, false)
         case 400: SPECTRE_CT(8, 192, 20, 20, 1, false)
-        case 448: SPECTRE_CT(8, 512, 7, 8, 8, false)
+        case 448: SPECTRE_CT_FEW(4, 256, 7, 8, 8) SPECTRE_CT(8, 512, 7, 8, 8, false)
         case 512: SPECTRE_CT(8, 512, 8, 8, 8, false)
+        case 576: SPECTRE_CT_FEW(4, 192, 12, 12, 4) SPECTRE_CT(8, 192, 24, 24, 1, false)
         case 640: SPECTRE_CT(8, 256, 20, 32, 1, false)
-        case 768: SPECTRE_CT(8, 512, 12, 8, 8, false)
-        case 896: SPECTRE_CT(8, 512, 14, 8, 8, false)
-        case 1024:
-            if (pairs <= 256) SPECTRE_CT(2, 256, 8, 16, 8, true)
-            SPECTRE_CT(4, 256, 16, 8, 8, false)
-        case 1280: SPECTRE_CT(4, 256, 20, 8, 8, false)
-        case 1536: SPECTRE_CT(4, 256, 24, 8, 8, false)
-        case 1792: SPECTRE_CT(4, 512, 14, 16, 8, false)
+        case 768: SPECTRE_CT_FEW(4, 256, 12, 8, 8) SPECTRE_CT(8, 512, 12, 8, 8, false)
+        case 784: SPECTRE_CT_FEW(4, 256, 14, 7, 8) SPECTRE_CT(8, 448, 14, 7, 8, false)
+        case 896: SPECTRE_CT_FEW(4, 256, 14, 8, 8) SPECTRE_CT(8, 512, 14, 8, 8, false)
+        case 1024: SPECTRE_CT_FEW(2, 256, 8, 16, 8) SPECTRE_CT(4, 256, 16, 8, 8, false)
+        case 1280: SPECTRE_CT_FEW(4, 256, 20, 8, 8) SPECTRE_CT(4, 256, 20, 8, 8, false)
+        case 1536: SPECTRE_CT_FEW(2, 256, 12, 16, 8) SPECTRE_CT(4, 256, 24, 8, 8, false)
+        case 1792: SPECTRE_CT_FEW(2, 256, 14, 16, 8) SPECTRE_CT(4, 512, 14, 16, 8, false)
         case 2048: SPECTRE_CT(4, 512, 16, 16, 8, false)
         default: return false;
     }
 #undef SPECTRE_CT
+#undef SPECTRE_CT_FEW
 #undef SPECTRE_CT_LINES
 }
 

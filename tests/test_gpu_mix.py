@@ -224,6 +224,28 @@ def test_lengths_of_compile_time_radices(oracle, options, B, L, H, io):
     assert rel_l2(got, general) <= (1e-6 if io == "f32" else 2e-3)
 
 
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+@pytest.mark.parametrize("L,most", [(144, 128), (196, 128), (256, 64), (448, 32), (576, 42), (768, 32), (784, 32), (896, 32),
+                                    (1024, 16), (1280, 32), (1536, 16), (1792, 16)])
+def test_forms_for_few_and_for_many_heads(oracle, options, L, most, io):
+    """The last call that takes the form for few heads and the first that takes the other, against the general kernel (bounds as
+    above), and the first head of both against the oracle."""
+    from paper_2502_18394_amd import binding
+    for H in (most, most + 1):
+        print(f"case L={L} H={H} io={io}", flush=True)
+        vals, store = synth.tokens(synth.BASE_SEED + 41 * L, (1, L, H, 64), io)
+        gate = synth.random_gate(synth.BASE_SEED + 41 * L + 1, 1, H, L)
+        v, g = to_device(vals, store, io), torch.from_numpy(gate).cuda()
+        got = from_device(binding.mix_forward(v, g))
+        options(binding.OPT_SLAB_COMPILE_TIME, 0)
+        general = from_device(binding.mix_forward(v, g))
+        options(binding.OPT_SLAB_COMPILE_TIME, -1)
+        assert rel_l2(got, general) <= (1e-6 if io == "f32" else 2e-3)
+        want = oracle.mix_forward(np.ascontiguousarray(vals[:, :, :1]).astype(np.float64),
+                                  np.ascontiguousarray(gate[:, :1]).astype(np.complex128))
+        assert_close_elementwise(got[:, :, :1], want, io, L)
+
+
 @pytest.mark.parametrize("B,L,H,io", [(1, 12288, 3, "f32"), (1, 12288, 8, "bf16"), (1, 20480, 1, "f32"), (3, 24576, 3, "bf16"),
                                       (1, 28672, 2, "f32"), (1, 32768, 5, "bf16"), (1, 24576, 27, "f32")])
 def test_columns_of_1024_points(oracle, B, L, H, io):
