@@ -8,10 +8,11 @@
 namespace spectre {
 
 // ------------------------------------------------------------------------------------------
-// gates: grid (B*H, ceil(nout / 64)); every workgroup of 256 lanes repeats the LayerNorm (statistics in fp64) and the first
-// layer and emits 64 outputs, the terms of both layers split over its four waves (sums added in wave order).
-// What bounds it is the chain of latencies: with the statistics added up by one lane and each layer's terms in one it took
-// 19 us at any size (24576 rows, 13 levels, 32 heads), now 7.
+// gates: grid (B*H, parts); a workgroup of 256 lanes evaluates the LayerNorm (statistics in fp64) and the first layer and
+// emits every parts-th tile of 64 outputs, the terms of both layers split over its four waves (sums added in wave order).
+// What bounds it is the chain of latencies with few heads and the reads of W2 from L2 with many: 13 levels, 32 heads, 8.5 us
+// with the statistics added up by one lane and each layer's terms in one, now 5.4; 256 heads 9.8 -> 7.8, 4096 heads 62 -> 45.
+// A hidden layer 200 wide, 6 levels: 32 heads 12.6 -> 8.1, 2048 heads 39 -> 34.
 __device__ __forceinline__ double wrm_block_sum(double x, double *red, int wave) {
     red[wave] = wave_sum(x);                           // the same value in all lanes of the wave
     __syncthreads();
@@ -24,20 +25,23 @@ __global__ __launch_bounds__(256) void k_wrm_gates(const double *__restrict__ su
                                                    const float *__restrict__ b1, const float *__restrict__ W2,
                                                    const float *__restrict__ b2, float *__restrict__ s, int H, int Hg,
                                                    int d, int dw, int nout) {
-    __shared__ float qbar[256], hid[256], part[256];
+    __shared__ float qbar[256], hid[256], part[2][256];
     __shared__ double red[8];
     const int bh = blockIdx.x, h = bh % H, hp = (Hg == 1) ? 0 : h;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int o = blockIdx.y * 64 + lane;
+    const int step = gridDim.y * 64;
+    int o = blockIdx.y * 64 + lane;
     // the weights' latency passes behind the statistics (the usual widths only; any other is read where it is used)
     const bool usual = d == 64 && dw == 64;
     float w1[16], w2[16];
+    auto load_w2 = [&](int out) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) w2[i] = W2[((size_t)hp * 64 + wave + 4 * i) * nout + min(out, nout - 1)];
+    };
     if (usual) {
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
-            w1[i] = W1[(size_t)hp * 4096 + (wave + 4 * i) * 64 + lane];
-            w2[i] = W2[((size_t)hp * 64 + wave + 4 * i) * nout + min(o, nout - 1)];
-        }
+        for (int i = 0; i < 16; ++i) w1[i] = W1[(size_t)hp * 4096 + (wave + 4 * i) * 64 + lane];
+        load_w2(o);
     }
     const double x = tid < d ? inv_count * sum_q[(size_t)bh * d + tid] : 0.0;
     const double gam = tid < d ? (double)gamma[hp * d + tid] : 0.0, bet = tid < d ? (double)beta[hp * d + tid] : 0.0;
@@ -46,37 +50,52 @@ __global__ __launch_bounds__(256) void k_wrm_gates(const double *__restrict__ su
     const double rstd = 1.0 / sqrt(wrm_block_sum(dev * dev, red + 4, wave) / d + (double)eps);
     qbar[tid] = (float)(gam * dev * rstd + bet);
     __syncthreads();
-    // first layer: wave w takes the inputs w, w + 4, ..., a lane every 64th hidden unit
-    for (int j0 = 0; j0 < dw; j0 += 64) {
-        const int j = j0 + lane;
-        float a = 0.f;
-        if (usual) {
+    // sum of four over j mod 4: the terms of a column in the sums that the four waves add up otherwise
+    auto column = [&](const float *in, const float *w, int n, int stride) {
+        float a[4] = {0.f, 0.f, 0.f, 0.f};
+        int j = 0;
+#pragma unroll 4
+        for (; j + 4 <= n; j += 4)
 #pragma unroll
-            for (int i = 0; i < 16; ++i) a = fmaf(qbar[wave + 4 * i], w1[i], a);
-        } else if (j < dw) {
-            const float *w = W1 + (size_t)hp * d * dw + j;
-            for (int i = wave; i < d; i += 4) a = fmaf(qbar[i], w[(size_t)i * dw], a);
-        }
-        part[tid] = a;
+            for (int i = 0; i < 4; ++i) a[i] = fmaf(in[j + i], w[(size_t)(j + i) * stride], a[i]);
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            if (j + i < n) a[i] = fmaf(in[j + i], w[(size_t)(j + i) * stride], a[i]);
+        return (a[0] + a[1]) + (a[2] + a[3]);
+    };
+    float t = 0.f;
+    if (usual) {                                       // first layer: wave w takes the inputs w, w + 4, ...
+        float a = 0.f;
+#pragma unroll
+        for (int i = 0; i < 16; ++i) a = fmaf(qbar[wave + 4 * i], w1[i], a);
+        part[0][tid] = a;
         __syncthreads();
-        if (wave == 0 && j < dw) {
-            const float t = b1[hp * dw + j] + ((part[lane] + part[64 + lane]) + (part[128 + lane] + part[192 + lane]));
-            hid[j] = 0.5f * t * (1.0f + erff(t * 0.70710678118654752440f));
-        }
-        __syncthreads();
+        t = (part[0][lane] + part[0][64 + lane]) + (part[0][128 + lane] + part[0][192 + lane]);
+    } else if (tid < dw) {
+        t = column(qbar, W1 + (size_t)hp * d * dw + tid, d, dw);
     }
-    float a = 0.f;
-    if (usual) {
+    if (tid < dw) {
+        t += b1[hp * dw + tid];
+        hid[tid] = 0.5f * t * (1.0f + erff(t * 0.70710678118654752440f));
+    }
+    __syncthreads();
+    if (!usual) {                                      // a lane per output
+        for (o = blockIdx.y * 256 + tid; o < nout; o += gridDim.y * 256)
+            s[(size_t)bh * nout + o] = b2[(size_t)hp * nout + o] + column(hid, W2 + (size_t)hp * dw * nout + o, dw, nout);
+        return;
+    }
+    for (int buf = 0; o - lane < nout; o += step, buf ^= 1) {        // two staging rows, one barrier a tile
+        float a = 0.f;
 #pragma unroll
         for (int i = 0; i < 16; ++i) a = fmaf(hid[wave + 4 * i], w2[i], a);
-    } else if (o < nout) {
-        const float *w = W2 + (size_t)hp * dw * nout + o;
-        for (int j = wave; j < dw; j += 4) a = fmaf(hid[j], w[(size_t)j * nout], a);
+        if (o - lane + step < nout) load_w2(o + step);
+        part[buf][tid] = a;
+        __syncthreads();
+        if (wave == 0 && o < nout) {
+            const float *p = part[buf] + lane;
+            s[(size_t)bh * nout + o] = b2[(size_t)hp * nout + o] + ((p[0] + p[64]) + (p[128] + p[192]));
+        }
     }
-    part[tid] = a;
-    __syncthreads();
-    if (wave == 0 && o < nout)
-        s[(size_t)bh * nout + o] = b2[(size_t)hp * nout + o] + ((part[lane] + part[64 + lane]) + (part[128 + lane] + part[192 + lane]));
 }
 
 // ------------------------------------------------------------------------------------------
@@ -550,11 +569,19 @@ __global__ __launch_bounds__(256) void k_wrm_upper_coeff(const float *__restrict
 }
 
 // ------------------------------------------------------------------------------------------
+// Every workgroup repeats the first layer: one per 64 outputs while there are no more than four per compute unit, else fewer of
+// several tiles (one per 64 outputs / at most 512 / 1024 / 2048 workgroups, 13 levels, us: 256 heads 11 / 8.8 / 7.9 / 8.8, 512
+// heads 15 / 12.7 / 10.9 / 11.8, 4096 heads 101 / 47 / 46 / 46).
+constexpr int kWrmGateGroups = 1024;
+
 hipError_t launch_wrm_gates(const double *sum_q, double inv_count, const WrmDev &P, int B, int H, float *s,
                             hipStream_t st) {
     const int nout = (P.levels + 1) * P.d;
-    k_wrm_gates<<<dim3(B * H, (nout + 63) / 64), 256, 0, st>>>(sum_q, inv_count, P.ln_gamma, P.ln_beta, P.ln_eps, P.W1,
-                                                                P.b1, P.W2, P.b2, s, H, P.Hg, P.d, P.d_w, nout);
+    const int tile = P.d == 64 && P.d_w == 64 ? 64 : 256;            // outputs of a workgroup's round
+    int parts = (nout + tile - 1) / tile;
+    while (parts > 1 && (long long)parts * B * H > kWrmGateGroups) parts = (parts + 1) / 2;
+    k_wrm_gates<<<dim3(B * H, parts), 256, 0, st>>>(sum_q, inv_count, P.ln_gamma, P.ln_beta, P.ln_eps, P.W1, P.b1, P.W2, P.b2, s,
+                                                    H, P.Hg, P.d, P.d_w, nout);
     return hipGetLastError();
 }
 

@@ -109,6 +109,23 @@ def test_wrm_gates_match_oracle(oracle, shared, pooled, io):
     assert err <= 1e-5
 
 
+@pytest.mark.parametrize("B,H,d,dw,J,shared", [(1, 3, 64, 64, 0, False), (100, 3, 64, 64, 3, False), (103, 10, 64, 64, 2, True),
+                                               (100, 3, 64, 64, 4, False), (2, 3, 64, 200, 6, False), (86, 6, 64, 37, 4, True),
+                                               (350, 3, 64, 256, 4, False), (2, 2, 100, 5, 3, False)])
+def test_wrm_gates_of_any_width_and_number_of_heads(oracle, B, H, d, dw, J, shared):
+    """One workgroup per 64 outputs, workgroups of several tiles (more than 1024 of the former) with an even and a ragged split,
+    one per head; hidden widths and channel counts that are no multiple of four, with 256 outputs a round."""
+    from paper_2502_18394_amd import binding
+    print(f"case B={B} H={H} d={d} dw={dw} J={J} shared={shared}", flush=True)
+    p = synth.wrm_params(360 + dw + J, 1 if shared else H, d, J, d_w=dw)
+    sum_q = 40.0 * np.random.default_rng(361 + B).standard_normal((B, H, d))
+    s = binding.wrm_gates(torch.from_numpy(sum_q).cuda(), binding.WrmParams(p), 1.0 / 777, pooled=True)
+    torch.cuda.synchronize()
+    err = rel_l2(s.cpu().numpy(), oracle.wrm_gates(sum_q, 1.0 / 777, f64(p), J))
+    print(f"  rel_l2={err:.3e}", flush=True)
+    assert err <= 1e-6                                                         # fp32 sums of at most 256 terms
+
+
 def test_mixer_then_refinement_end_to_end(oracle):
     """Gate -> mixer -> level gates -> refinement on one query/value pair, against the oracle chain."""
     from paper_2502_18394_amd import binding
