@@ -248,8 +248,10 @@ __global__ __launch_bounds__(256) void k_wrm_upper(const float *__restrict__ S, 
 
 // What bounds it is the stream of rows in and out: L = 24576, 32 heads of bf16 rows, 201 MB, 53 -> 44 us.  16 rows per lane
 // and 512 lanes, at three or four waves per SIMD, took 59 and 57.
-template <typename IO>
-__global__ __launch_bounds__(256, 3) void k_wrm_apply(const typename IO::pair_t *__restrict__ v,
+// LATE: every gate is read where it is used, a level at a time, for long fp32 streams: a workgroup that waits between its loads
+// and its stores, and fewer of them on a compute unit, leave memory with fewer streams at once, which it moves faster.
+template <typename IO, bool LATE>
+__global__ __launch_bounds__(256, LATE ? 1 : 3) void k_wrm_apply(const typename IO::pair_t *__restrict__ v,
                                                    const float *__restrict__ s, const float2 *__restrict__ U,
                                                    typename IO::pair_t *__restrict__ out, int L, int H, int J,
                                                    int ntiles) {
@@ -264,12 +266,19 @@ __global__ __launch_bounds__(256, 3) void k_wrm_apply(const typename IO::pair_t 
     // gates of bands 0 .. 9 and the upper levels' term, under way with the rows: read where they are used, a level at a
     // time behind its test, they cost more than the arithmetic
     f32x2_elem_t gate[kWrmTileLevels + 2];
-#pragma unroll
-    for (int l = 0; l < kWrmTileLevels + 2; ++l)
-        gate[l] = *reinterpret_cast<const f32x2_elem_t *>(s + ((size_t)bh * (J + 1) + min(l, J)) * 64 + c0);
+    const float *sb = s + (size_t)bh * (J + 1) * 64;
     float2 corr = make_float2(0.f, 0.f);
-    if (J > kWrmTileLevels) corr = U[((size_t)bh * ntiles + tile) * 32 + p];
+    if (!LATE) {
+#pragma unroll
+        for (int l = 0; l < kWrmTileLevels + 2; ++l)
+            gate[l] = *reinterpret_cast<const f32x2_elem_t *>(sb + min(l, J) * 64 + c0);
+        if (J > kWrmTileLevels) corr = U[((size_t)bh * ntiles + tile) * 32 + p];
+    }
     auto coef = [&](int l) {                        // of the level-l block sum; levels above J carry no term
+        if (LATE) {
+            const float sc = exp2f(-(float)l);
+            return l <= J ? make_float2(wrm_coef(sb, l, J, c0) * sc, wrm_coef(sb, l, J, c0 + 1) * sc) : make_float2(0.f, 0.f);
+        }
         const f32x2_elem_t c = l < J ? gate[l + 1] - gate[l] : l == J ? gate[0] - gate[l] : f32x2_elem_t{0.f, 0.f};
         const float sc = exp2f(-(float)l);
         return make_float2(c.x * sc, c.y * sc);
@@ -298,6 +307,7 @@ __global__ __launch_bounds__(256, 3) void k_wrm_apply(const typename IO::pair_t 
     // levels 6..8 across the 8 row groups of the tile
     part[r][p] = s5;
     __syncthreads();
+    if (LATE && J > kWrmTileLevels) corr = U[((size_t)bh * ntiles + tile) * 32 + p];
     auto add_level = [&](int l, float2 sum) {       // corr += coef_l * (block sum / 2^l)
         if (l <= J) {
             const float2 c = coef(l);
@@ -330,7 +340,8 @@ __global__ __launch_bounds__(256, 3) void k_wrm_apply(const typename IO::pair_t 
         cf[l - 1][0] = c.x;
         cf[l - 1][1] = c.y;
     }
-    const float f0x = 1.0f + gate[1].x, f0y = 1.0f + gate[1].y;      // band min(1, J)
+    const f32x2_elem_t first = LATE ? *reinterpret_cast<const f32x2_elem_t *>(sb + min(1, J) * 64 + c0) : gate[1];
+    const float f0x = 1.0f + first.x, f0y = 1.0f + first.y;
 #pragma unroll
     for (int i4 = 0; i4 < 2; ++i4) {
         const float2 c4 = make_float2(fmaf(cf[3][0], s4[i4].x, corr.x), fmaf(cf[3][1], s4[i4].y, corr.y));
@@ -632,12 +643,20 @@ hipError_t launch_wrm_apply(int io, const void *v, const float *s, void *out, fl
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
-    if (io) k_wrm_apply<IoBf16><<<grid, 256, 0, st>>>(static_cast<const uint32_t *>(v), s,
-                                                      reinterpret_cast<const float2 *>(upper),
-                                                      static_cast<uint32_t *>(out), L, H, levels, ntiles);
-    else k_wrm_apply<IoF32><<<grid, 256, 0, st>>>(static_cast<const float2 *>(v), s,
-                                                  reinterpret_cast<const float2 *>(upper),
-                                                  static_cast<float2 *>(out), L, H, levels, ntiles);
+    // fp32 rows, us, gates read with the rows / late / late and two workgroups per compute unit instead of three (by the LDS asked
+    // for): 25 MB, 8 levels and fewer, 6.5 / 7.2 / -; 67 MB 26.9 / 27.3 / 24.5; 268 MB 101 / 99 / 96; 822 MB 302 / 289 / 276; 1.1 GB
+    // 397 / 388 / 364; more levels, with a pass in front, 67 MB 53.4 / 53.6 / 51.4, 268 MB 146 / 143 / 146, 1.1 GB 565 / 558 / 557.
+    // bf16 rows gain from early gates at any size (411 MB 186 -> 163).
+    const bool late = !io && (size_t)BH * L * 64 * sizeof(float) >= ((size_t)32 << 20);
+    constexpr size_t kLateLds = (size_t)56 << 10;
+#define SPECTRE_WRM_APPLY(IO, LATE)                                                                            \
+    k_wrm_apply<IO, LATE><<<grid, 256, LATE ? kLateLds : 0, st>>>(static_cast<const IO::pair_t *>(v), s,       \
+                                                                  reinterpret_cast<const float2 *>(upper),     \
+                                                                  static_cast<IO::pair_t *>(out), L, H, levels, ntiles)
+    if (io) SPECTRE_WRM_APPLY(IoBf16, false);
+    else if (late) SPECTRE_WRM_APPLY(IoF32, true);
+    else SPECTRE_WRM_APPLY(IoF32, false);
+#undef SPECTRE_WRM_APPLY
     return hipGetLastError();
 }
 

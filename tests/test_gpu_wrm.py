@@ -70,6 +70,26 @@ def test_wrm_apply_seeded_shapes(oracle, B, L, H, J, io):
     test_wrm_apply_matches_oracle(oracle, B, L, H, J, io)
 
 
+@pytest.mark.parametrize("B,L,J", [(33, 1056, 5), (32, 1024, 5), (33, 1024, 0), (2, 16384, 14)])
+def test_wrm_apply_of_long_fp32_streams(oracle, B, L, J):
+    """fp32 rows of 32 MiB and more, whose gates are read late (whole and ragged tiles, with and without levels
+    above a tile's): the first and the last head against the oracle, and a part of the batch alone, on the other side of the
+    line, bit for bit."""
+    from paper_2502_18394_amd import binding
+    H = 4
+    print(f"case B={B} L={L} J={J}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(370 + L)
+    v = torch.randn((B, L, H, 64), generator=gen, device="cuda")
+    gates = level_gates(371, B, H, J)
+    s = torch.from_numpy(gates).cuda()
+    out = binding.wrm_apply(v, s)
+    assert torch.equal(binding.wrm_apply(v[:1].contiguous(), s[:1].contiguous()), out[:1])
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        want = oracle.wrm_apply(np.ascontiguousarray(v[b:b + 1, :, h:h + 1].cpu().numpy()).astype(np.float64),
+                                np.ascontiguousarray(gates[b:b + 1, h:h + 1]).astype(np.float64), J)
+        assert rel_l2(out[b:b + 1, :, h:h + 1].cpu().numpy(), want) <= 1e-6
+
+
 def test_wrm_special_gates_and_in_place(oracle):
     from paper_2502_18394_amd import binding
     B, L, H, J = 1, 2048, 2, 11
