@@ -6,7 +6,8 @@
 //   prep    : x = inv_count * sum;  qbar = LayerNorm(x);  hid = GELU(qbar W1 + b1)
 //   out     : u = W2 hid + b2 on the matrix cores (fp32 MFMA, v_mfma_f32_4x4x1_16B_f32: 64
 //             output reals x 4 rows per instruction), with bias and modReLU in the epilogue
-//   phase   : the positional phase, when a position is given: in the epilogue of `out`, or a separate pass over g
+//   phase   : the positional phase, when a position is given: in the epilogue of `out`, or a separate pass over g (k_gate_small, the
+//             Toeplitz update, very many tiles)
 #include "gate.h"
 
 #include "common.h"
@@ -305,13 +306,19 @@ __device__ __forceinline__ void gate_load_tile(float4 (&a)[16], const float *__r
     }
 }
 
-// v exp(+j 2 pi ((k p) mod n)/n), the positional phase: angle reduced in integers and evaluated in fp64
-__device__ __forceinline__ float2 gate_turn(float2 v, long long k, int n_fft, long long phase) {
-    const long long m = (k * phase) % n_fft;
+// exp(+j 2 pi ((k p) mod n)/n), the positional phase of bin k < n at position p < n: angle reduced in integers (the quotient is
+// below 2^31, so its estimate in fp64 is off by one at most) and evaluated in fp64.
+struct GatePhase {
+    unsigned p, n;
+    double inv_n;
+};
+__device__ __forceinline__ float2 gate_phase(unsigned k, GatePhase ph) {
+    const unsigned q = (unsigned)((double)k * (double)ph.p * ph.inv_n);
+    long long m = (long long)((unsigned long long)k * ph.p - (unsigned long long)q * ph.n);
+    m += m < 0 ? (long long)ph.n : m >= (long long)ph.n ? -(long long)ph.n : 0;
     double s, c;
-    sincospi(2.0 * (double)m / (double)n_fft, &s, &c);
-    const float cf = (float)c, sf = (float)s;
-    return make_float2(v.x * cf - v.y * sf, v.x * sf + v.y * cf);
+    sincospi(2.0 * (double)(int)m * ph.inv_n, &s, &c);
+    return make_float2((float)c, (float)s);
 }
 
 // modReLU (Sec. 3.2 step 3c) of one bin and its store
@@ -326,13 +333,16 @@ __device__ __forceinline__ void gate_store_bin(float2 *dst, float re, float im, 
     *dst = make_float2(re, im);
 }
 
-// TURN: the positional phase is applied as well (a pass of its own over g took 5.5 us, B=4 H=32 n=8192).
+// TURN: the positional phase is applied as well.  The workgroup evaluates it once for every bin of its `rounds` tiles per wave,
+// while its first weights are under way, and keeps it in LDS: inside the loop over the tiles, fp64 constants and temporaries cost
+// a wave per SIMD or spills.  Gate of pooled sums with a position, us, as a pass of its own over g / evaluated in the loop / now, H=32:
+// B=4 n=8192 21.3 / 21.5 / 17.1; B=8 29.9 / 33.0 / 22.2; B=64 n=1024 29.4 / 33.8 / 21.8.
 template <bool VEC, int RG, bool TURN>   // VEC: d_g % 4 == 0 and 16-byte aligned rows; RG: row groups of 4
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4 : 2))) void k_gate_out(const float *__restrict__ hid, const float *__restrict__ W2,
                                                   const float *__restrict__ b2,
                                                   const float *__restrict__ mbias, float2 *__restrict__ g,
-                                                  int B, int H, int Hg, int dg, int F, int r_base0, int n_fft,
-                                                  long long phase) {
+                                                  int B, int H, int Hg, int dg, int F, int r_base0,
+                                                  int rounds, GatePhase phase) {
     extern __shared__ float hs[];
     const int r_base = r_base0 + 4 * RG * (int)blockIdx.z;   // blockIdx.z: tile of the rows (sequences)                    // [4*RG][dgs] hidden rows of this pass, zero padded
     const int dgp = (dg + 3) & ~3, dgs = dgp + 4;    // row stride padded against bank conflicts
@@ -356,7 +366,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
         if (r < M && j < dg) v = hid[(size_t)((Hg == 1) ? r : r * H + hsel) * dg + j];
         hs[idx] = v;
     }
+    float2 *turn = reinterpret_cast<float2 *>(hs + 4 * RG * dgs + 4 * 64 * ((VEC && dg == 64) ? kHalfStride : kTileStride));
+    if (TURN)
+        for (int e = threadIdx.x; e < 128 * rounds; e += 256)        // [round][wave][bin of the tile]
+            turn[e] = gate_phase(((unsigned)(blockIdx.x * 4 + ((e >> 5) & 3) + (e >> 7) * tstep)) * 32 + (e & 31), phase);
     __syncthreads();
+    turn += wave * 32 + ((lane & ~3) >> 1);                          // this lane's two bins of a tile
     const int jrow = lane & 3;
     // per-wave staging tile [64 rows][kTileStride floats]: filled with fully coalesced 16-byte
     // loads (a wave instruction covers 4 whole rows of 64 weights), read back one row per lane
@@ -409,6 +424,11 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
 #pragma unroll
             for (int jj = 0; jj < 32; jj += 4) gate_mfma4<RG>(acc, arow + jj, hrow + 32 + jj, dgs);
             __builtin_amdgcn_wave_barrier();
+            float4 ph = make_float4(1.f, 0.f, 1.f, 0.f);
+            if (TURN) {
+                ph = *reinterpret_cast<const float4 *>(turn);
+                turn += 128;
+            }
 #pragma unroll
             for (int q = 0; q < RG; ++q) {
                 const int r = r_base + 4 * q + jrow;
@@ -418,8 +438,8 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
                 gate_store_bin(&v0, acc[q][0] + bias4.x, acc[q][1] + bias4.y, mbias != nullptr, mb2.x);
                 gate_store_bin(&v1, acc[q][2] + bias4.z, acc[q][3] + bias4.w, mbias != nullptr, mb2.y);
                 if (TURN) {
-                    v0 = gate_turn(v0, n4 >> 1, n_fft, phase);
-                    v1 = gate_turn(v1, (n4 >> 1) + 1, n_fft, phase);
+                    v0 = cmul(v0, make_float2(ph.x, ph.y));
+                    v1 = cmul(v1, make_float2(ph.z, ph.w));
                 }
                 g[(size_t)bh * F + (n4 >> 1)] = v0;
                 if (e_ok2) g[(size_t)bh * F + (n4 >> 1) + 1] = v1;
@@ -454,6 +474,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
         }
         // epilogue: this lane holds reals n4 .. n4+3 (two bins) of row r for every row group
         const int n4 = tile * 64 + (lane & ~3);
+        float2 ph[2] = {};
+        if (TURN) {
+            ph[0] = turn[0];
+            ph[1] = turn[1];
+            turn += 128;
+        }
 #pragma unroll
         for (int q = 0; q < RG; ++q) {
             const int r = r_base + 4 * q + jrow;
@@ -467,7 +493,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
                 float2 v;
                 gate_store_bin(&v, acc[q][2 * half] + b2[(size_t)hp * twoF + nn], acc[q][2 * half + 1] + b2[(size_t)hp * twoF + nn + 1],
                                mbias != nullptr, mbias ? mbias[(size_t)hp * F + k] : 0.0f);
-                g[(size_t)bh * F + k] = TURN ? gate_turn(v, k, n_fft, phase) : v;
+                g[(size_t)bh * F + k] = TURN ? cmul(v, ph[half]) : v;
             }
         }
     }
@@ -622,11 +648,10 @@ __global__ __launch_bounds__(256) void k_gate_toeplitz(const float2 *__restrict_
 
 // positional phase: g[bh][k] *= exp(+j 2 pi ((k p) mod n)/n), angle reduced in integers and
 // evaluated in fp64.  One lane per gate entry; only launched when p != 0.
-__global__ __launch_bounds__(256) void k_gate_phase(float2 *__restrict__ g, int F, int n_fft, long long phase,
-                                                    size_t total) {
+__global__ __launch_bounds__(256) void k_gate_phase(float2 *__restrict__ g, int F, GatePhase phase, size_t total) {
     const size_t idx = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (idx >= total) return;
-    g[idx] = gate_turn(g[idx], (long long)(idx % F), n_fft, phase);
+    g[idx] = cmul(g[idx], gate_phase((unsigned)(idx % F), phase));
 }
 
 // ------------------------------------------------------------------------------------------
@@ -696,6 +721,10 @@ hipError_t launch_gate_prep(const double *partial, int nchunks, const float *Wq,
 }
 
 // Toeplitz update and positional phase, the passes over g behind the output layer.
+static GatePhase gate_phase_of(const GateDev &P, long long phase) {
+    return {(unsigned)(phase % P.n_fft), (unsigned)P.n_fft, 1.0 / (double)P.n_fft};
+}
+
 static hipError_t launch_gate_tail(const GateDev &P, const float2 *raw, int B, int H, long long phase, float2 *g,
                                    hipStream_t st) {
     const int F = P.n_fft / 2 + 1;
@@ -707,7 +736,7 @@ static hipError_t launch_gate_tail(const GateDev &P, const float2 *raw, int B, i
         if (e != hipSuccess) return e;
     }
     if (phase == 0) return hipSuccess;
-    k_gate_phase<<<(unsigned)((total + 255) / 256), 256, 0, st>>>(g, F, P.n_fft, phase, total);
+    k_gate_phase<<<(unsigned)((total + 255) / 256), 256, 0, st>>>(g, F, gate_phase_of(P, phase), total);
     return hipGetLastError();
 }
 
@@ -775,17 +804,17 @@ hipError_t launch_gate_out(const float *hid, const GateDev &P, float2 *raw, int 
     const int gy = P.Hg == 1 ? 1 : H;
     int gx = (4096 + gy - 1) / gy;                 // about 16 workgroups per compute unit in total (1024: 5 % slower)
     if (gx > (ntiles + 3) / 4) gx = (ntiles + 3) / 4;
-    {   // shrink the grid to the smallest one with the same number of tiles per wave (no ragged last round)
-        const int iters = (ntiles + 4 * gx - 1) / (4 * gx);
-        gx = (ntiles + 4 * iters - 1) / (4 * iters);
-    }
+    // shrink the grid to the smallest one with the same number of tiles per wave (no ragged last round)
+    const int rounds = (ntiles + 4 * gx - 1) / (4 * gx);
+    gx = (ntiles + 4 * rounds - 1) / (4 * rounds);
     dim3 grid(gx, gy);
     const bool vec = (P.d_g % 4 == 0) && (reinterpret_cast<uintptr_t>(P.W2) & 15) == 0;
     const int dgp = (P.d_g + 3) & ~3;
     // with the Toeplitz update the MLP output goes to `raw` un-activated and a second pass finishes it
     const float *out_bias = P.toeplitz ? nullptr : P.modrelu_bias;
     float2 *out_g = P.toeplitz ? raw : g;
-    const bool turn = phase != 0 && !P.toeplitz;
+    // the phase of a wave's tiles takes 1 KB of LDS a round; beyond 16 rounds (hundreds of heads with long gates) it is a pass of its own
+    const bool turn = phase != 0 && !P.toeplitz && rounds <= 16;
     {
         // every tile of the rows in one launch (grid.z); a single tile takes the narrowest kernel that fits
         // rows per tile: 32, fewer while the launch would have less than four workgroups per compute unit (B=256 H=12
@@ -801,16 +830,17 @@ hipError_t launch_gate_out(const float *hid, const GateDev &P, float2 *raw, int 
         const int rows = (ntile > 1) ? per : M;
         const int rg = (rows + 3) / 4;            // 1..8 row groups per tile
         const size_t lds = ((size_t)4 * (rg <= 1 ? 1 : rg <= 2 ? 2 : rg <= 4 ? 4 : 8) * (dgp + 4) +
-                            4 * 64 * ((vec && P.d_g == 64) ? kHalfStride : kTileStride)) * sizeof(float);
+                            4 * 64 * ((vec && P.d_g == 64) ? kHalfStride : kTileStride)) * sizeof(float) +
+                           (turn ? rounds * 128 * sizeof(float2) : 0);
         for (int z0 = 0; z0 < ntile; z0 += 65535) {
             const int nz = (ntile - z0 < 65535) ? ntile - z0 : 65535;
             const dim3 grid3(grid.x, grid.y, nz);
             const int r_base = per * z0;
 #define SPECTRE_GATE_OUT(V, R)                                                                                              \
     if (turn) k_gate_out<V, R, true><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F, r_base, \
-                                                              P.n_fft, phase);                                               \
+                                                              rounds, gate_phase_of(P, phase));                              \
     else k_gate_out<V, R, false><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F, r_base,     \
-                                                          P.n_fft, phase)
+                                                          rounds, gate_phase_of(P, phase))
             if (vec) {
                 if (rg <= 1) { SPECTRE_GATE_OUT(true, 1); } else if (rg <= 2) { SPECTRE_GATE_OUT(true, 2); }
                 else if (rg <= 4) { SPECTRE_GATE_OUT(true, 4); } else { SPECTRE_GATE_OUT(true, 8); }

@@ -192,3 +192,27 @@ def test_gate_of_many_heads_and_of_large_weights(oracle, B, H, n, d, dg, Hg):
     sq = np.random.default_rng(84).standard_normal((B, H, d)) * 40.0
     got = binding.gate(torch.from_numpy(sq).cuda(), binding.GateParams(p), 1.0 / n, pooled=True).cpu().numpy()
     assert rel_l2(got, oracle.gate(sq, 1.0 / n, f64(p), n, 0)) <= 1e-5
+
+
+@pytest.mark.parametrize("B,H,Hg,n,dg", [(1, 1, 1, 256, 64), (5, 2, 2, 8192, 64), (12, 3, 3, 2560, 64), (7, 20, 1, 4096, 64),
+                                         (2, 32, 32, 65536, 64), (3, 4096, 4096, 2048, 64), (1, 4096, 4096, 4096, 64),
+                                         (6, 3, 3, 1792, 37), (33, 1, 1, 768, 100), (1, 2, 2, 21, 64)])
+def test_positional_phase_turns_the_gate(B, H, Hg, n, dg):
+    """The gate with a position against the gate without one, turned in 64 bits: every number of row groups per tile, one and
+    several tiles per wave, and so many (17: 4096 heads of 4096 points) that the phase is a pass of its own; positions below and
+    far above n.  The turn is one fp32 complex product with a factor rounded once: 3 * 2^-24 of the bin at most, twice that
+    here."""
+    from paper_2502_18394_amd import binding
+    F, s = n // 2 + 1, 0.02
+    gen = torch.Generator(device="cuda").manual_seed(n + H)
+    r = lambda *shape: torch.randn(shape, generator=gen, device="cuda") * s
+    P = binding.GateParams(dict(n_fft=n, ln_eps=synth.LN_EPS, ln_gamma=1 + r(Hg, 64), ln_beta=r(Hg, 64), W1=r(Hg, 64, dg),
+                                b1=r(Hg, dg), W2=r(Hg, dg, 2 * F), b2=r(Hg, 2 * F), modrelu_bias=r(Hg, F)))
+    q = 30 * torch.randn((B, H, 64), generator=gen, device="cuda", dtype=torch.float64)
+    plain = binding.gate(q, P, 1.0 / n, pooled=True).to(torch.complex128)
+    for p in (1, n // 2 + 1, n, 10**12 + 7):
+        print(f"case B={B} H={H} Hg={Hg} n={n} dg={dg} p={p}", flush=True)
+        g = binding.gate(q, P, 1.0 / n, pooled=True, phase_pos=p).to(torch.complex128)
+        angle = (torch.arange(F, device="cuda") * (p % n) % n).double() * (2 * np.pi / n)
+        err = (g - plain * torch.polar(torch.ones_like(angle), angle)).abs()
+        assert bool((err <= 6 * 2.0 ** -24 * plain.abs()).all())
