@@ -846,6 +846,9 @@ hipError_t launch_sweep_lazy(bool flush, bool read, float2 *X, const float *pend
         k_sweep_lazy<<<grid, 256, 0, st>>>(X4, tw, g, partial, kpart, F, N, BH, slot_new, ps, nch);
         return hipGetLastError();
     }
+    // Always by k_append_fold where it can be, for the smaller error (16 tokens 1.67e-7 -> 1.36e-7).  k_flush_mfma would be faster
+    // with up to 8 tokens in spectra of 30 to 70 MB (B=8 H=32 N=512 18.0 us, fold 19.9; B=4 N=2048 31.1 and 33.2) and up to 16
+    // on one head of N = 131072, whose 16 bins lie 4 MB apart (17.3 and 23.6).
     bool consecutive = npend > 0;                          // as roots of order N see the slots, i.e. modulo N
     for (int i = 1; i < npend; ++i) consecutive = consecutive && slots[i] == (slots[i - 1] + 1) % N;
     if (consecutive) {
@@ -908,10 +911,12 @@ hipError_t launch_set_memory(const float *mem, int mem_batch, float *v_buf, int 
 }
 
 // Tokens per workgroup: 256, halved (down to 16, and to no more partial sums than the pooling pass of T rows has) while the
-// launch would have less than eight workgroups per compute unit.
+// launch would have less than two workgroups per compute unit: every chunk's sums are read back by a few workgroups, and with
+// four times the chunks that costs more than the shorter chunks save (to 512 / 1024 / 2048 workgroups: prompts of 13653 tokens
+// into 4 heads of N = 20480 36 / 39 / 43 us, 10922 into 4 of 32768 40 / 41 / 46, 85 into 512 of 256 38 / 39 / 41.5).
 int ring_append_rows(int B, int T, int H) {
     int rows = kPoolRows;
-    while (rows > pool_rows(B, T, H, 64) && (long long)B * H * ((T + rows - 1) / rows) < 2048) rows /= 2;
+    while (rows > pool_rows(B, T, H, 64) && (long long)B * H * ((T + rows - 1) / rows) < 512) rows /= 2;
     return rows;
 }
 
