@@ -54,9 +54,9 @@ def run_layer(oracle, B, L, H, io, J, seed, Hw=None):
     return from_device(out), from_device(ref), want
 
 
-# four-step lengths, bf16 rows: the fused route.  N1 = 256 and 4096, even and odd N2 (3 * 256: 48 tile rows, a ragged
-# last group of the matrix-core prologue), one and several head groups, shared projection weights, refinement depths
-# below and above the 8 levels a tile holds.
+# bf16 rows on the four-step route, where the row transforms project: columns of 256, 1024 and 4096 points, one and several head
+# groups, shared projection weights, refinement depths below and above the 8 levels a tile holds (an odd number of rows per
+# lane, and with it a ragged last group of the matrix-core prologue: the many heads of 1792 points below; 768 runs in LDS).
 @pytest.mark.parametrize("B,L,H,J,Hw", [(1, 8192, 8, None, None), (2, 8192, 3, 13, None), (1, 16384, 5, 6, None),
                                          (1, 768, 2, 8, None), (1, 12288, 2, 12, 1), (1, 32768, 4, 15, None),
                                          (1, 131072, 2, 17, None), (3, 2560, 2, 9, None), (1, 7168, 1, None, 1)])
@@ -82,6 +82,37 @@ def test_layer_on_the_other_routes_matches_oracle_chain(oracle, B, L, H, io, J):
     print(f"  vs oracle chain {err:.3e}  identical to separate calls {np.array_equal(got, ref)}", flush=True)
     assert err <= (TOL["bf16"] if io == "bf16" else 2e-5)     # fp32: the gate's 1e-5 bar and the mixer's, chained
     assert np.array_equal(got, ref)                           # the very same kernels in the same order
+
+
+@pytest.mark.parametrize("B,L,H,J", [(18, 1792, 32, None), (19, 1792, 31, 8), (32, 2048, 16, 11), (19, 2048, 28, 11)])
+def test_layer_of_many_heads_of_1792_and_2048_points(oracle, B, L, H, J):
+    """bf16 rows on both sides of 2^20 positions, from which these lengths take the projecting row transforms: 16 * 7 tile rows at
+    1792 points, no multiple of the 32 of a matrix instruction.  Sampled heads against the oracle chain, and the whole against
+    the separate calls."""
+    from paper_2502_18394_amd import binding
+    print(f"case B={B} L={L} H={H} J={J}", flush=True)
+    d, seed = 64, synth.BASE_SEED + 730 + L + H
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    x = torch.randn((B, L, H, d), generator=gen, device="cuda").bfloat16()
+    rng = np.random.default_rng(seed + 1)
+    Wq, Wv = ((0.125 * rng.standard_normal((H, d, d))).astype(np.float32) for _ in range(2))
+    p, wp = synth.gate_params(seed + 2, H, d, L), synth.wrm_params(seed + 3, H, d, J) if J is not None else None
+    P, W = binding.GateParams(p), binding.WrmParams(wp) if wp is not None else None
+    Wq_d, Wv_d = torch.from_numpy(Wq).cuda(), torch.from_numpy(Wv).cuda()
+    out = binding.layer_forward(x, Wq_d, Wv_d, P, W)
+    v, _, sq = binding.project(x, Wq_d, Wv_d)
+    ref = binding.mix_forward(v, binding.gate(sq, P, 1.0 / L, pooled=True))
+    if W is not None:
+        ref = binding.wrm_apply(ref, binding.wrm_gates(sq, W, 1.0 / L, pooled=True))
+    e_ref = float(torch.linalg.vector_norm(out.float() - ref.float()) / torch.linalg.vector_norm(ref.float()))
+    print(f"  vs separate calls {e_ref:.3e}", flush=True)
+    assert e_ref <= 2e-3                                       # bf16 steps of the rows, from sums in another order
+    one = lambda q, h: {k: (a[h:h + 1] if isinstance(a, np.ndarray) else 1 if k == "Hg" else a) for k, a in q.items()}
+    for b, h in ((0, 0), (B - 1, H - 1), (B // 2, H // 2)):
+        rows = x[b:b + 1, :, h:h + 1].float().cpu().numpy().astype(np.float64)
+        want = oracle_chain(oracle, rows, Wq[h:h + 1].astype(np.float64), Wv[h:h + 1].astype(np.float64), f64(one(p, h)),
+                            f64(one(wp, h)) if wp is not None else None, J)
+        assert rel_l2(from_device(out[b:b + 1, :, h:h + 1].contiguous()), want) <= TOL["bf16"]
 
 
 def test_layer_of_many_heads(oracle):

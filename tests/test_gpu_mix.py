@@ -117,9 +117,9 @@ def test_head_groups_of_any_size_give_the_same_rows(oracle, options, B, H, mb, o
 @pytest.mark.parametrize("io", ["f32", "bf16"])
 @pytest.mark.parametrize("B,H", [(64, 8), (43, 12), (171, 3)])
 def test_patch_grid_length_with_many_heads_takes_its_own_kernel(oracle, options, B, H, io):
-    """L = 196 (14 x 14 patches) with at least 512 heads runs a variant of the in-LDS kernel whose length and radices
-    (14, 14) are compile-time constants and whose workgroups are seven waves on a whole head.  Same passes, same
-    arithmetic as the general kernel (the compile-time-length option, switched off, forces that one): both must match the oracle and each other."""
+    """L = 196 (14 x 14 patches) with many heads: the compile-time form of the in-LDS kernel for many heads against the general
+    kernel (the compile-time option, switched off, forces that one).  Both must match the oracle and, to the rounding of two fp32
+    transforms, each other."""
     L = 196
     seed = synth.BASE_SEED + 19 * H + B
     from paper_2502_18394_amd import binding
@@ -131,10 +131,9 @@ def test_patch_grid_length_with_many_heads_takes_its_own_kernel(oracle, options,
     assert e1 <= TOL[io] and e2 <= TOL[io] and e12 <= (1e-6 if io == "f32" else 2e-3)
 
 
-@pytest.mark.parametrize("B,L,H,io", [(1, 8192, 8, "f32"), (2, 7168, 12, "bf16"), (1, 6144, 16, "bf16"), (1, 12288, 8, "f32"),
-                                       (3, 5120, 8, "bf16")])
+@pytest.mark.parametrize("B,L,H,io", [(1, 8192, 8, "f32"), (2, 7168, 12, "bf16"), (1, 6144, 16, "bf16"), (3, 5120, 8, "bf16")])
 def test_head_affine_placement_changes_no_bit(oracle, options, B, L, H, io):
-    """Four-step lengths up to 12288 with a multiple of 8 heads in a call place every workgroup of a head on one XCD
+    """Four-step lengths up to 8192 with a multiple of 8 heads in a call place every workgroup of a head on one XCD
     and walk the heads up, down, up through the three kernels (L2 reuse).  It is only a renumbering of workgroups:
     the rows must equal those of the plain numbering (head-affine option off) bit for bit, and match the oracle."""
     seed = synth.BASE_SEED + 23 * H + L
@@ -145,6 +144,46 @@ def test_head_affine_placement_changes_no_bit(oracle, options, B, L, H, io):
     err = rel_l2(got, want)
     print(f"case B={B} L={L} H={H} io={io}: rel_l2 {err:.3e} identical {np.array_equal(got, plain)}", flush=True)
     assert err <= TOL[io] and np.array_equal(got, plain)
+
+
+@pytest.mark.parametrize("B,H,io", [(1, 8, "f32"), (2, 8, "bf16")])
+def test_head_affine_placement_of_4096_point_columns_changes_no_bit(oracle, options, B, H, io):
+    """The same at 12288 points on 4096-point columns, which mix_forward_static takes there (mix_forward has 1024-point ones)."""
+    from paper_2502_18394_amd import binding
+    L = 12288
+    print(f"case B={B} H={H} io={io}", flush=True)
+    vals, store = synth.tokens(synth.BASE_SEED + 24 * H + B, (B, L, H, 64), io)
+    gate = synth.random_gate(synth.BASE_SEED + 25, B, H, L)
+    v, g = to_device(vals, store, io), torch.from_numpy(gate).cuda()
+    got = from_device(binding.mix_forward_static(v, g))
+    options(binding.OPT_HEAD_AFFINE, 0)
+    plain = from_device(binding.mix_forward_static(v, g))
+    assert np.array_equal(got, plain)
+    assert rel_l2(got, oracle.mix_forward(vals.astype(np.float64), gate.astype(np.complex128))) <= TOL[io]
+
+
+@pytest.mark.parametrize("L,most", [(1792, 585), (2048, 512)])
+def test_bf16_rows_beyond_the_memory_side_cache_take_the_four_step_kernels(oracle, L, most):
+    """bf16 rows of 1792 and 2048 points: the largest call in LDS (2^20 positions) and the first on the four-step route.  Other
+    kernels, so not the same bits, but the same rows to a bf16 step; the first and the last head against the oracle.  fp32 rows
+    stay in LDS: the same bits on both sides."""
+    from paper_2502_18394_amd import binding
+    print(f"case L={L} most={most}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    v = torch.randn((1, L, most + 1, 64), generator=gen, device="cuda")
+    g = torch.view_as_complex(torch.randn((1, most + 1, L // 2 + 1, 2), generator=gen, device="cuda"))
+    f32 = binding.mix_forward(v, g)
+    assert torch.equal(binding.mix_forward(v[:, :, :most].contiguous(), g[:, :most].contiguous()), f32[:, :, :most])
+    v = v.bfloat16()
+    many = binding.mix_forward(v, g)
+    few = binding.mix_forward(v[:, :, :most].contiguous(), g[:, :most].contiguous())
+    assert not torch.equal(many[:, :, :most], few)
+    diff = torch.linalg.vector_norm(many[:, :, :most].float() - few.float()) / torch.linalg.vector_norm(few.float())
+    assert float(diff) <= 2e-3
+    for out, h in ((few, 0), (few, most - 1), (many, 0), (many, most)):
+        want = oracle.mix_forward(v[:, :, h:h + 1].float().cpu().numpy().astype(np.float64),
+                                  g[:, h:h + 1].cpu().numpy().astype(np.complex128))
+        assert_close_elementwise(from_device(out[:, :, h:h + 1].contiguous()), want, "bf16", L)
 
 
 @pytest.mark.parametrize("B,L,H,io", [(1, 7168, 8, "bf16"), (2, 2048 * 3, 3, "f32"), (1, 16384, 5, "f32"), (1, 131072, 2, "bf16")])
