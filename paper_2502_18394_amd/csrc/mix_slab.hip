@@ -511,10 +511,11 @@ static bool mix_ct(int L, const void *v, const float2 *g, void *out, const float
     constexpr int kSimds = 1024;
     const long long heads = (long long)B * H;
     // Rows that will not be found in the memory-side cache again pass it by, where a workgroup's piece of a row is whole
-    // 128-byte lines (fp32, L = 196, H = 12: B = 256 71 -> 68 us, 128 38 -> 36, but 64 19.6 -> 20.3; 256 at B = 256 86 -> 80,
-    // bf16 53 -> 49).
-    const bool stream = 64 * heads * rows * (long long)sizeof(typename IO::pair_t) > 100000000 &&
-                        ((reinterpret_cast<uintptr_t>(v) | reinterpret_cast<uintptr_t>(out)) & 127) == 0;
+    // 128-byte lines (fp32, H = 12, us: L = 196, B = 256 67.7 -> 62.1, 128 35.4 -> 34.0, but 64 16.5 -> 17.6; 256 at B = 256 86 -> 80,
+    // bf16 53 -> 49).  fp32 rows of 196 go by whole heads from there on (half / whole heads, B = 64 16.5 / 17.6, 256 64.3 / 62.1,
+    // 1300 315 / 296).
+    const bool large = 64 * heads * rows * (long long)sizeof(typename IO::pair_t) > 100000000;
+    const bool stream = large && ((reinterpret_cast<uintptr_t>(v) | reinterpret_cast<uintptr_t>(out)) & 127) == 0;
 #define SPECTRE_CT(PP, NT, R0, R1, R2, ...)                                                                             \
     {                                                                                                                   \
         *e = mix_ct_t<IO, PP, NT, R0, R1, R2, __VA_ARGS__>(v, g, out, roots, B, H, rows, st);                           \
@@ -535,8 +536,8 @@ static bool mix_ct(int L, const void *v, const float2 *g, void *out, const float
             else SPECTRE_CT_LINES(16, 192, 12, 12, 1)
         case 196:
             SPECTRE_CT_FEW(4, 64, 14, 14, 1)
-            if constexpr (bf) SPECTRE_CT_LINES(32, 448, 14, 14, 1)
-            else SPECTRE_CT_LINES(16, 256, 14, 14, 1)
+            if (!bf && !large) SPECTRE_CT(16, 256, 14, 14, 1, false)
+            SPECTRE_CT_LINES(32, 448, 14, 14, 1)
         case 256:
             SPECTRE_CT_FEW(4, 128, 8, 8, 4)
             if constexpr (bf) SPECTRE_CT_LINES(32, 512, 16, 16, 1)

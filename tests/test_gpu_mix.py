@@ -285,6 +285,29 @@ def test_forms_for_few_and_for_many_heads(oracle, options, L, most, io):
         assert_close_elementwise(got[:, :, :1], want, io, L)
 
 
+@pytest.mark.parametrize("io", ["f32", "bf16"])
+@pytest.mark.parametrize("L", [144, 196, 256])
+def test_patch_grids_whose_rows_pass_the_caches_by(oracle, L, io):
+    """More than 100 MB in and out: rows on a 128-byte boundary bypass the caches, others do not, fp32 rows of 196 also change
+    the pairs per workgroup.  All the same bits as a part of the heads below that size; first and last head against the oracle."""
+    from paper_2502_18394_amd import binding
+    B, H = -(-120_000_000 // (L * 12 * 256 * (2 if io == "f32" else 1))), 12
+    print(f"case B={B} L={L} H={H} io={io}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    v = torch.randn((B, L, H, 64), generator=gen, device="cuda").to(torch.float32 if io == "f32" else torch.bfloat16)
+    g = torch.view_as_complex(torch.randn((B, H, L // 2 + 1, 2), generator=gen, device="cuda"))
+    out = binding.mix_forward(v, g)
+    n = B // 3
+    assert torch.equal(binding.mix_forward(v[:n].contiguous(), g[:n].contiguous()), out[:n])
+    aside = torch.empty(v.numel() + 16, dtype=v.dtype, device="cuda")[16:].view(v.shape)
+    aside.copy_(v)
+    assert aside.data_ptr() % 128 != 0 and torch.equal(binding.mix_forward(aside, g, out=torch.empty_like(v)), out)
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        want = oracle.mix_forward(v[b:b + 1, :, h:h + 1].float().cpu().numpy().astype(np.float64),
+                                  g[b:b + 1, h:h + 1].cpu().numpy().astype(np.complex128))
+        assert_close_elementwise(from_device(out[b:b + 1, :, h:h + 1].contiguous()), want, io, L)
+
+
 @pytest.mark.parametrize("B,L,H,io", [(1, 12288, 3, "f32"), (1, 12288, 8, "bf16"), (1, 20480, 1, "f32"), (3, 24576, 3, "bf16"),
                                       (1, 28672, 2, "f32"), (1, 32768, 5, "bf16"), (1, 24576, 27, "f32")])
 def test_columns_of_1024_points(oracle, B, L, H, io):
