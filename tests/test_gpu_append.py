@@ -116,3 +116,21 @@ def test_rows_and_sums_need_no_more_than_the_alignment_of_an_element(T, io):
         states.append([c.prefix_fft, c.v_buf, c.q_buf, c.sum_q, out, g])
     for a, b in zip(*states):
         assert torch.equal(torch.view_as_real(a) if a.is_complex() else a, torch.view_as_real(b) if b.is_complex() else b)
+
+
+@pytest.mark.parametrize("N,T", [(2560, 1023), (2560, 1024), (2560, 2560), (3072, 2561)])
+def test_prompts_around_the_sizes_whose_query_rows_stay_cached(N, T):
+    """fp32 prompts of 64 and 160 MiB of query rows, and one token to the other side of either: ring buffers bit for bit, sums of
+    fp64 terms in another order, and the spectra of two heads in 64 bits (bound as in test_append)."""
+    from paper_2502_18394_amd import binding
+    B, H = 8, 32
+    print(f"case N={N} T={T}", flush=True)
+    gen = torch.Generator(device="cuda").manual_seed(T)
+    v, q = (torch.randn((B, T, H, 64), generator=gen, device="cuda") for _ in range(2))
+    c = binding.PrefixCache(B, H, 64, N)
+    c.update(v, q)
+    assert torch.equal(c.v_buf[:, :, :T], v.transpose(1, 2)) and torch.equal(c.q_buf[:, :, :T], q.transpose(1, 2))
+    assert not bool(c.v_buf[:, :, T:].any()) and not bool(c.q_buf[:, :, T:].any())
+    assert rel_l2(c.sum_q.cpu().numpy(), q.double().sum(1).cpu().numpy()) <= 1e-12
+    for b, h in ((0, 0), (B - 1, H - 1)):
+        assert rel_l2(c.prefix_fft[b, h].cpu().numpy(), np.fft.rfft(c.v_buf[b, h].cpu().numpy().astype(np.float64), axis=0)) <= 1e-5
