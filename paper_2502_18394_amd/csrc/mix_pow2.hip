@@ -445,7 +445,7 @@ __global__ __launch_bounds__(256) void k_big(typename SC::elem_t *__restrict__ s
 // What bounds it is that its three phases, memory, arithmetic, memory, do not overlap in the one workgroup a compute unit
 // holds: with the rows staged in LDS on both sides of three radix-16 passes, two columns at a time, 32 heads of bf16 rows took
 // 29.5 us (38 from cold caches) and 512 heads 543, now 27 (34) and 466; fp32 rows, 128 heads 116 -> 107; one head 22 -> 16.5.
-// The eight workgroups of a head share its rows; their ids are 8 apart, so they run on the same XCD and a row is
+// The workgroups of a head (eight, or sixteen of two pairs) share its rows; their ids are 8 apart, so they run on the same XCD and a row is
 // fetched into one L2.  (The same construction for L = 8192, two columns per pair, leaves room for only two pairs
 // per workgroup, i.e. 8-byte pieces of every row, and measured slower than the three kernels.)
 // CL adjacent pairs of a row at the alignment of an element, 16 bytes at most.
@@ -724,30 +724,37 @@ hipError_t launch_small_fwd(const Pow2Plan &pl, int io, const void *v, float2 *s
     SPECTRE_DISPATCH_N2(small_fwd_t, pl, v, scratch, rows, H, bh0, nbh, st, aff, ring)
 }
 
-template <int N2, int TT, typename IO, typename SC>
-static hipError_t small_fwd_proj_t(const Pow2Plan &pl, const void *x, const void *wpack, int Hw, void *scr_v, int rows,
-                                   int H, int bh0, int nbh, hipStream_t st, int aff) {
-    if constexpr (!std::is_same<IO, IoBf16>::value || !std::is_base_of<ScrF32, SC>::value) return hipErrorInvalidValue;
-    else {
+template <int N2, typename SC>
+static hipError_t small_fwd_proj_t(const Pow2Plan &pl, const void *x, const void *wpack, int Hw, float2 *scr, int rows, int H,
+                                   int bh0, int nbh, hipStream_t st, int aff) {
     const size_t lds = (size_t)N2 * 16 * TileStride<IoBf16>::value * sizeof(uint32_t);
     auto kern = k_small_fwd_proj<N2, SC>;
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
     const dim3 grid = aff ? dim3(pl.N1 / 16 * nbh) : dim3(pl.N1 / 16, nbh);
     kern<<<grid, dim3(512), lds, st>>>(static_cast<const uint32_t *>(x), static_cast<const uint4 *>(wpack), Hw,
-                                       static_cast<float2 *>(scr_v), pl.twL, rows, H, pl.N1, bh0, aff);
+                                       scr, pl.twL, rows, H, pl.N1, bh0, aff);
     return hipGetLastError();
-    }
 }
 
+// bf16 rows.  N2 >= 7: shorter lengths of a plan run in LDS.
 hipError_t launch_small_fwd_proj(const Pow2Plan &pl, const void *x, const void *wpack, int Hw, float2 *scratch, int rows,
                                  int H, int bh0, int nbh, hipStream_t st, bool affine) {
     if (affine && nbh % 8 != 0) return hipErrorInvalidValue;
     const int aff = affine ? nbh : 0;
-    const int io = 1;
-    const bool scr16 = false;
-    if (pl.N1 == 1024) SPECTRE_DISPATCH_FINE(small_fwd_proj_t, pl, x, wpack, Hw, scratch, rows, H, bh0, nbh, st, aff)
-    SPECTRE_DISPATCH_N2(small_fwd_proj_t, pl, x, wpack, Hw, scratch, rows, H, bh0, nbh, st, aff)
+    const bool fine = pl.N1 == 1024;
+#define SPECTRE_PROJ(N, SC) return small_fwd_proj_t<N, SC>(pl, x, wpack, Hw, scratch, rows, H, bh0, nbh, st, aff);
+#define SPECTRE_PROJ_CASE(N) case N: SPECTRE_PROJ(N, ScrF32)
+#define SPECTRE_PROJ_CASE_FINE(N) case N: if (fine) SPECTRE_PROJ(N, ScrF32Fine) SPECTRE_PROJ(N, ScrF32)
+    switch (pl.N2) {
+        SPECTRE_PROJ_CASE(7) SPECTRE_PROJ_CASE(8) SPECTRE_PROJ_CASE(10) SPECTRE_PROJ_CASE_FINE(12) SPECTRE_PROJ_CASE(14)
+        SPECTRE_PROJ_CASE_FINE(16) SPECTRE_PROJ_CASE_FINE(20) SPECTRE_PROJ_CASE_FINE(24) SPECTRE_PROJ_CASE_FINE(28)
+        SPECTRE_PROJ_CASE_FINE(32)
+        default: return hipErrorInvalidValue;
+    }
+#undef SPECTRE_PROJ_CASE_FINE
+#undef SPECTRE_PROJ_CASE
+#undef SPECTRE_PROJ
 }
 
 int small_tile_rows(int io) { (void)io; return 16; }
