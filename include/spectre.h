@@ -96,9 +96,9 @@ void spectre_shutdown(void);
 
 /*
  * Tuning switches for measurements and tests.  Process-wide, host-side, read at every call; they
- * must not change between a *_workspace_bytes query and the call it sizes.  None changes a result
- * (the same arithmetic in the same order; at most which of two kernels of identical arithmetic
- * runs, where tests compare the two).  value < 0 restores the default.
+ * must not change between a *_workspace_bytes query and the call it sizes.  FUSED_4096 and
+ * SLAB_COMPILE_TIME choose between transforms of other radices, whose results agree to fp32
+ * rounding (tests compare the two); the others change no bit.  value < 0 restores the default.
  *   SPECTRE_OPT_LANES              1 keeps every head group of a long spectre_mix_forward call on
  *                                  `stream`; 2 (default) alternates them with the helper stream
  *   SPECTRE_OPT_SCRATCH_MB         total transform scratch in flight, MiB (default 204: sized for
@@ -108,7 +108,8 @@ void spectre_shutdown(void);
  *   SPECTRE_OPT_SLAB_COMPILE_TIME  0 makes the in-LDS kernel take its run-time-length form also
  *                                  for the lengths that have a compile-time form (default 1)
  *   SPECTRE_OPT_HEAD_AFFINE        0 switches off the placement of all workgroups of a head on one
- *                                  XCD that four-step lengths up to 12288 use (default 1)
+ *                                  XCD that four-step lengths up to 8192 use, and spectre_mix_forward_static
+ *                                  up to 12288 (default 1)
  *   SPECTRE_OPT_LANE_SHUFFLES      1 makes the column kernel of the four-step route exchange values
  *                                  between the 16 lanes of a sub-transform with cross-lane (DPP) moves
  *                                  instead of through LDS (default 0: measured slower or equal)
@@ -250,7 +251,8 @@ int spectre_wrm_apply_coeff(const void *v, const void *s, void *out, int B, int 
  *
  *   v     [B, L, H, d] of dtype io        g    complex64 [B, H, F], F = L/2 + 1
  *   out   [B, L, H, d] of dtype io; must not overlap v (SPECTRE_EINVAL if it does)
- *   ws    scratch of at least spectre_mix_workspace_bytes(B, L, H, d, io) bytes, 256-byte aligned
+ *   ws    scratch of at least spectre_mix_workspace_bytes(B, L, H, d, io) bytes, 256-byte aligned; an upper bound: lengths
+ *         with a four-step plan that run in LDS (up to 2048) still ask for that plan's scratch and use none
  */
 size_t spectre_mix_workspace_bytes(int B, int L, int H, int d, spectre_dtype io);
 int spectre_mix_forward(const void *v, const void *g, void *out, int B, int L, int H, int d,
@@ -272,7 +274,8 @@ int spectre_mix_forward_ex(const void *v, const void *g, void *out, int B, int L
 /*
  * spectre_mix_forward_static - spectre_mix_forward for callers that cannot allocate or hand over a
  * workspace: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
- * Same arguments without `ws`, same result to rounding (same kernels; the roots of unity are
+ * Same arguments without `ws`, same result to rounding (always by the four-step kernels, on columns of 256 or 4096
+ * points, where spectre_mix_forward has others at L <= 2048, 4096 and 12288 .. 32768; the roots of unity are
  * evaluated on the device in fp64 at every call instead of being taken from spectre_prepare's tables,
  * which can differ in the last bit of a table entry).  All scratch - tables, expanded gate, transform
  * columns - lives in one array of spectre_mix_static_bytes() = 98 MiB that is part of the library's

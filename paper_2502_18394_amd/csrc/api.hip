@@ -537,7 +537,8 @@ size_t spectre_mix_workspace_bytes(int B, int L, int H, int d, spectre_dtype io)
     const int BH = B * H;
     const int route = mix_route(BH, L, d, io);
     if (route == 0) return 0;
-    // a length that also has a four-step plan keeps the size that asks for, except where few or short sequences never did
+    // a length that also has a four-step plan keeps the size that plan asks for, which sizes of buffers in callers' hands rely
+    // on, though the in-LDS kernel uses none of it; few or short sequences never asked for it
     int N1, N2, P;
     if (route == 1 && (!pow2_split(L, &N1, &N2, &P) || (L <= 512 && BH >= 256) || (long long)BH * L <= 65536)) return 256;
     if (route == 3) return chirp_layout(BH, L, d).total();
@@ -623,7 +624,7 @@ static int mix_four_step(const Pow2Plan &pl, const void *v, const float2 *g, voi
         const int lane = side ? (group & 1) : 0;
         hipStream_t ls = lane ? side->stream : st;
         float2 *scr = reinterpret_cast<float2 *>(scr_base + (size_t)lane * lane_bytes);
-        // short columns (L <= 12288): a head's scratch fits the 4 MB L2 of one XCD, see head_affine() in mix_pow2.hip;
+        // short columns (L <= 8192; 12288 with columns of 4096 points): a head's scratch fits the 4 MB L2 of one XCD, see head_affine() in mix_pow2.hip;
         // measured -7 % at L = 8192, -10 % at 4096 (three kernels), nothing or a loss from 16384 on
         const bool affine = !scr16 && pl.P != 0 && nbh % 8 == 0 && (size_t)L * (d / 2) * sizeof(float2) <= ((size_t)3 << 20) &&
                             option(SPECTRE_OPT_HEAD_AFFINE) != 0;

@@ -720,11 +720,11 @@ hipError_t launch_gate_prep(const double *partial, int nchunks, const float *Wq,
     return hipGetLastError();
 }
 
-// Toeplitz update and positional phase, the passes over g behind the output layer.
 static GatePhase gate_phase_of(const GateDev &P, long long phase) {
     return {(unsigned)(phase % P.n_fft), (unsigned)P.n_fft, 1.0 / (double)P.n_fft};
 }
 
+// Toeplitz update and positional phase, the passes over g behind the output layer.
 static hipError_t launch_gate_tail(const GateDev &P, const float2 *raw, int B, int H, long long phase, float2 *g,
                                    hipStream_t st) {
     const int F = P.n_fft / 2 + 1;
