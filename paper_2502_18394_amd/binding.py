@@ -101,17 +101,16 @@ def _dtype_code(t):
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
-def _dev(t, name):
-    if not (t.is_cuda and t.is_contiguous()):
-        raise ValueError(f"{name} must be a contiguous device tensor")
-    return ctypes.c_void_p(t.data_ptr())
-
-
 def _ptr(t, name):
-    """_dev for the functions whose argument types are declared."""
+    """Address of a contiguous device tensor, for the functions whose argument types are declared."""
     if not (t.is_cuda and t.is_contiguous()):
         raise ValueError(f"{name} must be a contiguous device tensor")
     return t.data_ptr()
+
+
+def _dev(t, name):
+    """The same for the others."""
+    return ctypes.c_void_p(_ptr(t, name))
 
 
 def _stream(stream):
