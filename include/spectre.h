@@ -275,7 +275,7 @@ int spectre_mix_forward_ex(const void *v, const void *g, void *out, int B, int L
  * spectre_mix_forward_static - spectre_mix_forward for callers that cannot allocate or hand over a
  * workspace: code under HIP graph capture, tight serving loops, harnesses that forbid hipMalloc.
  * Same arguments without `ws`, same result to rounding (always by the four-step kernels, on columns of 256 or 4096
- * points, where spectre_mix_forward has others at L <= 2048, 4096 and 12288 .. 32768; the roots of unity are
+ * points, where spectre_mix_forward has others at L <= 2048, 4096, 8192 and 12288 .. 32768; the roots of unity are
  * evaluated on the device in fp64 at every call instead of being taken from spectre_prepare's tables,
  * which can differ in the last bit of a table entry).  All scratch - tables, expanded gate, transform
  * columns - lives in one array of spectre_mix_static_bytes() = 98 MiB that is part of the library's

@@ -563,7 +563,8 @@ static int check_mix_args(const void *v, const void *g, const void *out, int B, 
 // rows of 16384 and 32768, whose error against 64 bits would grow by 1.9 and 0.4 % (all others' falls by 2 to 4 %, and the
 // rounding of bf16 rows hides it) and where they gain least (32 heads, 4096- and 1024-point columns, us: bf16 12288 107 and 95,
 // 20480 164 and 147, 24576 191 and 174, 28672 231 and 217, 32768 245 and 240; fp32 12288 120 and 111, 24576 214 and 212, 16384
-// 152 and 142, 32768 289 and 293).
+// 152 and 142, 32768 289 and 293).  fp32 rows of 24576 and 28672 beyond 32 heads stay for their smaller error: by head count it
+// is 5 % slower to 4 % faster there (24576, 64 heads 425 and 441, 72 heads 504 and 485).
 static int get_mix_plan(int L, spectre_dtype io, Pow2Plan *pl) {
     const int rc = get_pow2_plan(L, pl);
     int N1, N2;

@@ -208,7 +208,7 @@ __global__ __launch_bounds__(NT) void k_mix_slab(const typename IO::pair_t *__re
 // row of pairs spans them all).  After the forward passes value u of block blk (blk = u0, or u0 R1 + u1) holds bin
 // u0 + R0 (u1 + R1 u).
 // What bounds it is memory at the shortest lengths and the vector units (butterflies and LDS accesses) above.  Against the
-// general structure with compile-time lengths, us: B=256 H=12 L=196 bf16 52 -> 44 (fp32, at 4.7 TB/s, 71 -> 69); 2048 heads of
+// general structure with compile-time lengths, us: B=256 H=12 L=196 bf16 48.5 -> 40.8 (fp32, at 5.1 TB/s, 63.8 -> 61.6); 2048 heads of
 // bf16 rows at 256 47 -> 33, at 512 152 -> 92; 64 heads of fp32 at 1024 25 -> 13; 32 heads at 2048 30 -> 13; kernel alone for
 // one head of fp32 rows at 1024 10.1 -> 7.9, for 32 of bf16 at 512 9.4 -> 6.7.
 // DIRECT (few workgroups, where the chain of latencies counts and registers do not): every lane loads its factors and its
