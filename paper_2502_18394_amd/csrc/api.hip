@@ -1124,7 +1124,7 @@ int spectre_layer_forward(const void *x, const float *Wq, const float *Wv, int H
         if (e != hipSuccess) return fail_hip(e, "project");
     }
     const GateDev gd = gate_dev(P);
-    e = launch_gate_prep(partial, y.fused ? pool_chunks(B, L, H, d) : project_chunks(L), Wq, Hw, W ? sum_q : nullptr,
+    e = launch_gate_prep(partial, y.fused ? pool_chunks((int)io, B, L, H, d) : project_chunks(L), Wq, Hw, W ? sum_q : nullptr,
                          1.0 / (double)L, gd, hid, B, H, st);
     if (e != hipSuccess) return fail_hip(e, "gate_prep");
     e = launch_gate_out(hid, gd, raw, B, H, 0, g, st);

@@ -28,9 +28,9 @@ hipError_t launch_pool(int io, const void *q, double *partial, double *sum_q, in
 hipError_t launch_pool_final(const double *partial, double *sum, int B, int row, int nchunks, hipStream_t st,
                              bool accumulate = false);
 
-// The two halves of launch_pool: partial [B][pool_chunks][H*d], one workgroup's sums of pool_rows rows each.
+// The two halves of launch_pool: partial [B][pool_chunks][H*d]; pool_rows is the least number of rows a chunk stands for.
 int pool_rows(int B, int L, int H, int d);
-int pool_chunks(int B, int L, int H, int d);
+int pool_chunks(int io, int B, int L, int H, int d);
 hipError_t launch_pool_partial(int io, const void *q, double *partial, int B, int L, int H, int d, hipStream_t st);
 
 // hid [B,H,d_g] from partial sums [B][nchunks][H*d] of the query rows, or (Wq != nullptr, d = 64) of the rows X that

@@ -3,7 +3,7 @@
 //
 //   pool    : sum of the query rows over positions, accumulated in fp64 in a fixed order (short sequences: one kernel
 //             for everything, k_gate_small)
-//   prep    : x = inv_count * sum;  qbar = LayerNorm(x);  hid = GELU(qbar W1 + b1)
+//   prep    : x = inv_count * sum;  qbar = LayerNorm(x);  hid = GELU(qbar W1 + b1); inside `out` where that has few workgroups
 //   out     : u = W2 hid + b2 on the matrix cores (fp32 MFMA, v_mfma_f32_4x4x1_16B_f32: 64
 //             output reals x 4 rows per instruction), with bias and modReLU in the epilogue
 //   phase   : the positional phase, when a position is given: in the epilogue of `out`, or a separate pass over g (k_gate_small, the
@@ -93,6 +93,63 @@ __global__ __launch_bounds__(256) void k_pool_partial_x16(const uint4 *__restric
     double *dst = partial + ((size_t)b * nchunks + chunk) * ((size_t)NCH * ppv) + (size_t)NCH * pi;
 #pragma unroll
     for (int i = 0; i < NCH; i += 2) *reinterpret_cast<double2 *>(dst + i) = make_double2(s[i], s[i + 1]);
+}
+
+// The same for short sequences of rows of whole 128-byte lines: 512 lanes take COLS adjacent pieces of 512 / COLS rows at a
+// time, so that a chunk of the partial sums stands for 64 to 256 rows where whole rows on so many compute units leave 16, and
+// what adds the chunks up reads a sixteenth (32 heads of 8192 bf16 rows: 32 chunks for 512, and with the hidden layer inside
+// the output layer's launch the gate takes 22 instead of 30 us).
+template <bool BF16, int COLS>
+__global__ __launch_bounds__(512) void k_pool_deep(const void *__restrict__ q, double *__restrict__ partial, int L, int ppv,
+                                                   int R, int nchunks) {
+    constexpr int NCH = BF16 ? 8 : 4, GRP = 512 / COLS, kU = 8;          // channels per 16 bytes, rows at a time, in flight
+    typedef unsigned int u32x4_a4 __attribute__((ext_vector_type(4), aligned(4)));   // the same sums at any alignment
+    __shared__ double red[8][COLS * NCH];
+    const int tid = threadIdx.x, col = tid % COLS, grp = tid / COLS;
+    const int chunk = blockIdx.y, b = blockIdx.z, l1 = min(L, (chunk + 1) * R);
+    int l = chunk * R + grp;
+    const u32x4_a4 *src = static_cast<const u32x4_a4 *>(q) + ((size_t)b * L + l) * ppv + (size_t)blockIdx.x * COLS + col;
+    double s[NCH];
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) s[i] = 0.0;
+    for (; l < l1; l += GRP * kU) {
+        u32x4_a4 w[kU];
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+            w[u] = u32x4_a4{0, 0, 0, 0};
+            if (l + GRP * u < l1) w[u] = __builtin_nontemporal_load(src + (size_t)(GRP * u) * ppv);
+        }
+#pragma unroll
+        for (int u = 0; u < kU; ++u) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                if (BF16) {
+                    const float2 v = IoBf16::unpack(w[u][i]);
+                    s[(2 * i) % NCH] += (double)v.x;
+                    s[(2 * i + 1) % NCH] += (double)v.y;
+                } else {
+                    s[i] += (double)__uint_as_float(w[u][i]);
+                }
+            }
+        }
+        src += (size_t)(GRP * kU) * ppv;
+    }
+#pragma unroll
+    for (int off = COLS; off < 64; off <<= 1) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) s[c] += __shfl_xor(s[c], off);
+    }
+    if ((tid & 63) < COLS) {
+#pragma unroll
+        for (int c = 0; c < NCH; ++c) red[tid >> 6][NCH * col + c] = s[c];
+    }
+    __syncthreads();
+    if (tid < COLS * NCH) {
+        double t = red[0][tid];
+#pragma unroll
+        for (int r = 1; r < 8; ++r) t += red[r][tid];
+        partial[(((size_t)b * nchunks + chunk) * ppv + (size_t)blockIdx.x * COLS) * NCH + tid] = t;
+    }
 }
 
 // pool, stage 2: sum_q[b][ch] = sum over chunks.  grid (row/32, B); 256 lanes = 32 channels x 8
@@ -333,16 +390,95 @@ __device__ __forceinline__ void gate_store_bin(float2 *dst, float re, float im, 
     *dst = make_float2(re, im);
 }
 
+struct GatePrep {                // the hidden layer's operands where k_gate_out forms it itself
+    const double *partial;       // [B][nchunks][H*64]
+    int nchunks;
+    double inv_count;
+    const float *ln_gamma, *ln_beta, *W1, *b1;
+    float ln_eps;
+};
+
+// Hidden layer of the M <= 4 rows of one weight set by one workgroup of 256 lanes (d = d_g = 64): pooled sums (fp64, fixed
+// order), LayerNorm with fp64 statistics, first layer, GELU.  hs [4][dgs] receives the rows; buf is scratch of 17 KB.
+__device__ __forceinline__ void gate_hidden_rows(float *hs, int dgs, double *buf, const GatePrep &pr, int H, int Hg, int hsel,
+                                                 int M) {
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, hp = (Hg == 1) ? 0 : hsel;
+    double *s_sum = buf;                                             // [row][wave][channel]
+    float *s_qb = reinterpret_cast<float *>(buf + 4 * 4 * 64);       // [row][channel]
+    float *s_part = s_qb + 4 * 64;                                   // [row][input / 8][hidden unit]
+    const float gam = pr.ln_gamma[hp * 64 + lane], bet = pr.ln_beta[hp * 64 + lane], b1 = pr.b1[hp * 64 + lane];
+    const size_t row = (size_t)H * 64;
+    auto sums_of = [&](int r) {
+        const int b = (Hg == 1) ? r / H : r, h = (Hg == 1) ? r % H : hsel;
+        return pr.partial + (size_t)b * pr.nchunks * row + (size_t)h * 64 + lane;
+    };
+    double x = 0.0;
+    if (pr.nchunks == 1) {                                           // sums already: a wave takes its row
+        if (wave < M) x = *sums_of(wave);
+    } else {
+#pragma unroll 1
+        for (int r = 0; r < M; ++r) {
+            const double *src = sums_of(r);
+            double t = 0.0;
+            int c = wave;
+            for (; c + 28 < pr.nchunks; c += 32) {                   // eight loads in flight, added in chunk order
+                double v[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) v[i] = src[(size_t)(c + 4 * i) * row];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) t += v[i];
+            }
+            for (; c < pr.nchunks; c += 4) t += src[(size_t)c * row];
+            s_sum[(r * 4 + wave) * 64 + lane] = t;
+        }
+        __syncthreads();
+        if (wave < M) {
+            const double *t = s_sum + wave * 256 + lane;
+            x = (t[0] + t[64]) + (t[128] + t[192]);
+        }
+    }
+    float w1[16];                                                    // 16 of the 64 inputs per wave, lane = hidden unit
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w1[i] = pr.W1[(size_t)hp * 4096 + (16 * wave + i) * 64 + lane];
+    if (wave < M) {
+        x *= pr.inv_count;
+        const double dev = x - wave_sum(x) / 64;
+        const double rstd = 1.0 / sqrt(wave_sum(dev * dev) / 64 + (double)pr.ln_eps);
+        s_qb[wave * 64 + lane] = (float)((double)gam * dev * rstd + (double)bet);
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (int r = 0; r < M; ++r) {                                    // eight inputs at a time, as k_gate_prep<512> adds them
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+            float a = 0.f;
+#pragma unroll
+            for (int i = 8 * e; i < 8 * e + 8; ++i) a = fmaf(s_qb[r * 64 + 16 * wave + i], w1[i], a);
+            s_part[(r * 8 + 2 * wave + e) * 64 + lane] = a;
+        }
+    }
+    __syncthreads();
+    float t = 0.f;
+    if (wave < M) {
+        const float *pp = s_part + wave * 512 + lane;
+        t = b1;
+#pragma unroll
+        for (int q = 0; q < 8; ++q) t += pp[64 * q];
+        t = 0.5f * t * (1.0f + erff(t * 0.70710678118654752440f));
+    }
+    hs[wave * dgs + lane] = t;                                       // rows beyond M are zero
+}
+
 // TURN: the positional phase is applied as well.  The workgroup evaluates it once for every bin of its `rounds` tiles per wave,
 // while its first weights are under way, and keeps it in LDS: inside the loop over the tiles, fp64 constants and temporaries cost
 // a wave per SIMD or spills.  Gate of pooled sums with a position, us, as a pass of its own over g / evaluated in the loop / now, H=32:
 // B=4 n=8192 21.3 / 21.5 / 17.1; B=8 29.9 / 33.0 / 22.2; B=64 n=1024 29.4 / 33.8 / 21.8.
-template <bool VEC, int RG, bool TURN>   // VEC: d_g % 4 == 0 and 16-byte aligned rows; RG: row groups of 4
+template <bool VEC, int RG, bool TURN, bool PREP = false>   // VEC: d_g % 4 == 0 and 16-byte aligned rows; RG: row groups of 4
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4 : 2))) void k_gate_out(const float *__restrict__ hid, const float *__restrict__ W2,
                                                   const float *__restrict__ b2,
                                                   const float *__restrict__ mbias, float2 *__restrict__ g,
                                                   int B, int H, int Hg, int dg, int F, int r_base0,
-                                                  int rounds, GatePhase phase) {
+                                                  int rounds, GatePhase phase, GatePrep pr) {
     extern __shared__ float hs[];
     const int r_base = r_base0 + 4 * RG * (int)blockIdx.z;   // blockIdx.z: tile of the rows (sequences)                    // [4*RG][dgs] hidden rows of this pass, zero padded
     const int dgp = (dg + 3) & ~3, dgs = dgp + 4;    // row stride padded against bank conflicts
@@ -351,7 +487,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
     const int hsel = blockIdx.y;                     // head of this block when weights are per head
     const int hp = (Hg == 1) ? 0 : hsel;
     const int M = (Hg == 1) ? B * H : B;
-    const int ntiles = (twoF + 63) / 64;
+    // an even length's two rows behind the last whole tile ride with the last workgroup (gate_grid)
+    const bool tail = VEC && dg == 64 && (twoF & 63) == 2 && twoF > 64;
+    const int ntiles = tail ? twoF / 64 : (twoF + 63) / 64;
     const float *w2h = W2 + (size_t)hp * twoF * dg;
     // the fast path's first tile is requested before anything else (with more than two row groups the registers it would
     // hold meanwhile cost a wave per SIMD)
@@ -360,16 +498,24 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
     int ftile = blockIdx.x * 4 + wave;
     float4 a[16];
     if (kEarly && VEC && dg == 64 && ftile < ntiles) gate_load_tile(a, w2h, ftile, lr, lc, twoF);
-    for (int idx = threadIdx.x; idx < 4 * RG * dgs; idx += 256) {
-        const int rr = idx / dgs, j = idx % dgs, r = r_base + rr;
-        float v = 0.f;
-        if (r < M && j < dg) v = hid[(size_t)((Hg == 1) ? r : r * H + hsel) * dg + j];
-        hs[idx] = v;
+    if (PREP) {
+        gate_hidden_rows(hs, dgs, reinterpret_cast<double *>(hs + 4 * dgs), pr, H, Hg, hsel, M);
+    } else {
+        for (int idx = threadIdx.x; idx < 4 * RG * dgs; idx += 256) {
+            const int rr = idx / dgs, j = idx % dgs, r = r_base + rr;
+            float v = 0.f;
+            if (r < M && j < dg) v = hid[(size_t)((Hg == 1) ? r : r * H + hsel) * dg + j];
+            hs[idx] = v;
+        }
     }
+    const bool mine = tail && wave == 3 && blockIdx.x == gridDim.x - 1;   // the two rows behind the last whole tile
+    float4 an = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (mine && lane < 32) an = *(reinterpret_cast<const float4 *>(w2h + (size_t)ntiles * 4096) + lane);
     float2 *turn = reinterpret_cast<float2 *>(hs + 4 * RG * dgs + 4 * 64 * ((VEC && dg == 64) ? kHalfStride : kTileStride));
     if (TURN)
         for (int e = threadIdx.x; e < 128 * rounds; e += 256)        // [round][wave][bin of the tile]
             turn[e] = gate_phase(((unsigned)(blockIdx.x * 4 + ((e >> 5) & 3) + (e >> 7) * tstep)) * 32 + (e & 31), phase);
+    const float2 turn_last = TURN && mine ? gate_phase(F - 1, phase) : make_float2(1.f, 0.f);
     __syncthreads();
     turn += wave * 32 + ((lane & ~3) >> 1);                          // this lane's two bins of a tile
     const int jrow = lane & 3;
@@ -443,6 +589,25 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
                 }
                 g[(size_t)bh * F + (n4 >> 1)] = v0;
                 if (e_ok2) g[(size_t)bh * F + (n4 >> 1) + 1] = v1;
+            }
+        }
+        if (mine) {                            // lanes 0-15 real, 16-31 imaginary part of the last bin
+            const float2 bias = make_float2(b2[(size_t)hp * twoF + twoF - 2], b2[(size_t)hp * twoF + twoF - 1]);
+            const float mb = mbias ? mbias[(size_t)hp * F + F - 1] : 0.f;
+            for (int rr = 0; rr < 4 * RG && r_base + rr < M; ++rr) {
+                const float4 hv = *reinterpret_cast<const float4 *>(hs + rr * dgs + 4 * (lane & 15));
+                float q = fmaf(an.x, hv.x, fmaf(an.y, hv.y, fmaf(an.z, hv.z, an.w * hv.w)));
+                q += partner16<8>(q);
+                q += partner16<4>(q);
+                q += partner16<2>(q);
+                q += partner16<1>(q);
+                const float im = __shfl(q, 16);
+                if (lane == 0) {
+                    const int r = r_base + rr, bh = (Hg == 1) ? r : r * H + hsel;
+                    float2 v;
+                    gate_store_bin(&v, q + bias.x, im + bias.y, mbias != nullptr, mb);
+                    g[(size_t)bh * F + F - 1] = TURN ? cmul(v, turn_last) : v;
+                }
             }
         }
         return;
@@ -664,18 +829,47 @@ int pool_rows(int B, int L, int H, int d) {
     return rows;
 }
 
+// Pieces of a row per workgroup of k_pool_deep, 0 where the pass of whole rows takes the sums: rows that are no whole number
+// of 128-byte lines, and sequences long enough for 256 rows a chunk (32 heads of 131072 bf16 rows: step of gate and mixer 1237
+// instead of 1226 us).
+static int pool_deep_cols(int io, int B, int L, int H, int d) {
+    const int bytes = H * d * (io ? 2 : 4), ppv = bytes / 16;
+    if (bytes % 128 || pool_rows(B, L, H, d) == kPoolRows) return 0;
+    return ppv % 32 == 0 ? 32 : ppv % 16 == 0 ? 16 : 8;
+}
+// Rows of one of its chunks: halved from 256 while there are less workgroups than compute units, and never fewer than the size
+// of the partial sums is for.
+static int pool_deep_rows(int io, int B, int L, int H, int d, int cols) {
+    const long long wide = (long long)H * d * (io ? 2 : 4) / 16 / cols;
+    const int least = pool_rows(B, L, H, d);
+    int rows = kPoolRows;
+    while (rows > 64 && rows > least && (long long)B * ((L + rows - 1) / rows) * wide < 256) rows /= 2;
+    return rows;
+}
+
 size_t gate_partial_bytes(int B, int L, int H, int d) {
     const int rows = pool_rows(B, L, H, d);
     const int nchunks = (L + rows - 1) / rows;
     return (size_t)B * nchunks * H * d * sizeof(double);
 }
 
-int pool_chunks(int B, int L, int H, int d) {
-    const int rows = pool_rows(B, L, H, d);
+int pool_chunks(int io, int B, int L, int H, int d) {
+    const int cols = pool_deep_cols(io, B, L, H, d);
+    const int rows = cols ? pool_deep_rows(io, B, L, H, d, cols) : pool_rows(B, L, H, d);
     return (L + rows - 1) / rows;
 }
 
 hipError_t launch_pool_partial(int io, const void *q, double *partial, int B, int L, int H, int d, hipStream_t st) {
+    if (const int cols = pool_deep_cols(io, B, L, H, d)) {
+        const int rows = pool_deep_rows(io, B, L, H, d, cols), nchunks = (L + rows - 1) / rows, ppv = H * d * (io ? 2 : 4) / 16;
+        const dim3 grid(ppv / cols, nchunks, B);
+#define SPECTRE_POOL_DEEP(C)                                                                \
+    if (io) k_pool_deep<true, C><<<grid, 512, 0, st>>>(q, partial, L, ppv, rows, nchunks); \
+    else k_pool_deep<false, C><<<grid, 512, 0, st>>>(q, partial, L, ppv, rows, nchunks)
+        if (cols == 32) { SPECTRE_POOL_DEEP(32); } else if (cols == 16) { SPECTRE_POOL_DEEP(16); } else { SPECTRE_POOL_DEEP(8); }
+#undef SPECTRE_POOL_DEEP
+        return hipGetLastError();
+    }
     const int ppr = H * d / 2;
     const int rows = pool_rows(B, L, H, d);
     const int nchunks = (L + rows - 1) / rows;
@@ -700,7 +894,7 @@ hipError_t launch_pool(int io, const void *q, double *partial, double *sum_q, in
                        hipStream_t st) {
     const hipError_t e = launch_pool_partial(io, q, partial, B, L, H, d, st);
     if (e != hipSuccess) return e;
-    k_pool_final<<<dim3((H * d + 31) / 32, B), 256, 0, st>>>(partial, sum_q, H * d, pool_chunks(B, L, H, d), 0);
+    k_pool_final<<<dim3((H * d + 31) / 32, B), 256, 0, st>>>(partial, sum_q, H * d, pool_chunks(io, B, L, H, d), 0);
     return hipGetLastError();
 }
 
@@ -738,6 +932,102 @@ static hipError_t launch_gate_tail(const GateDev &P, const float2 *raw, int B, i
     if (phase == 0) return hipSuccess;
     k_gate_phase<<<(unsigned)((total + 255) / 256), 256, 0, st>>>(g, F, gate_phase_of(P, phase), total);
     return hipGetLastError();
+}
+
+// Grid of the output layer: workgroups per weight set, tiles per wave.
+struct GateGrid {
+    int gx, gy, rounds;
+};
+static bool gate_vec(const GateDev &P) { return P.d_g % 4 == 0 && (reinterpret_cast<uintptr_t>(P.W2) & 15) == 0; }
+static GateGrid gate_grid(const GateDev &P, int H) {
+    const int twoF = 2 * (P.n_fft / 2 + 1), gy = P.Hg == 1 ? 1 : H;
+    // lengths that are a multiple of 64 have two rows more than whole tiles: as a tile of its own they made a workgroup per
+    // head (32 heads of n = 8192: 1056 for the 1024 places of the chip)
+    const bool tail = gate_vec(P) && P.d_g == 64 && twoF % 64 == 2 && twoF > 64;
+    const int ntiles = tail ? twoF / 64 : (twoF + 63) / 64;
+    int gx = (4096 + gy - 1) / gy;                 // about 16 workgroups per compute unit in total (1024: 5 % slower)
+    if (gx > (ntiles + 3) / 4) gx = (ntiles + 3) / 4;
+    // shrink the grid to the smallest one with the same number of tiles per wave (no ragged last round)
+    const int rounds = (ntiles + 4 * gx - 1) / (4 * gx);
+    return {(ntiles + 4 * rounds - 1) / (4 * rounds), gy, rounds};
+}
+
+// The hidden layer inside every workgroup of the output layer, whose weights are under way meanwhile: one dependent launch less,
+// for up to four rows per weight set and while all workgroups run at once, four to a compute unit.  Each forms the layer
+// again, so further rounds of them would pay for it again (32 heads, bf16, step of gate and mixer, separate / inside, us: L = 4096 45.5 /
+// 43.6, 8192 81.4 / 79.9, 131072 1236 / 1262; gate of pooled sums with a position, appended tokens and window, B = 4 n = 8192 295.2 / 293.2).
+// From 2048 heads on the separate launch adds the layer's terms in another order (launch_gate_prep).
+static bool gate_prep_inside(const GateDev &P, int B, int H) {
+    if (P.d != 64 || P.d_g != 64 || ((P.Hg == 1) ? B * H : B) > 4 || B * H >= 2048 || !gate_vec(P)) return false;
+    const GateGrid gr = gate_grid(P, H);
+    return (long long)gr.gx * gr.gy <= 1024;
+}
+
+// partial != nullptr: the hidden layer from these partial sums, inside the same launch (gate_prep_inside); else hid.
+static hipError_t gate_out(const float *hid, const double *partial, int nchunks, double inv_count, const GateDev &P, float2 *raw,
+                           int B, int H, long long phase, float2 *g, hipStream_t st) {
+    const int F = P.n_fft / 2 + 1;
+    const int M = (P.Hg == 1) ? B * H : B, twoF = 2 * F;
+    const GateGrid gr = gate_grid(P, H);
+    const int rounds = gr.rounds;
+    dim3 grid(gr.gx, gr.gy);
+    const GatePrep pr = {partial, nchunks, inv_count, P.ln_gamma, P.ln_beta, P.W1, P.b1, P.ln_eps};
+    const bool vec = gate_vec(P);
+    const int dgp = (P.d_g + 3) & ~3;
+    // with the Toeplitz update the MLP output goes to `raw` un-activated and a second pass finishes it
+    const float *out_bias = P.toeplitz ? nullptr : P.modrelu_bias;
+    float2 *out_g = P.toeplitz ? raw : g;
+    // the phase of a wave's tiles takes 1 KB of LDS a round; beyond 16 rounds (hundreds of heads with long gates) it is a pass of its own
+    const bool turn = phase != 0 && !P.toeplitz && rounds <= 16;
+    {
+        // every tile of the rows in one launch (grid.z); a single tile takes the narrowest kernel that fits
+        // rows per tile: 32, fewer while the launch would have less than four workgroups per compute unit (B=256 H=12
+        // L=196, 96 workgroups of 32 rows: 15 -> 7.4 us).  Every tile reads the weights again, so where those of one set
+        // do not stay in an XCD's 4 MB of L2, two workgroups per compute unit are enough and 16 rows the least (from pooled
+        // sums, 32 / 16 / 8 / 4 rows: n = 20480, 24 rows over 4 sets 20 / 17 / 17 / 21 us, 96 over one 19 / 16 / 17 / 22,
+        // 256 over one 27 / 31 / 36 / 51; n = 8192, 96 over one 18 / 13 / 12 / 12).
+        const bool large = (size_t)twoF * P.d_g * sizeof(float) > ((size_t)4 << 20);
+        int per = 32;
+        while (per > (large ? 16 : 4) && M > per / 2 &&
+               (long long)grid.x * grid.y * ((M + per - 1) / per) < (large ? 512 : 1024)) per /= 2;
+        const int ntile = (M + per - 1) / per;
+        const int rows = (ntile > 1) ? per : M;
+        const int rg = (rows + 3) / 4;            // 1..8 row groups per tile
+        const size_t lds = ((size_t)4 * (rg <= 1 ? 1 : rg <= 2 ? 2 : rg <= 4 ? 4 : 8) * (dgp + 4) +
+                            4 * 64 * ((vec && P.d_g == 64) ? kHalfStride : kTileStride)) * sizeof(float) +
+                           (turn ? rounds * 128 * sizeof(float2) : 0);
+        for (int z0 = 0; z0 < ntile; z0 += 65535) {
+            const int nz = (ntile - z0 < 65535) ? ntile - z0 : 65535;
+            const dim3 grid3(grid.x, grid.y, nz);
+            const int r_base = per * z0;
+#define SPECTRE_GATE_OUT(V, R)                                                                                              \
+    if (turn) k_gate_out<V, R, true><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F, r_base, \
+                                                              rounds, gate_phase_of(P, phase), pr);                          \
+    else k_gate_out<V, R, false><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F, r_base,     \
+                                                          rounds, gate_phase_of(P, phase), pr)
+            if (partial) {
+                if (turn) k_gate_out<true, 1, true, true><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g,
+                                                                                  F, r_base, rounds, gate_phase_of(P, phase), pr);
+                else k_gate_out<true, 1, false, true><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F,
+                                                                              r_base, rounds, gate_phase_of(P, phase), pr);
+            } else if (vec) {
+                if (rg <= 1) { SPECTRE_GATE_OUT(true, 1); } else if (rg <= 2) { SPECTRE_GATE_OUT(true, 2); }
+                else if (rg <= 4) { SPECTRE_GATE_OUT(true, 4); } else { SPECTRE_GATE_OUT(true, 8); }
+            } else {
+                if (rg <= 1) { SPECTRE_GATE_OUT(false, 1); } else if (rg <= 2) { SPECTRE_GATE_OUT(false, 2); }
+                else if (rg <= 4) { SPECTRE_GATE_OUT(false, 4); } else { SPECTRE_GATE_OUT(false, 8); }
+            }
+#undef SPECTRE_GATE_OUT
+            hipError_t e2 = hipGetLastError();
+            if (e2 != hipSuccess) return e2;
+        }
+    }
+    return launch_gate_tail(P, raw, B, H, turn ? 0 : phase, g, st);
+}
+
+hipError_t launch_gate_out(const float *hid, const GateDev &P, float2 *raw, int B, int H, long long phase, float2 *g,
+                           hipStream_t st) {
+    return gate_out(hid, nullptr, 0, 0.0, P, raw, B, H, phase, g, st);
 }
 
 // Short sequences: up to 256 KB of rows per head (B=1 H=32, step of gate and mixer: bf16 L=2048 46.0 -> 42.8 us, L=4096
@@ -784,76 +1074,19 @@ hipError_t launch_gate(int io, const void *q, double *partial, double inv_count,
     }
     hipError_t e = launch_pool_partial(io, q, partial, B, L, H, P.d, st);
     if (e != hipSuccess) return e;
-    e = launch_gate_prep(partial, pool_chunks(B, L, H, P.d), nullptr, 1, nullptr, inv_count, P, hid, B, H, st);
+    const int nchunks = pool_chunks(io, B, L, H, P.d);
+    if (gate_prep_inside(P, B, H)) return gate_out(hid, partial, nchunks, inv_count, P, raw, B, H, phase, g, st);
+    e = launch_gate_prep(partial, nchunks, nullptr, 1, nullptr, inv_count, P, hid, B, H, st);
     if (e != hipSuccess) return e;
     return launch_gate_out(hid, P, raw, B, H, phase, g, st);
 }
 
 hipError_t launch_gate_mlp(const double *sum_q, double inv_count, const GateDev &P, float *hid, float2 *raw,
                            int B, int H, long long phase, float2 *g, hipStream_t st) {
+    if (gate_prep_inside(P, B, H)) return gate_out(hid, sum_q, 1, inv_count, P, raw, B, H, phase, g, st);
     const hipError_t e = launch_gate_prep(sum_q, 1, nullptr, 1, nullptr, inv_count, P, hid, B, H, st);
     if (e != hipSuccess) return e;
     return launch_gate_out(hid, P, raw, B, H, phase, g, st);
-}
-
-hipError_t launch_gate_out(const float *hid, const GateDev &P, float2 *raw, int B, int H, long long phase, float2 *g,
-                           hipStream_t st) {
-    const int F = P.n_fft / 2 + 1;
-    const int M = (P.Hg == 1) ? B * H : B, twoF = 2 * F;
-    const int ntiles = (twoF + 63) / 64;
-    const int gy = P.Hg == 1 ? 1 : H;
-    int gx = (4096 + gy - 1) / gy;                 // about 16 workgroups per compute unit in total (1024: 5 % slower)
-    if (gx > (ntiles + 3) / 4) gx = (ntiles + 3) / 4;
-    // shrink the grid to the smallest one with the same number of tiles per wave (no ragged last round)
-    const int rounds = (ntiles + 4 * gx - 1) / (4 * gx);
-    gx = (ntiles + 4 * rounds - 1) / (4 * rounds);
-    dim3 grid(gx, gy);
-    const bool vec = (P.d_g % 4 == 0) && (reinterpret_cast<uintptr_t>(P.W2) & 15) == 0;
-    const int dgp = (P.d_g + 3) & ~3;
-    // with the Toeplitz update the MLP output goes to `raw` un-activated and a second pass finishes it
-    const float *out_bias = P.toeplitz ? nullptr : P.modrelu_bias;
-    float2 *out_g = P.toeplitz ? raw : g;
-    // the phase of a wave's tiles takes 1 KB of LDS a round; beyond 16 rounds (hundreds of heads with long gates) it is a pass of its own
-    const bool turn = phase != 0 && !P.toeplitz && rounds <= 16;
-    {
-        // every tile of the rows in one launch (grid.z); a single tile takes the narrowest kernel that fits
-        // rows per tile: 32, fewer while the launch would have less than four workgroups per compute unit (B=256 H=12
-        // L=196, 96 workgroups of 32 rows: 15 -> 7.4 us).  Every tile reads the weights again, so where those of one set
-        // do not stay in an XCD's 4 MB of L2, two workgroups per compute unit are enough and 16 rows the least (from pooled
-        // sums, 32 / 16 / 8 / 4 rows: n = 20480, 24 rows over 4 sets 20 / 17 / 17 / 21 us, 96 over one 19 / 16 / 17 / 22,
-        // 256 over one 27 / 31 / 36 / 51; n = 8192, 96 over one 18 / 13 / 12 / 12).
-        const bool large = (size_t)twoF * P.d_g * sizeof(float) > ((size_t)4 << 20);
-        int per = 32;
-        while (per > (large ? 16 : 4) && M > per / 2 &&
-               (long long)grid.x * grid.y * ((M + per - 1) / per) < (large ? 512 : 1024)) per /= 2;
-        const int ntile = (M + per - 1) / per;
-        const int rows = (ntile > 1) ? per : M;
-        const int rg = (rows + 3) / 4;            // 1..8 row groups per tile
-        const size_t lds = ((size_t)4 * (rg <= 1 ? 1 : rg <= 2 ? 2 : rg <= 4 ? 4 : 8) * (dgp + 4) +
-                            4 * 64 * ((vec && P.d_g == 64) ? kHalfStride : kTileStride)) * sizeof(float) +
-                           (turn ? rounds * 128 * sizeof(float2) : 0);
-        for (int z0 = 0; z0 < ntile; z0 += 65535) {
-            const int nz = (ntile - z0 < 65535) ? ntile - z0 : 65535;
-            const dim3 grid3(grid.x, grid.y, nz);
-            const int r_base = per * z0;
-#define SPECTRE_GATE_OUT(V, R)                                                                                              \
-    if (turn) k_gate_out<V, R, true><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F, r_base, \
-                                                              rounds, gate_phase_of(P, phase));                              \
-    else k_gate_out<V, R, false><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F, r_base,     \
-                                                          rounds, gate_phase_of(P, phase))
-            if (vec) {
-                if (rg <= 1) { SPECTRE_GATE_OUT(true, 1); } else if (rg <= 2) { SPECTRE_GATE_OUT(true, 2); }
-                else if (rg <= 4) { SPECTRE_GATE_OUT(true, 4); } else { SPECTRE_GATE_OUT(true, 8); }
-            } else {
-                if (rg <= 1) { SPECTRE_GATE_OUT(false, 1); } else if (rg <= 2) { SPECTRE_GATE_OUT(false, 2); }
-                else if (rg <= 4) { SPECTRE_GATE_OUT(false, 4); } else { SPECTRE_GATE_OUT(false, 8); }
-            }
-#undef SPECTRE_GATE_OUT
-            hipError_t e2 = hipGetLastError();
-            if (e2 != hipSuccess) return e2;
-        }
-    }
-    return launch_gate_tail(P, raw, B, H, turn ? 0 : phase, g, st);
 }
 
 // Loads this translation unit's code object (the runtime loads them on first use): called by spectre_prepare so
