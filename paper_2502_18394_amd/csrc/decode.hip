@@ -10,6 +10,13 @@
 // one head, i.e. 64 KB of each stream per sequence, and everything in front of them (64 x 64 first layer, LayerNorm) is
 // recomputed by every workgroup from L2: cheaper than the three dependent launches (ring update, hidden layer, output
 // layer) and the round trip of the gate through memory that it replaces.
+// A chip's workgroups of one round run in step, so what a workgroup waits for outside its two streams is time without
+// traffic.  Loads return in order: the first layer's operands are requested before the weights, whose arrival its chain then
+// passes behind, and the first rows of the half spectra as soon as the weights' registers are free, ahead of the factors; a
+// row's registers take the one after next when it is used.  us a token, before / now: B=1 H=32, deferred, N=4096 18.6 /
+// 16.8, 8192 27.5 / 27.0, 12288 40.8 / 39.1; every step updating, 4096 22.7 / 20.7.  (Plain loads, so that both streams stay
+// in the memory-side cache from token to token, gain another 2 to 15 % below 268 MB when nothing else runs between, and lose 6 to
+// 17 % when the caches and weights of eight layers take turns.)
 // Measured against ring update + hidden + output layer + sweep + final: B=1 H=32 N=8192, deferred updates, 39.7 ->
 // 30.5 us a token over 16 of them (a reading step moves 134 MB in 24 us, 5.6 TB/s); B=8 H=32 N=32768, every step
 // updating, 838 -> 812 us (4.56 GB, 5.6 TB/s).
@@ -68,7 +75,7 @@ __device__ __forceinline__ void decode_entry(float4 &x, float2 dl, float2 wk, fl
 // LAZY = false: X += Delta w_k, stored, and the readout sums of the updated entries (k_sweep<true, true>).
 // LAZY = true : X only read, plus the pending tokens' kappa sums (k_sweep_lazy); ps includes this token.
 template <typename T, bool LAZY>
-__global__ __launch_bounds__(256) void k_decode(float4 *__restrict__ X, DecodeRing rg, double inv_count, GateDev P,
+__global__ __launch_bounds__(256, 4) void k_decode(float4 *__restrict__ X, DecodeRing rg, double inv_count, GateDev P,
                                                 const float2 *__restrict__ tw, float *__restrict__ partial,
                                                 float *__restrict__ kpart, int B, int H, int N, int bpw,
                                                 PendingSlots ps, int nchunks) {
@@ -90,37 +97,58 @@ __global__ __launch_bounds__(256) void k_decode(float4 *__restrict__ X, DecodeRi
     const int k0 = chunk * kBins;
     const bool last = chunk == nchunks - 1;                          // has the Nyquist bin as its bin kBins
 
+    // loads return in the order they are issued: what the first layer needs goes in front of the weights
+    const int kl = tid & (kBins - 1), k = k0 + kl;
+    const float2 w = tw[mul_mod((unsigned)k, (unsigned)rg.slot, N)];
+    float w1[16];                                                    // first layer: 16 of the 64 inputs per wave
+#pragma unroll
+    for (int i = 0; i < 16; ++i) w1[i] = P.W1[(size_t)hp * 4096 + (16 * wave + i) * 64 + lane];
+    const float b1 = P.b1[hp * 64 + lane];
+    const bool act = P.modrelu_bias != nullptr;
+    const float2 bias = *reinterpret_cast<const float2 *>(P.b2 + ((size_t)hp * F + k) * 2);
+    const float mb = act ? P.modrelu_bias[(size_t)hp * F + k] : 0.0f;
+    float2 w_ny = make_float2(0.f, 0.f), bias_ny = w_ny;
+    float mb_ny = 0.f;
+    if (last) {
+        w_ny = tw[mul_mod((unsigned)N / 2, (unsigned)rg.slot, N)];
+        bias_ny = *reinterpret_cast<const float2 *>(P.b2 + ((size_t)hp * F + N / 2) * 2);
+        if (act) mb_ny = P.modrelu_bias[(size_t)hp * F + N / 2];
+    }
+    float qn = 0.f, qo = 0.f, gam = 0.f, bet = 0.f;
+    double sq = 0.0;
+    if (wave < nb) {                                                 // bpw <= 4: one sequence per wave, lane = channel
+        const int bh = (b0 + wave) * H + h;
+        const size_t i = (size_t)bh * 64 + lane;
+        qn = load_scalar<T>(static_cast<const T *>(rg.q_t), i);
+        qo = rg.q_buf[((size_t)bh * N + rg.slot) * 64 + lane];
+        sq = rg.sum_q[i];
+        gam = P.ln_gamma[hp * 64 + lane];
+        bet = P.ln_beta[hp * 64 + lane];
+    }
+    __builtin_amdgcn_sched_barrier(0);
+
     // this wave's 64 rows of W2 (whole rows of 64 weights, 1 KB per instruction), in flight during the first layer
     const float *w2h = P.W2 + (size_t)hp * 2 * F * 64;
     const float4 *w2 = reinterpret_cast<const float4 *>(w2h + (size_t)(2 * k0 + 64 * wave) * 64) + lane;
-    float4 a[16], an = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (nz > 1 || P.Hg == 1) {                                       // read again by others: keep it in the L2
+    float4 a[16], an;
+    if (nz > 1 || P.Hg == 1) {                            // read again by others: keep it in the L2
 #pragma unroll
         for (int s = 0; s < 16; ++s) a[s] = w2[64 * s];
     } else {
 #pragma unroll
         for (int s = 0; s < 16; ++s) a[s] = stream_load(w2 + 64 * s);
     }
-    if (last && tid < 32) an = reinterpret_cast<const float4 *>(w2h + (size_t)N * 64)[tid];
-    const int kl = tid & (kBins - 1), k = k0 + kl;
-    const float2 w = tw[mul_mod((unsigned)k, (unsigned)rg.slot, N)];
+    an = reinterpret_cast<const float4 *>(w2h + (size_t)(last ? N : 2 * k0) * 64)[tid & 31];   // the Nyquist bin's two rows
     if (tid < kBins) s_w[kl] = w;
-    if (last && tid == kBins) s_w[kBins] = tw[mul_mod((unsigned)N / 2, (unsigned)rg.slot, N)];
+    if (last && tid == kBins) s_w[kBins] = w_ny;
 
-    // LayerNorm of the descriptor, one sequence per wave at a time (lane = channel)
-    for (int bl = wave; bl < nb; bl += 4) {
-        const int bh = (b0 + bl) * H + h;
-        const size_t i = (size_t)bh * 64 + lane;
-        const float qn = load_scalar<T>(static_cast<const T *>(rg.q_t), i);
-        const float qo = rg.evict ? rg.q_buf[((size_t)bh * N + rg.slot) * 64 + lane] : 0.0f;
-        const double x = inv_count * (rg.sum_q[i] + ((double)qn - (double)qo));
+    // LayerNorm of the descriptor
+    if (wave < nb) {
+        const double x = inv_count * (sq + ((double)qn - (rg.evict ? (double)qo : 0.0)));
         const double dev = x - wave_sum(x) / 64;
         const double rstd = 1.0 / sqrt(wave_sum(dev * dev) / 64 + (double)P.ln_eps);
-        s_qb[bl * 64 + lane] = (float)((double)P.ln_gamma[hp * 64 + lane] * dev * rstd + (double)P.ln_beta[hp * 64 + lane]);
+        s_qb[wave * 64 + lane] = (float)((double)gam * dev * rstd + (double)bet);
     }
-    float w1[16];                                                    // first layer: 16 of the 64 inputs per wave
-#pragma unroll
-    for (int i = 0; i < 16; ++i) w1[i] = P.W1[(size_t)hp * 4096 + (16 * wave + i) * 64 + lane];
     __syncthreads();
     for (int bl = 0; bl < nb; ++bl) {
         float acc = 0.f;
@@ -132,7 +160,7 @@ __global__ __launch_bounds__(256) void k_decode(float4 *__restrict__ X, DecodeRi
     for (int idx = tid; idx < nb * 64; idx += 256) {
         const int bl = idx >> 6, j = idx & 63;
         const float *pp = s_part + bl * 256 + j;
-        const float t = P.b1[hp * 64 + j] + ((pp[0] + pp[64]) + (pp[128] + pp[192]));
+        const float t = b1 + ((pp[0] + pp[64]) + (pp[128] + pp[192]));
         s_hid[idx] = 0.5f * t * (1.0f + erff(t * 0.70710678118654752440f));
     }
     __syncthreads();
@@ -157,72 +185,81 @@ __global__ __launch_bounds__(256) void k_decode(float4 *__restrict__ X, DecodeRi
             if (lane == 0 || lane == 16) u[2 * kBins + (lane >> 4)] = q;
         }
     }
+    // the pass over the half spectra: 8 bins x 32 lanes, two channels per lane, eight rows of a lane at a time; the weights'
+    // registers are free now, and the first rows are under way while the factors are formed
+    const int cl = tid & 31, row = tid >> 5;
+    constexpr int kU = 8, kHalf = 8 * kU;
+    struct Sequence {                                                // what the pass needs besides the rows
+        float2 dl, e, rot;
+    };
+    auto head_of = [&](int bl) { return X + ((size_t)((b0 + bl) * H + h) * F + k0) * 32 + cl; };
+    unsigned mult = 0, m_item = 0, step_item = 0;
+    if (LAZY) {                                                      // see k_sweep_lazy
+        mult = (cl < ps.n) ? (unsigned)((rg.slot - ps.slot[cl] + N) % N) : 0u;
+        index_walk((unsigned)(k0 + row), mult, N, m_item, step_item);
+    }
+    auto load_sequence = [&](int bl) {
+        Sequence q = {make_float2(0.f, 0.f), make_float2(1.f, 0.f), make_float2(1.f, 0.f)};
+        if (LAZY) {
+            q.rot = tw[step_item];
+            q.e = tw[m_item];
+        } else {
+            const size_t i = (size_t)((b0 + bl) * H + h) * 64 + 2 * cl;
+            const T *vp = static_cast<const T *>(rg.v_t);
+            q.dl = make_float2(load_scalar<T>(vp, i), load_scalar<T>(vp, i + 1));
+            const float2 old = *reinterpret_cast<const float2 *>(rg.v_buf + ((size_t)((b0 + bl) * H + h) * N + rg.slot) * 64 + 2 * cl);
+            q.dl.x -= rg.evict ? old.x : 0.f;
+            q.dl.y -= rg.evict ? old.y : 0.f;
+        }
+        return q;
+    };
+    auto load_row = [&](int bl, int kc) { return stream_load(head_of(bl) + (size_t)kc * 32); };
+    Sequence sn = load_sequence(0);
+    float4 x[kU];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) x[u] = load_row(0, row + 8 * u);
     __syncthreads();
     {
         const float invN = 1.0f / (float)N;
-        const float2 bias = *reinterpret_cast<const float2 *>(P.b2 + ((size_t)hp * F + k) * 2);
-        const bool act = P.modrelu_bias != nullptr;
-        const float mb = act ? P.modrelu_bias[(size_t)hp * F + k] : 0.0f;
         for (int bl = tid >> 7; bl < nb; bl += 2)
             decode_factors<LAZY>(s_r + bl * kBinStride + kl, s_g + bl * kBinStride + kl, bias, act, mb,
                                  k == 0 ? invN : 2.0f * invN, w);
         if (last && tid < nb) {
             const int i = tid * kBinStride + kBins;
-            decode_factors<LAZY>(s_r + i, s_g + i, *reinterpret_cast<const float2 *>(P.b2 + ((size_t)hp * F + N / 2) * 2), act,
-                                 act ? P.modrelu_bias[(size_t)hp * F + N / 2] : 0.0f, invN, s_w[kBins]);
+            decode_factors<LAZY>(s_r + i, s_g + i, bias_ny, act, mb_ny, invN, w_ny);
         }
     }
     __syncthreads();
 
-    // the pass over the half spectra: 8 bins x 32 lanes, two channels per lane
-    const int cl = tid & 31, row = tid >> 5;
-    constexpr int kU = 8;
-    for (int bl = 0; bl < nb; ++bl) {
-        const int bh = (b0 + bl) * H + h;
-        float2 dl = make_float2(0.f, 0.f);
-        if (!LAZY) {
-            const size_t i = (size_t)bh * 64 + 2 * cl;
-            const T *vp = static_cast<const T *>(rg.v_t);
-            dl = make_float2(load_scalar<T>(vp, i), load_scalar<T>(vp, i + 1));
-            if (rg.evict) {
-                const float2 old = *reinterpret_cast<const float2 *>(rg.v_buf + ((size_t)bh * N + rg.slot) * 64 + 2 * cl);
-                dl.x -= old.x;
-                dl.y -= old.y;
-            }
-        }
-        unsigned mult = 0;
-        float2 e = make_float2(1.f, 0.f), rot = e;                   // LAZY: see k_sweep_lazy
-        if (LAZY) {
-            mult = (cl < ps.n) ? (unsigned)((rg.slot - ps.slot[cl] + N) % N) : 0u;
-            unsigned m_item, step_item;
-            index_walk((unsigned)(k0 + row), mult, N, m_item, step_item);
-            rot = tw[step_item];
-            e = tw[m_item];
-        }
-        float acc0 = 0.f, acc1 = 0.f, kacc = 0.f;
-        float4 *Xp = X + ((size_t)bh * F + k0) * 32 + cl;
-        const float2 *rp = s_r + bl * kBinStride, *gp = s_g + bl * kBinStride;
 #pragma unroll 1
-        for (int kk = row; kk < kBins; kk += 8 * kU) {
-            float4 x[kU];
-#pragma unroll
-            for (int u = 0; u < kU; ++u) x[u] = stream_load(Xp + (size_t)(kk + 8 * u) * 32);
+    for (int bl = 0; bl < nb; ++bl) {
+        const Sequence sq_now = sn;
+        float2 e = sq_now.e;
+        float acc0 = 0.f, acc1 = 0.f, kacc = 0.f;
+        float4 *Xp = head_of(bl);
+        const float2 *rp = s_r + bl * kBinStride, *gp = s_g + bl * kBinStride;
+        // a row's registers take the one after next (half a chunk on, then the next sequence's) as soon as it is used
+#pragma unroll 1
+        for (int half = 0; half < 2; ++half) {
+            const int next_bl = half ? bl + 1 : bl, next_k = half ? row : kHalf + row;
+            if (half && next_bl < nb) sn = load_sequence(next_bl);
 #pragma unroll
             for (int u = 0; u < kU; ++u) {
-                const int kc = kk + 8 * u;
-                decode_entry<LAZY>(x[u], dl, LAZY ? make_float2(0.f, 0.f) : s_w[kc], rp[kc], acc0, acc1);
+                const int kc = kHalf * half + row + 8 * u;
+                decode_entry<LAZY>(x[u], sq_now.dl, LAZY ? make_float2(0.f, 0.f) : s_w[kc], rp[kc], acc0, acc1);
                 if (!LAZY) stream_store(Xp + (size_t)kc * 32, x[u]);
                 if (LAZY) {
                     const float2 gc = gp[kc];
                     kacc = fmaf(gc.x, e.x, fmaf(gc.y, e.y, kacc));   // c_k/N Re(g_k conj(e_k))
-                    e = cmul(e, rot);
+                    e = cmul(e, sq_now.rot);
                 }
+                if (next_bl < nb) x[u] = load_row(next_bl, next_k + 8 * u);
             }
         }
         if (last && row == 0) {                                      // Nyquist
-            float4 x = stream_load(Xp + kBins * 32);
-            decode_entry<LAZY>(x, dl, s_w[kBins], rp[kBins], acc0, acc1);
-            if (!LAZY) stream_store(Xp + kBins * 32, x);
+            float4 xn = stream_load(Xp + kBins * 32);
+            decode_entry<LAZY>(xn, sq_now.dl, s_w[kBins], rp[kBins], acc0, acc1);
+            if (!LAZY) stream_store(Xp + kBins * 32, xn);
             if (LAZY) {
                 const float2 en = tw[mul_mod((unsigned)N / 2, mult, N)];
                 kacc = fmaf(gp[kBins].x, en.x, fmaf(gp[kBins].y, en.y, kacc));
