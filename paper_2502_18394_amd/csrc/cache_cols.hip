@@ -11,6 +11,7 @@
 // memory once less.  What bounds them is memory traffic, 16 bytes per pair and position: 25 heads of N = 32768 forward 134
 // -> 72 us (5.8 TB/s), 102 heads of N = 8192 inverse 134 -> 77 us (5.6 TB/s).  With 64-byte pieces of the rows of X and whole
 // columns in LDS the former took 105 us, with plain stores of X, which push the scratch out of the memory-side cache, 88.
+// The inverse writes its columns through the L2 (through_store; the readout's row transforms read them: 57 tokens and readout as below 294 -> 289 us).
 // Whole calls: prompt of 20011 tokens, B = 8 H = 32 N = 32768, 3603 -> 2956 us; 57 tokens and the window's readout, B = 4
 // H = 32 N = 8192, 427 -> 352 us.
 //
@@ -207,7 +208,7 @@ __global__ __launch_bounds__(2 * PW * R, R == 32 ? 4 : 6) void k_cache_inv(const
     if (s >= un.planes) return;
     float2 *col = scr + (((size_t)un.bhl * N2 + un.plane(s)) * 32 + un.pg * PW + pw) * N1 + tau;
 #pragma unroll
-    for (int j = 0; j < R; ++j) col[R * j] = x[j];
+    for (int j = 0; j < R; ++j) through_store(col + R * j, x[j]);
 }
 
 // The mixer's columns of R * R points in place: forward, times the expanded gate gp [bh][k2][k1], inverse.  R adjacent lanes
@@ -216,7 +217,8 @@ __global__ __launch_bounds__(2 * PW * R, R == 32 ? 4 : 6) void k_cache_inv(const
 // For L = 12288 ... 32768 instead of the 4096-point columns of k_big, whose three passes exchange twice across the waves of a
 // workgroup: here two longer passes exchange inside 32 lanes, without a barrier.  What bounds it is memory traffic, 16 bytes
 // per pair and position: 32 heads of L = 24576 94 -> 73 us (403 MB, 5.5 TB/s).
-template <int R, int PW>
+// THROUGH: see through_store and launch_mix_cols.
+template <int R, int PW, bool THROUGH>
 __global__ __launch_bounds__(PW * R, 3) void k_mix_cols(float2 *__restrict__ scr, const float2 *__restrict__ gp,
                                                         const float4 *__restrict__ tw, int N2, int bh0, int planes) {
     constexpr int N1 = R * R, NT = PW * R, kCol = N1 + N1 / R, G = 32 / PW;
@@ -251,7 +253,10 @@ __global__ __launch_bounds__(PW * R, 3) void k_mix_cols(float2 *__restrict__ scr
     for (int u = 1; u < R; ++u) x[u] = cmulc(x[u], w[u * R]);
     dft<R, true>(x);
 #pragma unroll
-    for (int j = 0; j < R; ++j) col[R * j] = x[j];
+    for (int j = 0; j < R; ++j) {
+        if (THROUGH) through_store(col + R * j, x[j]);
+        else col[R * j] = x[j];
+    }
 }
 
 // ------------------------------------------------------------------------------------------
@@ -301,13 +306,15 @@ hipError_t launch_cache_inv(const Pow2Plan &pl, const float2 *X, const float2 *g
     return cache_cols(true, pl, scr, const_cast<float2 *>(X), g, bh0, nbh, st);
 }
 
-hipError_t launch_mix_cols(const Pow2Plan &pl, float2 *scr, const float2 *gp, int bh0, int nbh, hipStream_t st) {
+hipError_t launch_mix_cols(const Pow2Plan &pl, float2 *scr, const float2 *gp, int bh0, int nbh, hipStream_t st, bool alone) {
     constexpr int R = 32, PW = 8;
     if (pl.N1 != R * R) return hipErrorInvalidValue;
     const size_t lds = (size_t)PW * (pl.N1 + R) * sizeof(float) + (size_t)pl.N1 * sizeof(float2);
     const int planes = nbh * pl.N2;
-    k_mix_cols<R, PW><<<(planes + 7) / 8 * 8 * (32 / PW), PW * R, lds, st>>>(scr, gp, reinterpret_cast<const float4 *>(pl.twN1),
-                                                                            pl.N2, bh0, planes);
+    // through_store for launches of up to 128 MB that have memory to themselves (32 heads of bf16 rows, mixer, us, plain / through: 12288,
+    // 100 MB, 95.9 / 92.8; layer of 24576, 201 MB, 318.8 / 324.2)
+    const auto kern = alone && (size_t)planes * 32 * R * R * sizeof(float2) <= ((size_t)128 << 20) ? k_mix_cols<R, PW, true> : k_mix_cols<R, PW, false>;
+    kern<<<(planes + 7) / 8 * 8 * (32 / PW), PW * R, lds, st>>>(scr, gp, reinterpret_cast<const float4 *>(pl.twN1), pl.N2, bh0, planes);
     return hipGetLastError();
 }
 

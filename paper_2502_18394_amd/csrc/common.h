@@ -38,6 +38,27 @@ __device__ __forceinline__ void stream_store(float2 *p, float2 v) {
     __builtin_nontemporal_store(w, reinterpret_cast<f32x2_t *>(p));
 }
 
+// Stores that go through the L2 at once.  What a kernel leaves dirty there, up to 4 MB on each of the eight XCDs, is written back
+// when it ends and before the next one starts, with nothing beside it; written through, it leaves while the kernel still
+// works.  For scratch the next kernel reads, of whole 128-byte lines per wave instruction, in launches that move up to a few
+// hundred MB alone (measured at the users; streaming stores instead cost 3 to 5 % there, the next kernel reads the scratch).
+template <typename T>
+__device__ __forceinline__ void through_store(T *p, T v) {
+    static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two words");
+    if constexpr (sizeof(T) == 8)
+        __hip_atomic_store(reinterpret_cast<unsigned long long *>(p), __builtin_bit_cast(unsigned long long, v), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    else
+        __hip_atomic_store(reinterpret_cast<unsigned int *>(p), __builtin_bit_cast(unsigned int, v), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+}
+// The same for 16 bytes at byte `at` of the `bytes` from a base that is the same in every lane.
+typedef unsigned int u32x4_store_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void through_store16(void *base, unsigned bytes, unsigned at, u32x4_store_t v) {
+    constexpr int kRaw = 0x00027000, kDeviceScope = 16;              // 32-bit elements without a format; the sc1 bit
+    __builtin_amdgcn_raw_buffer_store_b128(v, __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, kRaw), (int)at, 0, kDeviceScope);
+}
+
 // Two adjacent channels (2c, 2c+1) of one token row travel as one complex number
 // (even channel = real part).  Storage types: float2 for fp32 rows, one 32-bit
 // word holding two bfloat16 for bf16 rows.

@@ -7,6 +7,7 @@
 //                      first workgroups lay the gate out in the order of the column kernel's registers
 //   k_line           : a line at a time: forward transform, gate, inverse transform, in place
 //   k_line_turn<out> : lines -> rows
+// The lines are written through the L2 both times (through_store): 32 heads at L = 8192 55.7 -> 53.3 us, at 16384 112.8 -> 108.8.
 // 24 bytes per pair and position; the column kernel is bound by its vector arithmetic (about 90 instructions per point).
 // Measured: L = 8192 66 -> 61 us for 32 heads, 241 -> 189 us for 128; L = 16384 132 -> 113 us for 32 heads, 253 -> 206 us
 // for 64.  As many heads go through together as the scratch holds (line_group_heads; groups of 32 for 128 heads at
@@ -68,7 +69,7 @@ __global__ __launch_bounds__(256) void k_line_turn(const uint32_t *__restrict__ 
     if (bhl >= nbh) return;                    // whole workgroup: heads are padded to 8
     const int tau0 = (t % (NT / 32)) * 32, j0 = (t / (NT / 32)) * kVW;
     const int bh = bh0 + bhl, b = bh / H, h = bh % H;
-    uint32_t *line = lines + (size_t)bhl * 32 * L + (size_t)j0 * NT + (size_t)tau0 * kVW;
+    uint32_t *head = lines + (size_t)bhl * 32 * L, *line = head + (size_t)j0 * NT + (size_t)tau0 * kVW;
     const int tl = tid & 31, p0 = tid >> 5;    // line side: tau0 + tl of pairs p0 + 8 i
     const int piece = tid & 7, r0 = tid >> 3;  // row side: 16 bytes (four pairs) of rows r0 + 32 i
     const size_t row0 = (((size_t)b * L + tau0 + r0 + (size_t)NT * j0) * H + h) * 32 + 4 * piece, rstep = (size_t)NT * H * 32;
@@ -87,7 +88,7 @@ __global__ __launch_bounds__(256) void k_line_turn(const uint32_t *__restrict__ 
         for (int i = 0; i < 4; ++i) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) w[i][c] = tile[(c * 32 + tl) * S + p0 + 8 * i];
-            *(reinterpret_cast<u32x4_t *>(line + (size_t)(p0 + 8 * i) * L) + tl) = w[i];
+            through_store16(head, 128u * L, 4u * ((p0 + 8 * i) * L + j0 * NT + (tau0 + tl) * kVW), w[i]);
         }
     } else {
 #pragma unroll
@@ -219,7 +220,7 @@ __global__ __launch_bounds__(16 * R1, 2) void k_line(uint32_t *__restrict__ line
             u32x4_t o;
 #pragma unroll
             for (int e = 0; e < kVW; ++e) o[e] = IoBf16::pack(x[kVW * j + e]);
-            line_of(n)[j * NT] = o;
+            through_store16(lines + ((size_t)(8 * (n >> 5) + xcd) * 32 + (n & 31)) * L, 4u * L, 16u * (j * NT + tau), o);
         }
         if (n + 1 < n1) __syncthreads();                             // the next line's pass 0 writes what is read above
     }

@@ -68,7 +68,7 @@ bool pow2_split(int L, int *N1, int *N2, int *P);
 hipError_t launch_small_fwd(const Pow2Plan &pl, int io, const void *v, float2 *scratch, int rows, int H,
                             int bh0, int nbh, hipStream_t st, bool scr16 = false, bool affine = false,
                             float2 *ring = nullptr);
-// wide (mode 0, 4096-point columns, fp32 scratch): 8 instead of 4 columns per workgroup, for calls on two streams.
+// wide: for calls on two streams; 8 instead of 4 columns per workgroup (mode 0, 4096-point columns, fp32 scratch).
 hipError_t launch_big(const Pow2Plan &pl, float2 *scratch, const float2 *gp, int bh0, int nbh, int mode,
                       hipStream_t st, bool shared_gate = false, bool scr16 = false, bool affine = false,
                       bool wide = false);
@@ -84,8 +84,8 @@ hipError_t launch_small_inv(const Pow2Plan &pl, int io, const float2 *scratch, v
 hipError_t launch_small_fwd_proj(const Pow2Plan &pl, const void *x, const void *wpack, int Hw, float2 *scratch, int rows,
                                  int H, int bh0, int nbh, hipStream_t st, bool affine = false);
 // The column pass of a plan with 1024-point columns (P = 0, see cache_cols_split): forward, gate, inverse, in place, of heads
-// bh0 .. bh0 + nbh - 1; gp as launch_gate_expand lays it out for that plan.
-hipError_t launch_mix_cols(const Pow2Plan &pl, float2 *scratch, const float2 *gp, int bh0, int nbh, hipStream_t st);
+// bh0 .. bh0 + nbh - 1; gp as launch_gate_expand lays it out for that plan.  alone: no other lane runs beside it.
+hipError_t launch_mix_cols(const Pow2Plan &pl, float2 *scratch, const float2 *gp, int bh0, int nbh, hipStream_t st, bool alone);
 // g [BH, L/2+1] -> gp [BH][N2][N1] in the big kernel's register order (P = 0: in bin order), scaled by 1/L and
 // extended to all L bins by Hermitian symmetry (real parts only at DC and Nyquist).
 hipError_t launch_gate_expand(const Pow2Plan &pl, const float2 *g, float2 *gp, int BH, hipStream_t st);

@@ -329,7 +329,7 @@ __device__ __forceinline__ void transpose16(float2 (&x)[16], int tau) {
 template <int P, int MODE, typename SC, bool SHFL = false>
 __global__ __launch_bounds__(256) void k_big(typename SC::elem_t *__restrict__ scr, const float2 *__restrict__ gp,
                                              const float2 *__restrict__ twN1, int N2, int ppw, int bh0,
-                                             int nplanes_xcd, int g_step, int aff) {
+                                             int nplanes_xcd, int g_step, int aff, int through) {
     static_assert(P == 2 || P == 3, "N1 is 256 or 4096");
     constexpr int N1 = 1 << (4 * P), TPC = N1 / 16, CPI = 256 / TPC, COLW = N1 + N1 / 16;
     constexpr bool kCross = (P == 3);                // does the pass 0 <-> 1 exchange span waves?
@@ -378,6 +378,16 @@ __global__ __launch_bounds__(256) void k_big(typename SC::elem_t *__restrict__ s
     elem_t nx[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) nx[j] = col[tau + TPC * j];
+    // through: see through_store; for launches that have memory to themselves
+    auto store_column = [&](elem_t *to, const float2 (&x)[16]) {
+        if (through) {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) through_store(to + tau + TPC * j, SC::put(x[j]));
+        } else {
+#pragma unroll
+            for (int j = 0; j < 16; ++j) to[tau + TPC * j] = SC::put(x[j]);
+        }
+    };
     for (int c = ci; c < ppw; c += CPI) {
         float2 x[16];
 #pragma unroll
@@ -407,8 +417,7 @@ __global__ __launch_bounds__(256) void k_big(typename SC::elem_t *__restrict__ s
             for (int j = 0; j < 16; ++j) x[j] = cmul(x[j], G[j]);
         }
         if (MODE == 1) {
-#pragma unroll
-            for (int j = 0; j < 16; ++j) col[tau + TPC * j] = SC::put(x[j]);
+            store_column(col, x);
             if (kCross) __syncthreads();              // buf_f is rewritten by the next column
         } else {
             dft<16, true>(x);
@@ -424,8 +433,7 @@ __global__ __launch_bounds__(256) void k_big(typename SC::elem_t *__restrict__ s
 #pragma unroll
             for (int u = 1; u < 16; ++u) x[u] = cmulc(x[u], tw[0][u - 1]);
             dft<16, true>(x);
-#pragma unroll
-            for (int j = 0; j < 16; ++j) col[tau + TPC * j] = SC::put(x[j]);
+            store_column(col, x);
             if (kCross) __syncthreads();              // the next column's forward write reuses the buffer
         }
         col += (size_t)CPI * N1;
@@ -774,7 +782,7 @@ hipError_t launch_small_inv(const Pow2Plan &pl, int io, const float2 *scratch, v
 
 template <int P, int MODE, typename SC = ScrF32, bool SHFL = false>
 static hipError_t big_t(const Pow2Plan &pl, float2 *scr_v, const float2 *gp, int bh0, int nbh, bool shared_gate,
-                        hipStream_t st, int aff = 0, bool wide = false) {
+                        hipStream_t st, bool through, int aff = 0, bool wide = false) {
     constexpr int N1 = 1 << (4 * P), TPC = N1 / 16, CPI = 256 / TPC, COLW = N1 + N1 / 16;
     const size_t lds = (size_t)CPI * COLW * sizeof(float2);
     // pairs per workgroup; a multiple of CPI dividing 32.  `wide` (a call whose head groups alternate between two
@@ -789,39 +797,42 @@ static hipError_t big_t(const Pow2Plan &pl, float2 *scr_v, const float2 *gp, int
     const unsigned grid = (unsigned)nbh * pl.N2 * (32 / ppw);
     const int planes = nbh * pl.N2;                    // remapping needs the plane count to split 8 ways
     kern<<<dim3(grid), dim3(256), lds, st>>>(scr, gp, pl.twN1, pl.N2, ppw, bh0, planes % 8 == 0 ? planes : 0,
-                                             shared_gate ? 0 : 1, aff);
+                                             shared_gate ? 0 : 1, aff, through);
     return hipGetLastError();
 }
 
 hipError_t launch_big(const Pow2Plan &pl, float2 *scratch, const float2 *gp, int bh0, int nbh, int mode,
                       hipStream_t st, bool shared_gate, bool scr16, bool affine, bool wide) {
+    // through_store only where the launch has memory to itself (mixer, us, plain / through: one head of fp32 rows at 16384 32.6 / 30.8, 16
+    // at 6144 34.1 / 33.0; on two streams 512 heads of bf16 rows at 3072 347 / 350, 128 at 20480 579 / 587)
+    const bool alone = !wide;
     const bool shfl = option(SPECTRE_OPT_LANE_SHUFFLES) != 0 && mode == 0 && !scr16;
     if (affine) {                                      // the mixer's forward-gate-inverse pass, fp32 scratch
         if (mode != 0 || scr16 || nbh % 8 != 0) return hipErrorInvalidValue;
-        if (pl.P == 2) return shfl ? big_t<2, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st, nbh)
-                                   : big_t<2, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, nbh);
-        if (pl.P == 3) return shfl ? big_t<3, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st, nbh)
-                                   : big_t<3, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, nbh);
+        if (pl.P == 2) return shfl ? big_t<2, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone, nbh)
+                                   : big_t<2, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone, nbh);
+        if (pl.P == 3) return shfl ? big_t<3, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone, nbh)
+                                   : big_t<3, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone, nbh);
         return hipErrorInvalidValue;
     }
     if (shfl) {
-        if (pl.P == 2) return big_t<2, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st);
-        if (pl.P == 3) return big_t<3, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st);
+        if (pl.P == 2) return big_t<2, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
+        if (pl.P == 3) return big_t<3, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
         return hipErrorInvalidValue;
     }
     if (scr16) {                                       // the mixer's forward-gate-inverse pass only
         if (mode != 0) return hipErrorInvalidValue;
-        if (pl.P == 2) return big_t<2, 0, ScrBf16>(pl, scratch, gp, bh0, nbh, shared_gate, st);
-        if (pl.P == 3) return big_t<3, 0, ScrBf16>(pl, scratch, gp, bh0, nbh, shared_gate, st);
+        if (pl.P == 2) return big_t<2, 0, ScrBf16>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
+        if (pl.P == 3) return big_t<3, 0, ScrBf16>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
         return hipErrorInvalidValue;
     }
     if (pl.P == 2) {
-        if (mode == 0) return big_t<2, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st);
-        if (mode == 1) return big_t<2, 1>(pl, scratch, gp, bh0, nbh, shared_gate, st);
+        if (mode == 0) return big_t<2, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
+        if (mode == 1) return big_t<2, 1>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
     } else if (pl.P == 3) {
-        if (mode == 0) return big_t<3, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, 0, wide);
-        if (mode == 1) return big_t<3, 1>(pl, scratch, gp, bh0, nbh, shared_gate, st);
-        if (mode == 2) return big_t<3, 2>(pl, scratch, gp, bh0, nbh, shared_gate, st);
+        if (mode == 0) return big_t<3, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone, 0, wide);
+        if (mode == 1) return big_t<3, 1>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
+        if (mode == 2) return big_t<3, 2>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
     }
     return hipErrorInvalidValue;
 }
