@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <type_traits>
+
 namespace spectre {
 
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -16,6 +18,13 @@ __host__ __device__ __forceinline__ float2 cmulc(float2 a, float2 b) {  // a * c
     return make_float2(a.x * b.x + a.y * b.y, a.y * b.x - a.x * b.y);
 }
 __host__ __device__ __forceinline__ float2 cconj(float2 a) { return make_float2(a.x, -a.y); }
+
+// p + at bytes, p the same in every lane: the address goes into the instruction as a scalar base and a 32-bit offset.
+template <typename T>
+__device__ __forceinline__ T *lane_pointer(T *p, unsigned at) {
+    typedef typename std::conditional<std::is_const<T>::value, const char, char>::type byte_t;
+    return reinterpret_cast<T *>(reinterpret_cast<byte_t *>(p) + at);
+}
 
 // Streaming accesses for data that is touched once per kernel (the cache rows of a decode sweep,
 // the transform scratch): non-temporal loads and stores, which this GPU moves about 8 % faster

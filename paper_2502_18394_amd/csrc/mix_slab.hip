@@ -226,9 +226,15 @@ struct SlabPlan {
 };
 
 // STREAM: the rows pass the caches by.
-template <typename IO, int PP, int NT, int R0, int R1, int R2, bool DIRECT, bool STREAM>
-__global__ __launch_bounds__(NT) void k_mix_ct(const typename IO::pair_t *__restrict__ v, const float2 *__restrict__ g,
-                                               typename IO::pair_t *__restrict__ out, const float2 *__restrict__ roots_g,
+// HALF: the tensors hold `rows` <= L / 2 rows per sequence; the transform sees zeros behind them and only the first `rows` rows
+// of the result are kept (zero-padded linear convolution).  Otherwise rows = L.
+// Global addresses are one uniform base per row, table or head and one 32-bit offset of the lane.  As 64-bit products per lane
+// and row, with a test each, they were a fifth of the vector unit's time (a 64-bit multiply-add takes four slots), and the tests put
+// a branch around every load.  us, before / now: 768 heads of bf16 rows at 512 47 / 38, at 576 55 / 48, at 1024 115 / 101, of fp32 rows at
+// 784 95 / 82; B=256 H=12 L=196 fp32 62.0 / 56.5, bf16 41.2 / 36.0; the padded 197 of 768 heads 44.5 / 41.1 with its gate; one head of 1024 fp32 7.1 / 6.6.
+template <typename IO, int PP, int NT, int R0, int R1, int R2, bool DIRECT, bool STREAM, bool HALF>
+__global__ __launch_bounds__(NT) void k_mix_ct(const typename IO::pair_t *v, const float2 *g,
+                                               typename IO::pair_t *out, const float2 *roots_g,
                                                int H, int bh0, int BH, int rows, int affine) {
     typedef SlabPlan<R0, R1, R2> Plan;
     constexpr int L = Plan::L, R = Plan::R, F = L / 2 + 1, S0 = Plan::S0, PAD = PP < 16 ? 1 : 0, kParts = 32 / PP;
@@ -248,42 +254,54 @@ __global__ __launch_bounds__(NT) void k_mix_ct(const typename IO::pair_t *__rest
     const int b = bh / H, h = bh % H;
     auto at = [&](int p) { return slab + (p + PAD * (p / R)) * PP + col; };
     const bool live = S0 * PP == NT || i0 < S0;
-    const size_t rs = (size_t)H * 32, base = ((size_t)b * rows * H + h) * 32 + part * PP + col;
-    typename IO::pair_t raw[R0];
-#pragma unroll
-    for (int j = 0; j < R0; ++j) {
-        const int l = i0 + S0 * j;
-        raw[j] = IO::zero();
-        if (live && l < rows) raw[j] = STREAM ? IO::load_stream(v + base + (size_t)l * rs) : v[base + (size_t)l * rs];
-    }
+    typedef typename IO::pair_t pair_t;
+    constexpr int kIn = HALF ? (R0 + 1) / 2 : R0;                    // the lane's rows i0 + S0 j that exist
+    const int n_rows = HALF ? rows : L;
+    const size_t base = ((size_t)b * n_rows * H + h) * 32 + part * PP;
+    // below 2^32: i0 < S0 <= 128, H < 2^16 and rows of 256 bytes
+    const unsigned lane_at = ((unsigned)(S0 * PP == NT ? i0 : min(i0, S0 - 1)) * (unsigned)(H * 32) + (unsigned)col) * (unsigned)sizeof(pair_t);
+    // loads return in order: the tables' entries first, so that the tables are built while the rows are under way, and all of
+    // them before the first is waited for (with __restrict__ pointers the compiler moves the rows' behind the tables' writes)
     const float2 *gh = g + (size_t)bh * F;
+    constexpr int kPos = DIRECT ? 1 : (L + NT - 1) / NT;
+    float2 rv[kPos], gv[kPos];
+    if constexpr (!DIRECT) {
+#pragma unroll
+        for (int i = 0; i < kPos; ++i) {
+            const int p = min(tid + NT * i, L - 1), k = Plan::bin(p / R, p % R);
+            rv[i] = *lane_pointer(roots_g, 8u * p);
+            gv[i] = *lane_pointer(gh, 8u * (2 * k <= L ? k : L - k));
+        }
+    }
+    pair_t raw[kIn];
+#pragma unroll
+    for (int j = 0; j < kIn; ++j) {                                  // in HALF, the sweep's first row for lanes beyond the last one, then zero
+        const int first = HALF ? min(S0 * j, n_rows - 1) : S0 * j;
+        const pair_t *src = v + base + (size_t)first * (H * 32);
+        src = lane_pointer(src, !HALF || i0 + S0 * j < n_rows ? lane_at : col * (unsigned)sizeof(pair_t));
+        raw[j] = STREAM ? IO::load_stream(src) : *src;
+    }
+    __builtin_amdgcn_sched_barrier(0);
     constexpr float scale = 1.0f / (float)L;
     auto gate_fix = [&](float2 val, int k) {                         // Hermitian extension; real at DC and Nyquist
-        const float im = (k == 0 || 2 * k == L) ? 0.0f : 2 * k > L ? -val.y : val.y;
-        return make_float2(val.x * scale, im * scale);
+        // on the bits: selections of what a load returns become branches around it
+        const uint32_t keep = (k == 0 || 2 * k == L) ? 0u : ~0u, sign = 2 * k > L ? 0x80000000u : 0u;
+        return make_float2(val.x * scale, __uint_as_float((__float_as_uint(val.y) & keep) ^ sign) * scale);
     };
     float2 tw[DIRECT ? R0 : 1], G[DIRECT ? kInner * R : 1];
     if constexpr (DIRECT) {
 #pragma unroll
-        for (int u = 1; u < R0; ++u) tw[u] = roots_g[live ? i0 * u : 0];
+        for (int u = 1; u < R0; ++u) tw[u] = *lane_pointer(roots_g, live ? 8u * i0 * u : 0u);
 #pragma unroll
         for (int q = 0; q < kInner; ++q) {
             const int blk = min((tid + NT * q) / PP, Plan::blocks - 1);
 #pragma unroll
             for (int u = 0; u < R; ++u) {
                 const int k = Plan::bin(blk, u);
-                G[q * R + u] = gh[2 * k <= L ? k : L - k];
+                G[q * R + u] = *lane_pointer(gh, 8u * (2 * k <= L ? k : L - k));
             }
         }
     } else {
-        constexpr int kPos = (L + NT - 1) / NT;
-        float2 rv[kPos], gv[kPos];
-#pragma unroll
-        for (int i = 0; i < kPos; ++i) {
-            const int p = min(tid + NT * i, L - 1), k = Plan::bin(p / R, p % R);
-            rv[i] = roots_g[p];
-            gv[i] = gh[2 * k <= L ? k : L - k];
-        }
 #pragma unroll
         for (int i = 0; i < kPos; ++i) {
             const int p = min(tid + NT * i, L - 1);
@@ -296,7 +314,10 @@ __global__ __launch_bounds__(NT) void k_mix_ct(const typename IO::pair_t *__rest
     if (live) {
         float2 x[R0];
 #pragma unroll
-        for (int j = 0; j < R0; ++j) x[j] = IO::unpack(raw[j]);
+        for (int j = 0; j < R0; ++j) {
+            x[j] = make_float2(0.f, 0.f);
+            if (j < kIn && (!HALF || i0 + S0 * j < n_rows)) x[j] = IO::unpack(raw[j < kIn ? j : 0]);
+        }
         small_dft<R0, false>(x);
 #pragma unroll
         for (int u = 0; u < R0; ++u) *at(i0 + S0 * u) = u == 0 ? x[0] : cmul(x[u], factor0(u));
@@ -309,7 +330,7 @@ __global__ __launch_bounds__(NT) void k_mix_ct(const typename IO::pair_t *__rest
         static_assert(NT % PP == 0 && NT / PP % R2 == 0, "a lane keeps its i over the blocks");
         const int i1 = i0 % R2;
 #pragma unroll
-        for (int u = 1; u < R1; ++u) tm[u] = DIRECT ? roots_g[i1 * u * R0] : roots[i1 * u * R0];
+        for (int u = 1; u < R1; ++u) tm[u] = DIRECT ? *lane_pointer(roots_g, 8u * i1 * u * R0) : roots[i1 * u * R0];
 #pragma unroll
         for (int q = 0; q < kMid; ++q) {
             const int blk = i0 / R2 + NT / PP / R2 * q, p = blk * R1 * R2 + i1;
@@ -361,11 +382,11 @@ __global__ __launch_bounds__(NT) void k_mix_ct(const typename IO::pair_t *__rest
         for (int u = 0; u < R0; ++u) x[u] = u == 0 ? *at(i0) : cmulc(*at(i0 + S0 * u), factor0(u));
         small_dft<R0, true>(x);
 #pragma unroll
-        for (int j = 0; j < R0; ++j) {
-            const int l = i0 + S0 * j;
-            if (l < rows) {
-                if (STREAM) IO::store_stream(out + base + (size_t)l * rs, IO::pack(x[j]));
-                else out[base + (size_t)l * rs] = IO::pack(x[j]);
+        for (int j = 0; j < kIn; ++j) {
+            pair_t *dst = lane_pointer(out + base + (size_t)(S0 * j) * (H * 32), lane_at);
+            if (!HALF || i0 + S0 * j < n_rows) {
+                if (STREAM) IO::store_stream(dst, IO::pack(x[j]));
+                else *dst = IO::pack(x[j]);
             }
         }
     }
@@ -446,11 +467,11 @@ static hipError_t mix_slab_t(const void *v, const float2 *g, void *out, const fl
     return hipGetLastError();
 }
 
-template <typename IO, int PP, int NT, int R0, int R1, int R2, bool DIRECT, bool STREAM = false>
+template <typename IO, int PP, int NT, int R0, int R1, int R2, bool DIRECT, bool STREAM, bool HALF>
 static hipError_t mix_ct_t(const void *v, const float2 *g, void *out, const float2 *roots, int B, int H, int rows,
                            hipStream_t st) {
     constexpr size_t lds = SlabPlan<R0, R1, R2>::lds(PP, DIRECT);
-    auto kern = k_mix_ct<IO, PP, NT, R0, R1, R2, DIRECT, STREAM>;
+    auto kern = k_mix_ct<IO, PP, NT, R0, R1, R2, DIRECT, STREAM, HALF>;
     if (lds > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -504,6 +525,8 @@ int slab_pairs_per_workgroup(int io, int BH, int L) {
 // four / eight pairs / 12 x 8 x 8 74 / 61 / 60; 896 as 28 x 32 / 14 x 8 x 8 on four / eight 90 / 74 / 68; 1024 as 16 x 16 x 4 / 32
 // x 32 / 16 x 8 x 8 on eight / four 96 / 94 / 100 / 76; 640 as 10 x 8 x 8 / 20 x 32 55 / 49; 400 as 20 x 20 on sixteen / four /
 // eight pairs, 10 x 8 x 5 42 / 41 / 37 / 40; 384 heads of 1280 as 16 x 16 x 5 / 10 x 16 x 8 / 20 x 8 x 8 108 / 95 / 75).
+// the lengths that also serve as data length of the padded convolution
+constexpr bool chirp_uses(int L) { return L != 144 && L != 196 && L != 576 && L != 784; }
 template <typename IO>
 static bool mix_ct(int L, const void *v, const float2 *g, void *out, const float2 *roots, int B, int H, int rows,
                    hipStream_t st, hipError_t *e) {
@@ -516,18 +539,25 @@ static bool mix_ct(int L, const void *v, const float2 *g, void *out, const float
     // 1300 315 / 296).
     const bool large = 64 * heads * rows * (long long)sizeof(typename IO::pair_t) > 100000000;
     const bool stream = large && ((reinterpret_cast<uintptr_t>(v) | reinterpret_cast<uintptr_t>(out)) & 127) == 0;
-#define SPECTRE_CT(PP, NT, R0, R1, R2, ...)                                                                             \
+    if (rows != L && 2 * rows > L) return false;
+#define SPECTRE_CT_RUN(PP, NT, R0, R1, R2, DIRECT, STREAM, HALF)                                                        \
     {                                                                                                                   \
-        *e = mix_ct_t<IO, PP, NT, R0, R1, R2, __VA_ARGS__>(v, g, out, roots, B, H, rows, st);                           \
+        *e = mix_ct_t<IO, PP, NT, R0, R1, R2, DIRECT, STREAM, HALF>(v, g, out, roots, B, H, rows, st);                  \
         return true;                                                                                                    \
     }
+#define SPECTRE_CT(PP, NT, R0, R1, R2, DIRECT, STREAM)                                                                  \
+    {                                                                                                                   \
+        if constexpr (chirp_uses(R0 * R1 * R2))                                                                         \
+            if (rows != L) SPECTRE_CT_RUN(PP, NT, R0, R1, R2, DIRECT, STREAM, true)                                     \
+        SPECTRE_CT_RUN(PP, NT, R0, R1, R2, DIRECT, STREAM, false)                                                       \
+    }
 #define SPECTRE_CT_FEW(PP, NT, R0, R1, R2) \
-    if (heads * (32 / PP) * (NT / 64) <= kSimds) SPECTRE_CT(PP, NT, R0, R1, R2, true)
+    if (heads * (32 / PP) * (NT / 64) <= kSimds) SPECTRE_CT(PP, NT, R0, R1, R2, true, false)
 #define SPECTRE_CT_LINES(PP, NT, R0, R1, R2)                                                                            \
     {                                                                                                                   \
         static_assert(PP * sizeof(typename IO::pair_t) % 128 == 0, "whole lines");                                      \
         if (stream) SPECTRE_CT(PP, NT, R0, R1, R2, false, true)                                                         \
-        SPECTRE_CT(PP, NT, R0, R1, R2, false)                                                                           \
+        SPECTRE_CT(PP, NT, R0, R1, R2, false, false)                                                                    \
     }
     switch (L) {
         case 144:
@@ -536,28 +566,29 @@ static bool mix_ct(int L, const void *v, const float2 *g, void *out, const float
             else SPECTRE_CT_LINES(16, 192, 12, 12, 1)
         case 196:
             SPECTRE_CT_FEW(4, 64, 14, 14, 1)
-            if (!bf && !large) SPECTRE_CT(16, 256, 14, 14, 1, false)
+            if (!bf && !large) SPECTRE_CT(16, 256, 14, 14, 1, false, false)
             SPECTRE_CT_LINES(32, 448, 14, 14, 1)
         case 256:
             SPECTRE_CT_FEW(4, 128, 8, 8, 4)
             if constexpr (bf) SPECTRE_CT_LINES(32, 512, 16, 16, 1)
             else SPECTRE_CT_LINES(16, 512, 8, 8, 4)
-        case 320: SPECTRE_CT(16, 256, 20, 16, 1, false)
-        case 400: SPECTRE_CT(8, 192, 20, 20, 1, false)
-        case 448: SPECTRE_CT_FEW(4, 256, 7, 8, 8) SPECTRE_CT(8, 512, 7, 8, 8, false)
-        case 512: SPECTRE_CT(8, 512, 8, 8, 8, false)
-        case 576: SPECTRE_CT_FEW(4, 192, 12, 12, 4) SPECTRE_CT(8, 192, 24, 24, 1, false)
-        case 640: SPECTRE_CT(8, 256, 20, 32, 1, false)
-        case 768: SPECTRE_CT_FEW(4, 256, 12, 8, 8) SPECTRE_CT(8, 512, 12, 8, 8, false)
-        case 784: SPECTRE_CT_FEW(4, 256, 14, 7, 8) SPECTRE_CT(8, 448, 14, 7, 8, false)
-        case 896: SPECTRE_CT_FEW(4, 256, 14, 8, 8) SPECTRE_CT(8, 512, 14, 8, 8, false)
-        case 1024: SPECTRE_CT_FEW(2, 256, 8, 16, 8) SPECTRE_CT(4, 256, 16, 8, 8, false)
-        case 1280: SPECTRE_CT_FEW(4, 256, 20, 8, 8) SPECTRE_CT(4, 256, 20, 8, 8, false)
-        case 1536: SPECTRE_CT_FEW(2, 256, 12, 16, 8) SPECTRE_CT(4, 256, 24, 8, 8, false)
-        case 1792: SPECTRE_CT_FEW(2, 256, 14, 16, 8) SPECTRE_CT(4, 512, 14, 16, 8, false)
-        case 2048: SPECTRE_CT(4, 512, 16, 16, 8, false)
+        case 320: SPECTRE_CT(16, 256, 20, 16, 1, false, false)
+        case 400: SPECTRE_CT(8, 192, 20, 20, 1, false, false)
+        case 448: SPECTRE_CT_FEW(4, 256, 7, 8, 8) SPECTRE_CT(8, 512, 7, 8, 8, false, false)
+        case 512: SPECTRE_CT(8, 512, 8, 8, 8, false, false)
+        case 576: SPECTRE_CT_FEW(4, 192, 12, 12, 4) SPECTRE_CT(8, 192, 24, 24, 1, false, false)
+        case 640: SPECTRE_CT(8, 256, 20, 32, 1, false, false)
+        case 768: SPECTRE_CT_FEW(4, 256, 12, 8, 8) SPECTRE_CT(8, 512, 12, 8, 8, false, false)
+        case 784: SPECTRE_CT_FEW(4, 256, 14, 7, 8) SPECTRE_CT(8, 448, 14, 7, 8, false, false)
+        case 896: SPECTRE_CT_FEW(4, 256, 14, 8, 8) SPECTRE_CT(8, 512, 14, 8, 8, false, false)
+        case 1024: SPECTRE_CT_FEW(2, 256, 8, 16, 8) SPECTRE_CT(4, 256, 16, 8, 8, false, false)
+        case 1280: SPECTRE_CT_FEW(4, 256, 20, 8, 8) SPECTRE_CT(4, 256, 20, 8, 8, false, false)
+        case 1536: SPECTRE_CT_FEW(2, 256, 12, 16, 8) SPECTRE_CT(4, 256, 24, 8, 8, false, false)
+        case 1792: SPECTRE_CT_FEW(2, 256, 14, 16, 8) SPECTRE_CT(4, 512, 14, 16, 8, false, false)
+        case 2048: SPECTRE_CT(4, 512, 16, 16, 8, false, false)
         default: return false;
     }
+#undef SPECTRE_CT_RUN
 #undef SPECTRE_CT
 #undef SPECTRE_CT_FEW
 #undef SPECTRE_CT_LINES
