@@ -34,12 +34,19 @@ template <> struct RowTile<IoBf16> { static constexpr int kPairs = 32, kStride =
 template <> struct RowTile<IoF32> { static constexpr int kPairs = 16, kStride = 18; };
 template <typename IO> struct TileStride { static constexpr int value = RowTile<IO>::kStride; };
 
+// The addresses of the row kernels are a scalar base per row, plane or block and one 32-bit offset of the lane (lane_pointer): as
+// 64-bit products per lane and row they were a quarter of these kernels' vector time.
+//
 // small_fwd: grid (N1/TT * 32/PW, nbh); block PW*TT threads, PW = RowTile<IO>::kPairs.  Reads the N2*TT rows
 // {t1_0 + r + N1*t2} of one head (PW pairs each, one 128-byte segment per row),
 // stages them in LDS, then lane (pair p, t1_local) runs the N2-point DFT over t2.
 // ring != nullptr (pre-fill of an empty Prefix-FFT cache): every row read is also copied, as fp32, to row l of head bh
 // of the value ring buffer ring [B*H][N1 * N2][32 pairs] - the rows then cross HBM once for both purposes.
-template <int N2, int TT, typename IO, typename SC>
+// PART: fewer rows than the transform, or a ring.  Addresses stay per lane there: as scalar ones the row loads and the stores to ring and
+// scratch come in denser bursts, which memory moves more slowly (20011 tokens, B = 8 H = 32 N = 32768, 2760 -> 2815 us; mixer of
+// 2 x 8 heads at 5000 105 -> 106).  Whole transforms gain: mixer of 8 heads of fp32 rows at 8192 29.1 -> 26.7 us, 32 at 24576 233 ->
+// 225, at 131072 1139 -> 1105, of bf16 rows at 65536 517 -> 505.
+template <int N2, int TT, typename IO, typename SC, bool PART>
 __global__ __launch_bounds__(RowTile<IO>::kPairs * TT) void k_small_fwd(const typename IO::pair_t *__restrict__ v,
                                                        typename SC::elem_t *__restrict__ scr,
                                                        const float2 *__restrict__ twL, int rows, int H,
@@ -56,14 +63,21 @@ __global__ __launch_bounds__(RowTile<IO>::kPairs * TT) void k_small_fwd(const ty
     {
         const int lp = tid % PW, r = tid / PW;
         pair_t val[N2];
+        if (!PART) {
+            const unsigned lane_at = (unsigned)(r * H * 32 + lp) * (unsigned)sizeof(pair_t);   // r < 16
 #pragma unroll
-        for (int t2 = 0; t2 < N2; ++t2) {
-            const int l = t1_0 + r + N1 * t2;
-            val[t2] = (l < rows) ? IO::load_stream(v + (((size_t)b * rows + l) * H + h) * 32 + p0 + lp) : IO::zero();
+            for (int t2 = 0; t2 < N2; ++t2)
+                val[t2] = IO::load_stream(lane_pointer(v + (((size_t)b * rows + t1_0 + N1 * t2) * H + h) * 32 + p0, lane_at));
+        } else {                                                     // zeros behind the last row
+#pragma unroll
+            for (int t2 = 0; t2 < N2; ++t2) {
+                const int l = t1_0 + r + N1 * t2;
+                val[t2] = (l < rows) ? IO::load_stream(v + (((size_t)b * rows + l) * H + h) * 32 + p0 + lp) : IO::zero();
+            }
         }
 #pragma unroll
         for (int t2 = 0; t2 < N2; ++t2) lds[(t2 * TT + r) * S + lp] = val[t2];
-        if (ring) {
+        if (PART && ring) {
 #pragma unroll
             for (int t2 = 0; t2 < N2; ++t2) {
                 const int l = t1_0 + r + N1 * t2;
@@ -77,12 +91,14 @@ __global__ __launch_bounds__(RowTile<IO>::kPairs * TT) void k_small_fwd(const ty
 #pragma unroll
     for (int t2 = 0; t2 < N2; ++t2) x[t2] = IO::unpack(lds[(t2 * TT + tl) * S + p]);
     small_dft<N2, false>(x);
-    typename SC::elem_t *dst = scr + (((size_t)bhl * N2) * 32 + p0 + p) * N1 + t1;
+    typename SC::elem_t *dst = scr + (((size_t)bhl * N2) * 32 + p0) * N1 + t1_0, *own = dst + (size_t)p * N1 + tl;
+    const unsigned scr_at = (unsigned)(p * N1 + tl) * (unsigned)sizeof(typename SC::elem_t);
     const SmallTwiddles<N2, std::is_same<SC, ScrF32Fine>::value> tw(twL, t1);
 #pragma unroll
     for (int k2 = 0; k2 < N2; ++k2) {
         const float2 y = (k2 == 0) ? x[0] : cmul(x[k2], tw(k2));
-        dst[(size_t)k2 * 32 * N1] = SC::put(y);
+        if (PART) own[(size_t)k2 * 32 * N1] = SC::put(y);
+        else *lane_pointer(dst + (size_t)k2 * 32 * N1, scr_at) = SC::put(y);
     }
 }
 
@@ -115,10 +131,17 @@ __global__ __launch_bounds__(512) void k_small_fwd_proj(const uint32_t *__restri
     {
         const int lp = tid & 31, r = tid >> 5;
         uint32_t val[N2];
+        const unsigned lane_at = 4u * (r * H * 32 + lp);                 // r < 16
+        auto row = [&](int t2) { return x + (((size_t)b * rows + t1_0 + N1 * t2) * H + h) * 32; };
+        if (t1_0 + TT + N1 * (N2 - 1) <= rows) {
 #pragma unroll
-        for (int t2 = 0; t2 < N2; ++t2) {
-            const int l = t1_0 + r + N1 * t2;
-            val[t2] = (l < rows) ? IoBf16::load_stream(x + (((size_t)b * rows + l) * H + h) * 32 + lp) : 0u;
+            for (int t2 = 0; t2 < N2; ++t2) val[t2] = IoBf16::load_stream(lane_pointer(row(t2), lane_at));
+        } else {
+#pragma unroll
+            for (int t2 = 0; t2 < N2; ++t2) {
+                val[t2] = 0u;
+                if (t1_0 + r + N1 * t2 < rows) val[t2] = IoBf16::load_stream(lane_pointer(row(t2), lane_at));
+            }
         }
 #pragma unroll
         for (int t2 = 0; t2 < N2; ++t2) lds[(t2 * TT + r) * S + lp] = val[t2];
@@ -166,12 +189,13 @@ __global__ __launch_bounds__(512) void k_small_fwd_proj(const uint32_t *__restri
 #pragma unroll
     for (int t2 = 0; t2 < N2; ++t2) xv[t2] = IoBf16::unpack(lds[(t2 * TT + tl) * S + p]);
     small_dft<N2, false>(xv);
-    float2 *dst = scr + (((size_t)bhl * N2) * 32 + p) * N1 + t1;
+    float2 *dst = scr + (size_t)bhl * N2 * 32 * N1 + t1_0;
+    const unsigned scr_at = 8u * (p * N1 + tl);
     const SmallTwiddles<N2, std::is_same<SC, ScrF32Fine>::value> tw(twL, t1);
 #pragma unroll
     for (int k2 = 0; k2 < N2; ++k2) {
         const float2 y = (k2 == 0) ? xv[0] : cmul(xv[k2], tw(k2));
-        dst[(size_t)k2 * 32 * N1] = y;
+        *lane_pointer(dst + (size_t)k2 * 32 * N1, scr_at) = y;
     }
 }
 
@@ -199,10 +223,11 @@ __global__ __launch_bounds__(RowTile<IO>::kPairs * TT) void k_small_inv(const ty
     const int bh = bh0 + bhl, b = bh / H, h = bh % H;
     {
         const int tl = tid % TT, p = tid / TT, t1 = t1_0 + tl;
-        const typename SC::elem_t *src = scr + (((size_t)bhl * N2) * 32 + p0 + p) * N1 + t1;
+        const typename SC::elem_t *src = scr + (((size_t)bhl * N2) * 32 + p0) * N1 + t1_0;
+        const unsigned scr_at = (unsigned)(p * N1 + tl) * (unsigned)sizeof(typename SC::elem_t);
         typename SC::elem_t raw[N2];
 #pragma unroll
-        for (int k2 = 0; k2 < N2; ++k2) raw[k2] = src[(size_t)k2 * 32 * N1];
+        for (int k2 = 0; k2 < N2; ++k2) raw[k2] = *lane_pointer(src + (size_t)k2 * 32 * N1, scr_at);
         float2 y[N2];
 #pragma unroll
         for (int k2 = 0; k2 < N2; ++k2) y[k2] = SC::get(raw[k2]);
@@ -215,6 +240,7 @@ __global__ __launch_bounds__(RowTile<IO>::kPairs * TT) void k_small_inv(const ty
     }
     __syncthreads();
     const int lp = tid % PW, r = tid / PW;
+    // the rows' addresses stay per lane: as scalar ones too, the stores cost 32 heads of 131072 rows on two streams 0.3 %
 #pragma unroll
     for (int t2 = 0; t2 < N2; ++t2) {
         const int l = t1_0 + r + N1 * t2;
@@ -669,7 +695,11 @@ template <int N2, int TT, typename IO, typename SC>
 static hipError_t small_fwd_t(const Pow2Plan &pl, const void *v, void *scr_v, int rows, int H, int bh0,
                               int nbh, hipStream_t st, int aff, float2 *ring) {
     const size_t lds = (size_t)N2 * TT * TileStride<IO>::value * sizeof(typename IO::pair_t);
-    auto kern = k_small_fwd<N2, TT, IO, SC>;
+    const bool part = ring || rows < pl.N1 * N2;
+    if (part && std::is_same<SC, ScrBf16>::value) return hipErrorInvalidValue;                 // mixers alone take that scratch
+    auto kern = k_small_fwd<N2, TT, IO, SC, false>;
+    if constexpr (!std::is_same<SC, ScrBf16>::value)
+        if (part) kern = k_small_fwd<N2, TT, IO, SC, true>;
     typename SC::elem_t *scr = static_cast<typename SC::elem_t *>(scr_v);
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;

@@ -44,14 +44,14 @@ struct SmallTwiddles {
     __device__ __forceinline__ SmallTwiddles(const float2 *__restrict__ twL, int t1) {
         if (FINE) {
 #pragma unroll
-            for (int b = 0; b < 4; ++b) lo[b] = (b && b < N2) ? twL[t1 * b] : make_float2(1.f, 0.f);
+            for (int b = 0; b < 4; ++b) lo[b] = (b && b < N2) ? *lane_pointer(twL, 8u * (t1 * b)) : make_float2(1.f, 0.f);
 #pragma unroll
-            for (int a = 0; a < 8; ++a) hi[a] = (a && 4 * a < N2) ? twL[t1 * 4 * a] : make_float2(1.f, 0.f);
+            for (int a = 0; a < 8; ++a) hi[a] = (a && 4 * a < N2) ? *lane_pointer(twL, 8u * (t1 * 4 * a)) : make_float2(1.f, 0.f);
             return;
         }
         float2 p[5];
 #pragma unroll
-        for (int e = 0; e < 5; ++e) p[e] = ((1 << e) < N2) ? twL[t1 << e] : make_float2(1.f, 0.f);
+        for (int e = 0; e < 5; ++e) p[e] = ((1 << e) < N2) ? *lane_pointer(twL, 8u * (t1 << e)) : make_float2(1.f, 0.f);
         lo[0] = make_float2(1.f, 0.f);
         lo[1] = p[0];
         lo[2] = p[1];
