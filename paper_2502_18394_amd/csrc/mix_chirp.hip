@@ -92,16 +92,35 @@ struct ChirpColumn {
     int t, tau;
     float2 tw[15];                                                   // W_256^(tau u)
     __device__ __forceinline__ float2 *own() const { return buf + (t >> 4) * COLW; }
-    template <typename F>
-    __device__ __forceinline__ void rows_fwd(const float2 *twM, F element) {
-        for (int t1 = t; t1 < 256; t1 += NL) {
-            float2 x[N2];
+    // the lane's rows in batches of kBatch whose loads are all under way before the first is used: one row at a time, each waited
+    // for memory on its own
+    static constexpr int kTrips = (256 + NL - 1) / NL, kBatch = N2 == 1 ? 8 : N2 == 2 ? 4 : N2 == 3 ? 3 : N2 == 6 || N2 == 7 ? 1 : 2;
+    template <typename L, typename F>
+    __device__ __forceinline__ void rows_fwd(const float2 *twM, L load, F element) {
+#pragma unroll 1
+        for (int q0 = 0; q0 < kTrips; q0 += kBatch) {
+            decltype(load(0)) raw[kBatch][N2];
+            float2 tw_row[kBatch][N2];
 #pragma unroll
-            for (int j = 0; j < N2; ++j) x[j] = element(t1 + 256 * j);
-            small_dft<N2, false>(x);
+            for (int q = 0; q < kBatch; ++q) {
+                const int t1 = min(t + NL * (q0 + q), 255);
 #pragma unroll
-            for (int k2 = 0; k2 < N2; ++k2)
-                buf[k2 * COLW + t1 + (t1 >> 4)] = k2 == 0 ? x[0] : cmul(x[k2], twM[t1 * k2]);
+                for (int j = 0; j < N2; ++j) raw[q][j] = load(t1 + 256 * j);
+#pragma unroll
+                for (int k2 = 1; k2 < N2; ++k2) tw_row[q][k2] = *lane_pointer(twM, 8u * (t1 * k2));
+            }
+#pragma unroll
+            for (int q = 0; q < kBatch; ++q) {
+                const int t1 = t + NL * (q0 + q);
+                float2 x[N2];
+#pragma unroll
+                for (int j = 0; j < N2; ++j) x[j] = element(min(t1, 255) + 256 * j, raw[q][j]);
+                small_dft<N2, false>(x);
+                if (256 % NL == 0 || t1 < 256) {
+#pragma unroll
+                    for (int k2 = 0; k2 < N2; ++k2) buf[k2 * COLW + t1 + (t1 >> 4)] = k2 == 0 ? x[0] : cmul(x[k2], tw_row[q][k2]);
+                }
+            }
         }
     }
     __device__ __forceinline__ void cols_fwd(float2 (&y)[16]) {
@@ -159,31 +178,53 @@ __global__ __launch_bounds__(16 * N2 * kChirpHeads<N2>) void k_chirp_lds(const f
 #pragma unroll
     for (int j = 0; j < 16; ++j) f[j] = filt[256 * k2 + 16 * j + tau];
 
-    col.rows_fwd(twM, [&](int k) {
-        if (k >= L) return make_float2(0.f, 0.f);
-        float2 ge = gh[2 * k <= L ? k : L - k];
-        if (2 * k > L) ge.y = -ge.y;
-        if (k == 0 || 2 * k == L) ge.y = 0.f;
-        return cmul(ge, w[k]);
-    });
+    struct GateTimesChirp {
+        float2 g, w;
+    };
+    col.rows_fwd(twM,
+        [&](int k) {
+            const int at = min(k, L - 1);
+            return GateTimesChirp{gh[2 * at <= L ? at : L - at], *lane_pointer(w, 8u * at)};
+        },
+        [&](int k, GateTimesChirp v) {
+            if (k >= L) return make_float2(0.f, 0.f);
+            if (2 * k > L) v.g.y = -v.g.y;
+            if (k == 0 || 2 * k == L) v.g.y = 0.f;
+            return cmul(v.g, v.w);
+        });
     __syncthreads();
     col.cols_fwd(y);
 #pragma unroll
     for (int j = 0; j < 16; ++j) y[j] = cmul(y[j], f[j]);
     col.cols_inv(y);
     __syncthreads();
-    for (int t1 = t; t1 < 256; t1 += Col::NL) {
-        float2 x[N2];
+#pragma unroll 1
+    for (int q0 = 0; q0 < Col::kTrips; q0 += Col::kBatch) {
+        float2 tw_row[Col::kBatch][N2], wm[Col::kBatch][N2];
 #pragma unroll
-        for (int q = 0; q < N2; ++q) {
-            const float2 b = col.buf[q * Col::COLW + t1 + (t1 >> 4)];
-            x[q] = q == 0 ? b : cmulc(b, twM[t1 * q]);
+        for (int q = 0; q < Col::kBatch; ++q) {
+            const int t1 = min(t + Col::NL * (q0 + q), 255);
+#pragma unroll
+            for (int j = 0; j < N2; ++j) {
+                if (j) tw_row[q][j] = *lane_pointer(twM, 8u * (t1 * j));
+                wm[q][j] = *lane_pointer(w, 8u * min(t1 + 256 * j, L - 1));
+            }
         }
-        small_dft<N2, true>(x);
 #pragma unroll
-        for (int j = 0; j < N2; ++j) {
-            const int m = t1 + 256 * j;
-            if (m < L) kap[m] = (w[m].x * x[j].x - w[m].y * x[j].y) * (1.0f / (float)L);
+        for (int q = 0; q < Col::kBatch; ++q) {
+            const int t1 = t + Col::NL * (q0 + q), at = min(t1, 255);
+            float2 x[N2];
+#pragma unroll
+            for (int j = 0; j < N2; ++j) {
+                const float2 b = col.buf[j * Col::COLW + at + (at >> 4)];
+                x[j] = j == 0 ? b : cmulc(b, tw_row[q][j]);
+            }
+            small_dft<N2, true>(x);
+#pragma unroll
+            for (int j = 0; j < N2; ++j) {
+                const int m = t1 + 256 * j;
+                if (t1 < 256 && m < L) kap[m] = (wm[q][j].x * x[j].x - wm[q][j].y * x[j].y) * (1.0f / (float)L);
+            }
         }
     }
     __syncthreads();
@@ -213,7 +254,7 @@ __global__ __launch_bounds__(16 * N2 * kChirpHeads<N2>) void k_chirp_lds(const f
             }
         }
     } else {
-        col.rows_fwd(twM, extended);
+        col.rows_fwd(twM, extended, [](int, float2 v) { return v; });
         __syncthreads();
         col.cols_fwd(y);
 #pragma unroll
