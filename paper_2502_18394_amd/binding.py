@@ -120,6 +120,20 @@ def _stream(stream):
     return ctypes.c_void_p(stream.cuda_stream)
 
 
+def _raw_stream(stream):
+    """The same as a plain integer, for the functions whose argument types are declared."""
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream
+
+
+def _given(ws):
+    """(address, bytes) of the caller's workspace from its first 256-byte boundary on."""
+    at = ws.data_ptr()
+    off = -at % 256
+    return at + off, max(0, ws.numel() * ws.element_size() - off)
+
+
 def _workspace(nbytes, device, ws):
     nbytes = max(int(nbytes), 256)
     size = 0 if ws is None else ws.numel() * ws.element_size()
@@ -176,13 +190,19 @@ def mix_forward(v, g, out=None, ws=None, stream=None, flags=0):
     B, L, H, d = v.shape
     prepare(L, d)
     io = _dtype_code(v)
-    if g.dtype != torch.complex64 or tuple(g.shape) != (B, H, L // 2 + 1):
+    if g.dtype != torch.complex64 or g.shape != (B, H, L // 2 + 1):
         raise ValueError("g must be complex64 [B,H,L//2+1]")
     if out is None:
         out = torch.empty_like(v)
+    args = (_ptr(v, "v"), _ptr(g, "g"), _ptr(out, "out"), B, L, H, d, io, flags)
+    st = _raw_stream(stream)
+    if ws is not None:                     # the library checks its size; asking for the size first is a call of its own
+        rc = lib().spectre_mix_forward_ex(*args, *_given(ws), st)
+        if rc != EWORKSPACE:
+            _check(rc)
+            return out
     ws, wsp, wsn = _workspace(mix_workspace_bytes(B, L, H, d, io), v.device, ws)
-    _check(lib().spectre_mix_forward_ex(_ptr(v, "v"), _ptr(g, "g"), _ptr(out, "out"), B, L, H, d, io, flags, wsp, wsn,
-                                        _stream(stream)))
+    _check(lib().spectre_mix_forward_ex(*args, wsp, wsn, st))
     return out
 
 
@@ -270,9 +290,15 @@ def gate(q, P, inv_count, pooled=False, phase_pos=0, g_out=None, ws=None, stream
         raise ValueError("d mismatch")
     if g_out is None:
         g_out = torch.empty((B, H, P.F), dtype=torch.complex64, device=q.device)
+    args = (_ptr(q, "q"), 1 if pooled else 0, code, inv_count, ctypes.byref(P.c), B, L, H, int(phase_pos), _ptr(g_out, "g_out"))
+    st = _raw_stream(stream)
+    if ws is not None:                     # as in mix_forward
+        rc = lib().spectre_gate(*args, *_given(ws), st)
+        if rc != EWORKSPACE:
+            _check(rc)
+            return g_out
     ws, wsp, wsn = _workspace(gate_workspace_bytes(B, L, H, P), q.device, ws)
-    _check(lib().spectre_gate(_ptr(q, "q"), 1 if pooled else 0, code, inv_count, ctypes.byref(P.c), B, L, H,
-                              int(phase_pos), _ptr(g_out, "g_out"), wsp, wsn, _stream(stream)))
+    _check(lib().spectre_gate(*args, wsp, wsn, st))
     return g_out
 
 

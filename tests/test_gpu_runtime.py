@@ -230,3 +230,15 @@ def test_two_stream_call_is_ordered_on_the_callers_stream():
             out.zero_()
     s.synchronize()
     assert torch.equal(snap.view(torch.int16), ref.view(torch.int16))
+
+
+@pytest.mark.parametrize("L,H", [(512, 2), (12288, 1)])   # a mixer that uses no workspace, and one whose columns lie in it
+@pytest.mark.parametrize("size", [0, 100])                # none, and less than its first 256-byte boundary may be away
+def test_workspaces_that_are_too_small_are_replaced(L, H, size):
+    from paper_2502_18394_amd import binding
+    P = binding.GateParams(synth.gate_params(71, H, 64, L))
+    v = torch.randn(1, L, H, 64, device="cuda")
+    small = torch.empty(size + 1, dtype=torch.uint8, device="cuda")[1:]
+    g = binding.gate(v, P, 1.0 / L)
+    assert torch.equal(binding.gate(v, P, 1.0 / L, ws=small), g)
+    assert torch.equal(binding.mix_forward(v, g, ws=small), binding.mix_forward(v, g))
