@@ -505,17 +505,19 @@ int slab_pairs_per_workgroup(int io, int BH, int L) {
 // Most have two forms.
 //   few heads : four pairs per workgroup (1024, 1536 and 1792: two), every lane with its own loads of factors and gate, while the
 //               launch has at most a wave per SIMD: until then a call costs what one workgroup does, and above it the
-//               narrow pieces of rows and the repeated loads do.
+//               narrow pieces of rows and the repeated loads do.  Half a wave per SIMD for the two-pass lengths (80 heads, bf16: 144
+//               points 4.3 / 4.1 us, 196 5.7 / 5.4; 64 heads 4.0 / 4.0 and 4.9 / 5.1).
 //   otherwise : the tables in LDS, at the pairs per workgroup that are fastest for many heads.
-// Kernel alone, bf16 rows, us, few form / other form:
-//   heads       1             8            32           128           768       few up to
-//    196    5.4 /  6.1    5.5 /  6.2    5.6 /  6.3    6.6 /  6.7    19.0 / 14.4    128
-//    256    5.1 /  6.2    5.2 /  6.4    5.4 /  6.5    7.3 /  6.9    24.4 / 16.4     64
-//    448    5.0 /  5.4    5.1 /  5.5    5.5 /  5.8    9.8 /  9.1    41.6 / 32.5     32
-//    896    7.4 /  8.6    7.5 /  8.7    8.7 /  9.3   18.6 / 15.5    83.7 / 70.0     32
-//   1024    7.5 /  7.9    7.7 /  8.1   10.5 /  9.5   29.1 / 21.3     161 / 87.8     16
-//   1280    9.5 / 10.1    9.7 / 10.4   11.5 / 12.1   26.8 / 27.5     140 /  132     32
-//   1536    8.9 / 10.6    9.1 / 10.7   13.4 / 12.8   47.5 / 31.8     437 /  221     16
+// Kernel alone over rotating buffers, bf16 rows, us, few form / other form:
+//   heads       1             8            32            64           128           768       few up to
+//    196    3.9 /  4.6    4.0 /  4.8    4.2 /  4.8    4.9 /  5.1    6.6 /  5.7    25.2 / 15.1     64
+//    256    3.6 /  4.8    3.7 /  5.0    4.1 /  5.1    5.3 /  5.7    6.7 /  6.2    29.1 / 17.4     64
+//    448    4.1 /  4.5    4.2 /  4.6    5.1 /  5.4    6.8 /  6.0   10.4 /  8.8    54.2 / 36.9     32
+//    896    6.4 /  7.3    6.6 /  8.0    8.4 /  8.9   10.9 / 10.2   21.6 / 16.5     132 / 82.2     32
+//   1024    6.3 /  7.3    6.6 /  7.8   10.2 /  9.4   18.1 / 12.9   32.3 / 22.1     215 /  138     16
+//   1280    8.9 /  9.3    9.1 /  9.5   11.6 / 11.7   18.4 / 18.1   33.8 / 31.6     203 /  175     32
+//   1536    8.4 / 10.0    8.5 / 10.2   13.4 / 12.9   28.5 / 20.5   52.2 / 35.8     359 /  213     16
+// The figures below are of the kernel with per-lane addresses, which cost both sides alike.
 // None for few: 512 (5.3 / 5.4, 5.4 / 5.5, 6.1 / 5.8), 2048 (two pairs 11.1 / 10.6 at one head), and the two passes of radix 16
 // to 32 of 320, 400 and 640 (four pairs at one head 7.0 / 7.5, 7.1 / 7.9 and 7.5 / 8.1, but 9.7 / 8.5 at 48 of 400; three shorter
 // passes would take 5.8 at 320 and 400, with 3 and 5 % more error).
@@ -552,7 +554,7 @@ static bool mix_ct(int L, const void *v, const float2 *g, void *out, const float
         SPECTRE_CT_RUN(PP, NT, R0, R1, R2, DIRECT, STREAM, false)                                                       \
     }
 #define SPECTRE_CT_FEW(PP, NT, R0, R1, R2) \
-    if (heads * (32 / PP) * (NT / 64) <= kSimds) SPECTRE_CT(PP, NT, R0, R1, R2, true, false)
+    if (heads * (32 / PP) * (NT / 64) <= (R2 > 1 ? kSimds : kSimds / 2)) SPECTRE_CT(PP, NT, R0, R1, R2, true, false)
 #define SPECTRE_CT_LINES(PP, NT, R0, R1, R2)                                                                            \
     {                                                                                                                   \
         static_assert(PP * sizeof(typename IO::pair_t) % 128 == 0, "whole lines");                                      \

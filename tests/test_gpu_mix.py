@@ -264,7 +264,7 @@ def test_lengths_of_compile_time_radices(oracle, options, B, L, H, io):
 
 
 @pytest.mark.parametrize("io", ["f32", "bf16"])
-@pytest.mark.parametrize("L,most", [(144, 128), (196, 128), (256, 64), (448, 32), (576, 42), (768, 32), (784, 32), (896, 32),
+@pytest.mark.parametrize("L,most", [(144, 64), (196, 64), (144, 128), (196, 128), (256, 64), (448, 32), (576, 42), (768, 32), (784, 32), (896, 32),
                                     (1024, 16), (1280, 32), (1536, 16), (1792, 16)])
 def test_forms_for_few_and_for_many_heads(oracle, options, L, most, io):
     """The last call that takes the form for few heads and the first that takes the other, against the general kernel (bounds as
