@@ -19,9 +19,9 @@ __host__ __device__ __forceinline__ float2 cmulc(float2 a, float2 b) {  // a * c
 }
 __host__ __device__ __forceinline__ float2 cconj(float2 a) { return make_float2(a.x, -a.y); }
 
-// p + at bytes, p the same in every lane: the address goes into the instruction as a scalar base and a 32-bit offset.
-template <typename T>
-__device__ __forceinline__ T *lane_pointer(T *p, unsigned at) {
+// p + at bytes, p the same in every lane and at the lane's own: the address is formed from a scalar base, without a product.
+template <typename T, typename At>
+__device__ __forceinline__ T *lane_pointer(T *p, At at) {
     typedef typename std::conditional<std::is_const<T>::value, const char, char>::type byte_t;
     return reinterpret_cast<T *>(reinterpret_cast<byte_t *>(p) + at);
 }

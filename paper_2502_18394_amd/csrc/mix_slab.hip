@@ -228,11 +228,12 @@ struct SlabPlan {
 // STREAM: the rows pass the caches by.
 // HALF: the tensors hold `rows` <= L / 2 rows per sequence; the transform sees zeros behind them and only the first `rows` rows
 // of the result are kept (zero-padded linear convolution).  Otherwise rows = L.
-// Global addresses are one uniform base per row, table or head and one 32-bit offset of the lane.  As 64-bit products per lane
+// Global addresses are one uniform base per row, table or head and one offset of the lane.  As 64-bit products per lane
 // and row, with a test each, they were a fifth of the vector unit's time (a 64-bit multiply-add takes four slots), and the tests put
 // a branch around every load.  us, before / now: 768 heads of bf16 rows at 512 47 / 38, at 576 55 / 48, at 1024 115 / 101, of fp32 rows at
 // 784 95 / 82; B=256 H=12 L=196 fp32 62.0 / 56.5, bf16 41.2 / 36.0; the padded 197 of 768 heads 44.5 / 41.1 with its gate; one head of 1024 fp32 7.1 / 6.6.
-template <typename IO, int PP, int NT, int R0, int R1, int R2, bool DIRECT, bool STREAM, bool HALF>
+// WIDE: 64 bits for the lane's offset, where hundreds of thousands of heads make S0 rows 2^32 bytes (at 32 heads 1 to 4 % slower).
+template <typename IO, int PP, int NT, int R0, int R1, int R2, bool DIRECT, bool STREAM, bool HALF, bool WIDE>
 __global__ __launch_bounds__(NT) void k_mix_ct(const typename IO::pair_t *v, const float2 *g,
                                                typename IO::pair_t *out, const float2 *roots_g,
                                                int H, int bh0, int BH, int rows, int affine) {
@@ -258,8 +259,8 @@ __global__ __launch_bounds__(NT) void k_mix_ct(const typename IO::pair_t *v, con
     constexpr int kIn = HALF ? (R0 + 1) / 2 : R0;                    // the lane's rows i0 + S0 j that exist
     const int n_rows = HALF ? rows : L;
     const size_t base = ((size_t)b * n_rows * H + h) * 32 + part * PP;
-    // below 2^32: i0 < S0 <= 128, H < 2^16 and rows of 256 bytes
-    const unsigned lane_at = ((unsigned)(S0 * PP == NT ? i0 : min(i0, S0 - 1)) * (unsigned)(H * 32) + (unsigned)col) * (unsigned)sizeof(pair_t);
+    typedef typename std::conditional<WIDE, size_t, unsigned>::type at_t;
+    const at_t lane_at = ((at_t)(S0 * PP == NT ? i0 : min(i0, S0 - 1)) * (at_t)(H * 32) + (at_t)col) * (at_t)sizeof(pair_t);
     // loads return in order: the tables' entries first, so that the tables are built while the rows are under way, and all of
     // them before the first is waited for (with __restrict__ pointers the compiler moves the rows' behind the tables' writes)
     const float2 *gh = g + (size_t)bh * F;
@@ -278,7 +279,7 @@ __global__ __launch_bounds__(NT) void k_mix_ct(const typename IO::pair_t *v, con
     for (int j = 0; j < kIn; ++j) {                                  // in HALF, the sweep's first row for lanes beyond the last one, then zero
         const int first = HALF ? min(S0 * j, n_rows - 1) : S0 * j;
         const pair_t *src = v + base + (size_t)first * (H * 32);
-        src = lane_pointer(src, !HALF || i0 + S0 * j < n_rows ? lane_at : col * (unsigned)sizeof(pair_t));
+        src = lane_pointer(src, !HALF || i0 + S0 * j < n_rows ? lane_at : (at_t)col * (at_t)sizeof(pair_t));
         raw[j] = STREAM ? IO::load_stream(src) : *src;
     }
     __builtin_amdgcn_sched_barrier(0);
@@ -467,11 +468,11 @@ static hipError_t mix_slab_t(const void *v, const float2 *g, void *out, const fl
     return hipGetLastError();
 }
 
-template <typename IO, int PP, int NT, int R0, int R1, int R2, bool DIRECT, bool STREAM, bool HALF>
+template <typename IO, int PP, int NT, int R0, int R1, int R2, bool DIRECT, bool STREAM, bool HALF, bool WIDE>
 static hipError_t mix_ct_t(const void *v, const float2 *g, void *out, const float2 *roots, int B, int H, int rows,
                            hipStream_t st) {
     constexpr size_t lds = SlabPlan<R0, R1, R2>::lds(PP, DIRECT);
-    auto kern = k_mix_ct<IO, PP, NT, R0, R1, R2, DIRECT, STREAM, HALF>;
+    auto kern = k_mix_ct<IO, PP, NT, R0, R1, R2, DIRECT, STREAM, HALF, WIDE>;
     if (lds > 48 * 1024) {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -544,7 +545,13 @@ static bool mix_ct(int L, const void *v, const float2 *g, void *out, const float
     if (rows != L && 2 * rows > L) return false;
 #define SPECTRE_CT_RUN(PP, NT, R0, R1, R2, DIRECT, STREAM, HALF)                                                        \
     {                                                                                                                   \
-        *e = mix_ct_t<IO, PP, NT, R0, R1, R2, DIRECT, STREAM, HALF>(v, g, out, roots, B, H, rows, st);                  \
+        if constexpr (!DIRECT) {                                                                                        \
+            if ((long long)(R1 * R2) * H * 32 * (long long)sizeof(typename IO::pair_t) >= (1LL << 32)) {                \
+                *e = mix_ct_t<IO, PP, NT, R0, R1, R2, DIRECT, STREAM, HALF, true>(v, g, out, roots, B, H, rows, st);    \
+                return true;                                                                                            \
+            }                                                                                                           \
+        }                                                                                                               \
+        *e = mix_ct_t<IO, PP, NT, R0, R1, R2, DIRECT, STREAM, HALF, false>(v, g, out, roots, B, H, rows, st);           \
         return true;                                                                                                    \
     }
 #define SPECTRE_CT(PP, NT, R0, R1, R2, DIRECT, STREAM)                                                                  \

@@ -453,3 +453,21 @@ def test_shapes_around_the_route_boundaries(oracle, B, L, H, io):
     print(f"  rel_l2={err:.3e}", flush=True)
     assert err <= TOL[io]
     assert_close_elementwise(got, want, io, 16 * L)
+
+
+@pytest.mark.parametrize("H", [(1 << 19) - 1, 1 << 19])
+def test_rows_4_gb_apart(H):
+    """The last number of heads of 512 bf16 rows whose lanes' offsets fit 32 bits and the first that needs 64 (34 GB of rows): the first,
+    a middle and the last head bit for bit as in a call of a few of them."""
+    from paper_2502_18394_amd import binding
+    L, at = 512, [0, H // 2, H - 1]
+    v = torch.empty((1, L, H, 64), dtype=torch.bfloat16, device="cuda")
+    g = torch.empty((1, H, L // 2 + 1), dtype=torch.complex64, device="cuda")
+    few = torch.randn(1, L, 200, 64, device="cuda").to(torch.bfloat16)
+    gate = torch.view_as_complex(torch.randn(1, 200, L // 2 + 1, 2, device="cuda"))
+    for i, h in enumerate(at):
+        v[:, :, h], g[:, h] = few[:, :, i], gate[:, i]
+    want = binding.mix_forward(few, gate)
+    got = binding.mix_forward(v, g)
+    for i, h in enumerate(at):
+        assert torch.equal(got[:, :, h], want[:, :, i])
