@@ -1,7 +1,8 @@
-// Gate kernels: host-side launch declarations.
+// Gate kernels: host-side launch declarations and the rules of the output layer's launch.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stddef.h>
+#include <stdint.h>
 
 namespace spectre {
 
@@ -48,5 +49,38 @@ hipError_t launch_gate(int io, const void *q, double *partial, double inv_count,
 // P.toeplitz is set; phase already reduced modulo n_fft.
 hipError_t launch_gate_mlp(const double *sum_q, double inv_count, const GateDev &P, float *hid, float2 *raw,
                            int B, int H, long long phase, float2 *g, hipStream_t st);
+
+// Grid of the output layer: workgroups per weight set, tiles per wave.
+struct GateGrid {
+    int gx, gy, rounds;
+    bool tail;                       // the two rows behind the last whole tile ride with the last workgroup
+};
+// k_gate_out reads W2 in 16-byte pieces
+inline bool gate_vec(const GateDev &P) { return P.d_g % 4 == 0 && (reinterpret_cast<uintptr_t>(P.W2) & 15) == 0; }
+inline GateGrid gate_grid(const GateDev &P, int B, int H) {
+    const int twoF = 2 * (P.n_fft / 2 + 1), gy = P.Hg == 1 ? 1 : H, M = P.Hg == 1 ? B * H : B;
+    // lengths that are a multiple of 64 have two rows more than whole tiles: as a tile of its own they made a workgroup per
+    // head (32 heads of n = 8192: 1056 for the 1024 places of the chip).  Up to four rows per weight set, which that workgroup
+    // takes side by side: more rows one after the other would stand behind its last tile, where a tile of their own runs beside the
+    // others (from pooled sums, us, own tile / behind: 16 rows over one set n = 20480 12.3 / 14.5, over 32 sets 52.2 / 56.9; 250 over one 27.9 / 31.4).
+    const bool tail = M <= 4 && gate_vec(P) && P.d_g == 64 && twoF % 64 == 2 && twoF > 64;
+    const int ntiles = tail ? twoF / 64 : (twoF + 63) / 64;
+    int gx = (4096 + gy - 1) / gy;                 // about 16 workgroups per compute unit in total (1024: 5 % slower)
+    if (gx > (ntiles + 3) / 4) gx = (ntiles + 3) / 4;
+    // shrink the grid to the smallest one with the same number of tiles per wave (no ragged last round)
+    const int rounds = (ntiles + 4 * gx - 1) / (4 * gx);
+    return {(ntiles + 4 * rounds - 1) / (4 * rounds), gy, rounds, tail};
+}
+
+// The hidden layer inside every workgroup of the output layer, whose weights are under way meanwhile: one dependent launch less,
+// for up to four rows per weight set and while all workgroups run at once, four to a compute unit.  Each forms the layer
+// again, so further rounds of them would pay for it again (32 heads, bf16, step of gate and mixer, separate / inside, us: L = 4096 45.5 /
+// 43.6, 8192 81.4 / 79.9, 131072 1236 / 1262; gate of pooled sums with a position, appended tokens and window, B = 4 n = 8192 295.2 / 293.2).
+// From 2048 heads on the separate launch adds the layer's terms in another order (launch_gate_prep).
+inline bool gate_prep_inside(const GateDev &P, int B, int H) {
+    if (P.d != 64 || P.d_g != 64 || ((P.Hg == 1) ? B * H : B) > 4 || B * H >= 2048 || !gate_vec(P)) return false;
+    const GateGrid gr = gate_grid(P, B, H);
+    return (long long)gr.gx * gr.gy <= 1024;
+}
 
 }  // namespace spectre

@@ -473,12 +473,16 @@ __device__ __forceinline__ void gate_hidden_rows(float *hs, int dgs, double *buf
 // while its first weights are under way, and keeps it in LDS: inside the loop over the tiles, fp64 constants and temporaries cost
 // a wave per SIMD or spills.  Gate of pooled sums with a position, us, as a pass of its own over g / evaluated in the loop / now, H=32:
 // B=4 n=8192 21.3 / 21.5 / 17.1; B=8 29.9 / 33.0 / 22.2; B=64 n=1024 29.4 / 33.8 / 21.8.
-template <bool VEC, int RG, bool TURN, bool PREP = false>   // VEC: d_g % 4 == 0 and 16-byte aligned rows; RG: row groups of 4
+// FEW, for up to four rows per weight set (one tile of them) on the fast path: kTail, the two rows of W2 behind the last whole tile
+// ride with the last workgroup (gate_grid); kPrep, the hidden layer is formed here as well (gate_prep_inside), the two rows as `tail` says.
+enum { kTail = 1, kPrep = 2 };
+template <bool VEC, int RG, bool TURN, int FEW = 0>   // VEC: d_g % 4 == 0 and 16-byte aligned rows; RG: row groups of 4
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4 : 2))) void k_gate_out(const float *__restrict__ hid, const float *__restrict__ W2,
                                                   const float *__restrict__ b2,
                                                   const float *__restrict__ mbias, float2 *__restrict__ g,
                                                   int B, int H, int Hg, int dg, int F, int r_base0,
-                                                  int rounds, GatePhase phase, GatePrep pr) {
+                                                  int rounds, bool has_tail, GatePhase phase, GatePrep pr) {
+    static_assert(!FEW || (VEC && RG == 1), "four rows on the fast path");
     extern __shared__ float hs[];
     const int r_base = r_base0 + 4 * RG * (int)blockIdx.z;   // blockIdx.z: tile of the rows (sequences)                    // [4*RG][dgs] hidden rows of this pass, zero padded
     const int dgp = (dg + 3) & ~3, dgs = dgp + 4;    // row stride padded against bank conflicts
@@ -487,8 +491,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
     const int hsel = blockIdx.y;                     // head of this block when weights are per head
     const int hp = (Hg == 1) ? 0 : hsel;
     const int M = (Hg == 1) ? B * H : B;
-    // an even length's two rows behind the last whole tile ride with the last workgroup (gate_grid)
-    const bool tail = VEC && dg == 64 && (twoF & 63) == 2 && twoF > 64;
+    const bool tail = FEW == kTail || (FEW == kPrep && has_tail);
     const int ntiles = tail ? twoF / 64 : (twoF + 63) / 64;
     const float *w2h = W2 + (size_t)hp * twoF * dg;
     // the fast path's first tile is requested before anything else (with more than two row groups the registers it would
@@ -498,7 +501,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
     int ftile = blockIdx.x * 4 + wave;
     float4 a[16];
     if (kEarly && VEC && dg == 64 && ftile < ntiles) gate_load_tile(a, w2h, ftile, lr, lc, twoF);
-    if (PREP) {
+    if (FEW == kPrep) {
         gate_hidden_rows(hs, dgs, reinterpret_cast<double *>(hs + 4 * dgs), pr, H, Hg, hsel, M);
     } else {
         for (int idx = threadIdx.x; idx < 4 * RG * dgs; idx += 256) {
@@ -508,9 +511,13 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
             hs[idx] = v;
         }
     }
-    const bool mine = tail && wave == 3 && blockIdx.x == gridDim.x - 1;   // the two rows behind the last whole tile
-    float4 an = make_float4(0.f, 0.f, 0.f, 0.f);
-    if (mine && lane < 32) an = *(reinterpret_cast<const float4 *>(w2h + (size_t)ntiles * 4096) + lane);
+    const bool mine = FEW && tail && wave == 3 && blockIdx.x == gridDim.x - 1;
+    float4 w_re = make_float4(0.f, 0.f, 0.f, 0.f), w_im = w_re;
+    if (mine) {                                                      // lane = row of the hidden values and four of the 64 weights
+        const float4 *src = reinterpret_cast<const float4 *>(w2h + (size_t)ntiles * 4096) + (lane & 15);
+        w_re = src[0];
+        w_im = src[16];
+    }
     float2 *turn = reinterpret_cast<float2 *>(hs + 4 * RG * dgs + 4 * 64 * ((VEC && dg == 64) ? kHalfStride : kTileStride));
     if (TURN)
         for (int e = threadIdx.x; e < 128 * rounds; e += 256)        // [round][wave][bin of the tile]
@@ -591,23 +598,26 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(RG <= 2 ? 4
                 if (e_ok2) g[(size_t)bh * F + (n4 >> 1) + 1] = v1;
             }
         }
-        if (mine) {                            // lanes 0-15 real, 16-31 imaginary part of the last bin
+        if (mine) {                            // the last bin, all four rows at once
             const float2 bias = make_float2(b2[(size_t)hp * twoF + twoF - 2], b2[(size_t)hp * twoF + twoF - 1]);
             const float mb = mbias ? mbias[(size_t)hp * F + F - 1] : 0.f;
-            for (int rr = 0; rr < 4 * RG && r_base + rr < M; ++rr) {
-                const float4 hv = *reinterpret_cast<const float4 *>(hs + rr * dgs + 4 * (lane & 15));
-                float q = fmaf(an.x, hv.x, fmaf(an.y, hv.y, fmaf(an.z, hv.z, an.w * hv.w)));
-                q += partner16<8>(q);
-                q += partner16<4>(q);
-                q += partner16<2>(q);
-                q += partner16<1>(q);
-                const float im = __shfl(q, 16);
-                if (lane == 0) {
-                    const int r = r_base + rr, bh = (Hg == 1) ? r : r * H + hsel;
-                    float2 v;
-                    gate_store_bin(&v, q + bias.x, im + bias.y, mbias != nullptr, mb);
-                    g[(size_t)bh * F + F - 1] = TURN ? cmul(v, turn_last) : v;
-                }
+            const int r = lane >> 4;
+            const float4 hv = *reinterpret_cast<const float4 *>(hs + r * dgs + 4 * (lane & 15));
+            float re = fmaf(w_re.x, hv.x, fmaf(w_re.y, hv.y, fmaf(w_re.z, hv.z, w_re.w * hv.w)));
+            float im = fmaf(w_im.x, hv.x, fmaf(w_im.y, hv.y, fmaf(w_im.z, hv.z, w_im.w * hv.w)));
+            re += partner16<8>(re);
+            im += partner16<8>(im);
+            re += partner16<4>(re);
+            im += partner16<4>(im);
+            re += partner16<2>(re);
+            im += partner16<2>(im);
+            re += partner16<1>(re);
+            im += partner16<1>(im);
+            if ((lane & 15) == 0 && r < M) {
+                const int bh = (Hg == 1) ? r : r * H + hsel;
+                float2 v;
+                gate_store_bin(&v, re + bias.x, im + bias.y, mbias != nullptr, mb);
+                g[(size_t)bh * F + F - 1] = TURN ? cmul(v, turn_last) : v;
             }
         }
         return;
@@ -934,41 +944,12 @@ static hipError_t launch_gate_tail(const GateDev &P, const float2 *raw, int B, i
     return hipGetLastError();
 }
 
-// Grid of the output layer: workgroups per weight set, tiles per wave.
-struct GateGrid {
-    int gx, gy, rounds;
-};
-static bool gate_vec(const GateDev &P) { return P.d_g % 4 == 0 && (reinterpret_cast<uintptr_t>(P.W2) & 15) == 0; }
-static GateGrid gate_grid(const GateDev &P, int H) {
-    const int twoF = 2 * (P.n_fft / 2 + 1), gy = P.Hg == 1 ? 1 : H;
-    // lengths that are a multiple of 64 have two rows more than whole tiles: as a tile of its own they made a workgroup per
-    // head (32 heads of n = 8192: 1056 for the 1024 places of the chip)
-    const bool tail = gate_vec(P) && P.d_g == 64 && twoF % 64 == 2 && twoF > 64;
-    const int ntiles = tail ? twoF / 64 : (twoF + 63) / 64;
-    int gx = (4096 + gy - 1) / gy;                 // about 16 workgroups per compute unit in total (1024: 5 % slower)
-    if (gx > (ntiles + 3) / 4) gx = (ntiles + 3) / 4;
-    // shrink the grid to the smallest one with the same number of tiles per wave (no ragged last round)
-    const int rounds = (ntiles + 4 * gx - 1) / (4 * gx);
-    return {(ntiles + 4 * rounds - 1) / (4 * rounds), gy, rounds};
-}
-
-// The hidden layer inside every workgroup of the output layer, whose weights are under way meanwhile: one dependent launch less,
-// for up to four rows per weight set and while all workgroups run at once, four to a compute unit.  Each forms the layer
-// again, so further rounds of them would pay for it again (32 heads, bf16, step of gate and mixer, separate / inside, us: L = 4096 45.5 /
-// 43.6, 8192 81.4 / 79.9, 131072 1236 / 1262; gate of pooled sums with a position, appended tokens and window, B = 4 n = 8192 295.2 / 293.2).
-// From 2048 heads on the separate launch adds the layer's terms in another order (launch_gate_prep).
-static bool gate_prep_inside(const GateDev &P, int B, int H) {
-    if (P.d != 64 || P.d_g != 64 || ((P.Hg == 1) ? B * H : B) > 4 || B * H >= 2048 || !gate_vec(P)) return false;
-    const GateGrid gr = gate_grid(P, H);
-    return (long long)gr.gx * gr.gy <= 1024;
-}
-
 // partial != nullptr: the hidden layer from these partial sums, inside the same launch (gate_prep_inside); else hid.
 static hipError_t gate_out(const float *hid, const double *partial, int nchunks, double inv_count, const GateDev &P, float2 *raw,
                            int B, int H, long long phase, float2 *g, hipStream_t st) {
     const int F = P.n_fft / 2 + 1;
     const int M = (P.Hg == 1) ? B * H : B, twoF = 2 * F;
-    const GateGrid gr = gate_grid(P, H);
+    const GateGrid gr = gate_grid(P, B, H);
     const int rounds = gr.rounds;
     dim3 grid(gr.gx, gr.gy);
     const GatePrep pr = {partial, nchunks, inv_count, P.ln_gamma, P.ln_beta, P.W1, P.b1, P.ln_eps};
@@ -1000,22 +981,19 @@ static hipError_t gate_out(const float *hid, const double *partial, int nchunks,
             const int nz = (ntile - z0 < 65535) ? ntile - z0 : 65535;
             const dim3 grid3(grid.x, grid.y, nz);
             const int r_base = per * z0;
-#define SPECTRE_GATE_OUT(V, R)                                                                                              \
-    if (turn) k_gate_out<V, R, true><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F, r_base, \
-                                                              rounds, gate_phase_of(P, phase), pr);                          \
-    else k_gate_out<V, R, false><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F, r_base,     \
-                                                          rounds, gate_phase_of(P, phase), pr)
-            if (partial) {
-                if (turn) k_gate_out<true, 1, true, true><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g,
-                                                                                  F, r_base, rounds, gate_phase_of(P, phase), pr);
-                else k_gate_out<true, 1, false, true><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F,
-                                                                              r_base, rounds, gate_phase_of(P, phase), pr);
-            } else if (vec) {
-                if (rg <= 1) { SPECTRE_GATE_OUT(true, 1); } else if (rg <= 2) { SPECTRE_GATE_OUT(true, 2); }
-                else if (rg <= 4) { SPECTRE_GATE_OUT(true, 4); } else { SPECTRE_GATE_OUT(true, 8); }
+#define SPECTRE_GATE_OUT(V, R, FEW)                                                                                             \
+    if (turn) k_gate_out<V, R, true, FEW><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F,      \
+                                                                   r_base, rounds, gr.tail, gate_phase_of(P, phase), pr);       \
+    else k_gate_out<V, R, false, FEW><<<grid3, 256, lds, st>>>(hid, P.W2, P.b2, out_bias, out_g, B, H, P.Hg, P.d_g, F, r_base,  \
+                                                               rounds, gr.tail, gate_phase_of(P, phase), pr)
+            if (partial) { SPECTRE_GATE_OUT(true, 1, kPrep); }
+            else if (gr.tail) { SPECTRE_GATE_OUT(true, 1, kTail); }
+            else if (vec) {
+                if (rg <= 1) { SPECTRE_GATE_OUT(true, 1, 0); } else if (rg <= 2) { SPECTRE_GATE_OUT(true, 2, 0); }
+                else if (rg <= 4) { SPECTRE_GATE_OUT(true, 4, 0); } else { SPECTRE_GATE_OUT(true, 8, 0); }
             } else {
-                if (rg <= 1) { SPECTRE_GATE_OUT(false, 1); } else if (rg <= 2) { SPECTRE_GATE_OUT(false, 2); }
-                else if (rg <= 4) { SPECTRE_GATE_OUT(false, 4); } else { SPECTRE_GATE_OUT(false, 8); }
+                if (rg <= 1) { SPECTRE_GATE_OUT(false, 1, 0); } else if (rg <= 2) { SPECTRE_GATE_OUT(false, 2, 0); }
+                else if (rg <= 4) { SPECTRE_GATE_OUT(false, 4, 0); } else { SPECTRE_GATE_OUT(false, 8, 0); }
             }
 #undef SPECTRE_GATE_OUT
             hipError_t e2 = hipGetLastError();

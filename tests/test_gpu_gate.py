@@ -218,6 +218,21 @@ def test_positional_phase_turns_the_gate(B, H, Hg, n, dg):
         assert bool((err <= 6 * 2.0 ** -24 * plain.abs()).all())
 
 
+@pytest.mark.parametrize("phase", [0, 777])
+@pytest.mark.parametrize("B,H,Hg,n", [(1, 1, 1, 128), (3, 2, 2, 1600), (4, 1, 1, 8192), (5, 1, 1, 8192), (2, 2, 1, 65), (9, 3, 3, 2048),
+                                      (33, 2, 1, 1024), (4, 40, 40, 8192)])
+def test_last_bin_of_every_row(oracle, B, H, Hg, n, phase):
+    """Lengths whose last bin lies behind the last whole tile of the output layer, up to four rows per weight set (it rides with the last
+    workgroup) and more (a tile of its own)."""
+    from paper_2502_18394_amd import binding
+    print(f"case B={B} H={H} Hg={Hg} n={n} phase={phase}", flush=True)
+    p = synth.gate_params(61, Hg, 64, n)
+    sq = np.random.default_rng(62).standard_normal((B, H, 64)) * 40.0
+    got = binding.gate(torch.from_numpy(sq).cuda(), binding.GateParams(p), 1.0 / n, pooled=True, phase_pos=phase).cpu().numpy()
+    want = oracle.gate(sq, 1.0 / n, f64(p), n, phase)
+    assert rel_l2(got, want) <= 1e-5 and rel_l2(got[:, :, -1], want[:, :, -1]) <= 1e-5
+
+
 @pytest.mark.parametrize("B,L,H,io,shared,phase", [
     (1, 4096, 1, "f32", False, 0),      # chunks of 16-piece columns; a length with two output reals behind the last whole tile
     (1, 2113, 1, "f32", False, 0),      # odd length, ragged last chunk and tile

@@ -53,3 +53,17 @@ def test_launches_of_the_in_lds_mixer(tmp_path):
     run = subprocess.run([str(exe)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     print(run.stdout)
     assert run.returncode == 0 and " 0 failures" in run.stdout, run.stdout
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC) and shutil.which("hipcc") is None, reason="hipcc not found")
+def test_launches_of_the_gates_output_layer(tmp_path):
+    """`gate_grid` (csrc/gate.h): all rows of the weights, and none behind another workgroup's tiles that it would take in turn."""
+    exe = tmp_path / "gate_rules"
+    csrc = os.path.join(ROOT, "paper_2502_18394_amd", "csrc")
+    cmd = [HIPCC if os.path.exists(HIPCC) else "hipcc", "--cuda-host-only", "-x", "hip", "-std=c++17", "-O1", "-I", csrc,
+           os.path.join(ROOT, "tests", "host", "gate_rules.cpp"), "-o", str(exe)]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert res.returncode == 0, res.stdout[-3000:]
+    run = subprocess.run([str(exe)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    print(run.stdout)
+    assert run.returncode == 0 and " 0 failures" in run.stdout, run.stdout
