@@ -54,22 +54,31 @@ hipError_t launch_gate_mlp(const double *sum_q, double inv_count, const GateDev 
 struct GateGrid {
     int gx, gy, rounds;
     bool tail;                       // the two rows behind the last whole tile ride with the last workgroup
+    long long workgroups() const { return (long long)gx * gy; }
+    long long per_unit() const { return (workgroups() + 255) / 256; }   // workgroups of the compute unit that has most
 };
-// k_gate_out reads W2 in 16-byte pieces
-inline bool gate_vec(const GateDev &P) { return P.d_g % 4 == 0 && (reinterpret_cast<uintptr_t>(P.W2) & 15) == 0; }
-inline GateGrid gate_grid(const GateDev &P, int B, int H) {
-    const int twoF = 2 * (P.n_fft / 2 + 1), gy = P.Hg == 1 ? 1 : H, M = P.Hg == 1 ? B * H : B;
-    // lengths that are a multiple of 64 have two rows more than whole tiles: as a tile of its own they made a workgroup per
-    // head (32 heads of n = 8192: 1056 for the 1024 places of the chip).  Up to four rows per weight set, which that workgroup
-    // takes side by side: more rows one after the other would stand behind its last tile, where a tile of their own runs beside the
-    // others (from pooled sums, us, own tile / behind: 16 rows over one set n = 20480 12.3 / 14.5, over 32 sets 52.2 / 56.9; 250 over one 27.9 / 31.4).
-    const bool tail = M <= 4 && gate_vec(P) && P.d_g == 64 && twoF % 64 == 2 && twoF > 64;
-    const int ntiles = tail ? twoF / 64 : (twoF + 63) / 64;
+inline GateGrid gate_grid_of(int ntiles, int gy, bool tail) {
     int gx = (4096 + gy - 1) / gy;                 // about 16 workgroups per compute unit in total (1024: 5 % slower)
     if (gx > (ntiles + 3) / 4) gx = (ntiles + 3) / 4;
     // shrink the grid to the smallest one with the same number of tiles per wave (no ragged last round)
     const int rounds = (ntiles + 4 * gx - 1) / (4 * gx);
     return {(ntiles + 4 * rounds - 1) / (4 * rounds), gy, rounds, tail};
+}
+// k_gate_out reads W2 in 16-byte pieces
+inline bool gate_vec(const GateDev &P) { return P.d_g % 4 == 0 && (reinterpret_cast<uintptr_t>(P.W2) & 15) == 0; }
+inline GateGrid gate_grid(const GateDev &P, int B, int H) {
+    const int twoF = 2 * (P.n_fft / 2 + 1), gy = P.Hg == 1 ? 1 : H, M = P.Hg == 1 ? B * H : B;
+    const GateGrid own = gate_grid_of((twoF + 63) / 64, gy, false);
+    // Lengths that are a multiple of 64 have two rows more than whole tiles.  A tile of their own can cost every wave another tile, or,
+    // while all workgroups run at once, some compute units a workgroup more than the others have (32 heads of n = 8192: 1056 for 1024
+    // places).  Only there do they ride, and only for up to four rows per weight set, which that workgroup takes side by side.  us, own tile /
+    // riding: gate of bf16 rows, 32 heads of 131072 271.2 / 267.9, 65536 144.1 / 141.7, 4 x 16 heads of 8192 30.0 / 27.5; layer of 32 heads
+    // of 8192 92.9 / 91.7, 4096 55.9 / 55.2; but 512 24.5 / 25.5, and where there are several rounds of workgroups, 24576 248.6 / 250.6.
+    // More rows one after the other would stand behind the last tile (from pooled sums: 16 rows over one set n = 20480 12.3 / 14.5, over
+    // 32 sets 52.2 / 56.9; 250 over one 27.9 / 31.4).
+    if (M > 4 || !gate_vec(P) || P.d_g != 64 || twoF % 64 != 2 || twoF <= 64) return own;
+    const GateGrid ride = gate_grid_of(twoF / 64, gy, true);
+    return ride.rounds < own.rounds || (ride.workgroups() <= 1024 && ride.per_unit() < own.per_unit()) ? ride : own;
 }
 
 // The hidden layer inside every workgroup of the output layer, whose weights are under way meanwhile: one dependent launch less,
@@ -79,8 +88,7 @@ inline GateGrid gate_grid(const GateDev &P, int B, int H) {
 // From 2048 heads on the separate launch adds the layer's terms in another order (launch_gate_prep).
 inline bool gate_prep_inside(const GateDev &P, int B, int H) {
     if (P.d != 64 || P.d_g != 64 || ((P.Hg == 1) ? B * H : B) > 4 || B * H >= 2048 || !gate_vec(P)) return false;
-    const GateGrid gr = gate_grid(P, B, H);
-    return (long long)gr.gx * gr.gy <= 1024;
+    return gate_grid(P, B, H).workgroups() <= 1024;
 }
 
 }  // namespace spectre

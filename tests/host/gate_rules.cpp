@@ -1,5 +1,6 @@
 // Host check of how the gate's output layer is launched (csrc/gate.h).  The tiles of the grid cover the weights' rows, and the two
-// rows behind the last whole tile ride with another workgroup only where that takes all their sums side by side: four.
+// rows behind the last whole tile ride with another workgroup only where that takes all their sums side by side (four) and
+// the compute units then have less to do.
 #include <stdio.h>
 
 #include "gate.h"
@@ -7,7 +8,7 @@
 using namespace spectre;
 
 int main() {
-    int fails = 0, cases = 0;
+    int fails = 0, cases = 0, rides = 0;
     alignas(16) static float weights[4];
     for (int B : {1, 2, 3, 4, 5, 8, 16, 33, 250, 2048})
         for (int H : {1, 2, 3, 4, 12, 32, 4096})
@@ -25,7 +26,11 @@ int main() {
                             if (gr.gy != Hg || gr.gx < 1 || gr.rounds < 1) ++fails;
                             if (spare < 0 || spare >= 256LL * gr.rounds + 64) ++fails;
                             if (gr.tail && (M > 4 || !fast || (twoF - 2) % 64 || twoF <= 64)) ++fails;
+                            const GateGrid own = gate_grid_of((int)(twoF + 63) / 64, gr.gy, false);
+                            if (gr.tail && gr.rounds >= own.rounds && gr.per_unit() >= own.per_unit()) ++fails;
+                            rides += gr.tail;
                         }
-    printf("gate launches: %d cases, %d failures\n", cases, fails);
+    if (rides == 0) ++fails;
+    printf("gate launches: %d cases, %d with riding rows, %d failures\n", cases, rides, fails);
     return fails != 0;
 }

@@ -220,10 +220,10 @@ def test_positional_phase_turns_the_gate(B, H, Hg, n, dg):
 
 @pytest.mark.parametrize("phase", [0, 777])
 @pytest.mark.parametrize("B,H,Hg,n", [(1, 1, 1, 128), (3, 2, 2, 1600), (4, 1, 1, 8192), (5, 1, 1, 8192), (2, 2, 1, 65), (9, 3, 3, 2048),
-                                      (33, 2, 1, 1024), (4, 40, 40, 8192)])
+                                      (33, 2, 1, 1024), (4, 4, 4, 4096), (4, 16, 16, 4096), (2, 2048, 2048, 512)])
 def test_last_bin_of_every_row(oracle, B, H, Hg, n, phase):
-    """Lengths whose last bin lies behind the last whole tile of the output layer, up to four rows per weight set (it rides with the last
-    workgroup) and more (a tile of its own)."""
+    """Lengths whose last bin lies behind the last whole tile of the output layer: as a tile of its own, and with the last workgroup (up to
+    four rows per weight set; the last two cases, with the hidden layer inside the launch and in front of it)."""
     from paper_2502_18394_amd import binding
     print(f"case B={B} H={H} Hg={Hg} n={n} phase={phase}", flush=True)
     p = synth.gate_params(61, Hg, 64, n)
