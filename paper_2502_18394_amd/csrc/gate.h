@@ -81,14 +81,23 @@ inline GateGrid gate_grid(const GateDev &P, int B, int H) {
     return ride.rounds < own.rounds || (ride.workgroups() <= 1024 && ride.per_unit() < own.per_unit()) ? ride : own;
 }
 
-// The hidden layer inside every workgroup of the output layer, whose weights are under way meanwhile: one dependent launch less,
-// for up to four rows per weight set and while all workgroups run at once, four to a compute unit.  Each forms the layer
-// again, so further rounds of them would pay for it again (32 heads, bf16, step of gate and mixer, separate / inside, us: L = 4096 45.5 /
-// 43.6, 8192 81.4 / 79.9, 131072 1236 / 1262; gate of pooled sums with a position, appended tokens and window, B = 4 n = 8192 295.2 / 293.2).
+// The hidden layer inside every workgroup of the output layer, whose weights are under way meanwhile: one dependent launch less (about
+// 2 us), for up to four rows per weight set and while all workgroups run at once, four to a compute unit.  Each forms the layer again:
+//  - further rounds of workgroups would pay for it again (32 heads of 131072 bf16 rows, step of gate and mixer, 1236 -> 1262 us);
+//  - a wave adds its share of a row's chunk sums eight at a time, what is left over one at a time and the rows one after the other, each
+//    trip a round trip to the L2.  us, separate minus inside, over 3 to 14 shapes each: 2 to 4 trips 2 to 3, 6 trips 1, 8 trips 0 to 1, 12
+//    trips -1.8, 16 trips -2 to -3, 32 trips -8, 64 trips -24;
+//  - the workgroups' reads of the sums add up (one row, 128 chunks of 512 bytes, 512 workgroups +1, 768 -0.9; 256 chunks, 256 workgroups
+//    +1, 1024 -3.9), and so does the layer's arithmetic (32 chunks: 2, 3 and 4 rows in 1024 workgroups -0.5, -2 and -2.5, 4 rows in 512 0).
+// Pooled sums, which need neither, while the workgroups run at once (gate with a position, B = 4 H = 32 n = 8192 17.9 / 16.2).
 // From 2048 heads on the separate launch adds the layer's terms in another order (launch_gate_prep).
-inline bool gate_prep_inside(const GateDev &P, int B, int H) {
-    if (P.d != 64 || P.d_g != 64 || ((P.Hg == 1) ? B * H : B) > 4 || B * H >= 2048 || !gate_vec(P)) return false;
-    return gate_grid(P, B, H).workgroups() <= 1024;
+inline bool gate_prep_inside(const GateDev &P, int B, int H, int nchunks) {
+    const int M = P.Hg == 1 ? B * H : B;
+    if (P.d != 64 || P.d_g != 64 || M > 4 || B * H >= 2048 || !gate_vec(P)) return false;
+    const long long workgroups = gate_grid(P, B, H).workgroups();
+    if (nchunks == 1) return workgroups <= 1024;
+    const int trips = M * (nchunks / 32 + (nchunks % 32 + 3) / 4);
+    return trips <= 8 && workgroups * M <= 1024 && workgroups * M * nchunks <= 65536;
 }
 
 }  // namespace spectre

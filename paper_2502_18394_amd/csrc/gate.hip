@@ -1053,7 +1053,7 @@ hipError_t launch_gate(int io, const void *q, double *partial, double inv_count,
     hipError_t e = launch_pool_partial(io, q, partial, B, L, H, P.d, st);
     if (e != hipSuccess) return e;
     const int nchunks = pool_chunks(io, B, L, H, P.d);
-    if (gate_prep_inside(P, B, H)) return gate_out(hid, partial, nchunks, inv_count, P, raw, B, H, phase, g, st);
+    if (gate_prep_inside(P, B, H, nchunks)) return gate_out(hid, partial, nchunks, inv_count, P, raw, B, H, phase, g, st);
     e = launch_gate_prep(partial, nchunks, nullptr, 1, nullptr, inv_count, P, hid, B, H, st);
     if (e != hipSuccess) return e;
     return launch_gate_out(hid, P, raw, B, H, phase, g, st);
@@ -1061,7 +1061,7 @@ hipError_t launch_gate(int io, const void *q, double *partial, double inv_count,
 
 hipError_t launch_gate_mlp(const double *sum_q, double inv_count, const GateDev &P, float *hid, float2 *raw,
                            int B, int H, long long phase, float2 *g, hipStream_t st) {
-    if (gate_prep_inside(P, B, H)) return gate_out(hid, sum_q, 1, inv_count, P, raw, B, H, phase, g, st);
+    if (gate_prep_inside(P, B, H, 1)) return gate_out(hid, sum_q, 1, inv_count, P, raw, B, H, phase, g, st);
     const hipError_t e = launch_gate_prep(sum_q, 1, nullptr, 1, nullptr, inv_count, P, hid, B, H, st);
     if (e != hipSuccess) return e;
     return launch_gate_out(hid, P, raw, B, H, phase, g, st);

@@ -242,6 +242,8 @@ def test_last_bin_of_every_row(oracle, B, H, Hg, n, phase):
     (2, 2500, 2, "f32", True, 0),       # shared weights: rows over (b, h)
     (1, 33000, 3, "bf16", True, 0),     # many chunks
     (1, 40960, 32, "bf16", False, 0),   # more workgroups than run at once: hidden layer in its own launch
+    (4, 4096, 2, "f32", False, 777),    # 64 chunks of four rows: the most that the output layer's workgroups add up themselves
+    (1, 8192, 4, "bf16", True, 777),    # 128 of them: hidden layer in its own launch
 ])
 def test_gate_of_rows_summed_in_deep_chunks(oracle, B, L, H, io, shared, phase):
     """Lengths between the one-launch gate and 256 rows a chunk, at any alignment of a channel pair (same bits)."""

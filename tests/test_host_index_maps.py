@@ -57,7 +57,8 @@ def test_launches_of_the_in_lds_mixer(tmp_path):
 
 @pytest.mark.skipif(not os.path.exists(HIPCC) and shutil.which("hipcc") is None, reason="hipcc not found")
 def test_launches_of_the_gates_output_layer(tmp_path):
-    """`gate_grid` (csrc/gate.h): all rows of the weights, and none behind another workgroup's tiles that it would take in turn."""
+    """`gate_grid` and `gate_prep_inside` (csrc/gate.h): all rows of the weights, none behind another workgroup's tiles that it would
+    take in turn, and a bound on what the workgroups repeat."""
     exe = tmp_path / "gate_rules"
     csrc = os.path.join(ROOT, "paper_2502_18394_amd", "csrc")
     cmd = [HIPCC if os.path.exists(HIPCC) else "hipcc", "--cuda-host-only", "-x", "hip", "-std=c++17", "-O1", "-I", csrc,
