@@ -840,11 +840,13 @@ int pool_rows(int B, int L, int H, int d) {
 }
 
 // Pieces of a row per workgroup of k_pool_deep, 0 where the pass of whole rows takes the sums: rows that are no whole number
-// of 128-byte lines, and sequences long enough for 256 rows a chunk (32 heads of 131072 bf16 rows: step of gate and mixer 1237
-// instead of 1226 us).
+// of 128-byte lines; sequences long enough for 256 rows a chunk (32 heads of 131072 bf16 rows: step of gate and mixer 1237
+// instead of 1226 us); and chunks of 128 whole rows of 2 or 4 KB, which fill half or all of that pass's workgroups (gate, us, whole rows /
+// deep: 4 x 16 heads of 16384 bf16 42.9 / 45.2, fp32 60.8 / 64.5, 4 x 8 fp32 36.2 / 38.0, 4 x 32 bf16 74.3 / 77.3; rows of 1 KB, 4 x 8 bf16
+// 31.6 / 27.1, of 1.5 KB, 4 x 12 bf16 38.0 / 34.4, of 8 KB, 8 x 32 of 8192 fp32 110.5 / 108.0; chunks of 64 rows -2 to +4 %).
 static int pool_deep_cols(int io, int B, int L, int H, int d) {
-    const int bytes = H * d * (io ? 2 : 4), ppv = bytes / 16;
-    if (bytes % 128 || pool_rows(B, L, H, d) == kPoolRows) return 0;
+    const int bytes = H * d * (io ? 2 : 4), ppv = bytes / 16, rows = pool_rows(B, L, H, d);
+    if (bytes % 128 || rows == kPoolRows || (rows == kPoolRows / 2 && (bytes == 2048 || bytes == 4096))) return 0;
     return ppv % 32 == 0 ? 32 : ppv % 16 == 0 ? 16 : 8;
 }
 // Rows of one of its chunks: halved from 256 while there are less workgroups than compute units, and never fewer than the size

@@ -244,9 +244,11 @@ def test_last_bin_of_every_row(oracle, B, H, Hg, n, phase):
     (1, 40960, 32, "bf16", False, 0),   # more workgroups than run at once: hidden layer in its own launch
     (4, 4096, 2, "f32", False, 777),    # 64 chunks of four rows: the most that the output layer's workgroups add up themselves
     (1, 8192, 4, "bf16", True, 777),    # 128 of them: hidden layer in its own launch
+    (1, 65536, 8, "f32", False, 0),     # rows of 2 KB in chunks of 128: the pass of whole rows
 ])
 def test_gate_of_rows_summed_in_deep_chunks(oracle, B, L, H, io, shared, phase):
-    """Lengths between the one-launch gate and 256 rows a chunk, at any alignment of a channel pair (same bits)."""
+    """Lengths between the one-launch gate and 256 rows a chunk, at any alignment of a channel pair (same bits), and one that the pass of
+    whole rows takes."""
     from paper_2502_18394_amd import binding
     print(f"case B={B} L={L} H={H} io={io} shared={shared} phase={phase}", flush=True)
     p = synth.gate_params(41, 1 if shared else H, 64, L)
