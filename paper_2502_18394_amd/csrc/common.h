@@ -49,8 +49,10 @@ __device__ __forceinline__ void stream_store(float2 *p, float2 v) {
 
 // Stores that go through the L2 at once.  What a kernel leaves dirty there, up to 4 MB on each of the eight XCDs, is written back
 // when it ends and before the next one starts, with nothing beside it; written through, it leaves while the kernel still
-// works.  For scratch the next kernel reads, of whole 128-byte lines per wave instruction, in launches that move up to a few
-// hundred MB alone (measured at the users; streaming stores instead cost 3 to 5 % there, the next kernel reads the scratch).
+// works.  For scratch the next kernel reads, of whole 128-byte lines per wave instruction, in launches that have memory to
+// themselves (streaming stores instead cost 3 to 5 %, the next kernel reads the scratch).  Where the scratch is about what the
+// L2s hold together, the next kernel finds it there after plain stores: each user's rule leaves that range out, with both sides measured.
+constexpr size_t kL2Bytes = (size_t)32 << 20;
 template <typename T>
 __device__ __forceinline__ void through_store(T *p, T v) {
     static_assert(sizeof(T) == 4 || sizeof(T) == 8, "one or two words");

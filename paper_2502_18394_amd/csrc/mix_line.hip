@@ -7,7 +7,6 @@
 //                      first workgroups lay the gate out in the order of the column kernel's registers
 //   k_line           : a line at a time: forward transform, gate, inverse transform, in place
 //   k_line_turn<out> : lines -> rows
-// The lines are written through the L2 both times (through_store): 32 heads at L = 8192 55.7 -> 53.3 us, at 16384 112.8 -> 108.8.
 // 24 bytes per pair and position; the column kernel is bound by its vector arithmetic (about 90 instructions per point).
 // Measured: L = 8192 66 -> 61 us for 32 heads, 241 -> 189 us for 128; L = 16384 132 -> 113 us for 32 heads, 253 -> 206 us
 // for 64.  As many heads go through together as the scratch holds (line_group_heads; groups of 32 for 128 heads at
@@ -40,8 +39,8 @@ __device__ __forceinline__ void line_unit(int id, int per_head, int *bhl, int *w
 // A workgroup turns 4 j x 32 tau rows of one head, 128 bytes each, through LDS: 512-byte runs on the side of the lines.
 // grid: nexp gate blocks (IN only), then the tiles of 8 ceil(nbh / 8) heads.
 // ONCE: the rows pass the caches by; rows off a 16-byte boundary share lines with their neighbours and do not (L = 16384, 128
-// heads 528 instead of 600 us).
-template <bool IN, bool ONCE>
+// heads 528 instead of 600 us).  THROUGH: see line_t.
+template <bool IN, bool ONCE, bool THROUGH>
 __global__ __launch_bounds__(256) void k_line_turn(const uint32_t *__restrict__ rows_in, uint32_t *__restrict__ rows_out,
                                                    uint32_t *__restrict__ lines, int L, int NT, int H, int bh0, int nbh,
                                                    const float2 *__restrict__ g, float2 *__restrict__ gp, int R0, int R1,
@@ -88,7 +87,8 @@ __global__ __launch_bounds__(256) void k_line_turn(const uint32_t *__restrict__ 
         for (int i = 0; i < 4; ++i) {
 #pragma unroll
             for (int c = 0; c < 4; ++c) w[i][c] = tile[(c * 32 + tl) * S + p0 + 8 * i];
-            through_store16(head, 128u * L, 4u * ((p0 + 8 * i) * L + j0 * NT + (tau0 + tl) * kVW), w[i]);
+            if (THROUGH) through_store16(head, 128u * L, 4u * ((p0 + 8 * i) * L + j0 * NT + (tau0 + tl) * kVW), w[i]);
+            else *(reinterpret_cast<u32x4_t *>(line + (size_t)(p0 + 8 * i) * L) + tl) = w[i];
         }
     } else {
 #pragma unroll
@@ -124,7 +124,7 @@ __global__ __launch_bounds__(256) void k_line_turn(const uint32_t *__restrict__ 
 // 32, 100, 128 and 256 heads 61, 168, 187 and 402 us (66, 175, 241 and 464), now 61, 150, 189 and 374.
 // The factors are reloaded (five values per layer, from L1) where they are used: kept in registers over the loop, with the
 // products the compiler forms from them, they spilled.
-template <int R0, int R1>
+template <int R0, int R1, bool THROUGH>
 __global__ __launch_bounds__(16 * R1, 2) void k_line(uint32_t *__restrict__ lines, const float2 *__restrict__ gp,
                                                      const float2 *__restrict__ twL, int nbh) {
     constexpr int NT = 16 * R1, L = R0 * NT, Q1 = R0 / R1, Q2 = R0 / 16, S0 = NT + NT / 16;   // LDS position p + p / 16
@@ -220,7 +220,8 @@ __global__ __launch_bounds__(16 * R1, 2) void k_line(uint32_t *__restrict__ line
             u32x4_t o;
 #pragma unroll
             for (int e = 0; e < kVW; ++e) o[e] = IoBf16::pack(x[kVW * j + e]);
-            through_store16(lines + ((size_t)(8 * (n >> 5) + xcd) * 32 + (n & 31)) * L, 4u * L, 16u * (j * NT + tau), o);
+            if (THROUGH) through_store16(lines + ((size_t)(8 * (n >> 5) + xcd) * 32 + (n & 31)) * L, 4u * L, 16u * (j * NT + tau), o);
+            else line_of(n)[j * NT] = o;
         }
         if (n + 1 < n1) __syncthreads();                             // the next line's pass 0 writes what is read above
     }
@@ -229,23 +230,26 @@ __global__ __launch_bounds__(16 * R1, 2) void k_line(uint32_t *__restrict__ line
 // ------------------------------------------------------------------------------------------
 bool line_supported(int L, int io) { return io == 1 && (L == 8192 || L == 16384); }
 
-template <int R0, int R1>
+// THROUGH: the lines are written through the L2 both times (through_store) where they are more than the eight L2s hold, 32 MB; fewer
+// lines stay there for the next kernel.  us, plain / through: L = 8192, 6 heads 19.6 / 20.2, 16 28.1 / 29.1, 24 (25 MB) 42.1 / 42.9, 32
+// (34 MB) 55.4 / 53.5, 64 98 / 93; L = 16384, 6 heads 27.9 / 30.5, 8 29.8 / 31.7, 12 (25 MB) 44.5 / 44.9, 16 (34 MB) 58.5 / 56.9.
+template <int R0, int R1, bool THROUGH>
 static hipError_t line_t(const uint32_t *v, const float2 *g, uint32_t *out, float2 *gp, uint32_t *lines, const float2 *twL,
                          int H, int bh0, int nbh, hipStream_t st) {
     constexpr int NT = 16 * R1, L = R0 * NT;
     const int heads8 = (nbh + 7) / 8 * 8, tiles = L / kTurnRows * heads8, nexp = nbh * (L / 256);
-    const auto turn_in = reinterpret_cast<uintptr_t>(v) & 15 ? k_line_turn<true, false> : k_line_turn<true, true>;
+    const auto turn_in = reinterpret_cast<uintptr_t>(v) & 15 ? k_line_turn<true, false, THROUGH> : k_line_turn<true, true, THROUGH>;
     turn_in<<<nexp + tiles, 256, 0, st>>>(v, nullptr, lines, L, NT, H, bh0, nbh, g, gp, R0, R1, nexp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     const size_t lds = (size_t)R0 * (NT + NT / 16) * sizeof(float2);
-    auto kern = k_line<R0, R1>;
+    auto kern = k_line<R0, R1, THROUGH>;
     e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     kern<<<8 * line_workgroups(L, nbh), NT, lds, st>>>(lines, gp, twL, nbh);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const auto turn_out = reinterpret_cast<uintptr_t>(out) & 15 ? k_line_turn<false, false> : k_line_turn<false, true>;
+    const auto turn_out = reinterpret_cast<uintptr_t>(out) & 15 ? k_line_turn<false, false, false> : k_line_turn<false, true, false>;
     turn_out<<<tiles, 256, 0, st>>>(nullptr, out, lines, L, NT, H, bh0, nbh, nullptr, nullptr, R0, R1, 0);
     return hipGetLastError();
 }
@@ -254,8 +258,9 @@ hipError_t launch_mix_line(const void *v, const float2 *g, void *out, float2 *gp
                            int H, int bh0, int nbh, hipStream_t st) {
     const uint32_t *vp = static_cast<const uint32_t *>(v);
     uint32_t *op = static_cast<uint32_t *>(out), *lp = static_cast<uint32_t *>(lines);
-    if (L == 8192) return line_t<32, 16>(vp, g, op, gp, lp, twL, H, bh0, nbh, st);
-    if (L == 16384) return line_t<32, 32>(vp, g, op, gp, lp, twL, H, bh0, nbh, st);
+    const bool through = (size_t)nbh * L * 32 * sizeof(uint32_t) >= kL2Bytes;
+    if (L == 8192) return (through ? line_t<32, 16, true> : line_t<32, 16, false>)(vp, g, op, gp, lp, twL, H, bh0, nbh, st);
+    if (L == 16384) return (through ? line_t<32, 32, true> : line_t<32, 32, false>)(vp, g, op, gp, lp, twL, H, bh0, nbh, st);
     return hipErrorInvalidValue;
 }
 
@@ -263,7 +268,7 @@ hipError_t launch_mix_line(const void *v, const float2 *g, void *out, float2 *gp
 // that no compute call is the first to touch it.
 hipError_t load_kernels_mix_line() {
     hipFuncAttributes a;
-    return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(&k_line_turn<true, true>));
+    return hipFuncGetAttributes(&a, reinterpret_cast<const void *>(&k_line_turn<true, true, true>));
 }
 
 }  // namespace spectre

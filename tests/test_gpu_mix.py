@@ -455,6 +455,24 @@ def test_shapes_around_the_route_boundaries(oracle, B, L, H, io):
     assert_close_elementwise(got, want, io, 16 * L)
 
 
+@pytest.mark.parametrize("L,io,heads", [
+    (8192, "bf16", (31, 32)), (16384, "bf16", (15, 16)),                  # lines through the L2 from 32 MB on
+    (5120, "f32", (12, 13, 44, 45)), (7168, "bf16", (9, 10, 73, 74)),     # scalar addresses up to 16 MB, and from 56 and 128 MB on
+    (3072, "f32", (24, 32, 48)), (49152, "f32", (1, 2, 3)),               # columns through the L2 but for 24 to 32 and 20 to 26 MB
+])
+def test_forms_by_the_size_of_the_scratch_change_no_bit(L, io, heads):
+    from paper_2502_18394_amd import binding
+    gen = torch.Generator(device="cuda").manual_seed(L)
+    v = torch.randn((1, L, max(heads), 64), generator=gen, device="cuda").to(torch.bfloat16 if io == "bf16" else torch.float32)
+    g = torch.view_as_complex(torch.randn((1, max(heads), L // 2 + 1, 2), generator=gen, device="cuda"))
+    few = [binding.mix_forward(v[:, :, h:h + 1].contiguous(), g[:, h:h + 1].contiguous()) for h in (0, min(heads) - 1)]
+    for H in heads:
+        print(f"case L={L} io={io} H={H}", flush=True)
+        got = binding.mix_forward(v[:, :, :H].contiguous(), g[:, :H].contiguous())
+        for h, want in zip((0, min(heads) - 1), few):
+            assert torch.equal(got[:, :, h:h + 1], want)
+
+
 @pytest.mark.parametrize("H", [(1 << 19) - 1, 1 << 19])
 def test_rows_4_gb_apart(H):
     """The last number of heads of 512 bf16 rows whose lanes' offsets fit 32 bits and the first that needs 64 (34 GB of rows): the first,
