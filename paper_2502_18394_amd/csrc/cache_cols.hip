@@ -11,7 +11,6 @@
 // memory once less.  What bounds them is memory traffic, 16 bytes per pair and position: 25 heads of N = 32768 forward 134
 // -> 72 us (5.8 TB/s), 102 heads of N = 8192 inverse 134 -> 77 us (5.6 TB/s).  With 64-byte pieces of the rows of X and whole
 // columns in LDS the former took 105 us, with plain stores of X, which push the scratch out of the memory-side cache, 88.
-// The inverse writes its columns through the L2 (through_store; the readout's row transforms read them: 57 tokens and readout as below 294 -> 289 us).
 // Whole calls: prompt of 20011 tokens, B = 8 H = 32 N = 32768, 3603 -> 2956 us; 57 tokens and the window's readout, B = 4
 // H = 32 N = 8192, 427 -> 352 us.
 //
@@ -147,7 +146,8 @@ __global__ __launch_bounds__(2 * PW * R, R == 32 ? 4 : 6) void k_cache_fwd(const
     }
 }
 
-template <int R, int PW>
+// THROUGH: see through_store and cache_cols_t.
+template <int R, int PW, bool THROUGH>
 __global__ __launch_bounds__(2 * PW * R, R == 32 ? 4 : 6) void k_cache_inv(const float4 *__restrict__ X,
                                                                            const float2 *__restrict__ g,
                                                                            float2 *__restrict__ scr,
@@ -208,7 +208,10 @@ __global__ __launch_bounds__(2 * PW * R, R == 32 ? 4 : 6) void k_cache_inv(const
     if (s >= un.planes) return;
     float2 *col = scr + (((size_t)un.bhl * N2 + un.plane(s)) * 32 + un.pg * PW + pw) * N1 + tau;
 #pragma unroll
-    for (int j = 0; j < R; ++j) through_store(col + R * j, x[j]);
+    for (int j = 0; j < R; ++j) {
+        if (THROUGH) through_store(col + R * j, x[j]);
+        else col[R * j] = x[j];
+    }
 }
 
 // The mixer's columns of R * R points in place: forward, times the expanded gate gp [bh][k2][k1], inverse.  R adjacent lanes
@@ -278,14 +281,21 @@ static hipError_t cache_cols_t(bool inverse, const Pow2Plan &pl, float2 *scr, fl
     const size_t lds = Unit::kLds;
     const long long units = ((long long)nbh * cache_plane_pairs(pl.N2) + 7) / 8 * 8 * (32 / PW);
     if (units > 0x7fffffffLL) return hipErrorInvalidValue;
-    const void *kern = inverse ? reinterpret_cast<const void *>(&k_cache_inv<R, PW>)
+    // The inverse writes its columns through the L2, except those of 256 points that are about what the eight L2s hold: 18 to 40 MB, where
+    // the readout's row transforms find them after plain stores.  Readout of a window, us, plain / through: 16 heads of N = 8192 (34 MB)
+    // 26.5 / 28.4, 32 of 4096 27.1 / 28.6, 10 of 8192 (21 MB) 5 %; but 8 of 8192 (17 MB) 22.1 / 20.1, 64 of 4096 (67 MB) 43.1 / 42.6, 128 of
+    // 8192 (268 MB) 174 / 171.  Of 1024 points: 3 heads of 24576 (19 MB) 27.8 / 25.6, 4 of 32768 (34 MB) 30.9 / 30.5, 6 (50 MB) 44.6 / 42.1.
+    const size_t bytes = (size_t)nbh * pl.N1 * pl.N2 * 32 * sizeof(float2);
+    const bool through = R == 32 || bytes < ((size_t)18 << 20) || bytes > ((size_t)40 << 20);
+    auto inv = through ? k_cache_inv<R, PW, true> : k_cache_inv<R, PW, false>;
+    const void *kern = inverse ? reinterpret_cast<const void *>(inv)
                                : reinterpret_cast<const void *>(&k_cache_fwd<R, PW>);
     const hipError_t e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return e;
     float4 *X4 = reinterpret_cast<float4 *>(X);
     const float4 *tw = reinterpret_cast<const float4 *>(pl.twN1);
     const unsigned grid = (unsigned)units;
-    if (inverse) k_cache_inv<R, PW><<<grid, Unit::NT, lds, st>>>(X4, g, scr, tw, pl.N2, bh0, nbh);
+    if (inverse) inv<<<grid, Unit::NT, lds, st>>>(X4, g, scr, tw, pl.N2, bh0, nbh);
     else k_cache_fwd<R, PW><<<grid, Unit::NT, lds, st>>>(scr, X4, tw, pl.N2, bh0, nbh);
     return hipGetLastError();
 }

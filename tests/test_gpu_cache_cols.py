@@ -36,3 +36,25 @@ def test_window_transform_and_readout(oracle, N, B, H, io):
     y[:, :, [0, -1]] = y[:, :, [0, -1]].real
     want = np.fft.irfft(y, n=N, axis=2)[:, :, N - T:].transpose(0, 2, 1, 3)
     assert rel_l2(from_device(out), want) <= TOL[io]
+
+
+@pytest.mark.parametrize("N,heads", [(4096, (17, 18, 40, 41)), (16384, (4, 5, 14))])
+def test_readout_at_the_sizes_where_its_stores_change(N, heads):
+    """Columns through the L2 below 18 MB and above 40 MB, plain between (256-point columns; of 1024 points always through), and the window's
+    row transforms on both sides of 16 and 56 MB: the same bits as for two heads."""
+    from paper_2502_18394_amd import binding
+    gen = torch.Generator(device="cuda").manual_seed(N)
+    rows = [torch.randn((1, N + N // 8, max(heads), 64), generator=gen, device="cuda") for _ in range(2)]
+    g = torch.view_as_complex(torch.randn((1, max(heads), N // 2 + 1, 2), generator=gen, device="cuda"))
+
+    def window(H):
+        c = binding.PrefixCache(1, H, 64, N)
+        for part in (slice(0, N), slice(N, None)):                  # a prompt, then so many tokens that the window is transformed anew
+            c.update(*(r[:, part, :H].contiguous() for r in rows))
+        return c.prefix_fft, c.readout(g[:, :H].contiguous(), binding.READ_WINDOW)
+
+    spec, out = window(2)
+    for H in heads:
+        print(f"case N={N} H={H}", flush=True)
+        got_spec, got = window(H)
+        assert torch.equal(got_spec[:, :2], spec) and torch.equal(got[:, :, :2], out)
