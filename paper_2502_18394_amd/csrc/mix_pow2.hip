@@ -223,11 +223,10 @@ __global__ __launch_bounds__(RowTile<IO>::kPairs * TT) void k_small_inv(const ty
     const int bh = bh0 + bhl, b = bh / H, h = bh % H;
     {
         const int tl = tid % TT, p = tid / TT, t1 = t1_0 + tl;
-        const typename SC::elem_t *src = scr + (((size_t)bhl * N2) * 32 + p0) * N1 + t1_0;
-        const unsigned scr_at = (unsigned)(p * N1 + tl) * (unsigned)sizeof(typename SC::elem_t);
+        const typename SC::elem_t *src = scr + (((size_t)bhl * N2) * 32 + p0 + p) * N1 + t1;
         typename SC::elem_t raw[N2];
 #pragma unroll
-        for (int k2 = 0; k2 < N2; ++k2) raw[k2] = *lane_pointer(src + (size_t)k2 * 32 * N1, scr_at);
+        for (int k2 = 0; k2 < N2; ++k2) raw[k2] = src[(size_t)k2 * 32 * N1];
         float2 y[N2];
 #pragma unroll
         for (int k2 = 0; k2 < N2; ++k2) y[k2] = SC::get(raw[k2]);
@@ -240,7 +239,6 @@ __global__ __launch_bounds__(RowTile<IO>::kPairs * TT) void k_small_inv(const ty
     }
     __syncthreads();
     const int lp = tid % PW, r = tid / PW;
-    // the rows' addresses stay per lane: as scalar ones too, the stores cost 32 heads of 131072 rows on two streams 0.3 %
 #pragma unroll
     for (int t2 = 0; t2 < N2; ++t2) {
         const int l = t1_0 + r + N1 * t2;
