@@ -830,37 +830,43 @@ static hipError_t big_t(const Pow2Plan &pl, float2 *scr_v, const float2 *gp, int
 }
 
 hipError_t launch_big(const Pow2Plan &pl, float2 *scratch, const float2 *gp, int bh0, int nbh, int mode,
-                      hipStream_t st, bool shared_gate, bool scr16, bool affine, bool wide) {
-    // through_store only where the launch has memory to itself (mixer, us, plain / through: one head of fp32 rows at 16384 32.6 / 30.8, 16
-    // at 6144 34.1 / 33.0; on two streams 512 heads of bf16 rows at 3072 347 / 350, 128 at 20480 579 / 587)
-    const bool alone = !wide;
+                      hipStream_t st, bool shared_gate, bool scr16, bool affine, bool two_streams) {
+    // through_store where the launch has memory to itself (mixer, us, plain / through: one head of fp32 rows at 16384 32.6 / 30.8, 6 at 6144
+    // 27.4 / 24.1, one of bf16 rows at 65536 44.5 / 39.3, 20 of fp32 rows at 6144 46.5 / 45.0, 40 at 16384 186.8 / 184.6; on two streams 512
+    // heads of bf16 rows at 3072 347 / 350, 128 at 20480 579 / 587), except columns that the next kernel finds in the L2s: placed by head,
+    // 24 to 32 MB (fp32 rows, 32 heads at 3072 31.0 / 32.5, at 3584 35.6 / 37.3, 24 at 5120 40.7 / 42.3; 16 at 5120, 20 MB, 28.3 / 27.6, 32 at
+    // 6144, 48 MB, 60.9 / 59.9), of 4096 points 20 to 26 MB (bf16 rows, 2 heads at 49152 41.9 / 43.5, one at 98304 44.4 / 45.8; 2 at 57344, 28
+    // MB, 45.2 / 44.5; one at 65536, 16 MB, as above).
+    const size_t mb = ((size_t)nbh * pl.N1 * pl.N2 * 32 * (scr16 ? sizeof(uint32_t) : sizeof(float2))) >> 20;
+    const bool found = affine ? mb >= 24 && mb <= 32 : pl.P == 3 && mb >= 20 && mb <= 26;
+    const bool through = !two_streams && !found;
     const bool shfl = option(SPECTRE_OPT_LANE_SHUFFLES) != 0 && mode == 0 && !scr16;
     if (affine) {                                      // the mixer's forward-gate-inverse pass, fp32 scratch
         if (mode != 0 || scr16 || nbh % 8 != 0) return hipErrorInvalidValue;
-        if (pl.P == 2) return shfl ? big_t<2, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone, nbh)
-                                   : big_t<2, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone, nbh);
-        if (pl.P == 3) return shfl ? big_t<3, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone, nbh)
-                                   : big_t<3, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone, nbh);
+        if (pl.P == 2) return shfl ? big_t<2, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st, through, nbh)
+                                   : big_t<2, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, through, nbh);
+        if (pl.P == 3) return shfl ? big_t<3, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st, through, nbh)
+                                   : big_t<3, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, through, nbh);
         return hipErrorInvalidValue;
     }
     if (shfl) {
-        if (pl.P == 2) return big_t<2, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
-        if (pl.P == 3) return big_t<3, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
+        if (pl.P == 2) return big_t<2, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st, through);
+        if (pl.P == 3) return big_t<3, 0, ScrF32, true>(pl, scratch, gp, bh0, nbh, shared_gate, st, through);
         return hipErrorInvalidValue;
     }
     if (scr16) {                                       // the mixer's forward-gate-inverse pass only
         if (mode != 0) return hipErrorInvalidValue;
-        if (pl.P == 2) return big_t<2, 0, ScrBf16>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
-        if (pl.P == 3) return big_t<3, 0, ScrBf16>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
+        if (pl.P == 2) return big_t<2, 0, ScrBf16>(pl, scratch, gp, bh0, nbh, shared_gate, st, through);
+        if (pl.P == 3) return big_t<3, 0, ScrBf16>(pl, scratch, gp, bh0, nbh, shared_gate, st, through);
         return hipErrorInvalidValue;
     }
     if (pl.P == 2) {
-        if (mode == 0) return big_t<2, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
-        if (mode == 1) return big_t<2, 1>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
+        if (mode == 0) return big_t<2, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, through);
+        if (mode == 1) return big_t<2, 1>(pl, scratch, gp, bh0, nbh, shared_gate, st, through);
     } else if (pl.P == 3) {
-        if (mode == 0) return big_t<3, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone, 0, wide);
-        if (mode == 1) return big_t<3, 1>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
-        if (mode == 2) return big_t<3, 2>(pl, scratch, gp, bh0, nbh, shared_gate, st, alone);
+        if (mode == 0) return big_t<3, 0>(pl, scratch, gp, bh0, nbh, shared_gate, st, through, 0, two_streams);
+        if (mode == 1) return big_t<3, 1>(pl, scratch, gp, bh0, nbh, shared_gate, st, through);
+        if (mode == 2) return big_t<3, 2>(pl, scratch, gp, bh0, nbh, shared_gate, st, through);
     }
     return hipErrorInvalidValue;
 }
