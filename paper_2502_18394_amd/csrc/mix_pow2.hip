@@ -42,10 +42,9 @@ template <typename IO> struct TileStride { static constexpr int value = RowTile<
 // stages them in LDS, then lane (pair p, t1_local) runs the N2-point DFT over t2.
 // ring != nullptr (pre-fill of an empty Prefix-FFT cache): every row read is also copied, as fp32, to row l of head bh
 // of the value ring buffer ring [B*H][N1 * N2][32 pairs] - the rows then cross HBM once for both purposes.
-// PART: fewer rows than the transform, or a ring.  Addresses stay per lane there: as scalar ones the row loads and the stores to ring and
-// scratch come in denser bursts, which memory moves more slowly (20011 tokens, B = 8 H = 32 N = 32768, 2760 -> 2815 us; mixer of
-// 2 x 8 heads at 5000 105 -> 106).  Whole transforms gain: mixer of 8 heads of fp32 rows at 8192 29.1 -> 26.7 us, 32 at 24576 233 ->
-// 225, at 131072 1139 -> 1105, of bf16 rows at 65536 517 -> 505.
+// PART: fewer rows than the transform, a ring, or a size at which it is the faster (small_fwd_t).  Addresses stay per lane there: as scalar
+// ones the row loads and the stores to ring and scratch come in denser bursts, which memory moves more slowly (20011 tokens, B = 8 H =
+// 32 N = 32768, 2760 -> 2815 us; mixer of 2 x 8 heads at 5000 105 -> 106).
 template <int N2, int TT, typename IO, typename SC, bool PART>
 __global__ __launch_bounds__(RowTile<IO>::kPairs * TT) void k_small_fwd(const typename IO::pair_t *__restrict__ v,
                                                        typename SC::elem_t *__restrict__ scr,
@@ -693,11 +692,17 @@ template <int N2, int TT, typename IO, typename SC>
 static hipError_t small_fwd_t(const Pow2Plan &pl, const void *v, void *scr_v, int rows, int H, int bh0,
                               int nbh, hipStream_t st, int aff, float2 *ring) {
     const size_t lds = (size_t)N2 * TT * TileStride<IO>::value * sizeof(typename IO::pair_t);
+    // Scalar addresses for whole transforms of up to 16 MB and from 56 MB of fp32 rows or 128 MB of bf16 rows on, by the bytes of their
+    // scratch.  Between, the denser bursts of loads and stores lose more often than they gain.  Mixer, us, per lane / scalar, fp32 rows: 8
+    // heads at 5120 (10 MB) 19.4 / 18.6, 24 (31 MB) 38.3 / 42.3, 48 (63 MB) 76.1 / 74.5; 6 at 20480 (31 MB) 39.7 / 43.5; 2 at 49152 (25 MB)
+    // 46.1 / 48.5; 32 at 24576 (201 MB) 233 / 225; 16 at 28672 (117 MB) 142 / 136; bf16 rows: 32 at 7168 (59 MB) 54.6 / 57.6, 48 (88 MB)
+    // 77.1 / 81.9, 64 (117 MB) 2 %, 96 (176 MB) -1 %, 32 at 6144 (50 MB) 47.3 / 49.8.  Windows of a cache (fp32 ring) alike: 8 to 16 MB -2 to
+    // -3 %, 20 to 50 MB up to +5 %, 100 to 200 MB -1 to -5 %.
+    const size_t bytes = (size_t)nbh * pl.N1 * N2 * 32 * sizeof(typename SC::elem_t);
+    const size_t from = (size_t)(std::is_same<IO, IoF32>::value ? 56 : 128) << 20;
+    const bool scalar = bytes <= ((size_t)16 << 20) || bytes >= from;
     const bool part = ring || rows < pl.N1 * N2;
-    if (part && std::is_same<SC, ScrBf16>::value) return hipErrorInvalidValue;                 // mixers alone take that scratch
-    auto kern = k_small_fwd<N2, TT, IO, SC, false>;
-    if constexpr (!std::is_same<SC, ScrBf16>::value)
-        if (part) kern = k_small_fwd<N2, TT, IO, SC, true>;
+    auto kern = part || !scalar ? k_small_fwd<N2, TT, IO, SC, true> : k_small_fwd<N2, TT, IO, SC, false>;
     typename SC::elem_t *scr = static_cast<typename SC::elem_t *>(scr_v);
     hipError_t e = allow_lds(kern, lds);
     if (e != hipSuccess) return e;
