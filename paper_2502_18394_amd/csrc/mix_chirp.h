@@ -31,8 +31,20 @@ hipError_t launch_chirp_post(const float2 *U, const float2 *w, float2 *KK, int L
 hipError_t launch_chirp_gate(const float2 *scr, float2 *gp, int BH, int M, int N1, int N2, int ph0, int nphl,
                              hipStream_t st);
 
-// Length D of the data pass for L <= 1024 (an in-LDS length >= 2L-1, at most the padded length); 0: none.
-int chirp_data_length(int L);
+// Length D of the data pass for L <= 1024 (>= 2L-1, at most the padded length); 0: none.  In-LDS lengths of compile-time radices,
+// which have a form for half the rows (mix_slab.hip): the padded lengths of the chirp, multiples of 256, are up to a third longer
+// (B=64 H=12 fp32: L = 197 on 400 instead of 512 points 53.2 -> 41.8 us, L = 157 on 320 51 -> 32).
+constexpr int kChirpDataLengths[] = {256, 320, 400, 448, 512, 640, 768, 896, 1024, 1280, 1536, 1792, 2048};
+inline int chirp_data_length(int L) {
+    for (int D : kChirpDataLengths)
+        if (D >= 2 * L - 1) return D;
+    return 0;
+}
+constexpr bool chirp_uses(int D) {
+    for (int x : kChirpDataLengths)
+        if (x == D) return true;
+    return false;
+}
 // All of that in one launch for L <= 1024: g [BH, L/2+1] -> gp [BH][D/2+1] in plain bin order, unscaled, the gate argument
 // of the in-LDS kernel when it runs the padded convolution.  twM [M] = exp(-j 2 pi m / M), rootsD the same for D.
 hipError_t launch_chirp_lds(const float2 *g, const float2 *w, const float2 *filt, const float2 *twM, const float2 *rootsD,

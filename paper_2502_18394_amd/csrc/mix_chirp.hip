@@ -265,16 +265,6 @@ __global__ __launch_bounds__(16 * N2 * kChirpHeads<N2>) void k_chirp_lds(const f
     }
 }
 
-// Lengths of the data pass: the in-LDS lengths of compile-time radices, as the padded lengths of the chirp, multiples of 256,
-// are up to a third longer (B=64 H=12 fp32: L = 197 on 400 instead of 512 points 53.2 -> 41.8 us, L = 157 on 320 51 -> 32).
-static constexpr int kDataLengths[] = {256, 320, 400, 448, 512, 640, 768, 896, 1024, 1280, 1536, 1792, 2048};
-
-int chirp_data_length(int L) {
-    for (int D : kDataLengths)
-        if (D >= 2 * L - 1) return D;
-    return 0;
-}
-
 hipError_t launch_chirp_lds(const float2 *g, const float2 *w, const float2 *filt, const float2 *twM, const float2 *rootsD,
                             float2 *gp, int BH, int L, int M, hipStream_t st) {
     if (M != chirp_padded_length(L)) return hipErrorInvalidValue;

@@ -2,6 +2,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include "mix_chirp.h"
+
 namespace spectre {
 
 constexpr int kSlabMaxL = 2048;
@@ -11,6 +13,10 @@ bool slab_supported(int L);
 
 // Host: bin_of_pos[p] = the bin held by position p after the forward passes (mixed-radix digit reversal).
 void slab_bin_order(int L, int *bin_of_pos);
+
+// Whether the kernels of compile-time radices take `rows` rows per sequence for an L-point transform: all of them, or at most half at the
+// lengths that have a form which knows which rows are zero, the padded convolution's.  The other form reads and writes L rows.
+inline bool slab_ct_rows(int L, int rows) { return rows == L || (2 * rows <= L && chirp_uses(L)); }
 
 // Heads per launch, a multiple of 8, of a kernel with `parts` workgroups of `lanes` lanes to a head: the runtime takes fewer
 // than 2^32 lanes a launch (2^21 heads of 448 or 512 points, 230 to 275 GB of bf16 rows in and out, reach that).

@@ -528,8 +528,6 @@ int slab_pairs_per_workgroup(int io, int BH, int L) {
 // four / eight pairs / 12 x 8 x 8 74 / 61 / 60; 896 as 28 x 32 / 14 x 8 x 8 on four / eight 90 / 74 / 68; 1024 as 16 x 16 x 4 / 32
 // x 32 / 16 x 8 x 8 on eight / four 96 / 94 / 100 / 76; 640 as 10 x 8 x 8 / 20 x 32 55 / 49; 400 as 20 x 20 on sixteen / four /
 // eight pairs, 10 x 8 x 5 42 / 41 / 37 / 40; 384 heads of 1280 as 16 x 16 x 5 / 10 x 16 x 8 / 20 x 8 x 8 108 / 95 / 75).
-// the lengths that also serve as data length of the padded convolution
-constexpr bool chirp_uses(int L) { return L != 144 && L != 196 && L != 576 && L != 784; }
 template <typename IO>
 static bool mix_ct(int L, const void *v, const float2 *g, void *out, const float2 *roots, int B, int H, int rows,
                    hipStream_t st, hipError_t *e) {
@@ -542,7 +540,7 @@ static bool mix_ct(int L, const void *v, const float2 *g, void *out, const float
     // 1300 315 / 296).
     const bool large = 64 * heads * rows * (long long)sizeof(typename IO::pair_t) > 100000000;
     const bool stream = large && ((reinterpret_cast<uintptr_t>(v) | reinterpret_cast<uintptr_t>(out)) & 127) == 0;
-    if (rows != L && 2 * rows > L) return false;
+    if (!slab_ct_rows(L, rows)) return false;
 #define SPECTRE_CT_RUN(PP, NT, R0, R1, R2, DIRECT, STREAM, HALF)                                                        \
     {                                                                                                                   \
         if constexpr (!DIRECT) {                                                                                        \
@@ -556,8 +554,10 @@ static bool mix_ct(int L, const void *v, const float2 *g, void *out, const float
     }
 #define SPECTRE_CT(PP, NT, R0, R1, R2, DIRECT, STREAM)                                                                  \
     {                                                                                                                   \
-        if constexpr (chirp_uses(R0 * R1 * R2))                                                                         \
-            if (rows != L) SPECTRE_CT_RUN(PP, NT, R0, R1, R2, DIRECT, STREAM, true)                                     \
+        if (rows != L) {                                                                                                \
+            if constexpr (chirp_uses(R0 * R1 * R2)) SPECTRE_CT_RUN(PP, NT, R0, R1, R2, DIRECT, STREAM, true)            \
+            return false;                                                                                               \
+        }                                                                                                               \
         SPECTRE_CT_RUN(PP, NT, R0, R1, R2, DIRECT, STREAM, false)                                                       \
     }
 #define SPECTRE_CT_FEW(PP, NT, R0, R1, R2) \
