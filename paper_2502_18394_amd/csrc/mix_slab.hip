@@ -282,7 +282,10 @@ __global__ __launch_bounds__(NT) void k_mix_ct(const typename IO::pair_t *v, con
         src = lane_pointer(src, !HALF || i0 + S0 * j < n_rows ? lane_at : (at_t)col * (at_t)sizeof(pair_t));
         raw[j] = STREAM ? IO::load_stream(src) : *src;
     }
-    __builtin_amdgcn_sched_barrier(0);
+    // Above 1024 points the lanes of the form for few heads load so many factors of their own that those may go in between (us, held back /
+    // free / before the scalar addresses: one head of bf16 rows at 1792 8.93 / 8.79 / 8.66, 16 of fp32 10.84 / 10.70 / 10.50, 32 at 1280
+    // 11.49 / 11.31 / 11.22, one 8.83 / 8.67 / 8.81; but 32 at 784 8.22 / 8.41 / 7.97).
+    if constexpr (!DIRECT || L <= 1024) __builtin_amdgcn_sched_barrier(0);
     constexpr float scale = 1.0f / (float)L;
     auto gate_fix = [&](float2 val, int k) {                         // Hermitian extension; real at DC and Nyquist
         // on the bits: selections of what a load returns become branches around it
