@@ -113,18 +113,17 @@ def _dev(t, name):
     return ctypes.c_void_p(_ptr(t, name))
 
 
-def _stream(stream):
-    """Handle of `stream`, or of the current one (without the Stream object that torch.cuda.current_stream builds)."""
-    if stream is None:
-        return ctypes.c_void_p(torch._C._cuda_getCurrentRawStream(torch.cuda.current_device()))
-    return ctypes.c_void_p(stream.cuda_stream)
-
-
 def _raw_stream(stream):
-    """The same as a plain integer, for the functions whose argument types are declared."""
+    """Handle of `stream`, or of the current one (without the Stream object that torch.cuda.current_stream builds), as a plain integer, for
+    the functions whose argument types are declared."""
     if stream is None:
         return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
     return stream.cuda_stream
+
+
+def _stream(stream):
+    """The same for the others."""
+    return ctypes.c_void_p(_raw_stream(stream))
 
 
 def _given(ws):
