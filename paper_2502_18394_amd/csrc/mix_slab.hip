@@ -521,16 +521,21 @@ int slab_pairs_per_workgroup(int io, int BH, int L) {
 //   1024    6.3 /  7.3    6.6 /  7.8   10.2 /  9.4   18.1 / 12.9   32.3 / 22.1     215 /  138     16
 //   1280    8.9 /  9.3    9.1 /  9.5   11.6 / 11.7   18.4 / 18.1   33.8 / 31.6     203 /  175     32
 //   1536    8.4 / 10.0    8.5 / 10.2   13.4 / 12.9   28.5 / 20.5   52.2 / 35.8     359 /  213     16
-// The figures below are of the kernel with per-lane addresses, which cost both sides alike.
-// None for few: 512 (5.3 / 5.4, 5.4 / 5.5, 6.1 / 5.8), 2048 (two pairs 11.1 / 10.6 at one head), and the two passes of radix 16
-// to 32 of 320, 400 and 640 (four pairs at one head 7.0 / 7.5, 7.1 / 7.9 and 7.5 / 8.1, but 9.7 / 8.5 at 48 of 400; three shorter
-// passes would take 5.8 at 320 and 400, with 3 and 5 % more error).
-// Splits of the other form: three short passes on more lanes beat two passes of radix 28 and 32, which leave two waves per SIMD
-// (24 x 24 excepted: 768 heads of 576 42 us, 12 x 6 x 8 48), and eight pairs per workgroup beat four while a compute unit
-// still holds two or more (768 heads: 512 as 32 x 16 / 16 x 32 / 8 x 8 x 8 on four / eight pairs 54 / 54 / 45 / 43; 768 as 24 x 32 on
-// four / eight pairs / 12 x 8 x 8 74 / 61 / 60; 896 as 28 x 32 / 14 x 8 x 8 on four / eight 90 / 74 / 68; 1024 as 16 x 16 x 4 / 32
-// x 32 / 16 x 8 x 8 on eight / four 96 / 94 / 100 / 76; 640 as 10 x 8 x 8 / 20 x 32 55 / 49; 400 as 20 x 20 on sixteen / four /
-// eight pairs, 10 x 8 x 5 42 / 41 / 37 / 40; 384 heads of 1280 as 16 x 16 x 5 / 10 x 16 x 8 / 20 x 8 x 8 108 / 95 / 75).
+// Lengths without a form for few, and the splits of the other form: three short passes on more lanes beat two passes of radix 28 and 32,
+// which leave two waves per SIMD (24 x 24 excepted), and eight pairs per workgroup beat four while a compute unit still holds two or
+// more.  Chosen with per-lane addresses.  With scalar ones, bf16 rows over rotating buffers, us at one / 32 / 768 heads:
+//    512 as  8 x 8 x 8 on eight pairs 4.7 / 5.7 / 40.6; on four 4.4 / 5.5 / 54.6, as form for few 4.1 / 5.2 / 62.9; 32 x 16 7.3 / 8.3 / 50.9
+//    768 as 12 x 8 x 8 on eight (form for few 6.0 / 7.6) - / - / 67.6; 24 x 32 on four 7.3 / 8.9 / 96.5, on eight 7.4 / 8.9 / 69.4
+//    896 as 14 x 8 x 8 on eight (6.5 / 8.3) - / - / 80.5; on four 7.0 / 8.6 / 113; 28 x 32 on four 8.0 / 9.9 / 123
+//   1024 as 16 x 8 x 8 on four (6.4 / 9.3) - / - / 136; on eight 7.5 / 9.3 / 126; 16 x 16 x 4 6.9 / 9.0 / 130; 32 x 32 8.6 / 10.6 / 149
+//   1280 as 20 x 8 x 8 on four (9.3 / 11.5) - / - / 172; 16 x 16 x 5 8.7 / 10.7 / 256; 10 x 16 x 8 7.7 / 9.6 / 214
+//    576 as 24 x 24 on eight (5.3 / 6.6) - / - / 51.6; 12 x 6 x 8 5.7 / 6.9 / 54.4
+//    640 as 20 x 32 on eight 6.7 / 8.2 / 53.4; as form for few on four 6.5 / 7.9 / 90.1; 10 x 8 x 8 6.1 / 7.3 / 58.3
+//    400 as 20 x 20 on eight 6.1 / 7.0 / 36.2; on sixteen 5.8 / 6.6 / 30.3, as form for few on four 5.3 / 6.3 / 55.1; 10 x 8 x 5 5.5 / 6.4 / 40.4
+//    320 as 20 x 16 on sixteen 6.1 / 6.8 / 23.8; as form for few on four 5.6 / 6.4 / 44.9; 5 x 8 x 8 as form for few 3.7 / 4.5 / 40.4
+//   2048 as 16 x 16 x 8 on four 10.4 / 15.4 / 324; as form for few on two 10.3 / 22.8 / 324
+// So 512, 640 and 1280 would now gain by another form for few heads and 400 by sixteen pairs, which is not taken yet; three passes of 320 and
+// 400 have 3 and 5 % more error than two.
 template <typename IO>
 static bool mix_ct(int L, const void *v, const float2 *g, void *out, const float2 *roots, int B, int H, int rows,
                    hipStream_t st, hipError_t *e) {
