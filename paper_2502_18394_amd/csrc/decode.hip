@@ -12,9 +12,11 @@
 // layer) and the round trip of the gate through memory that it replaces.
 // A chip's workgroups of one round run in step, so what a workgroup waits for outside its two streams is time without
 // traffic.  Loads return in order: the first layer's operands are requested before the weights, whose arrival its chain then
-// passes behind, and the first rows of the half spectra as soon as the weights' registers are free, ahead of the factors; a
-// row's registers take the one after next when it is used.  us a token, before / now: B=1 H=32, deferred, N=4096 18.6 /
-// 16.8, 8192 27.5 / 27.0, 12288 40.8 / 39.1; every step updating, 4096 22.7 / 20.7.  (Plain loads, so that both streams stay
+// passes behind, and the first rows of the half spectra as soon as the weights' registers are free, ahead of the factors; in
+// steps that only read them a row's registers take the one after next when it is used.  Steps that write the rows back request
+// the next eight together: one by one between the stores they were 1 to 3 % slower in long caches (us, before / one by one / together:
+// B=3 H=20 N=32768 200 / 206 / 200, B=4 H=32 N=65536 856 / 864 / 854).  us a token, before / now: B=1 H=32, deferred, N=4096 18.6 / 16.8,
+// 8192 27.5 / 27.0, 12288 40.8 / 39.0; every step updating, 4096 22.5 / 21.0, 16384 72.3 / 71.9.  (Plain loads, so that both streams stay
 // in the memory-side cache from token to token, gain another 2 to 15 % below 268 MB when nothing else runs between, and lose 6 to
 // 17 % when the caches and weights of eight layers take turns.)
 // Measured against ring update + hidden + output layer + sweep + final: B=1 H=32 N=8192, deferred updates, 39.7 ->
@@ -238,7 +240,8 @@ __global__ __launch_bounds__(256, 4) void k_decode(float4 *__restrict__ X, Decod
         float acc0 = 0.f, acc1 = 0.f, kacc = 0.f;
         float4 *Xp = head_of(bl);
         const float2 *rp = s_r + bl * kBinStride, *gp = s_g + bl * kBinStride;
-        // a row's registers take the one after next (half a chunk on, then the next sequence's) as soon as it is used
+        // a row's registers take the one after next (half a chunk on, then the next sequence's) as soon as it is used; where the rows are
+        // written back, all eight together behind the last store
 #pragma unroll 1
         for (int half = 0; half < 2; ++half) {
             const int next_bl = half ? bl + 1 : bl, next_k = half ? row : kHalf + row;
@@ -253,7 +256,11 @@ __global__ __launch_bounds__(256, 4) void k_decode(float4 *__restrict__ X, Decod
                     kacc = fmaf(gc.x, e.x, fmaf(gc.y, e.y, kacc));   // c_k/N Re(g_k conj(e_k))
                     e = cmul(e, sq_now.rot);
                 }
-                if (next_bl < nb) x[u] = load_row(next_bl, next_k + 8 * u);
+                if (LAZY && next_bl < nb) x[u] = load_row(next_bl, next_k + 8 * u);
+            }
+            if (!LAZY && next_bl < nb) {
+#pragma unroll
+                for (int u = 0; u < kU; ++u) x[u] = load_row(next_bl, next_k + 8 * u);
             }
         }
         if (last && row == 0) {                                      // Nyquist
