@@ -601,7 +601,7 @@ static int mix_ready(int route, int L, spectre_dtype io) {
 static int mix_four_step(const Pow2Plan &pl, const void *v, const float2 *g, void *out, int BH, int L, int H, int d,
                          spectre_dtype io, float2 *gp, char *scr_base, size_t lane_bytes, const MixGroups &mg,
                          bool scr16, SideLane *side, hipStream_t st, const void *wpack = nullptr, int Hw = 0,
-                         float2 *bsum = nullptr) {
+                         float2 *bsum = nullptr, bool just_written = false) {
     hipError_t e = hipSuccess;
     if (side) {
         // fork: the helper stream starts after everything before this call on the caller's stream.  Its first
@@ -630,7 +630,7 @@ static int mix_four_step(const Pow2Plan &pl, const void *v, const float2 *g, voi
         const bool affine = !scr16 && pl.P != 0 && nbh % 8 == 0 && (size_t)L * (d / 2) * sizeof(float2) <= ((size_t)3 << 20) &&
                             option(SPECTRE_OPT_HEAD_AFFINE) != 0;
         e = wpack ? launch_small_fwd_proj(pl, v, wpack, Hw, scr, L, H, bh0, nbh, ls, affine)
-                  : launch_small_fwd(pl, (int)io, v, scr, L, H, bh0, nbh, ls, scr16, affine);
+                  : launch_small_fwd(pl, (int)io, v, scr, L, H, bh0, nbh, ls, scr16, affine, nullptr, just_written);
         if (e != hipSuccess) { what = "small_fwd"; break; }
         if (lane && !side_has_gate) {
             e = hipStreamWaitEvent(side->stream, side->gate, 0);
@@ -658,9 +658,10 @@ static int mix_four_step(const Pow2Plan &pl, const void *v, const float2 *g, voi
     return SPECTRE_OK;
 }
 
-// The mixer behind the checks of its arguments; ws holds what the route uses (at most spectre_mix_workspace_bytes).
+// The mixer behind the checks of its arguments; ws holds what the route uses (at most spectre_mix_workspace_bytes).  just_written: the
+// kernel in front of this call wrote v.
 static int mix_forward_checked(const void *v, const void *g, void *out, int B, int L, int H, int d, spectre_dtype io,
-                               unsigned flags, void *ws, hipStream_t st) {
+                               unsigned flags, void *ws, hipStream_t st, bool just_written = false) {
     int rc;
     const int BH = B * H;
     const int route = mix_route(BH, L, d, io);
@@ -714,7 +715,7 @@ static int mix_forward_checked(const void *v, const void *g, void *out, int B, i
         if (rc) return rc;
     }
     rc = mix_four_step(pl, v, static_cast<const float2 *>(g), out, BH, L, H, d, io, gp, scr_base, lane_bytes, mg, scr16,
-                       side, st);
+                       side, st, nullptr, 0, nullptr, just_written);
     if (side) release_lane(dev, side);
     return rc;
 }
@@ -1141,7 +1142,7 @@ int spectre_layer_forward(const void *x, const float *Wq, const float *Wv, int H
         if (side) release_lane(dev, side);
         if (rc) return rc;
     } else {
-        rc = mix_forward_checked(vbuf, g, out, B, L, H, d, io, 0u, mix_ws, st);
+        rc = mix_forward_checked(vbuf, g, out, B, L, H, d, io, 0u, mix_ws, st, true);
         if (rc) return rc;
     }
     if (W) {

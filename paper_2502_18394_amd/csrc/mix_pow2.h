@@ -64,10 +64,10 @@ bool pow2_split(int L, int *N1, int *N2, int *P);
 // affine (nbh a multiple of 8; big: mode 0, fp32 scratch): every workgroup of head bh0 + 8 s + x runs on XCD x, and the
 // three kernels walk s up, down, up, so that part of the scratch is read from the L2 it was written through.
 // ring (pre-fill of an empty cache without memory rows): the rows read are also stored, as fp32 pairs, to row l of head
-// bh of ring [B*H][L][32], the cache's value ring buffer.
+// bh of ring [B*H][L][32], the cache's value ring buffer.  just_written: the rows come from a kernel right before, not from memory.
 hipError_t launch_small_fwd(const Pow2Plan &pl, int io, const void *v, float2 *scratch, int rows, int H,
                             int bh0, int nbh, hipStream_t st, bool scr16 = false, bool affine = false,
-                            float2 *ring = nullptr);
+                            float2 *ring = nullptr, bool just_written = false);
 // two_streams: another launch of the call runs beside this one (8 instead of 4 columns per workgroup for mode 0, 4096-point columns and
 // fp32 scratch; no stores through the L2).
 hipError_t launch_big(const Pow2Plan &pl, float2 *scratch, const float2 *gp, int bh0, int nbh, int mode,
