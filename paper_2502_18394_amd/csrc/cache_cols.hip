@@ -321,8 +321,9 @@ hipError_t launch_mix_cols(const Pow2Plan &pl, float2 *scr, const float2 *gp, in
     if (pl.N1 != R * R) return hipErrorInvalidValue;
     const size_t lds = (size_t)PW * (pl.N1 + R) * sizeof(float) + (size_t)pl.N1 * sizeof(float2);
     const int planes = nbh * pl.N2;
-    // through_store for launches of up to 128 MB that have memory to themselves (32 heads of bf16 rows, mixer, us, plain / through: 12288,
-    // 100 MB, 95.9 / 92.8; layer of 24576, 201 MB, 318.8 / 324.2)
+    // through_store for launches of up to 128 MB that have memory to themselves (mixer of bf16 rows, us, plain / through: one head at 24576 (6 MB)
+    // 28.9 / 26.8, 8 at 28672 (59 MB) 3 %, 32 at 12288 (100 MB) 95.9 / 92.8, 40 (126 MB) 1 %; 48 to 128 heads at 12288 to 28672 -0.3 %, layer
+    // of 24576 (201 MB) 318.8 / 324.2)
     const auto kern = alone && (size_t)planes * 32 * R * R * sizeof(float2) <= ((size_t)128 << 20) ? k_mix_cols<R, PW, true> : k_mix_cols<R, PW, false>;
     kern<<<(planes + 7) / 8 * 8 * (32 / PW), PW * R, lds, st>>>(scr, gp, reinterpret_cast<const float4 *>(pl.twN1), pl.N2, bh0, planes);
     return hipGetLastError();

@@ -34,8 +34,8 @@ template <> struct RowTile<IoBf16> { static constexpr int kPairs = 32, kStride =
 template <> struct RowTile<IoF32> { static constexpr int kPairs = 16, kStride = 18; };
 template <typename IO> struct TileStride { static constexpr int value = RowTile<IO>::kStride; };
 
-// The addresses of the row kernels are a scalar base per row, plane or block and one 32-bit offset of the lane (lane_pointer): as
-// 64-bit products per lane and row they were a quarter of these kernels' vector time.
+// Where it gains, the addresses of the forward row kernels are a scalar base per row or block and one 32-bit offset of the lane
+// (lane_pointer): 64-bit products per lane and row are a quarter of these kernels' vector time.
 //
 // small_fwd: grid (N1/TT * 32/PW, nbh); block PW*TT threads, PW = RowTile<IO>::kPairs.  Reads the N2*TT rows
 // {t1_0 + r + N1*t2} of one head (PW pairs each, one 128-byte segment per row),
