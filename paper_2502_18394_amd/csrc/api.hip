@@ -630,7 +630,7 @@ static int mix_four_step(const Pow2Plan &pl, const void *v, const float2 *g, voi
         const bool affine = !scr16 && pl.P != 0 && nbh % 8 == 0 && (size_t)L * (d / 2) * sizeof(float2) <= ((size_t)3 << 20) &&
                             option(SPECTRE_OPT_HEAD_AFFINE) != 0;
         e = wpack ? launch_small_fwd_proj(pl, v, wpack, Hw, scr, L, H, bh0, nbh, ls, affine)
-                  : launch_small_fwd(pl, (int)io, v, scr, L, H, bh0, nbh, ls, scr16, affine, nullptr, just_written);
+                  : launch_small_fwd(pl, (int)io, v, scr, L, H, bh0, nbh, ls, scr16, affine, nullptr, just_written, side != nullptr);
         if (e != hipSuccess) { what = "small_fwd"; break; }
         if (lane && !side_has_gate) {
             e = hipStreamWaitEvent(side->stream, side->gate, 0);

@@ -67,8 +67,8 @@ bool pow2_split(int L, int *N1, int *N2, int *P);
 // bh of ring [B*H][L][32], the cache's value ring buffer.  just_written: the rows come from a kernel right before, not from memory.
 hipError_t launch_small_fwd(const Pow2Plan &pl, int io, const void *v, float2 *scratch, int rows, int H,
                             int bh0, int nbh, hipStream_t st, bool scr16 = false, bool affine = false,
-                            float2 *ring = nullptr, bool just_written = false);
-// two_streams: another launch of the call runs beside this one (8 instead of 4 columns per workgroup for mode 0, 4096-point columns and
+                            float2 *ring = nullptr, bool just_written = false, bool two_streams = false);
+// two_streams (here and above): another launch of the call runs beside this one (8 instead of 4 columns per workgroup for mode 0, 4096-point columns and
 // fp32 scratch; no stores through the L2).
 hipError_t launch_big(const Pow2Plan &pl, float2 *scratch, const float2 *gp, int bh0, int nbh, int mode,
                       hipStream_t st, bool shared_gate = false, bool scr16 = false, bool affine = false,

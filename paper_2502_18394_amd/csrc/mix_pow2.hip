@@ -690,18 +690,20 @@ static hipError_t allow_lds(K kernel, size_t bytes) {
 
 template <int N2, int TT, typename IO, typename SC>
 static hipError_t small_fwd_t(const Pow2Plan &pl, const void *v, void *scr_v, int rows, int H, int bh0,
-                              int nbh, hipStream_t st, int aff, float2 *ring, bool just_written) {
+                              int nbh, hipStream_t st, int aff, float2 *ring, bool just_written, bool two_streams) {
     const size_t lds = (size_t)N2 * TT * TileStride<IO>::value * sizeof(typename IO::pair_t);
-    // Scalar addresses for whole transforms of up to 16 MB and from 56 MB of fp32 rows or 128 MB of bf16 rows on, by the bytes of their
+    // Scalar addresses for whole transforms, alone, of up to 16 MB and from 56 MB of fp32 rows or 128 MB of bf16 rows on, by the bytes of their
     // scratch.  Between, the denser bursts of loads and stores lose more often than they gain.  Mixer, us, per lane / scalar, fp32 rows: 8
     // heads at 5120 (10 MB) 19.4 / 18.6, 24 (31 MB) 38.3 / 42.3, 48 (63 MB) 76.1 / 74.5; 6 at 20480 (31 MB) 39.7 / 43.5; 2 at 49152 (25 MB)
     // 46.1 / 48.5; 32 at 24576 (201 MB) 233 / 225; 16 at 28672 (117 MB) 142 / 136; bf16 rows: 32 at 7168 (59 MB) 54.6 / 57.6, 48 (88 MB)
     // 77.1 / 81.9, 64 (117 MB) 2 %, 96 (176 MB) -1 %, 32 at 6144 (50 MB) 47.3 / 49.8.  Windows of a cache (fp32 ring) alike: 8 to 16 MB -2 to
     // -3 %, 20 to 50 MB up to +5 %, 100 to 200 MB -1 to -5 %.  Rows that the projection has just written gain nothing above 16 MB and lose
-    // there too (layer of fp32 rows, 32 heads at 16384 249 / 254, 2 x 20 at 12288 214 / 218, 20 at 32768 321 / 324).
+    // there too (layer of fp32 rows, 32 heads at 16384 249 / 254, 2 x 20 at 12288 214 / 218, 20 at 32768 321 / 324).  Beside another launch
+    // scalar ones gain at every size (launches of 64 to 100 MB, 32 heads of bf16 rows at 49152 360 / 351, 64 697 / 683, 256 at 12288 656 / 637, at
+    // 131072 945 / 938; layer of 20 heads of fp32 rows at 65536 605 / 585, 77 at 24576 709 / 696).
     const size_t bytes = (size_t)nbh * pl.N1 * N2 * 32 * sizeof(typename SC::elem_t);
     const size_t from = (size_t)(std::is_same<IO, IoF32>::value ? 56 : 128) << 20;
-    const bool scalar = bytes <= ((size_t)16 << 20) || (bytes >= from && !just_written);
+    const bool scalar = bytes <= ((size_t)16 << 20) || two_streams || (bytes >= from && !just_written);
     const bool part = ring || rows < pl.N1 * N2;
     auto kern = part || !scalar ? k_small_fwd<N2, TT, IO, SC, true> : k_small_fwd<N2, TT, IO, SC, false>;
     typename SC::elem_t *scr = static_cast<typename SC::elem_t *>(scr_v);
@@ -758,12 +760,13 @@ static hipError_t small_inv_t(const Pow2Plan &pl, const void *scr_v, void *out, 
     }
 
 hipError_t launch_small_fwd(const Pow2Plan &pl, int io, const void *v, float2 *scratch, int rows, int H,
-                            int bh0, int nbh, hipStream_t st, bool scr16, bool affine, float2 *ring, bool just_written) {
+                            int bh0, int nbh, hipStream_t st, bool scr16, bool affine, float2 *ring, bool just_written,
+                            bool two_streams) {
     if (scr16 && !io) return hipErrorInvalidValue;
     if (affine && nbh % 8 != 0) return hipErrorInvalidValue;
     const int aff = affine ? nbh : 0;
-    if (pl.N1 == 1024 && !scr16) SPECTRE_DISPATCH_FINE(small_fwd_t, pl, v, scratch, rows, H, bh0, nbh, st, aff, ring, just_written)
-    SPECTRE_DISPATCH_N2(small_fwd_t, pl, v, scratch, rows, H, bh0, nbh, st, aff, ring, just_written)
+    if (pl.N1 == 1024 && !scr16) SPECTRE_DISPATCH_FINE(small_fwd_t, pl, v, scratch, rows, H, bh0, nbh, st, aff, ring, just_written, two_streams)
+    SPECTRE_DISPATCH_N2(small_fwd_t, pl, v, scratch, rows, H, bh0, nbh, st, aff, ring, just_written, two_streams)
 }
 
 template <int N2, typename SC>
