@@ -218,6 +218,33 @@ def test_positional_phase_turns_the_gate(B, H, Hg, n, dg):
         assert bool((err <= 6 * 2.0 ** -24 * plain.abs()).all())
 
 
+@pytest.mark.parametrize("B,L,H,io,shared,phase", [
+    (1, 4096, 1, "f32", False, 0),      # chunks of 16-piece columns; a length with two output reals behind the last whole tile
+    (1, 2113, 1, "f32", False, 0),      # odd length, ragged last chunk and tile
+    (4, 3008, 1, "bf16", False, 777),   # 8-piece columns, four rows of one weight set inside the output layer, phase on the last bin
+    (5, 3008, 1, "bf16", False, 777),   # a fifth: hidden layer in its own launch
+    (2, 2500, 5, "bf16", False, 0),     # 40 pieces a row
+    (2, 2500, 2, "f32", True, 0),       # shared weights: rows over (b, h)
+    (1, 33000, 3, "bf16", True, 0),     # many chunks
+    (1, 40960, 32, "bf16", False, 0),   # more workgroups than run at once: hidden layer in its own launch
+])
+def test_gate_of_rows_summed_in_deep_chunks(oracle, B, L, H, io, shared, phase):
+    """Lengths between the one-launch gate and 256 rows a chunk, at any alignment of a channel pair (same bits)."""
+    from paper_2502_18394_amd import binding
+    print(f"case B={B} L={L} H={H} io={io} shared={shared} phase={phase}", flush=True)
+    p = synth.gate_params(41, 1 if shared else H, 64, L)
+    vals, store = synth.tokens(42, (B, L, H, 64), io)
+    P = binding.GateParams(p)
+    q = to_device(store, io)
+    got = binding.gate(q, P, 1.0 / L, phase_pos=phase)
+    flat = torch.empty(q.numel() + 2, dtype=q.dtype, device="cuda")
+    off = flat[2:].view(B, L, H, 64)
+    off.copy_(q)
+    assert torch.equal(binding.gate(off, P, 1.0 / L, phase_pos=phase), got)
+    want = oracle.gate(oracle.pool_q(vals.astype(np.float64)), 1.0 / L, f64(p), L, phase)
+    assert rel_l2(got.cpu().numpy(), want) <= 1e-5
+
+
 @pytest.mark.parametrize("phase", [0, 777])
 @pytest.mark.parametrize("B,H,Hg,n", [(1, 1, 1, 128), (3, 2, 2, 1600), (4, 1, 1, 8192), (5, 1, 1, 8192), (2, 2, 1, 65), (9, 3, 3, 2048),
                                       (33, 2, 1, 1024), (4, 4, 4, 4096), (4, 16, 16, 4096), (2, 2048, 2048, 512)])
@@ -234,31 +261,9 @@ def test_last_bin_of_every_row(oracle, B, H, Hg, n, phase):
 
 
 @pytest.mark.parametrize("B,L,H,io,shared,phase", [
-    (1, 4096, 1, "f32", False, 0),      # chunks of 16-piece columns; a length with two output reals behind the last whole tile
-    (1, 2113, 1, "f32", False, 0),      # odd length, ragged last chunk and tile
-    (4, 3008, 1, "bf16", False, 777),   # 8-piece columns, four rows of one weight set inside the output layer, phase on the last bin
-    (5, 3008, 1, "bf16", False, 777),   # a fifth: hidden layer in its own launch
-    (2, 2500, 5, "bf16", False, 0),     # 40 pieces a row
-    (2, 2500, 2, "f32", True, 0),       # shared weights: rows over (b, h)
-    (1, 33000, 3, "bf16", True, 0),     # many chunks
-    (1, 40960, 32, "bf16", False, 0),   # more workgroups than run at once: hidden layer in its own launch
     (4, 4096, 2, "f32", False, 777),    # 64 chunks of four rows: the most that the output layer's workgroups add up themselves
     (1, 8192, 4, "bf16", True, 777),    # 128 of them: hidden layer in its own launch
     (1, 65536, 8, "f32", False, 0),     # rows of 2 KB in chunks of 128: the pass of whole rows
 ])
-def test_gate_of_rows_summed_in_deep_chunks(oracle, B, L, H, io, shared, phase):
-    """Lengths between the one-launch gate and 256 rows a chunk, at any alignment of a channel pair (same bits), and one that the pass of
-    whole rows takes."""
-    from paper_2502_18394_amd import binding
-    print(f"case B={B} L={L} H={H} io={io} shared={shared} phase={phase}", flush=True)
-    p = synth.gate_params(41, 1 if shared else H, 64, L)
-    vals, store = synth.tokens(42, (B, L, H, 64), io)
-    P = binding.GateParams(p)
-    q = to_device(store, io)
-    got = binding.gate(q, P, 1.0 / L, phase_pos=phase)
-    flat = torch.empty(q.numel() + 2, dtype=q.dtype, device="cuda")
-    off = flat[2:].view(B, L, H, 64)
-    off.copy_(q)
-    assert torch.equal(binding.gate(off, P, 1.0 / L, phase_pos=phase), got)
-    want = oracle.gate(oracle.pool_q(vals.astype(np.float64)), 1.0 / L, f64(p), L, phase)
-    assert rel_l2(got.cpu().numpy(), want) <= 1e-5
+def test_gate_on_both_sides_of_what_workgroups_repeat(oracle, B, L, H, io, shared, phase):
+    test_gate_of_rows_summed_in_deep_chunks(oracle, B, L, H, io, shared, phase)

@@ -267,8 +267,8 @@ def test_lengths_of_compile_time_radices(oracle, options, B, L, H, io):
 @pytest.mark.parametrize("L,most", [(144, 64), (196, 64), (144, 128), (196, 128), (256, 64), (448, 32), (576, 42), (768, 32), (784, 32), (896, 32),
                                     (1024, 16), (1280, 32), (1536, 16), (1792, 16)])
 def test_forms_for_few_and_for_many_heads(oracle, options, L, most, io):
-    """The last call that takes the form for few heads and the first that takes the other (and 128 and 129 heads of the two shortest,
-    all of the other form), against the general kernel (bounds as above), and the first head of both against the oracle."""
+    """The last call that takes the form for few heads and the first that takes the other, against the general kernel (bounds as
+    above), and the first head of both against the oracle."""
     from paper_2502_18394_amd import binding
     for H in (most, most + 1):
         print(f"case L={L} H={H} io={io}", flush=True)
@@ -455,6 +455,24 @@ def test_shapes_around_the_route_boundaries(oracle, B, L, H, io):
     assert_close_elementwise(got, want, io, 16 * L)
 
 
+@pytest.mark.parametrize("H", [(1 << 19) - 1, 1 << 19])
+def test_rows_4_gb_apart(H):
+    """The last number of heads of 512 bf16 rows whose lanes' offsets fit 32 bits and the first that needs 64 (34 GB of rows): the first,
+    a middle and the last head bit for bit as in a call of a few of them."""
+    from paper_2502_18394_amd import binding
+    L, at = 512, [0, H // 2, H - 1]
+    v = torch.empty((1, L, H, 64), dtype=torch.bfloat16, device="cuda")
+    g = torch.empty((1, H, L // 2 + 1), dtype=torch.complex64, device="cuda")
+    few = torch.randn(1, L, 200, 64, device="cuda").to(torch.bfloat16)
+    gate = torch.view_as_complex(torch.randn(1, 200, L // 2 + 1, 2, device="cuda"))
+    for i, h in enumerate(at):
+        v[:, :, h], g[:, h] = few[:, :, i], gate[:, i]
+    want = binding.mix_forward(few, gate)
+    got = binding.mix_forward(v, g)
+    for i, h in enumerate(at):
+        assert torch.equal(got[:, :, h], want[:, :, i])
+
+
 @pytest.mark.parametrize("L,io,heads", [
     (8192, "bf16", (31, 32)), (16384, "bf16", (15, 16)),                  # lines through the L2 from 32 MB on
     (5120, "f32", (12, 13, 44, 45)), (7168, "bf16", (9, 10, 73, 74)),     # scalar addresses up to 16 MB, and from 56 and 128 MB on
@@ -473,12 +491,10 @@ def test_forms_by_the_size_of_the_scratch_change_no_bit(L, io, heads):
             assert torch.equal(got[:, :, h:h + 1], want)
 
 
-@pytest.mark.parametrize("L,H", [(512, (1 << 19) - 1), (512, 1 << 19), (256, (1 << 21) - 1), (256, 1 << 21),
-                                 (101, (1 << 21) - 1), (101, 1 << 21)])
-def test_rows_4_gb_apart(L, H):
-    """The last number of heads of bf16 rows whose lanes' offsets fit 32 bits and the first that needs 64 (27 to 69 GB of rows): whole
-    transforms, rows that pass the caches by (256 points in 16 x 16) and padded rows (101 on the same). The first, a middle and the last
-    head bit for bit as in a call of a few of them."""
+@pytest.mark.parametrize("H", [(1 << 21) - 1, 1 << 21])
+@pytest.mark.parametrize("L", [256, 101])
+def test_streamed_and_padded_rows_4_gb_apart(L, H):
+    """As above for rows that pass the caches by (256 points in 16 x 16, 69 GB of rows) and padded rows (101 on the same, 27 GB)."""
     from paper_2502_18394_amd import binding
     at = [0, H // 2, H - 1]
     gen = torch.Generator(device="cuda").manual_seed(L)

@@ -43,12 +43,25 @@ def test_shares_of_the_whole_column_mixer(tmp_path):
 
 @pytest.mark.skipif(not os.path.exists(HIPCC) and shutil.which("hipcc") is None, reason="hipcc not found")
 def test_launches_of_the_in_lds_mixer(tmp_path):
-    """`slab_launch_heads` and `slab_ct_rows` (csrc/mix_slab.h): calls of millions of short heads are split into launches the runtime
-    takes; a kernel that moves all rows of a transform never gets tensors of fewer."""
+    """`slab_launch_heads` (csrc/mix_slab.h): calls of millions of short heads are split into launches the runtime takes."""
     exe = tmp_path / "slab_launch"
     csrc = os.path.join(ROOT, "paper_2502_18394_amd", "csrc")
     cmd = [HIPCC if os.path.exists(HIPCC) else "hipcc", "--cuda-host-only", "-x", "hip", "-std=c++17", "-O1", "-I", csrc,
            os.path.join(ROOT, "tests", "host", "slab_launch.cpp"), "-o", str(exe)]
+    res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    assert res.returncode == 0, res.stdout[-3000:]
+    run = subprocess.run([str(exe)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
+    print(run.stdout)
+    assert run.returncode == 0 and " 0 failures" in run.stdout, run.stdout
+
+
+@pytest.mark.skipif(not os.path.exists(HIPCC) and shutil.which("hipcc") is None, reason="hipcc not found")
+def test_rows_of_the_in_lds_mixer(tmp_path):
+    """`slab_ct_rows` (csrc/mix_slab.h): a kernel that moves all rows of a transform never gets tensors of fewer."""
+    exe = tmp_path / "slab_rows"
+    csrc = os.path.join(ROOT, "paper_2502_18394_amd", "csrc")
+    cmd = [HIPCC if os.path.exists(HIPCC) else "hipcc", "--cuda-host-only", "-x", "hip", "-std=c++17", "-O1", "-I", csrc,
+           os.path.join(ROOT, "tests", "host", "slab_rows.cpp"), "-o", str(exe)]
     res = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
     assert res.returncode == 0, res.stdout[-3000:]
     run = subprocess.run([str(exe)], stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True)
