@@ -13,10 +13,11 @@
 // A chip's workgroups of one round run in step, so what a workgroup waits for outside its two streams is time without
 // traffic.  Loads return in order: the first layer's operands are requested before the weights, whose arrival its chain then
 // passes behind, and the first rows of the half spectra as soon as the weights' registers are free, ahead of the factors; in
-// steps that only read them a row's registers take the one after next when it is used.  Steps that write the rows back request
-// the next eight together: one by one between the stores they were 1 to 3 % slower in long caches (us, before / one by one / together:
-// B=3 H=20 N=32768 200 / 206 / 200, B=4 H=32 N=65536 856 / 864 / 854).  us a token, before / now: B=1 H=32, deferred, N=4096 18.6 / 16.8,
-// 8192 27.5 / 27.0, 12288 40.8 / 39.0; every step updating, 4096 22.5 / 21.0, 16384 72.3 / 71.9.  (Plain loads, so that both streams stay
+// steps that only read them a row's registers take the one after next when it is used.  Steps that write the rows back do so only where one
+// workgroup has a block of weights to itself (B <= 2); where several take turns at one, the next eight are requested together behind the last
+// store (us of two tokens, one by one / together: B=1 H=32 N=32768 277 / 280, B=2 H=20 N=16384 154 / 156; B=3 H=20 N=32768 421 / 413, B=8 H=32
+// N=4096 212 / 208).  us, before / now: B=1 H=32, a deferred token, N=4096 18.6 / 16.8, 8192 27.5 / 27.0, 12288 40.8 / 39.0; two that
+// update, 4096 48.0 / 44.5, 16384 147 / 144.  (Plain loads, so that both streams stay
 // in the memory-side cache from token to token, gain another 2 to 15 % below 268 MB when nothing else runs between, and lose 6 to
 // 17 % when the caches and weights of eight layers take turns.)
 // Measured against ring update + hidden + output layer + sweep + final: B=1 H=32 N=8192, deferred updates, 39.7 ->
@@ -76,7 +77,8 @@ __device__ __forceinline__ void decode_entry(float4 &x, float2 dl, float2 wk, fl
 // 1-D grid over (chunk, head, group of bpw sequences), see below; 256 lanes.
 // LAZY = false: X += Delta w_k, stored, and the readout sums of the updated entries (k_sweep<true, true>).
 // LAZY = true : X only read, plus the pending tokens' kappa sums (k_sweep_lazy); ps includes this token.
-template <typename T, bool LAZY>
+// AT_ONCE: a row's registers take the next row when it is used, see above.
+template <typename T, bool LAZY, bool AT_ONCE>
 __global__ __launch_bounds__(256, 4) void k_decode(float4 *__restrict__ X, DecodeRing rg, double inv_count, GateDev P,
                                                 const float2 *__restrict__ tw, float *__restrict__ partial,
                                                 float *__restrict__ kpart, int B, int H, int N, int bpw,
@@ -240,8 +242,7 @@ __global__ __launch_bounds__(256, 4) void k_decode(float4 *__restrict__ X, Decod
         float acc0 = 0.f, acc1 = 0.f, kacc = 0.f;
         float4 *Xp = head_of(bl);
         const float2 *rp = s_r + bl * kBinStride, *gp = s_g + bl * kBinStride;
-        // a row's registers take the one after next (half a chunk on, then the next sequence's) as soon as it is used; where the rows are
-        // written back, all eight together behind the last store
+        // a row's registers take the one after next (half a chunk on, then the next sequence's): at once, or all eight behind the last store
 #pragma unroll 1
         for (int half = 0; half < 2; ++half) {
             const int next_bl = half ? bl + 1 : bl, next_k = half ? row : kHalf + row;
@@ -256,9 +257,9 @@ __global__ __launch_bounds__(256, 4) void k_decode(float4 *__restrict__ X, Decod
                     kacc = fmaf(gc.x, e.x, fmaf(gc.y, e.y, kacc));   // c_k/N Re(g_k conj(e_k))
                     e = cmul(e, sq_now.rot);
                 }
-                if (LAZY && next_bl < nb) x[u] = load_row(next_bl, next_k + 8 * u);
+                if (AT_ONCE && next_bl < nb) x[u] = load_row(next_bl, next_k + 8 * u);
             }
-            if (!LAZY && next_bl < nb) {
+            if (!AT_ONCE && next_bl < nb) {
 #pragma unroll
                 for (int u = 0; u < kU; ++u) x[u] = load_row(next_bl, next_k + 8 * u);
             }
@@ -421,8 +422,8 @@ static hipError_t decode_t(const DecodeRing &rg, float2 *X, double inv_count, co
                        (size_t)bpw * (kBinStride * sizeof(float2) * (lazy ? 2 : 1) + (64 + 64 + 256) * sizeof(float));
     const dim3 grid((unsigned)wgs);
     float4 *X4 = reinterpret_cast<float4 *>(X);
-    if (lazy) k_decode<T, true><<<grid, 256, lds, st>>>(X4, rg, inv_count, P, tw, partial, kpart, B, H, N, bpw, ps, nch);
-    else k_decode<T, false><<<grid, 256, lds, st>>>(X4, rg, inv_count, P, tw, partial, kpart, B, H, N, bpw, ps, nch);
+    const auto kern = lazy ? k_decode<T, true, true> : bpw == B ? k_decode<T, false, true> : k_decode<T, false, false>;
+    kern<<<grid, 256, lds, st>>>(X4, rg, inv_count, P, tw, partial, kpart, B, H, N, bpw, ps, nch);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     typename IO::pair_t *o = static_cast<typename IO::pair_t *>(out);
@@ -448,7 +449,7 @@ hipError_t launch_decode(int io, const void *v_t, const void *q_t, float *v_buf,
 // that no compute call is the first to touch it.
 hipError_t load_kernels_decode() {
     hipFuncAttributes a;
-    return hipFuncGetAttributes(&a, reinterpret_cast<const void *>((k_decode<float, false>)));
+    return hipFuncGetAttributes(&a, reinterpret_cast<const void *>((k_decode<float, false, false>)));
 }
 
 }  // namespace spectre
