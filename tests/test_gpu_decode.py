@@ -63,6 +63,12 @@ def test_decode_step_of_several_sequences_per_workgroup(oracle, B, H, N, Hg, io,
     run_steps(oracle, B, H, N, Hg, io, defer, steps=4)
 
 
+@pytest.mark.parametrize("Hg,io", [(32, "f32"), (1, "bf16")])
+def test_decode_step_of_all_sequences_in_one_workgroup(oracle, Hg, io):
+    """Updating steps of two sequences whose rows one workgroup takes: the rows are requested one by one, also across the sequences."""
+    run_steps(oracle, 2, 32, 8192, Hg, io, 0, steps=3)
+
+
 @pytest.mark.parametrize("B,H,N,Hg,io,defer,modrelu,d_g,taps,shift", [
     (2, 3, 768, 3, "f32", 0, True, 48, 0, 0), (2, 3, 768, 1, "bf16", 3, False, 48, 0, 0),       # another width
     (1, 2, 512, 2, "bf16", 0, True, 64, 2, 0), (2, 2, 1280, 1, "f32", 4, True, 64, 3, 0),       # Toeplitz taps
