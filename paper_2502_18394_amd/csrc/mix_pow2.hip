@@ -695,15 +695,19 @@ static hipError_t small_fwd_t(const Pow2Plan &pl, const void *v, void *scr_v, in
     // Scalar addresses for whole transforms, alone, of up to 16 MB and from 56 MB of fp32 rows or 128 MB of bf16 rows on, by the bytes of their
     // scratch.  Between, the denser bursts of loads and stores lose more often than they gain.  Mixer, us, per lane / scalar, fp32 rows: 8
     // heads at 5120 (10 MB) 19.4 / 18.6, 24 (31 MB) 38.3 / 42.3, 48 (63 MB) 76.1 / 74.5; 6 at 20480 (31 MB) 39.7 / 43.5; 2 at 49152 (25 MB)
-    // 46.1 / 48.5; 32 at 24576 (201 MB) 233 / 225; 16 at 28672 (117 MB) 142 / 136; bf16 rows: 32 at 7168 (59 MB) 54.6 / 57.6, 48 (88 MB)
-    // 77.1 / 81.9, 64 (117 MB) 2 %, 96 (176 MB) -1 %, 32 at 6144 (50 MB) 47.3 / 49.8.  Windows of a cache (fp32 ring) alike: 8 to 16 MB -2 to
+    // 46.1 / 48.5; bf16 rows: 32 at 7168 (59 MB) 54.6 / 57.6, 48 (88 MB) 77.1 / 81.9, 64 (117 MB) 2 %, 96 (176 MB) -1 %, 32 at 6144 (50 MB) 47.3 / 49.8.  Windows of a cache (fp32 ring) alike: 8 to 16 MB -2 to
     // -3 %, 20 to 50 MB up to +5 %, 100 to 200 MB -1 to -5 %.  Rows that the projection has just written gain nothing above 16 MB and lose
     // there too (layer of fp32 rows, 32 heads at 16384 249 / 254, 2 x 20 at 12288 214 / 218, 20 at 32768 321 / 324).  Beside another launch
     // scalar ones gain at every size (launches of 64 to 100 MB, 32 heads of bf16 rows at 49152 360 / 351, 64 697 / 683, 256 at 12288 656 / 637, at
     // 131072 945 / 938; layer of 20 heads of fp32 rows at 65536 605 / 585, 77 at 24576 709 / 696).
     const size_t bytes = (size_t)nbh * pl.N1 * N2 * 32 * sizeof(typename SC::elem_t);
     const size_t from = (size_t)(std::is_same<IO, IoF32>::value ? 56 : 128) << 20;
-    const bool scalar = bytes <= ((size_t)16 << 20) || two_streams || (bytes >= from && !just_written);
+    // 24 and 28 fp32 rows take scalar ones at every size (per lane, those keep 4 waves per SIMD instead of 6 or 7; 20 rows 5, 32 rows 3).  Mixer, 5
+    // heads at 24576 (31 MB) 45.3 / 43.7, 20 at 6144 (31 MB) 44.8 / 43.2, 5 at 28672 (37 MB) 52.9 / 51.4, one at 98304 46.3 / 45.6; windows, 24
+    // heads of 6144 39.1 / 37.0, 20 of 7168 39.2 / 37.5; layer, 8 heads at 24576 100.5 / 98.1, 32 354 / 345, 20 at 28672 277 / 266.  Between 16 and
+    // 56 MB 32 rows lose (windows of 6 heads of 32768 50.1 / 52.0), and so do bf16 rows (24 heads at 6144 40.1 / 41.7).
+    constexpr bool kEverySize = std::is_same<IO, IoF32>::value && (N2 == 24 || N2 == 28);
+    const bool scalar = kEverySize || bytes <= ((size_t)16 << 20) || two_streams || (bytes >= from && !just_written);
     const bool part = ring || rows < pl.N1 * N2;
     auto kern = part || !scalar ? k_small_fwd<N2, TT, IO, SC, true> : k_small_fwd<N2, TT, IO, SC, false>;
     typename SC::elem_t *scr = static_cast<typename SC::elem_t *>(scr_v);

@@ -476,6 +476,7 @@ def test_rows_4_gb_apart(H):
 @pytest.mark.parametrize("L,io,heads", [
     (8192, "bf16", (31, 32)), (16384, "bf16", (15, 16)),                  # lines through the L2 from 32 MB on
     (5120, "f32", (12, 13, 44, 45)), (7168, "bf16", (9, 10, 73, 74)),     # scalar addresses up to 16 MB, and from 56 and 128 MB on
+    (6144, "f32", (10, 11, 20)), (28672, "f32", (2, 3, 5)),               # scalar addresses of 24 and 28 fp32 rows at every size
     (3072, "f32", (24, 32, 48)), (49152, "f32", (1, 2, 3)),               # columns through the L2 but for 24 to 32 and 20 to 26 MB
 ])
 def test_forms_by_the_size_of_the_scratch_change_no_bit(L, io, heads):
