@@ -34,7 +34,7 @@ template <> struct RowTile<IoBf16> { static constexpr int kPairs = 32, kStride =
 template <> struct RowTile<IoF32> { static constexpr int kPairs = 16, kStride = 18; };
 template <typename IO> struct TileStride { static constexpr int value = RowTile<IO>::kStride; };
 
-// Where it gains, the addresses of the forward row kernels are a scalar base per row or block and one 32-bit offset of the lane
+// Where it gains, the addresses of the row kernels are a scalar base per row or block and one 32-bit offset of the lane
 // (lane_pointer): 64-bit products per lane and row are a quarter of these kernels' vector time.
 //
 // small_fwd: grid (N1/TT * 32/PW, nbh); block PW*TT threads, PW = RowTile<IO>::kPairs.  Reads the N2*TT rows
@@ -222,10 +222,15 @@ __global__ __launch_bounds__(RowTile<IO>::kPairs * TT) void k_small_inv(const ty
     const int bh = bh0 + bhl, b = bh / H, h = bh % H;
     {
         const int tl = tid % TT, p = tid / TT, t1 = t1_0 + tl;
-        const typename SC::elem_t *src = scr + (((size_t)bhl * N2) * 32 + p0 + p) * N1 + t1;
+        const typename SC::elem_t *src = scr + (((size_t)bhl * N2) * 32 + p0) * N1 + t1_0, *own = src + (size_t)p * N1 + tl;
+        const unsigned scr_at = (unsigned)(p * N1 + tl) * (unsigned)sizeof(typename SC::elem_t);
+        // scalar addresses for 28 fp32 rows only (us, per lane / scalar: readout of 40 heads of 7168 slots 55.2 / 52.7, mixer of 20 heads at 7168
+        // 49.1 / 48.0, 100 207.6 / 204.9, 2 at 114688 75.7 / 74.9, 9 at 28672 79.0 / 79.1; bf16 rows, readout of 40 47.7 / 48.7; 24 fp32 rows, window of 18
+        // heads of 6144 slots 27.5 / 28.2, mixer of 64 at 24576 418 / 422)
+        constexpr bool kScalar = std::is_same<IO, IoF32>::value && N2 == 28;
         typename SC::elem_t raw[N2];
 #pragma unroll
-        for (int k2 = 0; k2 < N2; ++k2) raw[k2] = src[(size_t)k2 * 32 * N1];
+        for (int k2 = 0; k2 < N2; ++k2) raw[k2] = kScalar ? *lane_pointer(src + (size_t)k2 * 32 * N1, scr_at) : own[(size_t)k2 * 32 * N1];
         float2 y[N2];
 #pragma unroll
         for (int k2 = 0; k2 < N2; ++k2) y[k2] = SC::get(raw[k2]);
