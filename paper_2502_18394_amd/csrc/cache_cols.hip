@@ -281,12 +281,14 @@ static hipError_t cache_cols_t(bool inverse, const Pow2Plan &pl, float2 *scr, fl
     const size_t lds = Unit::kLds;
     const long long units = ((long long)nbh * cache_plane_pairs(pl.N2) + 7) / 8 * 8 * (32 / PW);
     if (units > 0x7fffffffLL) return hipErrorInvalidValue;
-    // The inverse writes its columns through the L2, except those of 256 points that are about what the eight L2s hold: 18 to 40 MB, where
-    // the readout's row transforms find them after plain stores.  Readout of a window, us, plain / through: 16 heads of N = 8192 (34 MB)
-    // 26.5 / 28.4, 32 of 4096 27.1 / 28.6, 10 of 8192 (21 MB) 5 %; but 8 of 8192 (17 MB) 22.1 / 20.1, 64 of 4096 (67 MB) 43.1 / 42.6, 128 of
-    // 8192 (268 MB) 174 / 171.  Of 1024 points: 3 heads of 24576 (19 MB) 27.8 / 25.6, 4 of 32768 (34 MB) 30.9 / 30.5, 6 (50 MB) 44.6 / 42.1.
+    // The inverse writes its columns through the L2, except those of 256 points of windows of 2560 slots and more, 18 MB to what the eight L2s
+    // hold: there the readout's row transforms find them after plain stores.  Readout of a window, us, plain / through: 12 heads of N = 8192 (24
+    // MB) 22.8 / 23.6, 18 of 6144 (27 MB) 26.7 / 27.8, 20 of 5120 (25 MB) 23.1 / 24.1, 32 of 4096 (32 MB) 27.7 / 28.0, 50 of 2560 (31 MB) 25.1 /
+    // 25.5; but 9 of 8192 (18 MB) 22.1 / 22.3, 8 22.1 / 20.1; 17 (34 MB) 33.8 / 33.1, 26 of 5120 (32.5 MB) 31.9 / 29.6, 40 of 4096 (40 MB) 34.2 /
+    // 32.7, 128 of 8192 174 / 171; 64 of 2048 (32 MB) 25.8 / 25.3, 40 (20 MB) 19.9 / 19.4, 150 of 512 (19 MB) 19.5 / 19.0.  Of 1024 points: 3 heads of
+    // 24576 (18 MB) 27.8 / 25.6, 4 of 32768 (32 MB) 30.9 / 30.5, 6 (48 MB) 44.6 / 42.1.
     const size_t bytes = (size_t)nbh * pl.N1 * pl.N2 * 32 * sizeof(float2);
-    const bool through = R == 32 || bytes < ((size_t)18 << 20) || bytes > ((size_t)40 << 20);
+    const bool found = R == 16 && pl.N2 >= 10 && bytes >= ((size_t)18 << 20) && bytes <= kL2Bytes, through = !found;
     auto inv = through ? k_cache_inv<R, PW, true> : k_cache_inv<R, PW, false>;
     const void *kern = inverse ? reinterpret_cast<const void *>(inv)
                                : reinterpret_cast<const void *>(&k_cache_fwd<R, PW>);

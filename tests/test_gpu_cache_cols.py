@@ -38,9 +38,9 @@ def test_window_transform_and_readout(oracle, N, B, H, io):
     assert rel_l2(from_device(out), want) <= TOL[io]
 
 
-@pytest.mark.parametrize("N,heads", [(4096, (17, 18, 40, 41)), (16384, (4, 5, 14))])
+@pytest.mark.parametrize("N,heads", [(4096, (17, 18, 32, 33)), (2048, (40, 70)), (16384, (4, 5, 14))])
 def test_readout_at_the_sizes_where_its_stores_change(N, heads):
-    """Columns through the L2 below 18 MB and above 40 MB, plain between (256-point columns; of 1024 points always through), and the window's
+    """Columns through the L2 below 18 MB and above 32 MB, plain between (256-point columns from 2560 slots on, else always through), and the window's
     row transforms on both sides of 16 and 56 MB: the same bits as for two heads."""
     from paper_2502_18394_amd import binding
     gen = torch.Generator(device="cuda").manual_seed(N)
