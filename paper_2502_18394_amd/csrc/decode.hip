@@ -14,7 +14,8 @@
 // traffic.  Loads return in order: the first layer's operands are requested before the weights, whose arrival its chain then
 // passes behind, and the first rows of the half spectra as soon as the weights' registers are free, ahead of the factors; in
 // steps that only read them a row's registers take the one after next when it is used.  Steps that write the rows back do so only where one
-// workgroup has a block of weights to itself (B <= 2); where several take turns at one, the next eight are requested together behind the last
+// workgroup has a block of weights to itself (B <= 2) or the launch is so small that each takes one sequence (B=2 H=4 N=8192, 14 tokens 191 / 194);
+// elsewhere several take turns at one, and the next eight are requested together behind the last
 // store (us of two tokens, one by one / together: B=1 H=32 N=32768 277 / 280, B=2 H=20 N=16384 154 / 156; B=3 H=20 N=32768 421 / 413, B=8 H=32
 // N=4096 212 / 208).  us, before / now: B=1 H=32, a deferred token, N=4096 18.6 / 16.8, 8192 27.5 / 27.0, 12288 40.8 / 39.0; two that
 // update, 4096 48.0 / 44.5, 16384 147 / 144.  (Plain loads, so that both streams stay
@@ -422,7 +423,7 @@ static hipError_t decode_t(const DecodeRing &rg, float2 *X, double inv_count, co
                        (size_t)bpw * (kBinStride * sizeof(float2) * (lazy ? 2 : 1) + (64 + 64 + 256) * sizeof(float));
     const dim3 grid((unsigned)wgs);
     float4 *X4 = reinterpret_cast<float4 *>(X);
-    const auto kern = lazy ? k_decode<T, true, true> : bpw == B ? k_decode<T, false, true> : k_decode<T, false, false>;
+    const auto kern = lazy ? k_decode<T, true, true> : bpw == 1 || bpw == B ? k_decode<T, false, true> : k_decode<T, false, false>;
     kern<<<grid, 256, lds, st>>>(X4, rg, inv_count, P, tw, partial, kpart, B, H, N, bpw, ps, nch);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
